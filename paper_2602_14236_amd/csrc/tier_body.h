@@ -27,9 +27,9 @@ struct TierCounts {
 };
 
 struct TierShared {
-    uint4 key4[kTokens / 4];        // order-preserving integer image of the scores
+    uint32_t key[kTokens];          // order-preserving integer image of the scores
     int group_cnt[kTierGroups][4];
-    int part_rank[4][64];           // partial ranks of tokens 512..575, one row per wave
+    unsigned long long taken[3][kTierGroups];       // top-k counts: tokens of rank below each cutoff, a bit each
     int nan_flag;
     int q[3];                       // adaptive thresholds: quantiles found by the ranking
     int tau[3];                     // adaptive thresholds in force, units of 2^-16
@@ -41,37 +41,31 @@ __device__ __forceinline__ int to_lattice(float x) {
     return (int)floorf(fminf(fmaxf(x, 0.0f), 1.0f) * 65536.0f);
 }
 
-// Number of tokens j in key blocks [j4_lo, j4_hi) (four keys per block) that precede token i in
-// (key descending, index ascending) order; `me` = key of token i.  Blocks before the token's own
-// 64-token group count with >=, blocks after it with >, and only the 16 blocks of the own group
-// need the index test.  128-bit broadcast LDS reads, eight in flight.
-__device__ __forceinline__ int tier_count_above(const TierShared& sh, uint32_t me, int i, int j4_lo, int j4_hi) {
-    const int own0 = (i >> 6) * 16, own1 = own0 + 16;
-    int rank = 0;
-    const int a1 = own0 < j4_hi ? own0 : j4_hi;          // [j4_lo, a1): earlier groups
-    const int b0 = own0 > j4_lo ? own0 : j4_lo;          // [b0, b1): own group
-    const int b1 = own1 < j4_hi ? own1 : j4_hi;
-    const int c0 = own1 > j4_lo ? own1 : j4_lo;          // [c0, j4_hi): later groups
-#pragma unroll 8
-    for (int j4 = j4_lo; j4 < a1; ++j4) {
-        const uint4 v = sh.key4[j4];
-        rank += (v.x >= me ? 1 : 0) + (v.y >= me ? 1 : 0) + (v.z >= me ? 1 : 0) + (v.w >= me ? 1 : 0);
+// The n-th largest of the 576 keys (1 <= n <= 576), by ONE wave that holds them nine per lane: the
+// largest T with #{key >= T} >= n, built bit by bit from the top.  A step is nine compares whose lane
+// masks are counted by the scalar unit; bits that no two keys differ in are skipped (scores on the 2^-16
+// lattice leave about twenty).  Nothing here depends on another wave, so the three cutoffs of a frame
+// are three waves' work.  Counting for every token how many keys precede it (576 x 576 compares over
+// LDS broadcasts) is 324 16-byte LDS reads per wave instead: k_tier took 19.4 us with it and takes 7.8 with
+// this; k_pool_tail next to the pack kernel 40 against 16 us (4 frames) and 22 us (16 frames).
+__device__ __forceinline__ uint32_t wave_select(const uint32_t (&key)[kTierGroups], int n) {
+    const uint32_t first = (uint32_t)__builtin_amdgcn_readfirstlane((int)key[0]);
+    uint32_t diff = 0u;
+#pragma unroll
+    for (int j = 0; j < kTierGroups; ++j) diff |= key[j] ^ first;
+    for (int off = 32; off > 0; off >>= 1) diff |= (uint32_t)__shfl_xor((int)diff, off);
+    diff = (uint32_t)__builtin_amdgcn_readfirstlane((int)diff);
+    uint32_t t = first & ~diff;
+    while (diff != 0u) {                            // at most 32 steps
+        const uint32_t bit = 0x80000000u >> __builtin_clz(diff);
+        diff &= ~bit;
+        const uint32_t cand = t | bit;
+        int cnt = 0;
+#pragma unroll
+        for (int j = 0; j < kTierGroups; ++j) cnt += __popcll(__ballot(key[j] >= cand));
+        if (cnt >= n) t = cand;
     }
-#pragma unroll 8
-    for (int j4 = b0; j4 < b1; ++j4) {
-        const uint4 v = sh.key4[j4];
-        const int j = 4 * j4;
-        rank += (v.x > me || (v.x == me && j < i)) ? 1 : 0;
-        rank += (v.y > me || (v.y == me && j + 1 < i)) ? 1 : 0;
-        rank += (v.z > me || (v.z == me && j + 2 < i)) ? 1 : 0;
-        rank += (v.w > me || (v.w == me && j + 3 < i)) ? 1 : 0;
-    }
-#pragma unroll 8
-    for (int j4 = c0; j4 < j4_hi; ++j4) {
-        const uint4 v = sh.key4[j4];
-        rank += (v.x > me ? 1 : 0) + (v.y > me ? 1 : 0) + (v.z > me ? 1 : 0) + (v.w > me ? 1 : 0);
-    }
-    return rank;
+    return t;
 }
 
 // Assigns tier, slot (rank inside the tier in token order) and the pool-order token list of one
@@ -168,20 +162,18 @@ __device__ __forceinline__ TierCounts tier_rank(TierShared& sh, const TierScores
 
     if (tid == 0) sh.nan_flag = 0;
     float s[kTierSlots];
-    uint32_t key[kTierSlots];
     bool has_nan = false;
 #pragma unroll
     for (int k = 0; k < kTierSlots; ++k) {
         const int i = tid + k * kTierThreads;
         s[k] = 0.0f;
-        key[k] = 0u;
         if (i < kTokens) {
             s[k] = loaded.s[k];
             has_nan |= s[k] != s[k];
             // unsigned key with the same order as the float (and -0 == +0, as the float comparison has it)
             const uint32_t bits = (s[k] == 0.0f) ? 0u : __builtin_bit_cast(uint32_t, s[k]);
-            key[k] = (bits & 0x80000000u) ? ~bits : (bits | 0x80000000u);
-            reinterpret_cast<uint32_t*>(sh.key4)[i] = key[k];
+            const uint32_t key = (bits & 0x80000000u) ? ~bits : (bits | 0x80000000u);
+            sh.key[i] = key;
         }
     }
     __syncthreads();
@@ -196,36 +188,42 @@ __device__ __forceinline__ TierCounts tier_rank(TierShared& sh, const TierScores
     if (tp.mode == 0) {
         tier_by_thresholds(s, tp.tau_high, tp.tau_med, tp.tau_low, tier);
     } else {
-        // rank by (score descending, token index ascending) = number of tokens j with a larger key,
-        // or an equal key and j < i.  Work is dealt evenly: tokens 0..511 are two per thread against
-        // all 576 keys; the last 64 tokens are taken by all four waves, a quarter of the keys each
-        // (partial counts meet in LDS).  All lanes of a wave share the 64-token group of their
-        // token, so the comparison regime of a key block is uniform in the wave.
-        int rank[kTierSlots];
+        // rank = place in (score descending, token index ascending) order.  Waves 0, 1 and 2 take one
+        // cutoff each; the thresholds are all that the ranking has to yield.
+        const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+        const int cut = wave == 0 ? tp.k16 : (wave == 1 ? tp.k16 + tp.k8 : tp.k16 + tp.k8 + tp.k4);
+        if (wave < 3) {
+            uint32_t all[kTierGroups];
 #pragma unroll
-        for (int k = 0; k < 2; ++k) rank[k] = tier_count_above(sh, key[k], tid + k * kTierThreads, 0, kTokens / 4);
-        {
-            const int wave = tid >> 6;
-            const int i = 2 * kTierThreads + lane;                      // 512 + lane, every wave
-            const uint32_t me = reinterpret_cast<const uint32_t*>(sh.key4)[i];
-            const int part = tier_count_above(sh, me, i, wave * (kTokens / 16), (wave + 1) * (kTokens / 16));
-            sh.part_rank[wave][lane] = part;
-        }
-        if (tid < 3) sh.q[tid] = 0;
-        __syncthreads();
-        rank[2] = sh.part_rank[0][lane] + sh.part_rank[1][lane] + sh.part_rank[2][lane] + sh.part_rank[3][lane];
-        if (tp.mode == 2) {
-            // adaptive thresholds: only the quantiles at the target ranks are taken from the ranking
-            // (every rank belongs to exactly one token; a rank past the last token leaves 0)
+            for (int j = 0; j < kTierGroups; ++j) all[j] = sh.key[64 * j + lane];
+            if (tp.mode == 2) {
+                // adaptive thresholds: the score of rank `cut` (0 where the rank does not exist)
+                const uint32_t t = cut < kTokens ? wave_select(all, cut + 1) : 0x80000000u;
+                if (lane == 0)
+                    sh.q[wave] = to_lattice(__builtin_bit_cast(float, (t & 0x80000000u) ? (t & 0x7FFFFFFFu) : ~t));
+            } else {
+                // ranks below `cut`: the keys above the cut-th largest, and of those equal to it the first
+                // ones in token order, as many as are missing
+                const uint32_t t = cut > 0 ? wave_select(all, cut) : 0xFFFFFFFFu;      // no score has that key
+                unsigned long long above[kTierGroups];
+                int missing = cut;
 #pragma unroll
-            for (int k = 0; k < kTierSlots; ++k) {
-                const int i = tid + k * kTierThreads;
-                if (i >= kTokens) continue;
-                if (rank[k] == tp.k16) sh.q[0] = to_lattice(s[k]);
-                if (rank[k] == tp.k16 + tp.k8) sh.q[1] = to_lattice(s[k]);
-                if (rank[k] == tp.k16 + tp.k8 + tp.k4) sh.q[2] = to_lattice(s[k]);
+                for (int j = 0; j < kTierGroups; ++j) {
+                    above[j] = __ballot(all[j] > t);
+                    missing -= __popcll(above[j]);
+                }
+                const unsigned long long lt_mask = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
+#pragma unroll
+                for (int j = 0; j < kTierGroups; ++j) {
+                    const unsigned long long equal = __ballot(all[j] == t);
+                    const unsigned long long m = above[j] | __ballot(all[j] == t && (int)__popcll(equal & lt_mask) < missing);
+                    missing -= __popcll(equal);
+                    if (lane == 0) sh.taken[wave][j] = m;
+                }
             }
-            __syncthreads();
+        }
+        __syncthreads();
+        if (tp.mode == 2) {
             res.state = 3;
 #pragma unroll
             for (int j = 0; j < 3; ++j) res.q[j] = sh.q[j];
@@ -236,9 +234,9 @@ __device__ __forceinline__ TierCounts tier_rank(TierShared& sh, const TierScores
             const int i = tid + k * kTierThreads;
             tier[k] = SALI_TIER_PRUNE;
             if (i >= kTokens) continue;
-            if (rank[k] < tp.k16 + tp.k8 + tp.k4) tier[k] = SALI_TIER_INT4;
-            if (rank[k] < tp.k16 + tp.k8) tier[k] = SALI_TIER_INT8;
-            if (rank[k] < tp.k16) tier[k] = SALI_TIER_FP16;
+            if ((sh.taken[2][i >> 6] >> lane) & 1ull) tier[k] = SALI_TIER_INT4;
+            if ((sh.taken[1][i >> 6] >> lane) & 1ull) tier[k] = SALI_TIER_INT8;
+            if ((sh.taken[0][i >> 6] >> lane) & 1ull) tier[k] = SALI_TIER_FP16;
         }
     }
     return tier_finish(sh, tier, tier_out, slot_out, order_out);
