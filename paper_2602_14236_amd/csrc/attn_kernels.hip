@@ -35,7 +35,8 @@ typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
 typedef _Float16 half2_t __attribute__((ext_vector_type(2)));
 
 constexpr int kRowsPerStep = 4;               // rows in flight per lane group (K and V each)
-constexpr int kResidentBlocks = 256 * 8;      // compute units x blocks of the main kernel that fit on one
+constexpr int kComputeUnits = 256;
+constexpr int kResidentBlocks = kComputeUnits * 8;      // compute units x blocks of the main kernel that fit on one
 constexpr int kPartialStride = kAttnPartialStride;   // max, sum, 128 values, padded to whole 128-byte lines
 
 union Row16B {
@@ -377,20 +378,19 @@ __global__ __launch_bounds__(256) void k_attn_merge(const float* __restrict__ pa
 }
 
 // ---------------------------------------------------------------------------------------------
-// Many queries per K/V head (16, 32 or 64: the tokens of a prompt attending to the cached video, or
+// Many queries per K/V head (9 to 64: the tokens of a prompt attending to the cached video, or
 // large query groups): Q K^T and P V are real matrix products, so they run on the matrix cores
-// (v_mfma_f32_32x32x16_f16) and every compressed row is still read once for all queries.
+// (v_mfma_f32_32x32x16_f16) and every compressed row is read once per 32 queries.
 //
-// One wave = one work item (a chunk of frames x a row split, as in the single-query kernel) x one
-// K/V head x one tile of 32 queries; the four waves of a block share the 32 queries (LDS).  Per tile
-// of 32 cached rows:
+// One block = one K/V head x one tile of 32 queries x one share of the frame range; its eight waves take
+// the share's tiles of 32 cached rows in turn and meet once, at the end.  Per tile:
 //   S^T = K^ Q^T : A operand = K^ tile (lane = row n, registers = head-dim values), B operand = the
 //        queries (lane = query m); the result has lane = query, registers = rows, so the softmax
 //        over rows is a reduction over the lane's 16 registers and one exchange between the two
 //        lane halves, and P in that layout IS the B operand of the second product (the rows of the
 //        tile are contracted in the order the registers hold them);
 //   out^T = V^^T P^T : A operand = V^^T (lane = head-dim value d, registers = two runs of 4
-//        consecutive rows), read column-wise from the wave's LDS tile, which holds K^ first and V^ after.
+//        consecutive rows), read from the wave's LDS tile with the transposing 8-byte LDS read.
 // The head-dim index of the contraction is permuted (lane half hh of a row holds values
 // [64 hh, 64 hh + 64), k-step t takes 8 of them from each half) so that a lane reads one contiguous
 // piece of its row; Q uses the same permutation.  Here the dequantised values DO exist as fp16
@@ -399,131 +399,146 @@ __global__ __launch_bounds__(256) void k_attn_merge(const float* __restrict__ pa
 // as well.  Both stay inside the tolerance of the floating-point results (largest error printed by
 // the tests).  Accumulation, softmax state and partials are fp32; partials have the layout of the
 // single-query kernel and are merged by the same k_attn_merge.
-// The kernel is bound by instruction issue (conversions of the codes, softmax, LDS traffic and the
-// matrix instructions of a tile share one SIMD): one, two or three resident waves per SIMD take the
-// same time, and so do 16 and 32 queries.
+//
+// What bounds it: the trip to memory of a tile (waves wait for it about half their time), then the vector
+// instructions of a tile (600, conversions and softmax).  Hence: a tile's K^ and V^ rows are asked for a
+// whole tile ahead, across tiers and frames; the launch is one block of eight waves per compute unit, forced
+// to one by its LDS, so that all start at once; and a block writes one partial instead of one per wave.
+// 32 heads x 32 queries over 20 frames (173 / 200 / 203 rows, 118 MB): 34.5 us + 4.6 us of merge.  The same
+// tiles as 512 independent blocks of four waves that should just have fitted twice per compute unit, a
+// tier's loads one tile ahead and a partial per wave, took 69.6 us + 8.0 us of merge: such blocks do not
+// pack perfectly, the last of them ran alone in a second round (mean wave lifetime 26 us).
 typedef _Float16 half4_t __attribute__((ext_vector_type(4)));
 typedef _Float16 half8_t __attribute__((ext_vector_type(8)));
+typedef short short4_t __attribute__((ext_vector_type(4)));
 typedef float float16_t __attribute__((ext_vector_type(16)));
 
 namespace {
 
 constexpr int kPfRows = 32;                       // cached rows per tile
-constexpr int kPfVStride = kHeadDim + 8;          // halves per LDS row of a tile (skewed against bank conflicts)
-constexpr int kPfWavesPerSimd = 2;                // resident waves the launch is sized for
+constexpr int kPfWaves = 8;                       // waves of a block
+constexpr int kPfKStride = kHeadDim + 8;          // halves per LDS row: lane = row reads of 16 bytes, eight lanes cover all banks
+constexpr int kPfVStride = kHeadDim + 16;         // transposing reads: four rows of 64 bytes, eight banks apart
+constexpr int kPfTileHalves = kPfRows * (kPfKStride + kPfVStride);
+constexpr int kPfGroup = 64;                      // frames looked up at a time
+constexpr int kPfOutStride = 33;                  // floats per head-dim value of a wave's result in LDS
+static_assert(kHeadDim * kPfOutStride * 4 <= kPfTileHalves * 2, "a wave's result fits its tiles");
 
 union Half8 {
     u32x4 u;
     half4_t h4[2];
+    half8_t h8;
     _Float16 h[8];
 };
 
-// A tile of 32 pool rows is read with fully coalesced 16-byte loads (consecutive lanes read
-// consecutive memory: a lane-per-row pattern, which the matrix-core operands would suggest, was
-// measured at 1.6 TB/s), dequantised to fp16 where it lies, and written to the wave's LDS tile
-// [32 rows][128 values]; the operands are then read from LDS in the layout the instruction wants.
-// Piece `idx` of a tile = 16 bytes of row idx / (pieces per row).  Rows past the end of the run
-// repeat its last row (their softmax weight is zero).
-template <int kTier>
-struct PfRaw;
-template <>
-struct PfRaw<SALI_TIER_FP16> {
-    u32x4 c[8];                 // 8 values each
-};
-template <>
-struct PfRaw<SALI_TIER_INT8> {
-    u32x4 c[4];                 // 16 codes each
-    float sc[4];
-};
-template <>
-struct PfRaw<SALI_TIER_INT4> {
-    u32x4 c[2];                 // 32 codes each = one quantisation group
-    float sc[2], zp[2];
+// what a block takes from one stored frame: its tiles i0 .. of the tiers in pool order (FP16, INT8, INT4)
+struct PfFrame {
+    int start;                  // number of the frame's first tile in the block's sequence
+    int i0;                     // its index among the frame's tiles
+    int base[3], n[3];
+    float mult;                 // how often the frame counts (itself and the pointer entries behind it)
 };
 
-__device__ __forceinline__ void pf_load_tile(const Pools& pools, size_t row0, int jb, int count, int lane,
-                                             PfRaw<SALI_TIER_FP16>& r) {
-#pragma unroll
-    for (int u = 0; u < 8; ++u) {
-        const int idx = u * 64 + lane;
-        const size_t frow = row0 + (size_t)min(jb + (idx >> 4), count - 1);
-        r.c[u] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(pools.p16 + frow * kHeadDim) + (idx & 15));
-    }
-}
-__device__ __forceinline__ void pf_load_tile(const Pools& pools, size_t row0, int jb, int count, int lane,
-                                             PfRaw<SALI_TIER_INT8>& r) {
-#pragma unroll
-    for (int u = 0; u < 4; ++u) {
-        const int idx = u * 64 + lane;
-        const size_t frow = row0 + (size_t)min(jb + (idx >> 3), count - 1);
-        r.c[u] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(pools.c8 + frow * kHeadDim) + (idx & 7));
-        r.sc[u] = pools.s8[frow * kGroupsPerRow + ((idx & 7) >> 1)];
-    }
-}
-__device__ __forceinline__ void pf_load_tile(const Pools& pools, size_t row0, int jb, int count, int lane,
-                                             PfRaw<SALI_TIER_INT4>& r) {
-#pragma unroll
-    for (int u = 0; u < 2; ++u) {
-        const int idx = u * 64 + lane;
-        const size_t frow = row0 + (size_t)min(jb + (idx >> 2), count - 1);
-        r.c[u] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(pools.c4 + frow * (kHeadDim / 2)) + (idx & 3));
-        r.sc[u] = pools.s4[frow * kGroupsPerRow + (idx & 3)];
-        r.zp[u] = (float)__builtin_bit_cast(_Float16, pools.z4[frow * kGroupsPerRow + (idx & 3)]);
-    }
-}
+__device__ __forceinline__ int pf_tiles(int rows) { return (rows + kPfRows - 1) / kPfRows; }
 
-// dequantise the lane's pieces and put them where they belong in the LDS tile
-__device__ __forceinline__ void pf_store_tile(const PfRaw<SALI_TIER_FP16>& r, int lane, _Float16 (*tile)[kPfVStride]) {
+// A tile of 32 pool rows as it comes from memory, a lane's share: 16-byte pieces of codes, consecutive
+// lanes reading consecutive memory (a lane-per-row pattern, which the matrix-core operands would suggest,
+// was measured at 1.6 TB/s), and the scales / zero-points of their groups.  Rows past the end of
+// the run repeat its last row (their softmax weight is zero).
+struct PfRaw {
+    u32x4 c[8];                 // FP16: 8 x 8 values.  INT8: 4 x 16 codes, scales in c[4].  INT4: 2 x 32 codes,
+};                              // scales in c[2].xy, zero-points in c[2].zw
+
+struct PfRows {                 // the rows of one tier of one frame and plane
+    const char* codes;
+    const float* scale;
+    const uint16_t* zero;
+};
+
+__device__ __forceinline__ void pf_load_tile(int tier, const PfRows& src, int jb, int count, int lane, PfRaw& r) {
+    const int last = count - 1;
+    if (tier == SALI_TIER_FP16) {
 #pragma unroll
-    for (int u = 0; u < 8; ++u) {
-        const int idx = u * 64 + lane;
-        *reinterpret_cast<u32x4*>(&tile[idx >> 4][8 * (idx & 15)]) = r.c[u];
-    }
-}
-__device__ __forceinline__ void pf_store_tile(const PfRaw<SALI_TIER_INT8>& r, int lane, _Float16 (*tile)[kPfVStride]) {
-#pragma unroll
-    for (int u = 0; u < 4; ++u) {
-        const int idx = u * 64 + lane;
-        Half8 o[2];
-#pragma unroll
-        for (int w = 0; w < 4; ++w) {
-            const uint32_t word = w == 0 ? r.c[u].x : (w == 1 ? r.c[u].y : (w == 2 ? r.c[u].z : r.c[u].w));
-#pragma unroll
-            for (int i = 0; i < 4; ++i)
-                o[w >> 1].h[4 * (w & 1) + i] = (_Float16)((float)(int)(int8_t)((word >> (8 * i)) & 0xFF) * r.sc[u]);
+        for (int u = 0; u < 8; ++u) {
+            const uint32_t row = (uint32_t)min(jb + 4 * u + (lane >> 4), last);
+            r.c[u] = __builtin_nontemporal_load(
+                reinterpret_cast<const u32x4*>(src.codes + (row * (uint32_t)(kHeadDim * 2) + (uint32_t)(lane & 15) * 16u)));
         }
-        u32x4* dst = reinterpret_cast<u32x4*>(&tile[idx >> 3][16 * (idx & 7)]);
-        dst[0] = o[0].u;
-        dst[1] = o[1].u;
+    } else if (tier == SALI_TIER_INT8) {
+        float sc[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const uint32_t row = (uint32_t)min(jb + 8 * u + (lane >> 3), last);
+            r.c[u] = __builtin_nontemporal_load(
+                reinterpret_cast<const u32x4*>(src.codes + (row * (uint32_t)kHeadDim + (uint32_t)(lane & 7) * 16u)));
+            sc[u] = src.scale[row * (uint32_t)kGroupsPerRow + (uint32_t)((lane & 7) >> 1)];
+        }
+        r.c[4] = (u32x4){__builtin_bit_cast(uint32_t, sc[0]), __builtin_bit_cast(uint32_t, sc[1]),
+                         __builtin_bit_cast(uint32_t, sc[2]), __builtin_bit_cast(uint32_t, sc[3])};
+    } else {
+        float sc[2];
+        uint32_t zp[2];
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+            const uint32_t row = (uint32_t)min(jb + 16 * u + (lane >> 2), last);
+            r.c[u] = __builtin_nontemporal_load(
+                reinterpret_cast<const u32x4*>(src.codes + (row * (uint32_t)(kHeadDim / 2) + (uint32_t)(lane & 3) * 16u)));
+            sc[u] = src.scale[row * (uint32_t)kGroupsPerRow + (uint32_t)(lane & 3)];
+            zp[u] = src.zero[row * (uint32_t)kGroupsPerRow + (uint32_t)(lane & 3)];
+        }
+        r.c[2] = (u32x4){__builtin_bit_cast(uint32_t, sc[0]), __builtin_bit_cast(uint32_t, sc[1]), zp[0], zp[1]};
     }
 }
-__device__ __forceinline__ void pf_store_tile(const PfRaw<SALI_TIER_INT4>& r, int lane, _Float16 (*tile)[kPfVStride]) {
+
+// dequantise the lane's pieces and put them where they belong in the LDS tile [32 rows][kStride halves]
+template <int kStride>
+__device__ __forceinline__ void pf_store_tile(int tier, const PfRaw& r, int lane, _Float16* tile) {
+    if (tier == SALI_TIER_FP16) {
+        u32x4* dst = reinterpret_cast<u32x4*>(tile + (lane >> 4) * kStride + 8 * (lane & 15));
 #pragma unroll
-    for (int u = 0; u < 2; ++u) {
-        const int idx = u * 64 + lane;
-        u32x4* dst = reinterpret_cast<u32x4*>(&tile[idx >> 2][32 * (idx & 3)]);
+        for (int u = 0; u < 8; ++u) dst[u * (4 * kStride / 8)] = r.c[u];
+    } else if (tier == SALI_TIER_INT8) {
+        u32x4* dst = reinterpret_cast<u32x4*>(tile + (lane >> 3) * kStride + 16 * (lane & 7));
 #pragma unroll
-        for (int w = 0; w < 4; ++w) {                               // 8 values = one word of codes
-            const uint32_t word = w == 0 ? r.c[u].x : (w == 1 ? r.c[u].y : (w == 2 ? r.c[u].z : r.c[u].w));
-            // nibbles to bytes first (even elements in one word, odd ones in another): a byte converts to
-            // fp32 in one instruction, a nibble needs a shift and a mask each
-            uint32_t ev = word & 0x0F0F0F0Fu, od = (word >> 4) & 0x0F0F0F0Fu;
-            asm volatile("" : "+v"(ev), "+v"(od));      // (keeps the compiler from folding the bytes back into nibbles)
-            Half8 o;
+        for (int u = 0; u < 4; ++u) {
+            const uint32_t sbits = r.c[4][u];           // (a copy: bit_cast of a vector element reads element 0)
+            const float sc = __builtin_bit_cast(float, sbits);
+            Half8 o[2];
 #pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                o.h[2 * i] = (_Float16)__builtin_fmaf((float)((ev >> (8 * i)) & 0xFFu), r.sc[u], r.zp[u]);
-                o.h[2 * i + 1] = (_Float16)__builtin_fmaf((float)((od >> (8 * i)) & 0xFFu), r.sc[u], r.zp[u]);
+            for (int w = 0; w < 4; ++w) {
+                const uint32_t word = r.c[u][w];
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+                    o[w >> 1].h[4 * (w & 1) + i] = (_Float16)((float)(int)(int8_t)((word >> (8 * i)) & 0xFF) * sc);
             }
-            dst[w] = o.u;
+            dst[u * (8 * kStride / 8)] = o[0].u;
+            dst[u * (8 * kStride / 8) + 1] = o[1].u;
+        }
+    } else {
+        u32x4* dst = reinterpret_cast<u32x4*>(tile + (lane >> 2) * kStride + 32 * (lane & 3));
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+            const uint32_t sbits = r.c[2][u], zbits = r.c[2][2 + u];
+            const float sc = __builtin_bit_cast(float, sbits);
+            const float zp = (float)__builtin_bit_cast(_Float16, (uint16_t)zbits);
+#pragma unroll
+            for (int w = 0; w < 4; ++w) {                           // 8 values = one word of codes
+                const uint32_t word = r.c[u][w];
+                // nibbles to bytes first (even elements in one word, odd ones in another): a byte converts to
+                // fp32 in one instruction, a nibble needs a shift and a mask each
+                uint32_t ev = word & 0x0F0F0F0Fu, od = (word >> 4) & 0x0F0F0F0Fu;
+                asm volatile("" : "+v"(ev), "+v"(od));  // (keeps the compiler from folding the bytes back into nibbles)
+                Half8 o;
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    o.h[2 * i] = (_Float16)__builtin_fmaf((float)((ev >> (8 * i)) & 0xFFu), sc, zp);
+                    o.h[2 * i + 1] = (_Float16)__builtin_fmaf((float)((od >> (8 * i)) & 0xFFu), sc, zp);
+                }
+                dst[u * (16 * kStride / 8) + w] = o.u;
+            }
         }
     }
 }
-
-struct PfState {
-    float mx, lsum;
-    float16_t acc[4];           // acc[dt][r] = out[m][32 dt + 8 (r / 4) + 4 hh + r % 4], not yet normalised
-};
 
 // LDS operations of one wave execute in order, so the wave's private tiles need no barrier, only
 // that the compiler keeps the order
@@ -533,164 +548,276 @@ __device__ __forceinline__ void pf_lds_order() {
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-// the tiles of one tier of one stored frame that fall to this wave
-template <int kTier>
-__device__ __forceinline__ void pf_tier(const Pools& pools, size_t plane_k, size_t plane_v, int base, int count,
-                                        int split, int n_splits, int lane, const _Float16 (*s_q)[kPfVStride],
-                                        float softmax_scale, float mult, _Float16 (*s_t)[kPfVStride], PfState& st) {
-    const int m = lane & 31, hh = lane >> 5;
-    const size_t row0_k = pool_row0(pools, base, count, plane_k), row0_v = pool_row0(pools, base, count, plane_v);
-    // Software pipeline: the loads of the next tile are in flight while this one is worked on (K^ rows
-    // are asked for as soon as this tile's K^ registers have gone to LDS, V^ rows likewise), and they are
-    // issued without a branch: past the end of the run every row index clamps to the run's last row, one
-    // cache line.  Without it the waves of the chip run in step, all waiting for memory and then all
-    // computing, and the kernel takes the sum of the two times instead of the larger.
-    const int step = n_splits * kPfRows;
-    int jb = split * kPfRows;
-    if (jb >= count) return;
-    PfRaw<kTier> rk, rv;
-    pf_load_tile(pools, row0_k, jb, count, lane, rk);
-    pf_load_tile(pools, row0_v, jb, count, lane, rv);
-    for (; jb < count; jb += step) {
-        pf_lds_order();                                            // the previous tile's reads are done
-        pf_store_tile(rk, lane, s_t);
-        pf_lds_order();
-        pf_load_tile(pools, row0_k, jb + step, count, lane, rk);
-        // S^T = K^ Q^T with v_mfma_f32_32x32x16_f16 (A[i][k]: lane = i + 32 (k / 8), element k % 8; B alike;
-        // D[i][j]: lane = j + 32 hh, register r holds i = 8 (r / 4) + 4 hh + r % 4).  Lane (row m, half hh),
-        // step t: values 64 hh + 8 t .. + 7 of the row; the queries use the same assignment
-        float16_t s;
-#pragma unroll
-        for (int r = 0; r < 16; ++r) s[r] = 0.0f;
-#pragma unroll
-        for (int t = 0; t < 8; ++t) {
-            const half8_t ka = *reinterpret_cast<const half8_t*>(&s_t[m][64 * hh + 8 * t]);
-            const half8_t qb = *reinterpret_cast<const half8_t*>(&s_q[m][64 * hh + 8 * t]);
-            s = __builtin_amdgcn_mfma_f32_32x32x16_f16(ka, qb, s, 0, 0, 0);
-        }
-        // s[r] = <K^ row jb + n(r), query m>, n(r) = 8 (r / 4) + 4 hh + r % 4
-        float tmax = -INFINITY;
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-            const int n = 8 * (r / 4) + 4 * hh + (r % 4);
-            s[r] = (jb + n < count) ? s[r] * softmax_scale : -INFINITY;
-            tmax = fmaxf(tmax, s[r]);
-        }
-        tmax = fmaxf(tmax, __shfl_xor(tmax, 32));
-        const float mnew = fmaxf(st.mx, tmax);
-        const float corr = __expf(st.mx - mnew);
-        float psum = 0.0f;
-        // the softmax weights in the order the second product wants them: step jj of two, element e of the
-        // lane's eight = row 16 jj + 8 (e / 4) + 4 hh + e % 4 of the tile, which is register 8 jj + e
-        half8_t pb[2];
-#pragma unroll
-        for (int jj = 0; jj < 2; ++jj)
-#pragma unroll
-            for (int e = 0; e < 8; ++e) {
-                const float p = mult * __expf(s[8 * jj + e] - mnew);
-                psum += p;
-                pb[jj][e] = (_Float16)p;
-            }
-        psum += __shfl_xor(psum, 32);
-        st.lsum = st.lsum * corr + psum;
-        st.mx = mnew;
-        // the 64 accumulators are rescaled only when some query of the wave saw a new maximum (rare after
-        // the first tiles); the test is wave-uniform
-        if (__builtin_amdgcn_ballot_w64(corr != 1.0f) != 0) {
-#pragma unroll
-            for (int dt = 0; dt < 4; ++dt)
-#pragma unroll
-                for (int r = 0; r < 16; ++r) st.acc[dt][r] *= corr;
-        }
-        // out^T += V^^T P^T: A operand lane (value d = 32 dt + m, half hh): the same eight rows of column d
-        pf_lds_order();                                            // the K^ reads come first: same tile
-        pf_store_tile(rv, lane, s_t);
-        pf_lds_order();
-        pf_load_tile(pools, row0_v, jb + step, count, lane, rv);
-#pragma unroll
-        for (int dt = 0; dt < 4; ++dt)
-#pragma unroll
-            for (int jj = 0; jj < 2; ++jj) {
-                half8_t va;
-#pragma unroll
-                for (int e = 0; e < 8; ++e) va[e] = s_t[16 * jj + 8 * (e / 4) + 4 * hh + (e % 4)][32 * dt + m];
-                st.acc[dt] = __builtin_amdgcn_mfma_f32_32x32x16_f16(va, pb[jj], st.acc[dt], 0, 0, 0);
-            }
+// Four rows x 16 columns of halves, transposed: the 16 lanes of a group give the addresses of the four rows'
+// 8-byte pieces (lane i: row i / 4, columns 4 (i % 4) ..), lane i receives column i of the four rows.
+__device__ __forceinline__ half4_t pf_read_transposed(const _Float16* p) {
+    typedef __attribute__((address_space(3))) short4_t lds_short4;
+    const short4_t v = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_short4*)(p));
+    return __builtin_bit_cast(half4_t, v);
+}
+
+// ONE wave: the frames g0 .. g0 + 63 (below f_end) that bring tiles into the block's share, as a list in
+// `list`; returns its length and, in n_tiles, the tiles.  The share of block `part` of `parts` is the
+// stretch [part * n, (part + 1) * n) of the range's n frames in units of 1 / parts frame, a frame's part of
+// it the same fraction of its tiles: every tile belongs to exactly one block, and with frames of like size
+// the blocks get equal work.
+// A stored frame counts for itself and for the redundant frames behind it (up to the next stored frame or
+// the end of the range); redundant frames at the head of the range, whose source lies before it, are
+// counted at the first of them.
+__device__ __forceinline__ int pf_list_frames(const sali_frame_row* __restrict__ rows, int frame_lo, int frame_hi, int g0,
+                                              int f_end, int part, int parts, int lane, int* s_src, PfFrame* list,
+                                              int* n_tiles) {
+    const int f = g0 + lane, g_end = min(f_end, g0 + kPfGroup);
+    const bool valid = f < g_end;
+    sali_frame_row row = {};
+    row.src = -1;
+    if (valid) row = rows[f];
+    const bool stored = valid && row.stored != 0;
+    s_src[lane] = row.src;
+    pf_lds_order();
+    const unsigned long long stored_mask = __ballot(stored);
+    bool leader = stored;
+    const int src = row.src;
+    if (valid && !stored && src >= 0 && src < frame_lo) {
+        leader = true;
+        for (int t = frame_lo; t < f; ++t)
+            if (rows[t].src == src) leader = false;          // an earlier frame of the run counts them
     }
+    int n_uses = 1;
+    if (leader) {
+        const unsigned long long behind = lane == 63 ? 0ull : stored_mask >> (lane + 1);
+        const int run_end = behind != 0ull ? f + 1 + __builtin_ctzll(behind) : g_end;
+        for (int t = f + 1; t < run_end; ++t)
+            if (s_src[t - g0] == src) ++n_uses;
+        if (behind == 0ull)
+            for (int t = g_end; t < frame_hi && rows[t].stored == 0; ++t)
+                if (rows[t].src == src) ++n_uses;
+        if (!stored) row = rows[src];
+    }
+    int i0 = 0, cnt = 0;
+    if (leader) {
+        const long long n = frame_hi - frame_lo, at = (long long)(f - frame_lo) * parts;
+        const long long lo = max(0ll, part * n - at), hi = min((long long)parts, (part + 1) * n - at);
+        const int t = pf_tiles(row.n16) + pf_tiles(row.n8) + pf_tiles(row.n4);
+        if (hi > lo) {
+            i0 = (int)(t * lo / parts);
+            cnt = (int)(t * hi / parts) - i0;
+        }
+    }
+    int incl = cnt;
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+        const int v = __shfl_up(incl, off);
+        if (lane >= off) incl += v;
+    }
+    const unsigned long long use = __ballot(cnt > 0);
+    if (cnt > 0) {
+        PfFrame e;
+        e.start = incl - cnt;
+        e.i0 = i0;
+        e.base[0] = row.base16;
+        e.base[1] = row.base8;
+        e.base[2] = row.base4;
+        e.n[0] = row.n16;
+        e.n[1] = row.n8;
+        e.n[2] = row.n4;
+        e.mult = (float)n_uses;
+        list[__popcll(use & (lane == 0 ? 0ull : (~0ull >> (64 - lane))))] = e;
+    }
+    *n_tiles = __shfl(incl, 63);
+    return (int)__popcll(use);
 }
 
 }  // namespace
 
-// grid (ceil(n_partials / 4), n_heads, ceil(q_per_kv / 32)), 256 threads = four independent waves
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_attn_prefill(const sali_frame_row* __restrict__ rows, Pools pools, int layer,
-                                                      int n_heads, const _Float16* __restrict__ q, int q_per_kv,
-                                                      int frame_lo, int frame_hi, int frames_per_chunk, int n_splits,
-                                                      int n_partials, float softmax_scale, float* __restrict__ partial) {
-    __shared__ __align__(16) _Float16 s_q[32][kPfVStride];               // the block's 32 queries (zeros past q_per_kv)
-    __shared__ __align__(16) _Float16 s_t_all[4][kPfRows][kPfVStride];   // one K^ / V^ tile per wave
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+// grid (parts of the frame range, n_heads, ceil(q_per_kv / 32)), 512 threads
+__global__ __launch_bounds__(64 * kPfWaves) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_attn_prefill(
+    const sali_frame_row* __restrict__ rows, Pools pools, int layer, int n_heads, const _Float16* __restrict__ q,
+    int q_per_kv, int frame_lo, int frame_hi, float softmax_scale, float* __restrict__ partial) {
+    __shared__ __align__(16) _Float16 s_tiles[kPfWaves][kPfTileHalves];     // a K^ and a V^ tile per wave; the results at the end
+    __shared__ PfFrame s_list[kPfGroup];
+    __shared__ int s_src[kPfGroup];
+    __shared__ int s_n[2];
+    __shared__ float s_m[kPfWaves][32], s_l[kPfWaves][32];
+    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)), lane = threadIdx.x & 63;
     const int m = lane & 31, hh = lane >> 5;
-    const int h = blockIdx.y;
-    for (int idx = threadIdx.x; idx < 32 * 16; idx += 256) {
-        const int qrow = idx >> 4, piece = idx & 15;
-        const int qq = (int)blockIdx.z * 32 + qrow;
-        u32x4 v = (u32x4){0u, 0u, 0u, 0u};
-        if (qq < q_per_kv) v = reinterpret_cast<const u32x4*>(q + ((size_t)h * q_per_kv + qq) * kHeadDim)[piece];
-        *reinterpret_cast<u32x4*>(&s_q[qrow][8 * piece]) = v;
-    }
-    __syncthreads();
-    const int item = (int)blockIdx.x * 4 + wave;
-    if (item >= n_partials) return;
-    const int chunk = item / n_splits, split = item % n_splits;
+    const int h = blockIdx.y, part = blockIdx.x, parts = gridDim.x;
     const int qi = (int)blockIdx.z * 32 + m;                 // this lane's query among the q_per_kv of the K/V head
-    const bool q_valid = qi < q_per_kv;
-    const size_t q_head = (size_t)h * q_per_kv + (q_valid ? qi : 0);
     const size_t plane_k = ((size_t)layer * 2 + 0) * n_heads + h;
     const size_t plane_v = ((size_t)layer * 2 + 1) * n_heads + h;
+    _Float16* s_k = s_tiles[wave];
+    _Float16* s_v = s_k + kPfRows * kPfKStride;
 
-    PfState st;
-    st.mx = -INFINITY;
-    st.lsum = 0.0f;
+    // the queries stay in registers, as the B operand wants them (zeros past q_per_kv)
+    half8_t qb[8];
+#pragma unroll
+    for (int t = 0; t < 8; ++t) {
+        Half8 v;
+        v.u = (u32x4){0u, 0u, 0u, 0u};
+        if (qi < q_per_kv) v.u = reinterpret_cast<const u32x4*>(q + ((size_t)h * q_per_kv + qi) * kHeadDim + 64 * hh)[t];
+        qb[t] = v.h8;
+    }
+    const float scale2 = softmax_scale * 1.44269504088896340736f;      // scores in units of log 2 from here on
+    float mx = -INFINITY, lsum = 0.0f;
+    float16_t acc[4];           // acc[dt][r] = out[m][32 dt + 8 (r / 4) + 4 hh + r % 4], not yet normalised
 #pragma unroll
     for (int dt = 0; dt < 4; ++dt)
 #pragma unroll
-        for (int r = 0; r < 16; ++r) st.acc[dt][r] = 0.0f;
+        for (int r = 0; r < 16; ++r) acc[dt][r] = 0.0f;
 
-    const int f0 = frame_lo + chunk * frames_per_chunk;
-    const int f1 = min(frame_hi, f0 + frames_per_chunk);
-    for (int f = f0; f < f1; ++f) {
-        // which stored frame frame f brings in, and how often: as in k_attn_partial
-        const sali_frame_row r = rows[f];
-        bool leader = r.stored != 0;
-        if (!leader && r.src >= 0 && r.src < frame_lo) {
-            leader = true;
-            for (int t = frame_lo; t < f; ++t)
-                if (rows[t].src == r.src) leader = false;
+    const long long n_range = frame_hi - frame_lo;
+    const int f_begin = frame_lo + (int)(part * n_range / parts);
+    const int f_end = frame_lo + (int)(((part + 1) * n_range + parts - 1) / parts);
+    for (int g0 = f_begin; g0 < f_end; g0 += kPfGroup) {
+        if (g0 != f_begin) __syncthreads();                 // every wave is through with the list
+        if (wave == 0) {
+            int n_tiles;
+            const int len = pf_list_frames(rows, frame_lo, frame_hi, g0, f_end, part, parts, lane, s_src, s_list, &n_tiles);
+            if (lane == 0) {
+                s_n[0] = len;
+                s_n[1] = n_tiles;
+            }
         }
-        if (!leader) continue;
-        const int src = r.src;
-        int n_uses = 1;
-        for (int t = f + 1; t < frame_hi && rows[t].stored == 0; ++t)
-            if (rows[t].src == src) ++n_uses;
-        const float mult = (float)n_uses;
-        const sali_frame_row row = rows[src];
-        pf_tier<SALI_TIER_FP16>(pools, plane_k, plane_v, row.base16, row.n16, split, n_splits, lane, s_q, softmax_scale, mult,
-                                s_t_all[wave], st);
-        pf_tier<SALI_TIER_INT8>(pools, plane_k, plane_v, row.base8, row.n8, split, n_splits, lane, s_q, softmax_scale, mult,
-                                s_t_all[wave], st);
-        pf_tier<SALI_TIER_INT4>(pools, plane_k, plane_v, row.base4, row.n4, split, n_splits, lane, s_q, softmax_scale, mult,
-                                s_t_all[wave], st);
+        __syncthreads();
+        const int len = __builtin_amdgcn_readfirstlane(s_n[0]), n_tiles = __builtin_amdgcn_readfirstlane(s_n[1]);
+        int e = 0;                                          // list entry of the tile in flight
+        // tile `g` of the block's sequence: its tier and rows, all uniform over the wave
+        int tier = 0, jb = 0, count = 0;
+        float mult = 1.0f;
+        PfRaw rk, rv;
+        auto request = [&](int g) {
+            while (e + 1 < len && g >= __builtin_amdgcn_readfirstlane(s_list[e + 1].start)) ++e;
+            const PfFrame& fr = s_list[e];
+            int i = __builtin_amdgcn_readfirstlane(fr.i0 + g - fr.start);
+            const int n0 = __builtin_amdgcn_readfirstlane(fr.n[0]), n1 = __builtin_amdgcn_readfirstlane(fr.n[1]);
+            const int t0 = pf_tiles(n0), t1 = pf_tiles(n1);
+            tier = i < t0 ? SALI_TIER_FP16 : (i < t0 + t1 ? SALI_TIER_INT8 : SALI_TIER_INT4);
+            i -= tier == SALI_TIER_FP16 ? 0 : (tier == SALI_TIER_INT8 ? t0 : t0 + t1);
+            jb = i * kPfRows;
+            count = __builtin_amdgcn_readfirstlane(fr.n[tier]);
+            mult = __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, fr.mult)));
+            const int base = __builtin_amdgcn_readfirstlane(fr.base[tier]);
+            const size_t row_k = pool_row0(pools, base, count, plane_k), row_v = pool_row0(pools, base, count, plane_v);
+            const char* codes = tier == SALI_TIER_FP16 ? reinterpret_cast<const char*>(pools.p16)
+                                : tier == SALI_TIER_INT8 ? reinterpret_cast<const char*>(pools.c8)
+                                                         : reinterpret_cast<const char*>(pools.c4);
+            const uint32_t row_bytes = tier == SALI_TIER_FP16 ? kHeadDim * 2 : (tier == SALI_TIER_INT8 ? kHeadDim : kHeadDim / 2);
+            const float* scale = tier == SALI_TIER_INT8 ? pools.s8 : pools.s4;
+            const PfRows k = {codes + row_k * row_bytes, scale + row_k * kGroupsPerRow, pools.z4 + row_k * kGroupsPerRow};
+            const PfRows v = {codes + row_v * row_bytes, scale + row_v * kGroupsPerRow, pools.z4 + row_v * kGroupsPerRow};
+            pf_load_tile(tier, k, jb, count, lane, rk);
+            pf_load_tile(tier, v, jb, count, lane, rv);
+        };
+        if (wave < n_tiles) request(wave);
+        for (int g = wave; g < n_tiles; g += kPfWaves) {
+            pf_lds_order();                                 // the previous tile's reads are done
+            pf_store_tile<kPfKStride>(tier, rk, lane, s_k);
+            pf_store_tile<kPfVStride>(tier, rv, lane, s_v);
+            pf_lds_order();
+            const int left = count - jb;                    // rows of this tile that exist
+            const float times = mult;
+            if (g + kPfWaves < n_tiles) request(g + kPfWaves);      // in flight while this tile is worked on
+
+            // S^T = K^ Q^T with v_mfma_f32_32x32x16_f16 (A[i][k]: lane = i + 32 (k / 8), element k % 8; B alike;
+            // D[i][j]: lane = j + 32 hh, register r holds i = 8 (r / 4) + 4 hh + r % 4).  Lane (row m, half hh),
+            // step t: values 64 hh + 8 t .. + 7 of the row; the queries use the same assignment
+            float16_t s;
+#pragma unroll
+            for (int r = 0; r < 16; ++r) s[r] = 0.0f;
+#pragma unroll
+            for (int t = 0; t < 8; ++t) {
+                const half8_t ka = *reinterpret_cast<const half8_t*>(s_k + m * kPfKStride + 64 * hh + 8 * t);
+                s = __builtin_amdgcn_mfma_f32_32x32x16_f16(ka, qb[t], s, 0, 0, 0);
+            }
+            // s[r] = <K^ row jb + n(r), query m>, n(r) = 8 (r / 4) + 4 hh + r % 4
+#pragma unroll
+            for (int r = 0; r < 16; ++r) s[r] *= scale2;
+            if (left < kPfRows) {
+#pragma unroll
+                for (int r = 0; r < 16; ++r)
+                    if (8 * (r / 4) + 4 * hh + (r % 4) >= left) s[r] = -INFINITY;
+            }
+            float tmax = s[0];
+#pragma unroll
+            for (int r = 1; r < 16; ++r) tmax = fmaxf(tmax, s[r]);
+            tmax = fmaxf(tmax, __shfl_xor(tmax, 32));
+            const float mnew = fmaxf(mx, tmax);
+            const float corr = __builtin_amdgcn_exp2f(mx - mnew);
+            // the softmax weights in the order the second product wants them: step jj of two, element e of the
+            // lane's eight = row 16 jj + 8 (e / 4) + 4 hh + e % 4 of the tile, which is register 8 jj + e
+            float psum = 0.0f;
+#pragma unroll
+            for (int r = 0; r < 16; ++r) s[r] = __builtin_amdgcn_exp2f(s[r] - mnew);
+            if (times != 1.0f) {
+#pragma unroll
+                for (int r = 0; r < 16; ++r) s[r] *= times;
+            }
+            half8_t pb[2];
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+                psum += s[r];
+                pb[r >> 3][r & 7] = (_Float16)s[r];
+            }
+            psum += __shfl_xor(psum, 32);
+            lsum = lsum * corr + psum;
+            mx = mnew;
+            // the 64 accumulators are rescaled only when some query of the wave saw a new maximum (rare after
+            // the first tiles); the test is wave-uniform
+            if (__builtin_amdgcn_ballot_w64(corr != 1.0f) != 0) {
+#pragma unroll
+                for (int dt = 0; dt < 4; ++dt)
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) acc[dt][r] *= corr;
+            }
+            // out^T += V^^T P^T: A operand lane (value d = 32 dt + m, half hh): the same eight rows of column d
+            const _Float16* tr = s_v + (4 * hh + ((lane & 15) >> 2)) * kPfVStride + 16 * ((lane >> 4) & 1) + 4 * (lane & 3);
+#pragma unroll
+            for (int jj = 0; jj < 2; ++jj)
+#pragma unroll
+                for (int dt = 0; dt < 4; ++dt) {
+                    Half8 va;
+                    va.h4[0] = pf_read_transposed(tr + (16 * jj) * kPfVStride + 32 * dt);
+                    va.h4[1] = pf_read_transposed(tr + (16 * jj + 8) * kPfVStride + 32 * dt);
+                    acc[dt] = __builtin_amdgcn_mfma_f32_32x32x16_f16(va.h8, pb[jj], acc[dt], 0, 0, 0);
+                }
+        }
     }
-    if (!q_valid) return;
-    float* mine = partial + (q_head * (size_t)n_partials + item) * kPartialStride;
+
+    // the eight waves meet: each rescales to the block's maximum and leaves its 128 x 32 values in the
+    // memory of its own tiles, then every thread adds up eight outputs
     if (hh == 0) {
-        mine[0] = st.mx;
-        mine[1] = st.lsum;
+        s_m[wave][m] = mx;
+        s_l[wave][m] = lsum;
     }
+    __syncthreads();
+    float big = -INFINITY;
+#pragma unroll
+    for (int w = 0; w < kPfWaves; ++w) big = fmaxf(big, s_m[w][m]);
+    const float fac = mx == -INFINITY ? 0.0f : __builtin_amdgcn_exp2f(mx - big);
+    float* mine = reinterpret_cast<float*>(s_tiles[wave]);
 #pragma unroll
     for (int dt = 0; dt < 4; ++dt)
 #pragma unroll
-        for (int r = 0; r < 16; ++r) mine[2 + 32 * dt + 8 * (r / 4) + 4 * hh + (r % 4)] = st.acc[dt][r];
+        for (int r = 0; r < 16; ++r) mine[(32 * dt + 8 * (r / 4) + 4 * hh + (r % 4)) * kPfOutStride + m] = acc[dt][r] * fac;
+    __syncthreads();
+    for (int idx = threadIdx.x; idx < 32 * kHeadDim; idx += 64 * kPfWaves) {
+        const int mm = idx / kHeadDim, d = idx % kHeadDim;
+        const int qq = (int)blockIdx.z * 32 + mm;
+        if (qq >= q_per_kv) continue;
+        float sum = 0.0f;
+#pragma unroll
+        for (int w = 0; w < kPfWaves; ++w) sum += reinterpret_cast<const float*>(s_tiles[w])[d * kPfOutStride + mm];
+        float* dst = partial + (((size_t)h * q_per_kv + qq) * parts + part) * kPartialStride;
+        dst[2 + d] = sum;
+        if (d == 0) {
+            float top = -INFINITY, lt = 0.0f;
+            for (int w = 0; w < kPfWaves; ++w) top = fmaxf(top, s_m[w][mm]);
+            if (top != -INFINITY)
+                for (int w = 0; w < kPfWaves; ++w) lt += s_l[w][mm] * __builtin_amdgcn_exp2f(s_m[w][mm] - top);
+            dst[0] = top * 0.69314718055994530942f;
+            dst[1] = lt;
+        }
+    }
 }
 
 hipError_t launch_attend(const sali_frame_row* d_rows, Pools pools, int layer, int n_heads, int q_per_kv,
@@ -699,36 +826,19 @@ hipError_t launch_attend(const sali_frame_row* d_rows, Pools pools, int layer, i
     const int n_range = frame_hi - frame_lo;
     int n_partials = 0;
     if (n_range > 0 && q_per_kv > kAttnMaxQPerKv) {
-        // matrix-core path: 32 queries per wave; the scratch holds kAttnSlotsPerHead partials per K/V head,
-        // shared out over the q_per_kv query heads
-        // and one resident round of waves (kPfWavesPerSimd per SIMD: 2048 on the chip) is the target, as for the streaming kernel
-        int per_head = kAttnSlotsPerHead / q_per_kv;
-        const int round = (kPfWavesPerSimd * 4 * 256) / (n_heads * ((q_per_kv + 31) / 32));
-        per_head = per_head > round ? (round < 1 ? 1 : round) : per_head;
-        per_head = per_head > kAttnPartials ? kAttnPartials : per_head;
-        // work items = chunks of whole frames x row splits inside a frame; of the few ways to get close to
-        // per_head items take the one with the most items
-        int fpc = (n_range + per_head - 1) / per_head, n_chunks = 0, n_splits = 0;
-        for (int cand = fpc; cand <= fpc + 3; ++cand) {
-            const int chunks = (n_range + cand - 1) / cand;
-            int splits = per_head / chunks;
-            splits = splits < 1 ? 1 : (splits > kTokens / kPfRows ? kTokens / kPfRows : splits);
-            if (chunks * splits > n_chunks * n_splits && chunks * splits <= per_head) {
-                fpc = cand;
-                n_chunks = chunks;
-                n_splits = splits;
-            }
-        }
-        if (n_chunks == 0) {            // per_head below the number of chunks cannot happen (fpc covers the range)
-            n_chunks = (n_range + fpc - 1) / fpc;
-            n_splits = 1;
-        }
-        n_partials = n_chunks * n_splits;
+        // matrix-core path: one block of eight waves per compute unit, as many parts of the range as that
+        // gives a K/V head, but no more than leave every wave a tile (a frame has up to kTokens / kPfRows + 3),
+        // and no more partials than the scratch holds (kAttnSlotsPerHead per K/V head, shared out over its queries)
+        int parts = kComputeUnits / (n_heads * ((q_per_kv + 31) / 32));
+        const long long fill = ((long long)n_range * (kTokens / kPfRows + 3) + kPfWaves - 1) / kPfWaves;
+        if (parts > fill) parts = (int)fill;
+        if (parts > kAttnSlotsPerHead / q_per_kv) parts = kAttnSlotsPerHead / q_per_kv;
+        if (parts > kAttnPartials) parts = kAttnPartials;
+        n_partials = parts < 1 ? 1 : parts;
         if (ev_start != nullptr && hipEventRecord(ev_start, s) != hipSuccess) return hipErrorUnknown;
-        const dim3 grid((n_partials + 3) / 4, n_heads, (q_per_kv + 31) / 32);
-        hipLaunchKernelGGL(k_attn_prefill, grid, dim3(256), 0, s, d_rows, pools, layer, n_heads,
-                           reinterpret_cast<const _Float16*>(d_q), q_per_kv, frame_lo, frame_hi, fpc, n_splits, n_partials,
-                           softmax_scale, d_partial);
+        const dim3 grid(n_partials, n_heads, (q_per_kv + 31) / 32);
+        hipLaunchKernelGGL(k_attn_prefill, grid, dim3(64 * kPfWaves), 0, s, d_rows, pools, layer, n_heads,
+                           reinterpret_cast<const _Float16*>(d_q), q_per_kv, frame_lo, frame_hi, softmax_scale, d_partial);
         if (ev_stop != nullptr && hipEventRecord(ev_stop, s) != hipSuccess) return hipErrorUnknown;
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;

@@ -256,3 +256,60 @@ def test_attend_argument_checks():
     torch.cuda.synchronize()
     assert not out.cpu().numpy().any() and np.all(np.isneginf(lse.cpu().numpy()))
     ctx.close()
+
+
+@pytest.mark.parametrize("heads,q_per_kv,frames,counts", [
+    (1, 9, 1, (1, 0, 0)),            # fewer tiles than waves, one row
+    (2, 33, 2, (31, 32, 33)),        # tile edges; a second query tile with one query
+    (3, 64, 5, (0, 65, 0)),          # one tier only
+    (64, 10, 200, (3, 2, 2)),        # four parts of the range: a block looks up more than 64 frames
+    (64, 40, 200, (33, 0, 1)),       # two parts, two query tiles
+])
+def test_many_queries_shares_of_the_range_and_pointer_runs(heads, q_per_kv, frames, counts):
+    """The matrix-core path where its split of the work has edges: tiles with few rows, blocks whose share
+    begins or ends inside a frame, more frames than are looked up at a time, runs of pointer frames across
+    those limits and at the head of the range.  Reference: float64 attention over the values dequantise-on-
+    read returns (the path's own operands), every frame counted as often as it is used.  What is left are
+    the fp16 rounding of the softmax weights (2^-11 relative, 2^-25 absolute below the normal numbers) and
+    fp32 accumulation (1e-5 relative covers n <= 50 000 rows' worth of it)."""
+    from paper_2602_14236_amd import binding
+    k16, k8, k4 = counts
+    p = params(96, 96, tier_mode=1, k_fp16=k16, k_int8=k8, k_int4=k4, n_layers=1, n_heads=heads,
+               cap_fp16=max(1, k16 * frames), cap_int8=max(1, k8 * frames), cap_int4=max(1, k4 * frames), max_frames=frames)
+    ctx = binding.SaliContext(lib_config(p))
+    g = torch.Generator(device="cuda").manual_seed(heads + frames)
+    stored_at = [t for t in range(frames) if t in (0, 1) or t % 97 in (3, 4, 60, 63, 64)]
+    rgb = torch.randint(0, 256, (96, 96, 3), generator=g, device="cuda", dtype=torch.uint8)
+    for t in range(frames):
+        # every frame with a predecessor is redundant under the first setting, none under the second
+        ctx.set_gate_thresholds(*((1.0, 2.0) if t in stored_at else (1e9, 0.0)))
+        kv = torch.randn((1, 2, heads, 576, 128), generator=g, device="cuda").to(torch.float16)
+        ctx.step(rgb, kv, t)
+    rows = ctx.read_frame_table(0, frames)
+    assert [t for t in range(frames) if rows[t].stored] == stored_at
+    dense, kept = {}, {}
+    for t in stored_at:
+        out, valid = torch.empty((1, 2, heads, 576, 128), dtype=torch.float16, device="cuda"), torch.empty(576, dtype=torch.uint8, device="cuda")
+        ctx.kv_decompress(t, out, valid)
+        kept[t] = valid.nonzero().flatten()
+        dense[t] = out[0][:, :, kept[t]].double()
+    q = torch.randn((heads * q_per_kv, 128), generator=g, device="cuda").to(torch.float16)
+    sm = 128.0 ** -0.5
+    got, lse = torch.empty((heads * q_per_kv, 128), device="cuda"), torch.empty(heads * q_per_kv, device="cuda")
+    for lo, hi in ((0, frames), (min(2, frames - 1), frames), (frames // 3, frames - frames // 4)):
+        ctx.attend_decode_gqa(0, q, q_per_kv, lo, hi, sm, got, lse)
+        uses = [rows[t].src for t in range(lo, hi)]
+        k = torch.cat([dense[t][0] for t in sorted(set(uses))], dim=1)
+        v = torch.cat([dense[t][1] for t in sorted(set(uses))], dim=1)
+        mult = torch.cat([torch.full((len(kept[t]),), float(uses.count(t)), dtype=torch.float64, device="cuda") for t in sorted(set(uses))])
+        s = torch.bmm(q.double().view(heads, q_per_kv, 128), k.transpose(1, 2).contiguous()) * sm + mult.log()
+        pr = torch.softmax(s, dim=-1)
+        exp, exp_lse = torch.bmm(pr, v).reshape(-1, 128), torch.logsumexp(s, dim=-1).reshape(-1)
+        top = pr.amax(-1, keepdim=True)
+        bound = (2.0 ** -11 + 1e-5) * torch.bmm(pr, v.abs()) + 2.0 ** -24 * top * v.abs().sum(1, keepdim=True)
+        err = (got.double() - exp).abs()
+        print(f"heads {heads} q {q_per_kv} frames [{lo}, {hi}): largest error / bound {(err / bound.reshape(-1, 128)).max():.3f}", flush=True)
+        assert bool((err <= bound.reshape(-1, 128)).all())
+        assert bool(((lse.double() - exp_lse).abs() <= 1e-5 * (1 + exp_lse.abs())).all())
+    assert ctx.get_status() == 0
+    ctx.close()
