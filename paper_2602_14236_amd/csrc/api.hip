@@ -49,7 +49,6 @@ struct TableLayout {
 };
 
 struct LaneCounters {         // arrival counters, all self-resetting
-    uint32_t patch_done;      // blocks of the stand-alone patch-motion kernel
     uint32_t skip;            // the saliency pre-pass found the lane's frame redundant (not a counter: a flag)
     uint32_t batch_done;      // frames of a pooling launch whose first frame sits in this lane
 };
@@ -237,7 +236,7 @@ __global__ void k_reset(Cursors* cur, sali_frame_row* rows, int max_frames, Lane
             lanes.lane[l].msum[1] = 0ull;
             sali_gate g = {0, 0.0f, 0, 0};
             *lanes.lane[l].gate = g;
-            LaneCounters z = {0u, 0u, 0u};
+            LaneCounters z = {0u, 0u};
             *lanes.lane[l].counters = z;
         }
     }
@@ -746,7 +745,7 @@ int sali_flow_score(sali_ctx* c, const uint8_t* d_prev_rgb, const uint8_t* d_cur
     rc = enqueue_flow(c, pb, &flow, s);
     if (rc != SALI_OK) return rc;
     SALI_TRY(launch_patch_gate(flow, c->cfg.src_h, c->cfg.src_w, c->cfg.tau_t, c->cfg.theta_r, d_patch_motion576,
-                               d_gate_out, &c->lane_ptrs(0).counters->patch_done, d_flow_uv_or_null, s));
+                               d_gate_out, d_flow_uv_or_null, s));
     return SALI_OK;
 }
 

@@ -19,9 +19,8 @@
 //                a chain of dependent HBM round trips, not a throughput limit (vector ALU 78 %,
 //                texture addresser 75 % busy at 1920x1080);
 //                tiles are handed to the XCDs in contiguous runs so that neighbours share an L2.
-//   k_patch_gate per patch RMS flow magnitude (Eq. 5); the last block to finish counts static
-//                patches and writes the gate (Eq. 6).  Stand-alone flow call only: the chained
-//                step does this inside the pooling kernel.
+//   k_patch_motion, k_gate   per patch RMS flow magnitude (Eq. 5); static patches counted, the gate (Eq. 6).
+//                Stand-alone flow call only: the chained step has them in its pooling kernels.
 //
 // The batched kernels take the frame as a grid dimension.  All stencils replicate the border.
 
@@ -598,50 +597,59 @@ __global__ __launch_bounds__(NT) void k_flow_iter(FlowBatch f, long long level_o
 }
 
 // ---------------------------------------------------------------------------------------------
-// Eq. 5 / Eq. 6.  One wave per patch, four patches per block of 256 threads (small blocks find
-// room next to other streams' kernels); the last block to finish evaluates the gate.
-constexpr int kGateBlocks = kTokens / 4;
-
-__global__ __launch_bounds__(256) void k_patch_gate(const float2* __restrict__ flow, int h, int w, float tau_t,
-                                                    float theta_r, float* dp_out, sali_gate* gate,
-                                                    uint32_t* done_counter, float* __restrict__ flow_uv) {
-    __shared__ int s_cnt[4];
-    __shared__ int s_last;
+// Eq. 5 of the stand-alone flow call: each patch's motion, and the flow field in the caller's layout (two
+// planes).  kWaves = 1: one wave per patch, four patches per block; kWaves = 4: the block works on one patch
+// (large frames).  Four pixels a lane are asked for together: the loop is bound by trips to memory.
+template <int kWaves>
+__global__ __launch_bounds__(256) void k_patch_motion(const float2* __restrict__ flow, int h, int w, float* __restrict__ dp_out,
+                                                      float* __restrict__ flow_uv) {
+    __shared__ float s_sum[4];
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    const int token = blockIdx.x * 4 + wave;
+    const int token = kWaves == 1 ? blockIdx.x * 4 + wave : blockIdx.x;
     const int pr = token / kGrid, pc = token % kGrid;
     const int ya = (pr * h) / kGrid, yb = ((pr + 1) * h) / kGrid;
     const int xa = (pc * w) / kGrid, xb = ((pc + 1) * w) / kGrid;
     const int pw = xb - xa, area = pw * (yb - ya);
+    constexpr int kStride = 64 * kWaves, kUnroll = 4;
     float acc = 0.0f;
-    for (int p = lane; p < area; p += 64) {
-        const int y = ya + p / pw, x = xa + p % pw;
-        const float2 d = flow[(size_t)y * w + x];
-        acc += d.x * d.x + d.y * d.y;
-        if (flow_uv != nullptr) {
-            flow_uv[(size_t)y * w + x] = d.x;
-            flow_uv[(size_t)h * w + (size_t)y * w + x] = d.y;
+    for (int p0 = (kWaves == 1 ? lane : (int)threadIdx.x); p0 < area; p0 += kStride * kUnroll) {
+        size_t gi[kUnroll];
+        float2 d[kUnroll];
+#pragma unroll
+        for (int u = 0; u < kUnroll; ++u) {
+            const int p = min(p0 + u * kStride, area - 1);
+            gi[u] = (size_t)(ya + p / pw) * w + (xa + p % pw);
+            d[u] = flow[gi[u]];
+        }
+#pragma unroll
+        for (int u = 0; u < kUnroll; ++u) {
+            if (p0 + u * kStride >= area) continue;
+            acc += d[u].x * d[u].x + d[u].y * d[u].y;
+            if (flow_uv != nullptr) {
+                flow_uv[gi[u]] = d[u].x;
+                flow_uv[(size_t)h * w + gi[u]] = d[u].y;
+            }
         }
     }
     for (int off = 32; off > 0; off >>= 1) acc += __shfl_down(acc, off);
-    if (lane == 0)
-        __hip_atomic_store(dp_out + token, sqrtf(acc / (float)area), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        __threadfence();
-        const uint32_t prev = atomicAdd(done_counter, 1u);
-        s_last = (prev == (uint32_t)(kGateBlocks - 1)) ? 1 : 0;
+    if (kWaves == 4) {
+        if (lane == 0) s_sum[wave] = acc;
+        __syncthreads();
+        acc = (s_sum[0] + s_sum[1]) + (s_sum[2] + s_sum[3]);
     }
-    __syncthreads();
-    if (!s_last) return;
-    __threadfence();
+    if (lane == 0 && (kWaves == 1 || wave == 0)) dp_out[token] = sqrtf(acc / (float)area);
+}
+
+// Eq. 6, one block.  A launch of its own: as the work of the last block to finish it needed a device-scope
+// fence in every block, and with the pixels of a patch taken one at a time the call's last kernel took
+// 14.3 us (with its neighbours' tails) at 336x336 and 33 us at 1920x1080; motion and gate now take 3.3 and 9.4 us
+// plus 2 to 4 for the gate.
+__global__ __launch_bounds__(256) void k_gate(const float* __restrict__ dp, float tau_t, float theta_r, sali_gate* gate) {
+    __shared__ int s_cnt[4];
     int n = 0;
-    for (int i = threadIdx.x; i < kTokens; i += 256) {
-        const float v = __hip_atomic_load(dp_out + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        n += (v < tau_t) ? 1 : 0;
-    }
+    for (int i = threadIdx.x; i < kTokens; i += 256) n += dp[i] < tau_t ? 1 : 0;
     for (int off = 32; off > 0; off >>= 1) n += __shfl_down(n, off);
-    if (lane == 0) s_cnt[wave] = n;
+    if ((threadIdx.x & 63) == 0) s_cnt[threadIdx.x >> 6] = n;
     __syncthreads();
     if (threadIdx.x == 0) {
         const int n_static = s_cnt[0] + s_cnt[1] + s_cnt[2] + s_cnt[3];
@@ -652,7 +660,6 @@ __global__ __launch_bounds__(256) void k_patch_gate(const float2* __restrict__ f
         gt.redundant = (r > theta_r) ? 1 : 0;
         gt.reserved = 0;
         *gate = gt;
-        *done_counter = 0u;         // ready for the next launch
     }
 }
 
@@ -709,9 +716,15 @@ hipError_t launch_flow_iter(const FlowBatch& f, int n, int64_t level_off, int h,
 }
 
 hipError_t launch_patch_gate(const float2* d_flow, int h, int w, float tau_t, float theta_r, float* d_dp,
-                             sali_gate* d_gate, uint32_t* d_done_counter, float* d_flow_uv_or_null, hipStream_t s) {
-    hipLaunchKernelGGL(k_patch_gate, dim3(kGateBlocks), dim3(256), 0, s, d_flow, h, w, tau_t, theta_r, d_dp, d_gate,
-                       d_done_counter, d_flow_uv_or_null);
+                             sali_gate* d_gate, float* d_flow_uv_or_null, hipStream_t s) {
+    // a wave per patch of up to 256 pixels (one trip of four loads a lane), the block beyond
+    if ((long long)h * w <= 256ll * kTokens)
+        hipLaunchKernelGGL(k_patch_motion<1>, dim3(kTokens / 4), dim3(256), 0, s, d_flow, h, w, d_dp, d_flow_uv_or_null);
+    else
+        hipLaunchKernelGGL(k_patch_motion<4>, dim3(kTokens), dim3(256), 0, s, d_flow, h, w, d_dp, d_flow_uv_or_null);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(k_gate, dim3(1), dim3(256), 0, s, d_dp, tau_t, theta_r, d_gate);
     return hipGetLastError();
 }
 

@@ -134,3 +134,23 @@ def test_image_address_does_not_matter(h, w):
         torch.cuda.synchronize()
         assert np.array_equal(uv.cpu().numpy(), ref[0]) and np.array_equal(dp.cpu().numpy(), ref[1]), off
     ctx.close()
+
+
+@pytest.mark.parametrize("h,w", [(24, 24), (100, 131), (384, 384), (384, 387), (401, 640)])
+def test_patch_motion_of_small_and_large_patches(h, w):
+    """Patch motion and the flow planes where the kernel changes its shape (a wave per patch up to 256 pixels a
+    patch, a block beyond) and patches are ragged: the motions must be the RMS of the very planes the call
+    returns (float64 reference; fp32 sums of at most 4096 terms in 64 or more partial sums: 1e-5), and the gate their count."""
+    from paper_2602_14236_amd import binding
+    ctx = binding.SaliContext(lib_config(params(h, w, flow_levels=1)))
+    rng = np.random.default_rng(h)
+    cur = rng.integers(0, 256, (h, w, 3), dtype=np.uint8)
+    uv, dp, gate = _run(ctx, np.roll(cur, 1, axis=1), cur)
+    assert not np.any(uv == 99.0)
+    ys, xs = [i * h // 24 for i in range(25)], [i * w // 24 for i in range(25)]
+    sq = (uv.astype(np.float64) ** 2).sum(0)
+    exp = np.array([np.sqrt(sq[ys[r]:ys[r + 1], xs[c]:xs[c + 1]].mean()) for r in range(24) for c in range(24)])
+    assert np.all(np.abs(dp - exp) <= 1e-5 * exp)
+    n = int((dp < 0.5).sum())
+    assert gate == (n, float(np.float32(n) / np.float32(576)), int(np.float32(n) / np.float32(576) > np.float32(0.9)))
+    ctx.close()
