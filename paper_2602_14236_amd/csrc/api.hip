@@ -38,7 +38,7 @@ struct LaneLayout {
 };
 
 struct ScratchLayout {
-    LaneLayout lane[kLanes];
+    LaneLayout lane[kLanes + 2];      // the last two: gray and pyramid of the stand-alone flow call's pair, its flow
     size_t expA[kExpSlots], expB[kExpSlots];
     size_t attn_partial;
     size_t total;
@@ -166,6 +166,15 @@ ScratchLayout scratch_layout(const sali_config& c, const LevelGeom& g) {
         L.gate = take(sizeof(sali_gate));
         L.counters = take(sizeof(LaneCounters));
         L.tcounts = take(8 * sizeof(int32_t));
+    }
+    for (int l = kLanes; l < kLanes + 2; ++l) {
+        LaneLayout& L = s.lane[l];
+        L.y8 = take(hw);
+        L.pyr = take(px * sizeof(float));
+        if (l == kLanes + 1) {
+            L.flow[0] = take(hw * sizeof(float2));
+            L.flow[1] = take(hw * sizeof(float2));
+        }
     }
     for (int i = 0; i < kExpSlots; ++i) {
         s.expA[i] = take(px * sizeof(float4));
@@ -730,21 +739,23 @@ int sali_flow_score(sali_ctx* c, const uint8_t* d_prev_rgb, const uint8_t* d_cur
         d_gate_out == nullptr)
         return SALI_ERR_NULL;
     hipStream_t s = static_cast<hipStream_t>(stream);
-    BatchPlan pa = {}, pb = {};
-    pa.n = pb.n = 1;
-    pa.slot[0] = kStepSlots;
-    pa.prev_slot[0] = -1;
-    pb.slot[0] = kStepSlots + 1;
-    pb.prev_slot[0] = kStepSlots;
-    int rc = enqueue_gray(c, &d_prev_rgb, pa, s);
-    if (rc == SALI_OK) rc = enqueue_expansion(c, pa, s);
-    if (rc == SALI_OK) rc = enqueue_gray(c, &d_cur_rgb, pb, s);
-    if (rc == SALI_OK) rc = enqueue_expansion(c, pb, s);
+    // both frames in one set of launches, in scratch of the call's own
+    BatchPlan pair = {};
+    pair.n = 2;
+    for (int i = 0; i < 2; ++i) {
+        pair.lane[i] = kLanes + i;
+        pair.slot[i] = kStepSlots + i;
+    }
+    pair.prev_slot[0] = -1;
+    pair.prev_slot[1] = kStepSlots;
+    const uint8_t* const d_rgb[2] = {d_prev_rgb, d_cur_rgb};
+    int rc = enqueue_gray(c, d_rgb, pair, s);
+    if (rc == SALI_OK) rc = enqueue_expansion(c, pair, s);
     if (rc != SALI_OK) return rc;
-    const float2* flow = nullptr;
-    rc = enqueue_flow(c, pb, &flow, s);
+    const float2* flow[kMaxBatch];
+    rc = enqueue_flow(c, pair, flow, s);
     if (rc != SALI_OK) return rc;
-    SALI_TRY(launch_patch_gate(flow, c->cfg.src_h, c->cfg.src_w, c->cfg.tau_t, c->cfg.theta_r, d_patch_motion576,
+    SALI_TRY(launch_patch_gate(flow[1], c->cfg.src_h, c->cfg.src_w, c->cfg.tau_t, c->cfg.theta_r, d_patch_motion576,
                                d_gate_out, d_flow_uv_or_null, s));
     return SALI_OK;
 }
