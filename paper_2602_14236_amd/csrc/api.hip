@@ -330,7 +330,7 @@ struct BatchPlan {
 };
 
 // Pyramid and polynomial expansion in one launch (k_expand: every tile rebuilds the pyramid values it
-// needs from the gray image in LDS) or level by level (k_pyr_down per level, then k_polyexp).  The fused
+// needs from the gray image in LDS) or in steps (k_pyr_pair per two levels, then k_polyexp).  The fused
 // launch saves two dependent launches, but does several times the work per
 // pixel (a 16x16 tile of level 2 reads a 97x97 gray patch), so it is the choice only while the launch
 // chain, not the work, bounds a batch: up to three levels and small frames.  Measured in the pipeline,
@@ -390,10 +390,12 @@ int enqueue_saliency(sali_ctx* c, const uint8_t* const* d_rgb, const BatchPlan& 
     return SALI_OK;
 }
 
-// pyramid and polynomial expansion of each frame's gray image into its expansion slot
-int enqueue_expansion(sali_ctx* c, const BatchPlan& bp, hipStream_t s) {
+// gray image, pyramid and polynomial expansion of each frame, the last into its expansion slot
+int enqueue_expansion(sali_ctx* c, const uint8_t* const* d_rgb, const BatchPlan& bp, hipStream_t s) {
     const LevelGeom& g = c->geom;
     if (fused_expansion(c, bp.n)) {
+        const int rc = enqueue_gray(c, d_rgb, bp, s);
+        if (rc != SALI_OK) return rc;
         ExpandBatch f = {};
         for (int i = 0; i < bp.n; ++i) {
             const LaneLayout& L = c->sl.lane[bp.lane[i]];
@@ -407,12 +409,18 @@ int enqueue_expansion(sali_ctx* c, const BatchPlan& bp, hipStream_t s) {
     PyrBatch f = {};
     for (int i = 0; i < bp.n; ++i) {
         const LaneLayout& L = c->sl.lane[bp.lane[i]];
+        f.rgb[i] = d_rgb[i];
         f.y8[i] = c->sc<uint8_t>(L.y8);
         f.pyr[i] = c->sc<float>(L.pyr);
         f.A[i] = c->sc<float4>(c->sl.expA[bp.slot[i]]);
         f.b[i] = c->sc<float>(c->sl.expB[bp.slot[i]]);
     }
-    for (int l = 1; l < g.levels; ++l) SALI_TRY(launch_pyr_down(f, bp.n, g, l, s));
+    if (g.levels == 1) {
+        const int rc = enqueue_gray(c, d_rgb, bp, s);
+        if (rc != SALI_OK) return rc;
+    } else {
+        SALI_TRY(launch_pyramid(f, bp.n, g, s));
+    }
     SALI_TRY(launch_polyexp(f, bp.n, g, c->fw, s));
     return SALI_OK;
 }
@@ -749,8 +757,7 @@ int sali_flow_score(sali_ctx* c, const uint8_t* d_prev_rgb, const uint8_t* d_cur
     pair.prev_slot[0] = -1;
     pair.prev_slot[1] = kStepSlots;
     const uint8_t* const d_rgb[2] = {d_prev_rgb, d_cur_rgb};
-    int rc = enqueue_gray(c, d_rgb, pair, s);
-    if (rc == SALI_OK) rc = enqueue_expansion(c, pair, s);
+    int rc = enqueue_expansion(c, d_rgb, pair, s);
     if (rc != SALI_OK) return rc;
     const float2* flow[kMaxBatch];
     rc = enqueue_flow(c, pair, flow, s);
@@ -891,8 +898,7 @@ int sali_analyze_batch(sali_ctx* c, const uint8_t* const* d_rgb_frames, int32_t 
         if (rc != SALI_OK) return rc;
     }
     // the temporal filter first: gray, pyramid + expansion, flow, per-patch motion
-    rc = enqueue_gray(c, d_rgb_frames, bp, s);
-    if (rc == SALI_OK) rc = enqueue_expansion(c, bp, s);
+    rc = enqueue_expansion(c, d_rgb_frames, bp, s);
     if (rc != SALI_OK) return rc;
     // the batch's events live in the ring entry of its last frame
     AnalysisRecord& rec = c->ring[n_last % kRing];

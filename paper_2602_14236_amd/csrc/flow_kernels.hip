@@ -9,7 +9,8 @@
 //                polynomial expansion of up to three levels in ONE launch: 16x16 tiles, the pyramid
 //                values a tile needs are rebuilt from the gray image in LDS; separable moments,
 //                closed-form solution of the 6-unknown weighted least-squares fit
-//   k_pyr_down, k_polyexp   the same per level (pyramid in HBM), used for more than three levels
+//   k_pyr_pair, k_polyexp   the same for more than three levels and larger frames: gray image and two
+//                pyramid levels per launch, the pyramid in HBM, then the expansion of all levels
 //   k_flow_iter  one displacement update: per cell of a tile (16x16 or 32x16, by level size) + 5-pixel
 //                halo, sample the new frame's expansion bilinearly at x + prior, build A^T A (3 values)
 //                and A^T db (2 values) in LDS, separable 11x11 Gaussian aggregation in LDS, 2x2 ridge
@@ -23,6 +24,8 @@
 //                Stand-alone flow call only: the chained step has them in its pooling kernels.
 //
 // The batched kernels take the frame as a grid dimension.  All stencils replicate the border.
+
+#include <type_traits>
 
 #include "sali_internal.h"
 
@@ -50,31 +53,126 @@ __device__ __forceinline__ uint32_t pix(int y, int w, int x) {          // y * w
 }  // namespace
 
 // ---------------------------------------------------------------------------------------------
-// One pyramid level of every frame of the batch (blockIdx.z): level `lvl` of f.pyr[z] from level
-// lvl - 1 (from the gray image f.y8[z] for lvl = 1).
-__global__ __launch_bounds__(256) void k_pyr_down(PyrBatch f, int from_gray, long long src_off, long long dst_off,
-                                                  int sh, int sw, int dh, int dw) {
-    const uint8_t* __restrict__ y8 = from_gray ? f.y8[blockIdx.z] : nullptr;
-    const float* __restrict__ src = f.pyr[blockIdx.z] + src_off;
-    float* __restrict__ dst = f.pyr[blockIdx.z] + dst_off;
-    const int x = blockIdx.x * 64 + (threadIdx.x & 63);
-    const int y = blockIdx.y * 4 + (threadIdx.x >> 6);
-    if (x >= dw || y >= dh) return;
+// Two pyramid levels of every frame of the batch (blockIdx.z) in one launch: a block makes a 32x32 tile of
+// level `lvl` and the 16x16 tile of level lvl + 1 under it (where there is one) from the source below, whose
+// 76x73 patch it holds in LDS.  kRgb: the source is the frame itself; the block converts its patch to gray
+// and also writes its 64x64 pixels of the gray image, so the frame is read once and no gray pass precedes.  The
+// first level is then an exact integer sum (weights 1 4 6 4 1 squared, at most 256 * 255) and one division.
+// Four 1920x1080 frames, five levels: 18 + 7.5 us for gray and four levels.  A thread per output with 25 byte
+// loads and divisions each, a launch per level, after a gray pass: 8.7 + 41.6 + 9.9 + 4.8 + 4.8 us.
+namespace {
+constexpr int kPyrT = 32;                       // tile side of the first level
+constexpr int kPyrR = kPyrT + 3;                // 35: cells of it that the second level reads
+constexpr int kPyrRows = 2 * (kPyrR - 1) + 5;   // 73: source rows under them
+constexpr int kPyrCols = 76;                    // source columns: from 64 bx - 8 (whole quads), 73 used
+}  // namespace
+
+template <bool kRgb>
+__global__ __launch_bounds__(256) void k_pyr_pair(PyrBatch f, LevelGeom g, int lvl) {
+    using Cell = typename std::conditional<kRgb, uint8_t, float>::type;
+    using Sum = typename std::conditional<kRgb, uint16_t, float>::type;
+    __shared__ __align__(16) Cell s_src[kPyrRows][kPyrCols];
+    __shared__ Sum s_h[kPyrRows][kPyrR + 1];            // horizontal sums
+    __shared__ float s_l1[kPyrR][kPyrR + 1];
+    const BlockId blk = xcd_block_id();
+    const int tid = threadIdx.x;
+    const int sh = g.h[lvl - 1], sw = g.w[lvl - 1], h1 = g.h[lvl], w1 = g.w[lvl];
+    float* __restrict__ pyr = f.pyr[blk.z];
+    const int qy = 64 * blk.y - 6, qx = 64 * blk.x - 8;         // origin of the patch
+    constexpr int kQuads = kPyrCols / 4, kItems = kPyrRows * kQuads, kN = (kItems + 255) / 256;
+    if constexpr (kRgb) {
+        // a thread takes four pixels (twelve bytes, the compiler is told nothing about their alignment) at a
+        // time and has all its loads in flight before the first is used
+        const uint8_t* __restrict__ rgb = f.rgb[blk.z];
+        uint32_t v[kN][3];
+#pragma unroll
+        for (int k = 0; k < kN; ++k) {
+            const int p = min(tid + 256 * k, kItems - 1);
+            const int x = qx + 4 * (p % kQuads);
+            const uint8_t* row = rgb + (size_t)clampi(qy + p / kQuads, 0, sh - 1) * sw * 3;
+            if (x >= 0 && x + 3 < sw) {
+                __builtin_memcpy(v[k], row + 3 * x, 12);
+            } else {
+                uint32_t c[12];
+#pragma unroll
+                for (int i = 0; i < 12; ++i) c[i] = row[3 * clampi(x + i / 3, 0, sw - 1) + i % 3];
+#pragma unroll
+                for (int i = 0; i < 3; ++i) v[k][i] = c[4 * i] | (c[4 * i + 1] << 8) | (c[4 * i + 2] << 16) | (c[4 * i + 3] << 24);
+            }
+        }
+#pragma unroll
+        for (int k = 0; k < kN; ++k) {
+            const int p = tid + 256 * k;
+            if (p < kItems) *reinterpret_cast<uint32_t*>(&s_src[p / kQuads][4 * (p % kQuads)]) = gray_of_quad(v[k]);
+        }
+    } else {
+        const float* __restrict__ src = pyr + g.off[lvl - 1];
+        constexpr int kCells = kPyrRows * kPyrCols;
+#pragma unroll 8
+        for (int p = tid; p < kCells; p += 256) {
+            const int gy = clampi(qy + p / kPyrCols, 0, sh - 1), gx = clampi(qx + p % kPyrCols, 0, sw - 1);
+            s_src[p / kPyrCols][p % kPyrCols] = src[(size_t)gy * sw + gx];
+        }
+    }
+    __syncthreads();
+    if constexpr (kRgb) {
+        uint8_t* __restrict__ y8 = f.y8[blk.z];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {                           // 64 rows of sixteen quads
+            const int p = tid + 256 * k;
+            const int gy = 64 * blk.y + p / 16, gx = 64 * blk.x + 4 * (p % 16);
+            if (gy >= sh || gx >= sw) continue;
+            const uint32_t quad = *reinterpret_cast<const uint32_t*>(&s_src[6 + p / 16][8 + 4 * (p % 16)]);
+            uint8_t* dst = y8 + (size_t)gy * sw + gx;
+            if ((sw & 3) == 0) {
+                *reinterpret_cast<uint32_t*>(dst) = quad;
+            } else {
+                for (int i = 0; i < 4 && gx + i < sw; ++i) dst[i] = (uint8_t)(quad >> (8 * i));
+            }
+        }
+    }
+    // Cells of the 35x35 region hold the value at the clamped coordinate of their place, as the patch does: a
+    // replicate-border stencil centred on an in-image pixel reads exactly that.
+    const int oy1 = kPyrT * blk.y - 2, ox1 = kPyrT * blk.x - 2;
+    for (int p = tid; p < kPyrRows * kPyrR; p += 256) {
+        const int ry = p / kPyrR, rx = p % kPyrR;
+        const Cell* c = &s_src[ry][2 * clampi(ox1 + rx, 0, w1 - 1) - qx];
+        if constexpr (kRgb) s_h[ry][rx] = (uint16_t)(c[-2] + c[2] + 4 * (c[-1] + c[1]) + 6 * c[0]);
+        else s_h[ry][rx] = (c[-2] + c[2]) * (1.0f / 16) + (c[-1] + c[1]) * (4.0f / 16) + c[0] * (6.0f / 16);
+    }
+    __syncthreads();
+    for (int p = tid; p < kPyrR * kPyrR; p += 256) {
+        const int ry = p / kPyrR, rx = p % kPyrR;
+        const int cy = 2 * clampi(oy1 + ry, 0, h1 - 1) - qy;
+        float v;
+        if constexpr (kRgb) {
+            const uint32_t sum = (uint32_t)s_h[cy - 2][rx] + s_h[cy + 2][rx] + 4u * ((uint32_t)s_h[cy - 1][rx] + s_h[cy + 1][rx]) +
+                                 6u * s_h[cy][rx];
+            v = (float)sum / 65280.0f;
+        } else {
+            v = (s_h[cy - 2][rx] + s_h[cy + 2][rx]) * (1.0f / 16) + (s_h[cy - 1][rx] + s_h[cy + 1][rx]) * (4.0f / 16) +
+                s_h[cy][rx] * (6.0f / 16);
+        }
+        s_l1[ry][rx] = v;
+        const int gy = oy1 + ry, gx = ox1 + rx;
+        if (ry >= 2 && ry < 2 + kPyrT && rx >= 2 && rx < 2 + kPyrT && gy < h1 && gx < w1)
+            pyr[g.off[lvl] + (size_t)gy * w1 + gx] = v;
+    }
+    if (lvl + 1 >= g.levels) return;
+    __syncthreads();
+    const int h2 = g.h[lvl + 1], w2 = g.w[lvl + 1];
+    const int ty = tid / 16, tx = tid % 16, gy = 16 * blk.y + ty, gx = 16 * blk.x + tx;
+    if (gy >= h2 || gx >= w2) return;
     const float k[5] = {1.0f / 16, 4.0f / 16, 6.0f / 16, 4.0f / 16, 1.0f / 16};
     float acc = 0.0f;
 #pragma unroll
-    for (int a = -2; a <= 2; ++a) {
-        const int yy = clampi(2 * y + a, 0, sh - 1);
+    for (int a = 0; a < 5; ++a) {
         float row = 0.0f;
 #pragma unroll
-        for (int b = -2; b <= 2; ++b) {
-            const int xx = clampi(2 * x + b, 0, sw - 1);
-            const float v = y8 != nullptr ? (float)y8[(size_t)yy * sw + xx] / 255.0f : src[(size_t)yy * sw + xx];
-            row += k[b + 2] * v;
-        }
-        acc += k[a + 2] * row;
+        for (int b = 0; b < 5; ++b) row += k[b] * s_l1[2 * ty + a][2 * tx + b];
+        acc += k[a] * row;
     }
-    dst[(size_t)y * dw + x] = acc;
+    pyr[g.off[lvl + 1] + (size_t)gy * w2 + gx] = acc;
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -664,11 +762,15 @@ __global__ __launch_bounds__(256) void k_gate(const float* __restrict__ dp, floa
 }
 
 // ---------------------------------------------------------------------------------------------
-hipError_t launch_pyr_down(const PyrBatch& f, int n, const LevelGeom& g, int lvl, hipStream_t s) {
-    dim3 grid((g.w[lvl] + 63) / 64, (g.h[lvl] + 3) / 4, n);
-    hipLaunchKernelGGL(k_pyr_down, grid, dim3(256), 0, s, f, lvl == 1 ? 1 : 0, (long long)g.off[lvl - 1],
-                       (long long)g.off[lvl], g.h[lvl - 1], g.w[lvl - 1], g.h[lvl], g.w[lvl]);
-    return hipGetLastError();
+hipError_t launch_pyramid(const PyrBatch& f, int n, const LevelGeom& g, hipStream_t s) {
+    for (int lvl = 1; lvl < g.levels; lvl += 2) {
+        const dim3 grid((g.w[lvl] + kPyrT - 1) / kPyrT, (g.h[lvl] + kPyrT - 1) / kPyrT, n);
+        if (lvl == 1) hipLaunchKernelGGL(k_pyr_pair<true>, grid, dim3(256), 0, s, f, g, lvl);
+        else hipLaunchKernelGGL(k_pyr_pair<false>, grid, dim3(256), 0, s, f, g, lvl);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
 }
 
 hipError_t launch_polyexp(const PyrBatch& f, int n, LevelGeom g, FlowWeights fw, hipStream_t s) {

@@ -140,8 +140,9 @@ struct ExpandBatch {
     float* b[kMaxBatch];
 };
 
-struct PyrBatch {                                 // per-level path (more than three levels)
-    const uint8_t* y8[kMaxBatch];
+struct PyrBatch {                                 // per-level path (more than three levels, larger frames)
+    const uint8_t* rgb[kMaxBatch];
+    uint8_t* y8[kMaxBatch];
     float* pyr[kMaxBatch];                        // all levels of the frame's pyramid, LevelGeom offsets
     float4* A[kMaxBatch];
     float* b[kMaxBatch];
@@ -209,6 +210,20 @@ __device__ __forceinline__ BlockId xcd_block_id() {
 }
 #endif
 
+#ifdef __HIPCC__
+// Y8 of one pixel, and of four pixels in three words (bytes RGBR GBRG BRGB)
+__device__ __forceinline__ uint32_t gray_of(uint32_t r, uint32_t g, uint32_t b) {
+    return (77u * r + 150u * g + 29u * b + 128u) >> 8;
+}
+__device__ __forceinline__ uint32_t gray_of_quad(const uint32_t* w) {
+    const uint32_t g0 = gray_of(w[0] & 0xFF, (w[0] >> 8) & 0xFF, (w[0] >> 16) & 0xFF);
+    const uint32_t g1 = gray_of(w[0] >> 24, w[1] & 0xFF, (w[1] >> 8) & 0xFF);
+    const uint32_t g2 = gray_of((w[1] >> 16) & 0xFF, w[1] >> 24, w[2] & 0xFF);
+    const uint32_t g3 = gray_of((w[2] >> 8) & 0xFF, (w[2] >> 16) & 0xFF, w[2] >> 24);
+    return g0 | (g1 << 8) | (g2 << 16) | (g3 << 24);
+}
+#endif
+
 // ---- launchers (each returns hipGetLastError()) ---------------------------------------------
 // kv_kernels.hip
 hipError_t launch_tier(const float* d_scores, const sali_gate* d_gate_or_null, TierParams tp, int frame_id,
@@ -248,7 +263,8 @@ hipError_t launch_pool(const PoolBatch& f, int n, int h, int w, uint8_t* d_salma
                        const TierLaunch* tier_or_null, GateParams gp, uint32_t* d_done_counter, hipStream_t s);
 
 // flow_kernels.hip
-hipError_t launch_pyr_down(const PyrBatch& f, int n, const LevelGeom& g, int lvl, hipStream_t s);
+// gray image and all pyramid levels (g.levels >= 2) from f.rgb
+hipError_t launch_pyramid(const PyrBatch& f, int n, const LevelGeom& g, hipStream_t s);
 hipError_t launch_polyexp(const PyrBatch& f, int n, LevelGeom g, FlowWeights fw, hipStream_t s);
 hipError_t launch_expand(const ExpandBatch& f, int n, LevelGeom g, FlowWeights fw, hipStream_t s);
 hipError_t launch_flow_iter(const FlowBatch& f, int n, int64_t level_off, int h, int w, int ch, int cw,

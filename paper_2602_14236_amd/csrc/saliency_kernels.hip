@@ -48,10 +48,6 @@ __device__ __forceinline__ int clampi(int v, int lo, int hi) { return v < lo ? l
 // gray only, blockIdx.y = frame of the batch: what the flow needs of a frame.  The rest of the spatial
 // filter waits until the reuse rule has spoken.  Sixteen pixels per thread (48 bytes in, 16 out) where
 // the caller's image is 16-byte aligned, else pixel by pixel.
-__device__ __forceinline__ uint32_t gray_of(uint32_t r, uint32_t g, uint32_t b) {
-    return (77u * r + 150u * g + 29u * b + 128u) >> 8;
-}
-
 __global__ __launch_bounds__(256) void k_gray(PrepBatch f, int n) {
     const uint8_t* __restrict__ rgb = f.rgb[blockIdx.y];
     uint8_t* __restrict__ y8 = f.y8[blockIdx.y];
@@ -63,13 +59,8 @@ __global__ __launch_bounds__(256) void k_gray(PrepBatch f, int n) {
         const uint32_t in[12] = {a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w, c.x, c.y, c.z, c.w};
         uint32_t out[4];
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {           // four pixels = three words: RGBR GBRG BRGB
-            const uint32_t w0 = in[3 * q], w1 = in[3 * q + 1], w2 = in[3 * q + 2];
-            const uint32_t g0 = gray_of(w0 & 0xFF, (w0 >> 8) & 0xFF, (w0 >> 16) & 0xFF);
-            const uint32_t g1 = gray_of(w0 >> 24, w1 & 0xFF, (w1 >> 8) & 0xFF);
-            const uint32_t g2 = gray_of((w1 >> 16) & 0xFF, w1 >> 24, w2 & 0xFF);
-            const uint32_t g3 = gray_of((w2 >> 8) & 0xFF, (w2 >> 16) & 0xFF, w2 >> 24);
-            out[q] = g0 | (g1 << 8) | (g2 << 16) | (g3 << 24);
+        for (int q = 0; q < 4; ++q) {
+            out[q] = gray_of_quad(in + 3 * q);
         }
         *reinterpret_cast<uint4*>(y8 + i0) = make_uint4(out[0], out[1], out[2], out[3]);   // lane scratch: 256-byte aligned
         return;

@@ -154,3 +154,34 @@ def test_patch_motion_of_small_and_large_patches(h, w):
     n = int((dp < 0.5).sum())
     assert gate == (n, float(np.float32(n) / np.float32(576)), int(np.float32(n) / np.float32(576) > np.float32(0.9)))
     ctx.close()
+
+
+@pytest.mark.parametrize("h,w,levels,shift", [
+    (64, 65, 4, 0), (65, 64, 4, 1), (131, 70, 5, 0), (33, 203, 4, 3),      # more than three levels: odd sizes, one tile and a bit
+    (400, 401, 2, 0), (402, 400, 3, 2),                                    # large enough for the same path with fewer levels
+])
+def test_pyramid_in_pairs_of_levels(h, w, levels, shift):
+    """Gray image and pyramid two levels at a time: borders of the 64-pixel tiles, last levels without a
+    second one, rows that are no multiple of four pixels and images at any address (`shift` bytes into an
+    allocation), against the oracle's flow."""
+    from paper_2602_14236_amd import binding
+    ctx = binding.SaliContext(lib_config(params(h, w, flow_levels=levels)))
+    yy, xx = np.mgrid[0:h, 0:w].astype(np.float64)
+    rng = np.random.default_rng(h * w)
+    frames = []
+    for d in (0.0, 1.5):
+        x, y = xx - d, yy - 0.7 * d
+        img = 128 + 50 * np.sin(x / 3.1) * np.sin(y / 2.7) + 40 * np.sin((x + y) / 9.0)
+        frames.append(np.clip(np.rint(img[..., None] + rng.normal(0, 1, (h, w, 3))), 0, 255).astype(np.uint8))
+    dev = []
+    for f in frames:
+        buf = torch.empty(f.size + shift, dtype=torch.uint8, device="cuda")
+        dev.append(buf[shift:].view(h, w, 3).copy_(torch.from_numpy(f)))
+    uv = torch.empty((2, h, w), dtype=torch.float32, device="cuda")
+    dp, gate = torch.empty(576, device="cuda"), torch.zeros(4, dtype=torch.int32, device="cuda")
+    ctx.flow_score(dev[0], dev[1], uv, dp, gate)
+    d = of.flow(frames[0], frames[1], levels)
+    got = uv.cpu().numpy()
+    print(f"{h}x{w}, {levels} levels: largest error {max(np.abs(got[0] - d[..., 0]).max(), np.abs(got[1] - d[..., 1]).max()):.2e}", flush=True)
+    assert close(got[0], d[..., 0]).all() and close(got[1], d[..., 1]).all()
+    ctx.close()
