@@ -27,14 +27,16 @@ __device__ __forceinline__ uint32_t uf_find(const uint32_t* parent, uint32_t key
     }
 }
 
-// for kernels that run after all links are final: ordinary cached loads
-__device__ __forceinline__ uint32_t uf_find_settled(const uint32_t* __restrict__ parent, uint32_t key) {
+// Is the component of a weak pixel (its key) without a strong pixel?  For kernels that run after all links
+// are final: ordinary cached loads.  A strong key on the way decides; the root need not be reached.
+__device__ __forceinline__ bool uf_stays_weak(const uint32_t* __restrict__ parent, uint32_t key) {
     uint32_t k = key;
-    for (;;) {
+    while (k & kWeakBit) {
         const uint32_t p = parent[k & ~kWeakBit];
-        if (p == k) return k;
+        if (p == k) return true;
         k = p;
     }
+    return false;
 }
 
 template <int kScope>
@@ -50,31 +52,63 @@ __device__ __forceinline__ void uf_unite(uint32_t* parent, uint32_t ka, uint32_t
     }
 }
 
-// Cross-tile part: a strip of 64 x 4 pixels per block of 256 threads; only pixels on a tile border
-// have neighbours in another tile of the pre-pass (pairs inside a tile were joined in LDS there).
-__device__ __forceinline__ void union_strip(const uint8_t* __restrict__ cls, uint32_t* parent, int h, int w,
-                                            int strip_x, int strip_y) {
-    const int x = strip_x * 64 + (int)(threadIdx.x & 63);
-    const int y = strip_y * 4 + (int)(threadIdx.x >> 6);
-    if (x >= w || y >= h) return;
-    const int lx = x % kTile, ly = y % kTile;
-    if (lx != 0 && lx != kTile - 1 && ly != kTile - 1) return;      // all forward neighbours in the same tile
-    const size_t gi = (size_t)y * w + x;
-    const int c = cls[gi];
-    if (c == 0) return;
-    const uint32_t me = (uint32_t)gi | (c == 1 ? kWeakBit : 0u);
-    const int ny[4] = {0, 1, 1, 1};
-    const int nx[4] = {1, -1, 0, 1};
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-        const int yy = y + ny[k], xx = x + nx[k];
-        if (yy >= h || xx < 0 || xx >= w) continue;
-        if (yy / kTile == y / kTile && xx / kTile == x / kTile) continue;     // joined in LDS already
-        const size_t gj = (size_t)yy * w + xx;
-        const int cj = cls[gj];
-        if (cj == 0) continue;
-        uf_unite<__HIP_MEMORY_SCOPE_AGENT>(parent, me, (uint32_t)gj | (cj == 1 ? kWeakBit : 0u));
+// The cross-tile part only has to carry "has a strong pixel" into the weak components it touches: two
+// components that are strong already are not joined, and a walk ends at the first strong key, whose
+// component's root is strong (keys decrease along links and strong keys are the smaller ones).  A step of a
+// walk is a trip past the L2 (agent scope), so both walks of a pair go in step.
+__device__ __forceinline__ void uf_spread_strong(uint32_t* parent, uint32_t ka, uint32_t kb) {
+    for (;;) {
+        for (;;) {
+            uint32_t pa = ka, pb = kb;
+            if (ka & kWeakBit) pa = uf_load<__HIP_MEMORY_SCOPE_AGENT>(parent, ka & ~kWeakBit);
+            if (kb & kWeakBit) pb = uf_load<__HIP_MEMORY_SCOPE_AGENT>(parent, kb & ~kWeakBit);
+            if (pa == ka && pb == kb) break;        // two roots or strong keys
+            ka = pa;
+            kb = pb;
+        }
+        if (ka == kb || ((ka | kb) & kWeakBit) == 0u) return;
+        if (ka < kb) { const uint32_t t = ka; ka = kb; kb = t; }      // ka is the larger key: a weak root
+        const uint32_t old = atomicMin(parent + (ka & ~kWeakBit), kb);
+        if (old == ka) return;      // ka was a root and now points at kb
+        ka = old;                   // somebody linked ka first: join where it pointed with kb (the smaller is ka's link)
     }
+}
+
+// Pixels that have neighbours across a border of the pre-pass's tiles (pairs inside a tile were joined in LDS
+// there): first the last rows of all tile rows but the lowest, pixel by pixel, then the last columns of all
+// tile columns but the rightmost.  Each looks at the three pixels across;
+// where runs of candidates touch along the border the contact is made once, by the first pair.
+__host__ __device__ inline int border_rows(int h, int w) { return ((h - 1) / kTile) * w; }
+__host__ __device__ inline int border_items(int h, int w) { return border_rows(h, w) + ((w - 1) / kTile) * h; }
+
+__device__ __forceinline__ void union_border(const uint8_t* __restrict__ cls, uint32_t* parent, int h, int w, int item) {
+    const int n_rows = border_rows(h, w);
+    const bool row = item < n_rows;
+    const int i = row ? item : item - n_rows, len = row ? w : h;
+    const int k = i / len, at = i - k * len;                        // border k, place along it
+    const int x = row ? at : kTile * k + kTile - 1, y = row ? kTile * k + kTile - 1 : at;
+    const int gi = y * w + x, across = row ? w : 1, along = row ? 1 : w;
+    // c[0][1] = this pixel, c[0][0] / c[0][2] = the ones beside it along the border, c[1][] = across
+    int c[2][3];
+#pragma unroll
+    for (int j = 0; j < 3; ++j) {
+        const bool in = at + j >= 1 && at + j <= len;
+        c[0][j] = in ? cls[gi + (j - 1) * along] : 0;
+        c[1][j] = in ? cls[gi + across + (j - 1) * along] : 0;
+    }
+    if (c[0][1] == 0) return;
+    const uint32_t me = (uint32_t)gi | (c[0][1] == 1 ? kWeakBit : 0u);
+    // Straight across, unless the pair before makes that contact: it lies in the same two tiles, whose pixels
+    // are joined in LDS (so not for the first pair of a tile: round a corner of four tiles each contact
+    // would count on the others).  A diagonal only if neither the pixel straight across nor the one beside this
+    // pixel leads there.
+    const bool straight = c[1][1] != 0 && !(at % kTile != 0 && c[0][0] != 0 && c[1][0] != 0);
+    if (straight) uf_spread_strong(parent, me, (uint32_t)(gi + across) | (c[1][1] == 1 ? kWeakBit : 0u));
+    if (c[1][1] != 0) return;
+#pragma unroll
+    for (int j = 0; j < 3; j += 2)
+        if (c[1][j] != 0 && c[0][j] == 0)
+            uf_spread_strong(parent, me, (uint32_t)(gi + across + (j - 1) * along) | (c[1][j] == 1 ? kWeakBit : 0u));
 }
 
 }  // namespace sali

@@ -14,7 +14,7 @@
 //            the smaller key, so the root of a component is a strong pixel iff it has one.
 //            k_prep labels the components of its own tile in LDS (label equivalence, no
 //            global traffic) and writes each pixel's link to its tile-local root.
-//   k_union  joins components across tile borders with global atomics (border pixels only).
+//   k_union  carries "has a strong pixel" across tile borders with global atomics (border pixels only).
 //   k_pool   per patch: E = edge pixel whose root is strong, C = V above the frame mean and
 //            above a floor; q = sum(E + C); score = floor(q * 2^15 / |P|) / 65536.  In the
 //            chained step it also reduces the flow field to the patch's motion (Eq. 5).
@@ -379,10 +379,13 @@ __global__ __launch_bounds__(kPrepThreads) void k_prep(PrepBatch f, int h, int w
     }
 }
 
-// hysteresis, cross-tile part
-__global__ __launch_bounds__(256) void k_union(PrepBatch f, int h, int w) {
-    if (*f.skip[blockIdx.z] != 0u) return;          // redundant frame, says the pre-pass
-    union_strip(f.cls[blockIdx.z], f.parent[blockIdx.z], h, w, blockIdx.x, blockIdx.y);
+// hysteresis, cross-tile part; blockIdx.y = frame of the batch.  A thread per border pixel: with a thread per
+// image pixel, nearly all of them idle, and walks to the root also between strong components sixteen 640x360
+// frames took 44 us in the pipeline, one frame alone 16.8; now 23.5 and 9.6 (chains of trips past the L2).
+__global__ __launch_bounds__(256) void k_union(PrepBatch f, int h, int w, int n_items) {
+    if (*f.skip[blockIdx.y] != 0u) return;          // redundant frame, says the pre-pass
+    const int item = blockIdx.x * 256 + threadIdx.x;
+    if (item < n_items) union_border(f.cls[blockIdx.y], f.parent[blockIdx.y], h, w, item);
 }
 
 // Gate (Eq. 6), tier assignment and compaction indices of frame `b` of a launch of `n_frames`, by
@@ -570,7 +573,7 @@ __global__ __launch_bounds__(kTierThreads) void k_pool(PoolBatch f, int h, int w
                 } else {
                     uint32_t e = 0;
                     if (c[u] == 2) e = 1;
-                    else if (c[u] == 1) e = (uf_find_settled(parent, (uint32_t)gi[u] | kWeakBit) & kWeakBit) ? 0u : 1u;
+                    else if (c[u] == 1) e = uf_stays_weak(parent, (uint32_t)gi[u] | kWeakBit) ? 0u : 1u;
                     const uint32_t cm = ((unsigned long long)v[u] * hw > m && v[u] >= kVMin) ? 1u : 0u;
                     q += e + cm;
                     if (salmap != nullptr) salmap[gi[u]] = (uint8_t)(e + cm);
@@ -627,8 +630,9 @@ hipError_t launch_prep(const PrepBatch& f, int n, int h, int w, GateParams gp, c
 }
 
 hipError_t launch_union(const PrepBatch& f, int n, int h, int w, hipStream_t s) {
-    dim3 grid((w + 63) / 64, (h + 3) / 4, n);
-    hipLaunchKernelGGL(k_union, grid, dim3(256), 0, s, f, h, w);
+    const int items = border_items(h, w);
+    if (items == 0) return hipSuccess;              // a single tile
+    hipLaunchKernelGGL(k_union, dim3((items + 255) / 256, n), dim3(256), 0, s, f, h, w, items);
     return hipGetLastError();
 }
 

@@ -101,3 +101,19 @@ def test_long_weak_spiral_reaches_its_one_strong_pixel():
     m = _check(ctx, rgb, 20, 200)
     assert (m >= 1).sum() > 200
     ctx.close()
+
+
+@pytest.mark.parametrize("h,w", [(33, 33), (64, 65), (100, 131), (161, 96)])
+def test_weak_chains_across_tile_borders_and_corners(h, w):
+    """Hysteresis where components are many, weak and cut by the 32-pixel tiles: noise of several grain sizes,
+    every local maximum a candidate (threshold 1) and few strong pixels, so that a contact missed at a border
+    or at a corner of four tiles changes the map."""
+    from paper_2602_14236_amd import binding
+    for seed, (grain, hi) in enumerate([(1, 900), (1, 600), (2, 500), (2, 300), (3, 250), (5, 120)]):
+        ctx = binding.SaliContext(lib_config(params(h, w, flow_levels=1, canny_lo=1, canny_hi=hi)))
+        rng = np.random.default_rng(seed)
+        coarse = rng.integers(0, 256, (h // grain + 2, w // grain + 2), dtype=np.uint8)
+        img = np.kron(coarse, np.ones((grain, grain), dtype=np.uint8))[:h, :w]
+        m = _check(ctx, np.stack([img, img, img], axis=-1), 1, hi)
+        print(f"{h}x{w} grain {grain}: {int((m >= 1).sum())} edge pixels", flush=True)
+        ctx.close()
