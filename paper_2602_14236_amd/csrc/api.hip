@@ -189,7 +189,7 @@ TableLayout table_layout(const sali_config& c) {
     TableLayout t = {};
     size_t o = 0;
     auto take = [&](size_t bytes) { size_t at = o; o = align_up(o + bytes); return at; };
-    t.lut = take((256 + 4096) * sizeof(uint16_t));
+    t.lut = take(kColourLutBytes);
     t.cursors = take(sizeof(Cursors));
     t.rows = take((size_t)c.max_frames * sizeof(sali_frame_row));
     t.tier = take((size_t)c.max_frames * kTokens);
@@ -384,7 +384,7 @@ int enqueue_saliency(sali_ctx* c, const uint8_t* const* d_rgb, const BatchPlan& 
     const sali_config& cfg = c->cfg;
     const PrepBatch f = prep_batch(c, d_rgb, bp, true, flow_or_null);
     const GateParams gp = gate_params(c);
-    SALI_TRY(launch_prep(f, bp.n, cfg.src_h, cfg.src_w, gp, c->tb<uint16_t>(c->tl.lut),
+    SALI_TRY(launch_prep(f, bp.n, cfg.src_h, cfg.src_w, gp, c->tb<uint8_t>(c->tl.lut),
                          cfg.canny_lo * cfg.canny_lo, cfg.canny_hi * cfg.canny_hi, s));
     SALI_TRY(launch_union(f, bp.n, cfg.src_h, cfg.src_w, s));
     return SALI_OK;
@@ -579,7 +579,7 @@ int static_scratch_for_device(int* device_out, float** ptr_out) {
 bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
 bool aligned256(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 255u) == 0; }
 
-void fill_luts(uint16_t* lin, uint16_t* fl) {
+void fill_luts(uint16_t* lin, uint16_t* fl, uint8_t* l8) {
     // sRGB decoding to 12-bit linear light, and the CIE L*a*b* companding function on a
     // 12-bit argument scaled by 2^15
     for (int v = 0; v < 256; ++v) {
@@ -592,6 +592,9 @@ void fill_luts(uint16_t* lin, uint16_t* fl) {
         const double u = t / 4095.0;
         const double f = u > d * d * d ? cbrt(u) : u / (3.0 * d * d) + 4.0 / 29.0;
         fl[t] = (uint16_t)floor(32768.0 * f + 0.5);
+        // L = 116 f - 16, scaled to a byte
+        const int l = ((116 * (int)fl[t] - 524288) * 255 + 1638400) / 3276800;
+        l8[t] = (uint8_t)(l < 0 ? 0 : (l > 255 ? 255 : l));
     }
 }
 
@@ -681,8 +684,8 @@ int sali_create(const sali_config* cfg, void* d_scratch, void* d_pools, void* d_
         }
     }
 
-    uint16_t lut[256 + 4096];
-    fill_luts(lut, lut + 256);
+    uint16_t lut[kColourLutBytes / 2];
+    fill_luts(lut, lut + 256, reinterpret_cast<uint8_t*>(lut + 256 + 4096));
     if (hipMemcpy(c->tables + c->tl.lut, lut, sizeof(lut), hipMemcpyHostToDevice) != hipSuccess ||
         sali_reset(c, nullptr) != SALI_OK || hipStreamSynchronize(nullptr) != hipSuccess) {
         sali_destroy(c);

@@ -1,7 +1,7 @@
 // Hysteresis of the Canny stage as a lock-free union-find, shared by the saliency kernels
 // (Implementation Details: Canny edge detection).
 // A pixel's key is its index with bit 31 set for weak pixels; links always point to the smaller
-// key, so the root of a component is a strong pixel iff the component has one.
+// key, so a walk along links meets a strong key iff the component has one.
 #pragma once
 
 #include "sali_internal.h"
@@ -17,16 +17,6 @@ __device__ __forceinline__ uint32_t uf_load(const uint32_t* parent, uint32_t idx
     return __hip_atomic_load(parent + idx, __ATOMIC_RELAXED, kScope);
 }
 
-template <int kScope>
-__device__ __forceinline__ uint32_t uf_find(const uint32_t* parent, uint32_t key) {
-    uint32_t k = key;               // keys strictly decrease along links, so this terminates
-    for (;;) {
-        const uint32_t p = uf_load<kScope>(parent, k & ~kWeakBit);
-        if (p == k) return k;
-        k = p;
-    }
-}
-
 // Is the component of a weak pixel (its key) without a strong pixel?  For kernels that run after all links
 // are final: ordinary cached loads.  A strong key on the way decides; the root need not be reached.
 __device__ __forceinline__ bool uf_stays_weak(const uint32_t* __restrict__ parent, uint32_t key) {
@@ -39,30 +29,26 @@ __device__ __forceinline__ bool uf_stays_weak(const uint32_t* __restrict__ paren
     return false;
 }
 
+// Joins the components of two pixels as far as the classes need it: "has a strong pixel" must reach the weak
+// components; two that are strong already are not joined, and a walk ends at the first strong key, whose
+// component's root is strong (keys decrease along links and strong keys are the smaller ones).  Both walks
+// of a pair go in step: a step is a trip to LDS or, at agent scope, past the L2.
 template <int kScope>
-__device__ __forceinline__ void uf_unite(uint32_t* parent, uint32_t ka, uint32_t kb) {
-    for (;;) {
-        ka = uf_find<kScope>(parent, ka);
-        kb = uf_find<kScope>(parent, kb);
-        if (ka == kb) return;
-        if (ka < kb) { const uint32_t t = ka; ka = kb; kb = t; }      // ka is the larger key
-        const uint32_t old = atomicMin(parent + (ka & ~kWeakBit), kb);
-        if (old == ka) return;      // ka was a root and now points at kb
-        ka = old;                   // somebody linked ka first: continue from where it pointed
-    }
-}
-
-// The cross-tile part only has to carry "has a strong pixel" into the weak components it touches: two
-// components that are strong already are not joined, and a walk ends at the first strong key, whose
-// component's root is strong (keys decrease along links and strong keys are the smaller ones).  A step of a
-// walk is a trip past the L2 (agent scope), so both walks of a pair go in step.
 __device__ __forceinline__ void uf_spread_strong(uint32_t* parent, uint32_t ka, uint32_t kb) {
     for (;;) {
+        uint32_t before_a = ka, before_b = kb;
         for (;;) {
             uint32_t pa = ka, pb = kb;
-            if (ka & kWeakBit) pa = uf_load<__HIP_MEMORY_SCOPE_AGENT>(parent, ka & ~kWeakBit);
-            if (kb & kWeakBit) pb = uf_load<__HIP_MEMORY_SCOPE_AGENT>(parent, kb & ~kWeakBit);
+            if (ka & kWeakBit) pa = uf_load<kScope>(parent, ka & ~kWeakBit);
+            if (kb & kWeakBit) pb = uf_load<kScope>(parent, kb & ~kWeakBit);
             if (pa == ka && pb == kb) break;        // two roots or strong keys
+            if constexpr (kScope == __HIP_MEMORY_SCOPE_WORKGROUP) {
+                // in LDS a passed node is linked on to its grandparent on the way, which keeps the paths short
+                if (pa != ka && before_a != ka) atomicMin(parent + (before_a & ~kWeakBit), pa);
+                if (pb != kb && before_b != kb) atomicMin(parent + (before_b & ~kWeakBit), pb);
+                before_a = ka;
+                before_b = kb;
+            }
             ka = pa;
             kb = pb;
         }
@@ -103,12 +89,12 @@ __device__ __forceinline__ void union_border(const uint8_t* __restrict__ cls, ui
     // would count on the others).  A diagonal only if neither the pixel straight across nor the one beside this
     // pixel leads there.
     const bool straight = c[1][1] != 0 && !(at % kTile != 0 && c[0][0] != 0 && c[1][0] != 0);
-    if (straight) uf_spread_strong(parent, me, (uint32_t)(gi + across) | (c[1][1] == 1 ? kWeakBit : 0u));
+    if (straight) uf_spread_strong<__HIP_MEMORY_SCOPE_AGENT>(parent, me, (uint32_t)(gi + across) | (c[1][1] == 1 ? kWeakBit : 0u));
     if (c[1][1] != 0) return;
 #pragma unroll
     for (int j = 0; j < 3; j += 2)
         if (c[1][j] != 0 && c[0][j] == 0)
-            uf_spread_strong(parent, me, (uint32_t)(gi + across + (j - 1) * along) | (c[1][j] == 1 ? kWeakBit : 0u));
+            uf_spread_strong<__HIP_MEMORY_SCOPE_AGENT>(parent, me, (uint32_t)(gi + across + (j - 1) * along) | (c[1][j] == 1 ? kWeakBit : 0u));
 }
 
 }  // namespace sali

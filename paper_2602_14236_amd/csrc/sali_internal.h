@@ -33,6 +33,10 @@ constexpr float kWinSigma = 2.5f;
 constexpr float kLamAbs = 1e-4f;
 constexpr float kLamRel = 1e-2f;
 
+// colour tables, in this order: sRGB decoding [256] and companding [4096], 16-bit each, then the L byte [4096]
+// of every argument of the companding
+constexpr int kColourLutBytes = (256 + 4096) * 2 + 4096;
+
 constexpr uint32_t kVMin = 10000u;          // floor of the colour-variance mask
 
 // Device-resident bookkeeping (lives in the caller's table buffer).
@@ -251,7 +255,7 @@ hipError_t launch_attend(const sali_frame_row* d_rows, Pools pools, int layer, i
 // f.dp are skipped (Algorithm 1: their saliency is not computed) and marked in f.skip, which launch_union
 // and launch_pool go by.
 hipError_t launch_gray(const PrepBatch& f, int n, int h, int w, hipStream_t s);
-hipError_t launch_prep(const PrepBatch& f, int n, int h, int w, GateParams gp, const uint16_t* d_lut,
+hipError_t launch_prep(const PrepBatch& f, int n, int h, int w, GateParams gp, const void* d_lut,
                        int lo2, int hi2, hipStream_t s);
 hipError_t launch_union(const PrepBatch& f, int n, int h, int w, hipStream_t s);
 // launch_motion: Eq. 5, per-patch motion of every frame of the batch from its flow (0 without flow).
