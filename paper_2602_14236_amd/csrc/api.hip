@@ -450,13 +450,14 @@ int enqueue_flow(sali_ctx* c, const BatchPlan& bp, const float2** flow, hipStrea
     int cur = 0;            // buffer holding the latest estimate
     bool have = false;
     for (int l = g.levels - 1; l >= 0; --l) {
-        for (int it = 0; it < c->cfg.flow_iters; ++it) {
-            int mode;
+        for (int it = 0; it < c->cfg.flow_iters;) {
+            int mode, done = 1;
             int ch = 0, cw = 0;
             if (it > 0) mode = 2;
             else if (!have) mode = 0;
             else { mode = 1; ch = g.h[l + 1]; cw = g.w[l + 1]; }
-            SALI_TRY(launch_flow_iter(f[cur], m, g.off[l], g.h[l], g.w[l], ch, cw, mode, c->fw, s));
+            SALI_TRY(launch_flow_updates(f[cur], m, g.off[l], g.h[l], g.w[l], ch, cw, mode, c->cfg.flow_iters - it, &done, c->fw, s));
+            it += done;
             cur ^= 1;
             have = true;
         }

@@ -20,6 +20,7 @@
 //                a chain of dependent HBM round trips, not a throughput limit (vector ALU 78 %,
 //                texture addresser 75 % busy at 1920x1080);
 //                tiles are handed to the XCDs in contiguous runs so that neighbours share an L2.
+//   k_flow_fused  three updates of a small level in one launch (halo recomputed)
 //   k_patch_motion, k_gate   per patch RMS flow magnitude (Eq. 5); static patches counted, the gate (Eq. 6).
 //                Stand-alone flow call only: the chained step has them in its pooling kernels.
 //
@@ -530,6 +531,50 @@ __device__ __forceinline__ float2 prior_at(const float2* __restrict__ d_in, int 
     return ld_at(d_in, pix(gy, w, gx));
 }
 
+// A^T A (xx, xy, yy) and A^T db (x, y) of the pixel (gy, gx) with prior displacement dp: the old frame's
+// expansion there, the new frame's sampled at the pixel + dp
+__device__ __forceinline__ void flow_terms(const float4* __restrict__ A1, const float* __restrict__ b1,
+                                           const float4* __restrict__ A2, const float* __restrict__ b2, int h, int w, int gy,
+                                           int gx, float2 dp, float (&t)[5]) {
+    const uint32_t gi = pix(gy, w, gx);
+    const float4 a1 = ld_at(A1, gi);
+    const float2 bb1 = make_float2(a1.w, ld_at(b1, gi));
+    const float sy = clampf((float)gy + dp.y, 0.0f, (float)(h - 1));
+    const float sx = clampf((float)gx + dp.x, 0.0f, (float)(w - 1));
+    const float fy0 = floorf(sy), fx0 = floorf(sx);
+    const int iy0 = (int)fy0, ix0 = (int)fx0;
+    const int iy1 = min(iy0 + 1, h - 1), ix1 = min(ix0 + 1, w - 1);
+    const float wy = sy - fy0, wx = sx - fx0;
+    const uint32_t i00 = pix(iy0, w, ix0), i10 = pix(iy1, w, ix0);
+    const uint32_t i01 = i00 + (uint32_t)(ix1 - ix0), i11 = i10 + (uint32_t)(ix1 - ix0);
+    const float4 a00 = ld_at(A2, i00), a01 = ld_at(A2, i01), a10 = ld_at(A2, i10), a11 = ld_at(A2, i11);
+    const float2 c00 = make_float2(a00.w, ld_at(b2, i00)), c01 = make_float2(a01.w, ld_at(b2, i01));
+    const float2 c10 = make_float2(a10.w, ld_at(b2, i10)), c11 = make_float2(a11.w, ld_at(b2, i11));
+    const float w00 = (1.0f - wx) * (1.0f - wy), w01 = wx * (1.0f - wy), w10 = (1.0f - wx) * wy, w11 = wx * wy;
+    const float a2xx = a00.x * w00 + a01.x * w01 + a10.x * w10 + a11.x * w11;
+    const float a2xy = a00.y * w00 + a01.y * w01 + a10.y * w10 + a11.y * w11;
+    const float a2yy = a00.z * w00 + a01.z * w01 + a10.z * w10 + a11.z * w11;
+    const float b2x = c00.x * w00 + c01.x * w01 + c10.x * w10 + c11.x * w11;
+    const float b2y = c00.y * w00 + c01.y * w01 + c10.y * w10 + c11.y * w11;
+    const float axx = 0.5f * (a1.x + a2xx), axy = 0.5f * (a1.y + a2xy), ayy = 0.5f * (a1.z + a2yy);
+    const float dbx = -0.5f * (b2x - bb1.x) + axx * dp.x + axy * dp.y;
+    const float dby = -0.5f * (b2y - bb1.y) + axy * dp.x + ayy * dp.y;
+    t[0] = axx * axx + axy * axy;
+    t[1] = axy * (axx + ayy);
+    t[2] = axy * axy + ayy * ayy;
+    t[3] = axx * dbx + axy * dby;
+    t[4] = axy * dbx + ayy * dby;
+}
+
+// the displacement from the windowed sums of the terms and the prior (ridge term centred on the prior)
+__device__ __forceinline__ float2 flow_solve(float g11, float g12, float g22, float h1, float h2, float2 dp) {
+    const float lam = kLamAbs + kLamRel * 0.5f * (g11 + g22);
+    const float m11 = g11 + lam, m22 = g22 + lam, m12 = g12;
+    const float r1 = h1 + lam * dp.x, r2 = h2 + lam * dp.y;
+    const float det = m11 * m22 - m12 * m12;
+    return make_float2((m22 * r1 - m12 * r2) / det, (m11 * r2 - m12 * r1) / det);
+}
+
 // Row and column of item p of a window pass over n_rows rows of TX outputs; false = an idle lane.
 // TX = 32: row-major.  TX = 16: the 32 lanes of a group take rows r and r + 8 (first the whole blocks of 16
 // rows: groups 0..7 take rows (0,8) .. (7,15); of the rest, n_rows - 16 k <= 15 rows, those that have a
@@ -600,37 +645,12 @@ __global__ __launch_bounds__(NT) void k_flow_iter(FlowBatch f, long long level_o
     for (int p = tid; p < RX * RY; p += NT) {
         const int ry = p / RX, rx = p % RX;
         const int gy = clampi(y0 - kWinR + ry, 0, h - 1), gx = clampi(x0 - kWinR + rx, 0, w - 1);
-        const uint32_t gi = pix(gy, w, gx);
         const float2 dp = prior_at(d_in, prior_mode, gy, gx, w, ch, cw);
         if (ry >= kWinR && ry < kWinR + TY && rx >= kWinR && rx < kWinR + TX) s_dp[ry - kWinR][rx - kWinR] = dp;
-        const float4 a1 = ld_at(A1, gi);
-        const float2 bb1 = make_float2(a1.w, ld_at(b1, gi));
-        // sample the new frame's expansion at x + prior
-        const float sy = clampf((float)gy + dp.y, 0.0f, (float)(h - 1));
-        const float sx = clampf((float)gx + dp.x, 0.0f, (float)(w - 1));
-        const float fy0 = floorf(sy), fx0 = floorf(sx);
-        const int iy0 = (int)fy0, ix0 = (int)fx0;
-        const int iy1 = min(iy0 + 1, h - 1), ix1 = min(ix0 + 1, w - 1);
-        const float wy = sy - fy0, wx = sx - fx0;
-        const uint32_t i00 = pix(iy0, w, ix0), i10 = pix(iy1, w, ix0);
-        const uint32_t i01 = i00 + (uint32_t)(ix1 - ix0), i11 = i10 + (uint32_t)(ix1 - ix0);
-        const float4 a00 = ld_at(A2, i00), a01 = ld_at(A2, i01), a10 = ld_at(A2, i10), a11 = ld_at(A2, i11);
-        const float2 c00 = make_float2(a00.w, ld_at(b2, i00)), c01 = make_float2(a01.w, ld_at(b2, i01));
-        const float2 c10 = make_float2(a10.w, ld_at(b2, i10)), c11 = make_float2(a11.w, ld_at(b2, i11));
-        const float w00 = (1.0f - wx) * (1.0f - wy), w01 = wx * (1.0f - wy), w10 = (1.0f - wx) * wy, w11 = wx * wy;
-        const float a2xx = a00.x * w00 + a01.x * w01 + a10.x * w10 + a11.x * w11;
-        const float a2xy = a00.y * w00 + a01.y * w01 + a10.y * w10 + a11.y * w11;
-        const float a2yy = a00.z * w00 + a01.z * w01 + a10.z * w10 + a11.z * w11;
-        const float b2x = c00.x * w00 + c01.x * w01 + c10.x * w10 + c11.x * w11;
-        const float b2y = c00.y * w00 + c01.y * w01 + c10.y * w10 + c11.y * w11;
-        const float axx = 0.5f * (a1.x + a2xx), axy = 0.5f * (a1.y + a2xy), ayy = 0.5f * (a1.z + a2yy);
-        const float dbx = -0.5f * (b2x - bb1.x) + axx * dp.x + axy * dp.y;
-        const float dby = -0.5f * (b2y - bb1.y) + axy * dp.x + ayy * dp.y;
-        s_in[0][ry][rx] = axx * axx + axy * axy;
-        s_in[1][ry][rx] = axy * (axx + ayy);
-        s_in[2][ry][rx] = axy * axy + ayy * ayy;
-        s_in[3][ry][rx] = axx * dbx + axy * dby;
-        s_in[4][ry][rx] = axy * dbx + ayy * dby;
+        float t[5];
+        flow_terms(A1, b1, A2, b2, h, w, gy, gx, dp, t);
+#pragma unroll
+        for (int c = 0; c < 5; ++c) s_in[c][ry][rx] = t[c];
     }
     __syncthreads();
 
@@ -684,14 +704,145 @@ __global__ __launch_bounds__(NT) void k_flow_iter(FlowBatch f, long long level_o
 #pragma unroll
             for (int c = 0; c < 5; ++c) acc[c] += wk * s_in[c][ty + k][tx];
         }
-        const float2 dp = s_dp[ty][tx];
-        const float lam = kLamAbs + kLamRel * 0.5f * (acc[0] + acc[2]);
-        const float m11 = acc[0] + lam, m22 = acc[2] + lam, m12 = acc[1];
-        const float r1 = acc[3] + lam * dp.x, r2 = acc[4] + lam * dp.y;
-        const float det = m11 * m22 - m12 * m12;
         *reinterpret_cast<float2*>(reinterpret_cast<char*>(d_out) + pix(gy, w, gx) * 8u) =
-            make_float2((m22 * r1 - m12 * r2) / det, (m11 * r2 - m12 * r1) / det);
+            flow_solve(acc[0], acc[1], acc[2], acc[3], acc[4], s_dp[ty][tx]);
     }
+}
+
+// ---------------------------------------------------------------------------------------------
+// Three updates of a level in one launch.  An update of a pixel needs the terms, hence the priors, of the
+// pixels within five of it, so a block that makes a TX x TY tile of the third update makes 10 more rows and
+// columns of the second and 20 more of the first (the warped samples come from memory wherever they lie).
+// That is several times the work per pixel of a launch per update, and it pays where a level is so
+// small that its blocks, one per compute unit, leave the chip idle and an update is a chain of
+// launch, trips to memory and window passes: 84x84 18.1 -> 11.5 us for three updates (tile 16x8), 168x168
+// 18.0 -> 12.4, two frames of it 18.1 -> 14.9 (16x16), 336x336 19.2 -> 17.5 (32x16).  With more than one
+// block per compute unit it loses (168x168 x 4: 21.5 against 27).  The results are the same numbers.
+// Cells outside the image stand for the clamped coordinate, as in k_flow_iter.
+constexpr int kFusedUpdates = 3;
+constexpr int kFusedThreads = 1024;
+
+template <int TX, int TY>
+struct FusedTile {
+    static constexpr int SX = TX + 10 * kFusedUpdates, SY = TY + 10 * kFusedUpdates;      // the first update's terms
+    static constexpr int PX = SX - 10, PY = SY - 10;                                      // the first update's results
+    float in[5][SY][SX];
+    float2 p[SY * SX];          // priors of the first update, then of the third
+    float2 q[PY * PX];          // priors of the second update
+};
+
+// Update I of the block: terms of its region plus five cells all round, window passes, solve; the priors
+// (region of the terms, row-major) come from `prior`, the results go to `next` or, the last ones, to d_out.
+template <int TX, int TY, int I>
+__device__ __forceinline__ void fused_update(FusedTile<TX, TY>& sh, float2* prior, float2* next, const float4* __restrict__ A1,
+                                             const float* __restrict__ b1, const float4* __restrict__ A2,
+                                             const float* __restrict__ b2, const float2* __restrict__ d_in,
+                                             float2* __restrict__ d_out, int h, int w, int ch, int cw, int prior_mode, int x0,
+                                             int y0, const FlowWeights& fw) {
+    constexpr int kLeft = kFusedUpdates - 1 - I, NT = kFusedThreads;
+    constexpr int DX = TX + 10 * kLeft, DY = TY + 10 * kLeft, RX = DX + 10, RY = DY + 10;
+    const int tid = threadIdx.x;
+    const int ox = x0 - 5 * (kLeft + 1), oy = y0 - 5 * (kLeft + 1);
+#pragma unroll 2
+    for (int p = tid; p < RX * RY; p += NT) {
+        const int ry = p / RX, rx = p % RX;
+        const int gy = clampi(oy + ry, 0, h - 1), gx = clampi(ox + rx, 0, w - 1);
+        float2 dp;
+        if constexpr (I == 0) {
+            dp = prior_at(d_in, prior_mode, gy, gx, w, ch, cw);
+            prior[p] = dp;
+        } else {
+            dp = prior[(gy - oy) * RX + (gx - ox)];         // the clamped cell lies in the region: the tile meets the image
+        }
+        float t[5];
+        flow_terms(A1, b1, A2, b2, h, w, gy, gx, dp, t);
+#pragma unroll
+        for (int c = 0; c < 5; ++c) sh.in[c][ry][rx] = t[c];
+    }
+    __syncthreads();
+    // Window passes, two outputs an item: twelve reads a field for two outputs; with one the passes
+    // wait for LDS, with four too few lanes have work.  Row pass in place, as in k_flow_iter.
+    {
+        constexpr int kItems = RY * (DX / 2), kN = (kItems + NT - 1) / NT;
+        static_assert(DX % 2 == 0 && DY % 2 == 0, "pairs");
+        float acc[kN][5][2];
+#pragma unroll
+        for (int n = 0; n < kN; ++n) {
+            const int p = tid + n * NT;
+            if (p >= kItems) continue;
+            const int ry = p / (DX / 2), cx = 2 * (p % (DX / 2));
+#pragma unroll
+            for (int c = 0; c < 5; ++c) {
+                float v[12];
+#pragma unroll
+                for (int k = 0; k < 12; ++k) v[k] = sh.in[c][ry][cx + k];
+                acc[n][c][0] = acc[n][c][1] = 0.0f;
+#pragma unroll
+                for (int k = 0; k <= 2 * kWinR; ++k) {
+                    acc[n][c][0] += fw.win_g[k] * v[k];
+                    acc[n][c][1] += fw.win_g[k] * v[k + 1];
+                }
+            }
+        }
+        __syncthreads();
+#pragma unroll
+        for (int n = 0; n < kN; ++n) {
+            const int p = tid + n * NT;
+            if (p >= kItems) continue;
+            const int ry = p / (DX / 2), cx = 2 * (p % (DX / 2));
+#pragma unroll
+            for (int c = 0; c < 5; ++c) {
+                sh.in[c][ry][cx] = acc[n][c][0];
+                sh.in[c][ry][cx + 1] = acc[n][c][1];
+            }
+        }
+        __syncthreads();
+    }
+    for (int p = tid; p < (DY / 2) * DX; p += NT) {
+        const int ty0 = 2 * (p / DX), tx = p % DX;
+        float acc[5][2];
+#pragma unroll
+        for (int c = 0; c < 5; ++c) {
+            float v[12];
+#pragma unroll
+            for (int k = 0; k < 12; ++k) v[k] = sh.in[c][ty0 + k][tx];
+            acc[c][0] = acc[c][1] = 0.0f;
+#pragma unroll
+            for (int k = 0; k <= 2 * kWinR; ++k) {
+                acc[c][0] += fw.win_g[k] * v[k];
+                acc[c][1] += fw.win_g[k] * v[k + 1];
+            }
+        }
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+            const int ty = ty0 + j;
+            const float2 d = flow_solve(acc[0][j], acc[1][j], acc[2][j], acc[3][j], acc[4][j], prior[(ty + kWinR) * RX + tx + kWinR]);
+            if constexpr (kLeft == 0) {
+                const int gy = y0 + ty, gx = x0 + tx;
+                if (gy < h && gx < w) *reinterpret_cast<float2*>(reinterpret_cast<char*>(d_out) + pix(gy, w, gx) * 8u) = d;
+            } else {
+                next[ty * DX + tx] = d;
+            }
+        }
+    }
+    if constexpr (kLeft > 0) __syncthreads();
+}
+
+template <int TX, int TY>
+__global__ __launch_bounds__(kFusedThreads) void k_flow_fused(FlowBatch f, long long level_off, int h, int w, int ch, int cw,
+                                                              int prior_mode, FlowWeights fw) {
+    const BlockId blk = xcd_block_id();
+    const float4* __restrict__ A1 = f.A1[blk.z] + level_off;
+    const float* __restrict__ b1 = f.b1[blk.z] + level_off;
+    const float4* __restrict__ A2 = f.A2[blk.z] + level_off;
+    const float* __restrict__ b2 = f.b2[blk.z] + level_off;
+    const float2* __restrict__ d_in = f.d_in[blk.z];
+    float2* __restrict__ d_out = f.d_out[blk.z];
+    __shared__ FusedTile<TX, TY> sh;
+    const int x0 = blk.x * TX, y0 = blk.y * TY;
+    fused_update<TX, TY, 0>(sh, sh.p, sh.q, A1, b1, A2, b2, d_in, d_out, h, w, ch, cw, prior_mode, x0, y0, fw);
+    fused_update<TX, TY, 1>(sh, sh.q, sh.p, A1, b1, A2, b2, d_in, d_out, h, w, ch, cw, prior_mode, x0, y0, fw);
+    fused_update<TX, TY, 2>(sh, sh.p, sh.q, A1, b1, A2, b2, d_in, d_out, h, w, ch, cw, prior_mode, x0, y0, fw);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -793,8 +944,25 @@ hipError_t launch_expand(const ExpandBatch& f, int n, LevelGeom g, FlowWeights f
     return hipGetLastError();
 }
 
-hipError_t launch_flow_iter(const FlowBatch& f, int n, int64_t level_off, int h, int w, int ch, int cw,
-                            int prior_mode, FlowWeights fw, hipStream_t s) {
+hipError_t launch_flow_updates(const FlowBatch& f, int n, int64_t level_off, int h, int w, int ch, int cw,
+                               int prior_mode, int wanted, int* done, FlowWeights fw, hipStream_t s) {
+    // three updates in one launch where the blocks of some tile fit one per compute unit, the smallest such tile
+    constexpr int kComputeUnits = 256;
+    auto tiles = [&](int tx, int ty) { return (long long)((w + tx - 1) / tx) * ((h + ty - 1) / ty) * n; };
+#define SALI_FUSED_LAUNCH(TX, TY)                                                                                       \
+    do {                                                                                                                \
+        hipLaunchKernelGGL((k_flow_fused<TX, TY>), dim3((w + TX - 1) / TX, (h + TY - 1) / TY, n), dim3(kFusedThreads), 0, \
+                           s, f, (long long)level_off, h, w, ch, cw, prior_mode, fw);                                   \
+        *done = kFusedUpdates;                                                                                          \
+        return hipGetLastError();                                                                                       \
+    } while (0)
+    if (wanted >= kFusedUpdates) {
+        if (tiles(16, 8) <= kComputeUnits) SALI_FUSED_LAUNCH(16, 8);
+        if (tiles(16, 16) <= kComputeUnits) SALI_FUSED_LAUNCH(16, 16);
+        if (tiles(32, 16) <= kComputeUnits) SALI_FUSED_LAUNCH(32, 16);
+    }
+#undef SALI_FUSED_LAUNCH
+    *done = 1;
     // Tile and block by level size:
     //   below 40 000 pixels   16x16, 256 threads   (16 KB of LDS: eight blocks per compute unit)
     //   above                 32x16, 512 threads   (26 KB: four blocks; 2.1 instead of 2.6 halo cells per output)

@@ -271,8 +271,9 @@ hipError_t launch_pool(const PoolBatch& f, int n, int h, int w, uint8_t* d_salma
 hipError_t launch_pyramid(const PyrBatch& f, int n, const LevelGeom& g, hipStream_t s);
 hipError_t launch_polyexp(const PyrBatch& f, int n, LevelGeom g, FlowWeights fw, hipStream_t s);
 hipError_t launch_expand(const ExpandBatch& f, int n, LevelGeom g, FlowWeights fw, hipStream_t s);
-hipError_t launch_flow_iter(const FlowBatch& f, int n, int64_t level_off, int h, int w, int ch, int cw,
-                            int prior_mode, FlowWeights fw, hipStream_t s);
+// one launch of at most `wanted` (>= 1) updates of a level, as many as suit its size; *done = how many it makes
+hipError_t launch_flow_updates(const FlowBatch& f, int n, int64_t level_off, int h, int w, int ch, int cw,
+                               int prior_mode, int wanted, int* done, FlowWeights fw, hipStream_t s);
 hipError_t launch_patch_gate(const float2* d_flow, int h, int w, float tau_t, float theta_r, float* d_dp,
                              sali_gate* d_gate, float* d_flow_uv_or_null, hipStream_t s);
 

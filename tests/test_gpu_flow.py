@@ -185,3 +185,27 @@ def test_pyramid_in_pairs_of_levels(h, w, levels, shift):
     print(f"{h}x{w}, {levels} levels: largest error {max(np.abs(got[0] - d[..., 0]).max(), np.abs(got[1] - d[..., 1]).max()):.2e}", flush=True)
     assert close(got[0], d[..., 0]).all() and close(got[1], d[..., 1]).all()
     ctx.close()
+
+
+@pytest.mark.parametrize("h,w,levels,iters", [
+    (24, 25, 1, 3), (49, 33, 2, 3), (128, 129, 1, 4), (170, 168, 2, 3), (240, 433, 2, 3),     # 16x8, 16x16 and 32x16 tiles
+    (100, 90, 3, 1), (100, 90, 3, 2), (100, 90, 3, 7), (430, 440, 1, 3),                      # single updates, both mixed, too large
+])
+def test_updates_per_launch(h, w, levels, iters):
+    """Three updates of a small level in one launch, over its tile shapes, ragged tiles, frames smaller than the
+    halo, and update counts that are no multiple of three, against the oracle."""
+    from paper_2602_14236_amd import binding
+    ctx = binding.SaliContext(lib_config(params(h, w, flow_levels=levels, flow_iters=iters)))
+    yy, xx = np.mgrid[0:h, 0:w].astype(np.float64)
+    rng = np.random.default_rng(h + w + iters)
+    frames = []
+    for d in (0.0, 1.0):
+        x, y = xx - 1.2 * d, yy + 0.8 * d
+        img = 128 + 50 * np.sin(x / 2.9) * np.sin(y / 3.3) + 40 * np.sin((x - y) / 7.0)
+        frames.append(np.clip(np.rint(img[..., None] + rng.normal(0, 1, (h, w, 3))), 0, 255).astype(np.uint8))
+    uv, _, _ = _run(ctx, frames[0], frames[1])
+    d = of.flow(frames[0], frames[1], levels, iters)
+    print(f"{h}x{w}, {levels} levels, {iters} updates: largest error "
+          f"{max(np.abs(uv[0] - d[..., 0]).max(), np.abs(uv[1] - d[..., 1]).max()):.2e}", flush=True)
+    assert close(uv[0], d[..., 0]).all() and close(uv[1], d[..., 1]).all()
+    ctx.close()
