@@ -137,7 +137,9 @@ def _check(code: int, what: str):
 
 
 def _stream() -> int:
-    return torch.cuda.current_stream().cuda_stream
+    """Handle of the current device's current stream, without a Stream object made for it (of the 13 us that a
+    small attention call took in Python and ctypes, that and pointer objects were five)."""
+    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
 
 
 def _ptr_array(tensors):
@@ -146,7 +148,7 @@ def _ptr_array(tensors):
 
 
 def _ptr(t: Optional[torch.Tensor]):
-    return None if t is None else C.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()          # ctypes makes the pointer from the declared type
 
 
 def make_config(src_h, src_w, *, flow_levels=3, flow_iters=3, tau_t=0.5, theta_r=0.90, canny_lo=50, canny_hi=100,
@@ -335,21 +337,23 @@ class SaliContext:
         """The six pool arrays as they lie in memory: [cap * n_planes, row], frame-major (a stored frame
         with base b and n rows owns rows [b * P, (b + n) * P), plane p of it rows [b * P + p * n, ...))."""
         c, L, P = self.cfg, self.layout, self.n_planes
-        g = c.head_dim // c.group
-        buf = self.pools
+        d, g = c.head_dim, c.head_dim // c.group
+        # one typed view of the buffer per type and one strided view of it per array (slicing and reshaping each
+        # array by itself took 22 us, half of the smallest compress and read-back)
+        as_u8, as_i8, as_f16, as_f32 = (self.pools, self.pools.view(torch.int8), self.pools.view(torch.float16),
+                                        self.pools.view(torch.float32))
 
-        def view(off, count, dtype, shape):
-            nbytes = count * torch.empty((), dtype=dtype).element_size()
-            return buf[off:off + nbytes].view(dtype).view(shape)
+        def view(base, size, off, rows, row):
+            return base.as_strided((rows, row), (row, 1), base.storage_offset() + off // size)
 
+        n16, n8, n4 = P * c.cap_fp16, P * c.cap_int8, P * c.cap_int4
         return {
-            "fp16": view(L.off_fp16, P * c.cap_fp16 * c.head_dim, torch.float16, (P * c.cap_fp16, c.head_dim)),
-            "codes8": view(L.off_codes8, P * c.cap_int8 * c.head_dim, torch.int8, (P * c.cap_int8, c.head_dim)),
-            "scale8": view(L.off_scale8, P * c.cap_int8 * g, torch.float32, (P * c.cap_int8, g)),
-            "codes4": view(L.off_codes4, P * c.cap_int4 * c.head_dim // 2, torch.uint8,
-                           (P * c.cap_int4, c.head_dim // 2)),
-            "scale4": view(L.off_scale4, P * c.cap_int4 * g, torch.float32, (P * c.cap_int4, g)),
-            "zero4": view(L.off_zero4, P * c.cap_int4 * g, torch.float16, (P * c.cap_int4, g)),
+            "fp16": view(as_f16, 2, L.off_fp16, n16, d),
+            "codes8": view(as_i8, 1, L.off_codes8, n8, d),
+            "scale8": view(as_f32, 4, L.off_scale8, n8, g),
+            "codes4": view(as_u8, 1, L.off_codes4, n4, d // 2),
+            "scale4": view(as_f32, 4, L.off_scale4, n4, g),
+            "zero4": view(as_f16, 2, L.off_zero4, n4, g),
         }
 
     def pool_views(self, planes=None):
