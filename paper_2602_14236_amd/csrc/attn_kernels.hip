@@ -34,7 +34,6 @@ typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
 typedef _Float16 half2_t __attribute__((ext_vector_type(2)));
 
-constexpr int kRowsPerStep = 4;               // rows in flight per lane group (K and V each)
 constexpr int kComputeUnits = 256;
 constexpr int kResidentBlocks = kComputeUnits * 8;      // compute units x blocks of the main kernel that fit on one
 constexpr int kPartialStride = kAttnPartialStride;   // max, sum, 128 values, padded to whole 128-byte lines
@@ -151,15 +150,18 @@ struct SoftmaxState {
     float acc[8];
 };
 
-// The rows of one tier of one stored frame that fall to this block: 64-row groups split, split +
-// n_splits, ...; lane group g takes rows jb + g, jb + 16 + g, ...  `base` = first pool row of the
-// frame in this tier, `count` = its rows.  kQ queries share every row that is read.
-template <int kTier, int kQ>
-__device__ __forceinline__ void attend_tier(const Pools& pools, size_t plane_k, size_t plane_v, int base, int count,
-                                            int split, int n_splits, int g, int l, const QueryPiece (&q)[kQ],
-                                            float softmax_scale, float mult, SoftmaxState (&st)[kQ]) {
+// The rows of one tier of one stored frame that fall to this block: groups of 16 * kRowsPerStep rows split,
+// split + n_splits, ...; lane group g takes rows jb + g, jb + 16 + g, ... (kRowsPerStep of them in flight, K
+// and V each).  `base` = first pool row of the frame in this tier, `count` = its rows.  kQ queries share
+// every row that is read.  Returns the split that the next tier's first group falls to, so that the groups
+// of a frame's tiers go round all splits.
+template <int kTier, int kQ, int kRowsPerStep>
+__device__ __forceinline__ int attend_tier(const Pools& pools, size_t plane_k, size_t plane_v, int base, int count,
+                                           int split, int n_splits, int g, int l, const QueryPiece (&q)[kQ],
+                                           float softmax_scale, float mult, SoftmaxState (&st)[kQ]) {
+    constexpr int kGroupRows = 16 * kRowsPerStep;
     const size_t row0_k = pool_row0(pools, base, count, plane_k), row0_v = pool_row0(pools, base, count, plane_v);
-    for (int jb = split * 64; jb < count; jb += n_splits * 64) {
+    for (int jb = split * kGroupRows; jb < count; jb += n_splits * kGroupRows) {
         RawRow<kTier> rk[kRowsPerStep], rv[kRowsPerStep];
         bool valid[kRowsPerStep];
 #pragma unroll
@@ -229,15 +231,16 @@ __device__ __forceinline__ void attend_tier(const Pools& pools, size_t plane_k, 
             }
         }
     }
+    const int next = split - (count + kGroupRows - 1) / kGroupRows % n_splits;
+    return next < 0 ? next + n_splits : next;
 }
 
 }  // namespace
 
 // grid (n_chunks * n_splits, n_heads).  Block (c, s) of K/V head h takes the frames
-// [frame_lo + c * frames_per_chunk, ...) and of each source frame the 64-row groups s, s + n_splits, ...
-// of every tier, for kQ of the query heads that share the K/V head (gridDim.z such sets:
+// [frame_lo + c * frames_per_chunk, ...) and of each source frame every n_splits-th group of rows, for kQ of the query heads that share the K/V head (gridDim.z such sets:
 // q_per_kv = kQ * gridDim.z), and writes one partial per query head.
-template <int kQ>
+template <int kQ, int kRowsPerStep>
 __global__ __launch_bounds__(256) void k_attn_partial(const sali_frame_row* __restrict__ rows, Pools pools, int layer,
                                                       int n_heads, const _Float16* __restrict__ q, int frame_lo,
                                                       int frame_hi, int frames_per_chunk, int n_splits,
@@ -295,12 +298,13 @@ __global__ __launch_bounds__(256) void k_attn_partial(const sali_frame_row* __re
             if (rows[t].src == src) ++n_uses;
         const float mult = (float)n_uses;
         const sali_frame_row row = rows[src];
-        attend_tier<SALI_TIER_FP16, kQ>(pools, plane_k, plane_v, row.base16, row.n16, split, n_splits, g, l, qp,
-                                        softmax_scale, mult, st);
-        attend_tier<SALI_TIER_INT8, kQ>(pools, plane_k, plane_v, row.base8, row.n8, split, n_splits, g, l, qp,
-                                        softmax_scale, mult, st);
-        attend_tier<SALI_TIER_INT4, kQ>(pools, plane_k, plane_v, row.base4, row.n4, split, n_splits, g, l, qp,
-                                        softmax_scale, mult, st);
+        int at = split;
+        at = attend_tier<SALI_TIER_FP16, kQ, kRowsPerStep>(pools, plane_k, plane_v, row.base16, row.n16, at, n_splits, g, l, qp,
+                                                           softmax_scale, mult, st);
+        at = attend_tier<SALI_TIER_INT8, kQ, kRowsPerStep>(pools, plane_k, plane_v, row.base8, row.n8, at, n_splits, g, l, qp,
+                                                           softmax_scale, mult, st);
+        attend_tier<SALI_TIER_INT4, kQ, kRowsPerStep>(pools, plane_k, plane_v, row.base4, row.n4, at, n_splits, g, l, qp,
+                                                      softmax_scale, mult, st);
     }
 
     // merge the 16 lane groups, one query head after the other
@@ -861,7 +865,7 @@ __global__ __launch_bounds__(64 * kPfWaves) __attribute__((amdgpu_waves_per_eu(2
 }
 
 hipError_t launch_attend(const sali_frame_row* d_rows, Pools pools, int layer, int n_heads, int q_per_kv,
-                         const void* d_q, int frame_lo, int frame_hi, float softmax_scale, float* d_partial,
+                         const void* d_q, int frame_lo, int frame_hi, int rows_per_frame, float softmax_scale, float* d_partial,
                          float* d_out, float* d_lse_or_null, hipEvent_t ev_start, hipEvent_t ev_stop, hipStream_t s) {
     const int n_range = frame_hi - frame_lo;
     int n_partials = 0;
@@ -886,6 +890,9 @@ hipError_t launch_attend(const sali_frame_row* d_rows, Pools pools, int layer, i
         return hipGetLastError();
     }
     if (n_range > 0) {
+        // eight queries per K/V head run as two sets of four (two blocks read the same rows, the second
+        // mostly from cache): a block with eight query states needs 256 registers per lane and was slower
+        const int kq = q_per_kv == 8 ? 4 : q_per_kv, sets = q_per_kv / kq;
         // One resident round of blocks: at 8 blocks of 256 threads per compute unit the chip holds
         // kResidentBlocks; more blocks than that leave a second, nearly empty round at the end of a
         // bandwidth-bound kernel.  Blocks of a head: whole frames per block for long ranges, row
@@ -894,31 +901,34 @@ hipError_t launch_attend(const sali_frame_row* d_rows, Pools pools, int layer, i
         per_head = per_head < 1 ? 1 : (per_head > kAttnPartials ? kAttnPartials : per_head);
         const int fpc = (n_range + per_head - 1) / per_head;
         const int n_chunks = (n_range + fpc - 1) / fpc;
+        // Small ranges: with groups of 64 rows fewer than two blocks per compute unit would have any (at most
+        // rows_per_frame / 64 + 3 groups a frame), and each would be a chain of three tiers' loads and four rows'
+        // arithmetic per lane group.  Groups of 16 rows then, one row per lane group, over up to twice the splits:
+        // 4 queries x 8 heads, 2 frames of 124 / 28 / 84 rows 11.3 -> 6.6 us, 1 query 6.3 -> 4.2.
+        const bool small = (long long)n_range * (rows_per_frame / 64 + 1) * n_heads * sets < 2 * kComputeUnits;
+        const int most = small ? 18 : 9;
         int n_splits = per_head / n_chunks;
-        n_splits = n_splits < 1 ? 1 : (n_splits > 9 ? 9 : n_splits);
+        n_splits = n_splits < 1 ? 1 : (n_splits > most ? most : n_splits);
         n_partials = n_chunks * n_splits;
         if (ev_start != nullptr && hipEventRecord(ev_start, s) != hipSuccess) return hipErrorUnknown;
-        // eight queries per K/V head run as two sets of four (two blocks read the same rows, the second
-        // mostly from cache): a block with eight query states needs 256 registers per lane and was slower
-        const int kq = q_per_kv == 8 ? 4 : q_per_kv;
-        const dim3 grid(n_partials, n_heads, q_per_kv / kq);
+        const dim3 grid(n_partials, n_heads, sets);
         const _Float16* q = reinterpret_cast<const _Float16*>(d_q);
+#define SALI_ATTN_LAUNCH(KQ)                                                                                              \
+    do {                                                                                                                  \
+        if (small)                                                                                                        \
+            hipLaunchKernelGGL((k_attn_partial<KQ, 1>), grid, dim3(256), 0, s, d_rows, pools, layer, n_heads, q, frame_lo, \
+                               frame_hi, fpc, n_splits, softmax_scale, d_partial);                                        \
+        else                                                                                                              \
+            hipLaunchKernelGGL((k_attn_partial<KQ, 4>), grid, dim3(256), 0, s, d_rows, pools, layer, n_heads, q, frame_lo, \
+                               frame_hi, fpc, n_splits, softmax_scale, d_partial);                                        \
+    } while (0)
         switch (kq) {
-            case 1:
-                hipLaunchKernelGGL(k_attn_partial<1>, grid, dim3(256), 0, s, d_rows, pools, layer, n_heads, q, frame_lo,
-                                   frame_hi, fpc, n_splits, softmax_scale, d_partial);
-                break;
-            case 2:
-                hipLaunchKernelGGL(k_attn_partial<2>, grid, dim3(256), 0, s, d_rows, pools, layer, n_heads, q, frame_lo,
-                                   frame_hi, fpc, n_splits, softmax_scale, d_partial);
-                break;
-            case 4:
-                hipLaunchKernelGGL(k_attn_partial<4>, grid, dim3(256), 0, s, d_rows, pools, layer, n_heads, q, frame_lo,
-                                   frame_hi, fpc, n_splits, softmax_scale, d_partial);
-                break;
-            default:
-                return hipErrorInvalidValue;
+            case 1: SALI_ATTN_LAUNCH(1); break;
+            case 2: SALI_ATTN_LAUNCH(2); break;
+            case 4: SALI_ATTN_LAUNCH(4); break;
+            default: return hipErrorInvalidValue;
         }
+#undef SALI_ATTN_LAUNCH
         if (ev_stop != nullptr && hipEventRecord(ev_stop, s) != hipSuccess) return hipErrorUnknown;
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;

@@ -313,3 +313,36 @@ def test_many_queries_shares_of_the_range_and_pointer_runs(heads, q_per_kv, fram
         assert bool(((lse.double() - exp_lse).abs() <= 1e-5 * (1 + exp_lse.abs())).all())
     assert ctx.get_status() == 0
     ctx.close()
+
+
+@pytest.mark.parametrize("q_per_kv", [1, 2, 4, 8])
+@pytest.mark.parametrize("frames,heads,counts", [
+    (1, 1, (1, 0, 0)), (1, 3, (0, 0, 17)), (2, 2, (15, 16, 33)), (3, 1, (64, 65, 63)), (1, 2, (288, 144, 144)),   # groups of 16 rows
+    (30, 2, (200, 180, 196)), (12, 5, (63, 65, 128)),                                                              # groups of 64
+])
+def test_few_queries_groups_of_rows(q_per_kv, frames, heads, counts):
+    """The streaming kernel on both sides of its rule (groups of 16 rows for small ranges, of 64 otherwise) where
+    groups end, tiers are empty and a frame has fewer groups than blocks.  fp32 sums of at most 20 000 terms
+    in hundreds of partial ones against the float64 oracle: 1e-5 relative to the largest output."""
+    from paper_2602_14236_amd import binding
+    k16, k8, k4 = counts
+    p = params(96, 96, tier_mode=1, k_fp16=k16, k_int8=k8, k_int4=k4, n_layers=1, n_heads=heads,
+               cap_fp16=k16 * frames + 1, cap_int8=k8 * frames + 1, cap_int4=k4 * frames + 1, max_frames=frames)
+    ctx = binding.SaliContext(lib_config(p))
+    orc = SaliCacheOracle(oracle_config(p))
+    g = torch.Generator(device="cpu").manual_seed(frames * 100 + heads)
+    for t in range(frames):
+        kv = torch.randn((1, 2, heads, 576, 128), generator=g).to(torch.float16)
+        scores = torch.rand(576, generator=g)
+        ctx.kv_compress(kv.cuda(), scores.cuda(), t)
+        orc.kv_compress(kv.numpy(), scores.numpy(), t)
+    q = _q(3, heads * q_per_kv)
+    out, lse = torch.empty((heads * q_per_kv, 128), device="cuda"), torch.empty(heads * q_per_kv, device="cuda")
+    for lo, hi in ((0, frames), (frames // 2, frames)):
+        ctx.attend_decode_gqa(0, q, q_per_kv, lo, hi, 128.0 ** -0.5, out, lse)
+        exp, exp_lse = attend_decode(orc, 0, q.cpu().numpy(), lo, hi, 128.0 ** -0.5, q_per_kv=q_per_kv)
+        err = np.abs(out.cpu().numpy() - exp).max() / np.abs(exp).max()
+        print(f"{frames} frames [{lo}, {hi}), {heads} heads, {q_per_kv} queries: relative error {err:.1e}", flush=True)
+        assert err <= 1e-5
+        assert np.all(np.abs(lse.cpu().numpy() - exp_lse) <= 1e-5 * (1 + np.abs(exp_lse)))
+    ctx.close()
