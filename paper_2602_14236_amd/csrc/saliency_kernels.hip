@@ -8,14 +8,15 @@
 //            tables held in LDS too):
 //            gray -> 5x5 binomial blur -> Sobel -> non-maximum suppression
 //            -> weak/strong class, and RGB -> 8-bit LAB -> 5x5 variance sum V, plus the frame
-//            sum of V (one 64-bit atomic per block).  Also emits the gray image for the flow.
+//            sum of V (one 64-bit atomic per block).
 //            8-connected hysteresis is a lock-free union-find over weak/strong pixels.  A
 //            pixel's key is its index with bit 31 set for weak pixels; links always point to
-//            the smaller key, so the root of a component is a strong pixel iff it has one.
-//            k_prep labels the components of its own tile in LDS (label equivalence, no
-//            global traffic) and writes each pixel's link to its tile-local root.
+//            the smaller key, so a walk along links meets a strong key iff the component has one.
+//            k_prep joins the components of its own tile in LDS (label equivalence, no
+//            global traffic) and writes each pixel's link to a strong pixel of its tile's part
+//            or, without one, to that part's root.
 //   k_union  carries "has a strong pixel" across tile borders with global atomics (border pixels only).
-//   k_pool   per patch: E = edge pixel whose root is strong, C = V above the frame mean and
+//   k_pool   per patch: E = edge pixel whose component is strong, C = V above the frame mean and
 //            above a floor; q = sum(E + C); score = floor(q * 2^15 / |P|) / 65536.  In the
 //            chained step it also reduces the flow field to the patch's motion (Eq. 5).
 //   k_pool_tail  one block per frame: the gate (Eq. 6) and the ranking of the frame's tokens; the
