@@ -785,6 +785,10 @@ __global__ __launch_bounds__(64 * kPfWaves) __attribute__((amdgpu_waves_per_eu(2
 #pragma unroll
             for (int r = 1; r < 16; ++r) tmax = fmaxf(tmax, s[r]);
             tmax = fmaxf(tmax, __shfl_xor(tmax, 32));
+            // a weight times its count must stay an fp16 number (at most 65 504) for the second product: what a count
+            // has above 2^15 raises the reference of the weights.  Up to there the counts stay out of the reference,
+            // so that rows counted once next to a frame counted often keep their place above the fp16 subnormals
+            if (times > 32768.0f) tmax += __log2f(times) - 15.0f;
             const float mnew = fmaxf(mx, tmax);
             const float corr = __builtin_amdgcn_exp2f(mx - mnew);
             // the softmax weights in the order the second product wants them: step jj of two, element e of the

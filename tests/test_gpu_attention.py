@@ -346,3 +346,52 @@ def test_few_queries_groups_of_rows(q_per_kv, frames, heads, counts):
         assert err <= 1e-5
         assert np.all(np.abs(lse.cpu().numpy() - exp_lse) <= 1e-5 * (1 + np.abs(exp_lse)))
     ctx.close()
+
+
+@pytest.mark.parametrize("stored_at", [(0,), (0, 100), (0, 33000)])
+def test_many_queries_frames_counted_tens_of_thousands_of_times(stored_at):
+    """The matrix-core path over a static camera's range: a stored frame with tens of thousands of pointer frames
+    behind it, alone, next to a frame of few uses in the same block's share, and next to one of as many.  A count
+    of more than 65 504 is no fp16 number, the operand type of the second product.  Reference and bounds as
+    above: rounding of the weights to fp16 (2^-11 relative, 2^-25 of the largest weight below the normal numbers)
+    and fp32 accumulation."""
+    from paper_2602_14236_amd import binding
+    n, q_per_kv, counts, sm = 70000, 9, (40, 70, 33), 128.0 ** -0.5
+    p = params(24, 24, flow_levels=1, tier_mode=1, k_fp16=counts[0], k_int8=counts[1], k_int4=counts[2], n_layers=1, n_heads=1,
+               cap_fp16=2 * counts[0], cap_int8=2 * counts[1], cap_int4=2 * counts[2], max_frames=n)
+    ctx = binding.SaliContext(lib_config(p))
+    g = torch.Generator(device="cuda").manual_seed(len(stored_at) + stored_at[-1])
+    rgb = torch.randint(0, 256, (24, 24, 3), generator=g, device="cuda", dtype=torch.uint8)
+    dense, t = {}, 0
+    while t < n:
+        if t in stored_at:
+            ctx.set_gate_thresholds(1.0, 2.0)           # no frame is redundant
+            kv = torch.randn((1, 2, 1, 576, 128), generator=g, device="cuda").to(torch.float16)
+            ctx.step(rgb, kv, t)
+            ctx.set_gate_thresholds(1e9, 0.0)           # every frame with a predecessor is
+            out, valid = torch.empty_like(kv), torch.empty(576, dtype=torch.uint8, device="cuda")
+            ctx.kv_decompress(t, out, valid)
+            dense[t] = out[0, :, 0, valid.bool()].double()
+            t += 1
+        else:
+            m = min([16, n - t] + [s - t for s in stored_at if s > t])
+            ctx.analyze_batch([rgb] * m, t)
+            t += m
+    rows = ctx.read_frame_table(0, n)
+    assert [t for t in range(n) if rows[t].stored] == list(stored_at)
+    uses = {s: sum(1 for r in rows if r.src == s) for s in stored_at}
+    assert sum(uses.values()) == n
+    q = torch.randn((q_per_kv, 128), generator=g, device="cuda").to(torch.float16)
+    got, lse = torch.empty((q_per_kv, 128), device="cuda"), torch.empty(q_per_kv, device="cuda")
+    ctx.attend_decode_gqa(0, q, q_per_kv, 0, n, sm, got, lse)
+    k, v = (torch.cat([dense[s][i] for s in stored_at]) for i in range(2))
+    mult = torch.cat([torch.full((sum(counts),), float(uses[s]), dtype=torch.float64, device="cuda") for s in stored_at])
+    s = q.double() @ k.t().contiguous() * sm + mult.log()
+    pr = torch.softmax(s, dim=-1)
+    exp, exp_lse = pr @ v, torch.logsumexp(s, dim=-1)
+    bound = (2.0 ** -11 + 1e-5) * (pr @ v.abs()) + 2.0 ** -24 * pr.amax(-1, keepdim=True) * v.abs().sum(0)
+    err = (got.double() - exp).abs()
+    print(f"uses {uses}: largest error / bound {(err / bound).max():.3f}", flush=True)
+    assert bool((err <= bound).all())
+    assert bool(((lse.double() - exp_lse).abs() <= 1e-5 * (1 + exp_lse.abs())).all())
+    ctx.close()
