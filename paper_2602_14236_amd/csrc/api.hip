@@ -518,9 +518,12 @@ TierParams tier_params(const sali_config& cfg) {
     return tp;
 }
 
-// rows that a stored frame keeps under the tier rule in force: exact with top-k counts, at most all tokens else
-int kept_per_frame(const sali_config& cfg) {
-    return cfg.tier_mode == 1 ? cfg.k_fp16 + cfg.k_int8 + cfg.k_int4 : kTokens;
+// rows that a stored frame keeps under the tier rule in force: exact with top-k counts, else as if it kept all
+// tokens in one tier
+RowsPerFrame kept_per_frame(const sali_config& cfg) {
+    RowsPerFrame r = {kTokens, 0, 0};
+    if (cfg.tier_mode == 1) r = {cfg.k_fp16, cfg.k_int8, cfg.k_int4};
+    return r;
 }
 
 TierLaunch tier_launch(sali_ctx* c, int frame_id) {

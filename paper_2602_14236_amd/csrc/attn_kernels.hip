@@ -160,6 +160,7 @@ __device__ __forceinline__ int attend_tier(const Pools& pools, size_t plane_k, s
                                            int split, int n_splits, int g, int l, const QueryPiece (&q)[kQ],
                                            float softmax_scale, float mult, SoftmaxState (&st)[kQ]) {
     constexpr int kGroupRows = 16 * kRowsPerStep;
+    if (count == 0) return split;
     const size_t row0_k = pool_row0(pools, base, count, plane_k), row0_v = pool_row0(pools, base, count, plane_v);
     for (int jb = split * kGroupRows; jb < count; jb += n_splits * kGroupRows) {
         RawRow<kTier> rk[kRowsPerStep], rv[kRowsPerStep];
@@ -869,7 +870,7 @@ __global__ __launch_bounds__(64 * kPfWaves) __attribute__((amdgpu_waves_per_eu(2
 }
 
 hipError_t launch_attend(const sali_frame_row* d_rows, Pools pools, int layer, int n_heads, int q_per_kv,
-                         const void* d_q, int frame_lo, int frame_hi, int rows_per_frame, float softmax_scale, float* d_partial,
+                         const void* d_q, int frame_lo, int frame_hi, RowsPerFrame kept, float softmax_scale, float* d_partial,
                          float* d_out, float* d_lse_or_null, hipEvent_t ev_start, hipEvent_t ev_stop, hipStream_t s) {
     const int n_range = frame_hi - frame_lo;
     int n_partials = 0;
@@ -906,11 +907,15 @@ hipError_t launch_attend(const sali_frame_row* d_rows, Pools pools, int layer, i
         const int fpc = (n_range + per_head - 1) / per_head;
         const int n_chunks = (n_range + fpc - 1) / fpc;
         // Small ranges: with groups of 64 rows fewer than two blocks per compute unit would have any (at most
-        // rows_per_frame / 64 + 3 groups a frame), and each would be a chain of three tiers' loads and four rows'
+        // rows / 64 + 3 groups a frame), and each would be a chain of three tiers' loads and four rows'
         // arithmetic per lane group.  Groups of 16 rows then, one row per lane group, over up to twice the splits:
-        // 4 queries x 8 heads, 2 frames of 124 / 28 / 84 rows 11.3 -> 6.6 us, 1 query 6.3 -> 4.2.
-        const bool small = (long long)n_range * (rows_per_frame / 64 + 1) * n_heads * sets < 2 * kComputeUnits;
-        const int most = small ? 18 : 9;
+        // 4 queries x 8 heads, 2 frames of 124 / 28 / 84 rows 11.3 -> 6.6 us, 1 query 6.3 -> 4.2.  No more splits
+        // than a frame has groups: with eighteen for frames of 64 rows, fourteen of them empty, 40 heads x 8
+        // queries x 2 frames took 17.6 us (groups of 64 rows: 12.4), and 8.0 with four.  Not fewer than four, for
+        // frames stored under an earlier tier rule that kept more.
+        const bool small = (long long)n_range * ((kept.n16 + kept.n8 + kept.n4) / 64 + 1) * n_heads * sets < 2 * kComputeUnits;
+        const int groups = (kept.n16 + 15) / 16 + (kept.n8 + 15) / 16 + (kept.n4 + 15) / 16;
+        const int most = small ? (groups < 4 ? 4 : (groups < 18 ? groups : 18)) : 9;
         int n_splits = per_head / n_chunks;
         n_splits = n_splits < 1 ? 1 : (n_splits > most ? most : n_splits);
         n_partials = n_chunks * n_splits;

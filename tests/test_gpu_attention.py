@@ -395,3 +395,32 @@ def test_many_queries_frames_counted_tens_of_thousands_of_times(stored_at):
     assert bool((err <= bound).all())
     assert bool(((lse.double() - exp_lse).abs() <= 1e-5 * (1 + exp_lse.abs())).all())
     ctx.close()
+
+
+@pytest.mark.parametrize("q_per_kv", [1, 4, 8])
+def test_few_queries_rows_other_than_the_tier_rule_in_force_says(q_per_kv):
+    """The streaming kernel's launch is shaped by the rows a frame keeps under the present tier rule; a frame stored
+    under another rule, with more or fewer rows or in other tiers, is read whole all the same.  Bounds as above."""
+    from paper_2602_14236_amd import binding
+    heads, frames = 2, 3
+    p = params(96, 96, tier_mode=1, k_fp16=150, k_int8=90, k_int4=110, n_layers=1, n_heads=heads, cap_fp16=600, cap_int8=600,
+               cap_int4=600, max_frames=frames)
+    ctx = binding.SaliContext(lib_config(p))
+    orc = SaliCacheOracle(oracle_config(p))
+    g = torch.Generator(device="cpu").manual_seed(5)
+    for t in range(frames):
+        kv, scores = torch.randn((1, 2, heads, 576, 128), generator=g).to(torch.float16), torch.rand(576, generator=g)
+        ctx.kv_compress(kv.cuda(), scores.cuda(), t)
+        orc.kv_compress(kv.numpy(), scores.numpy(), t)
+    q = _q(4, heads * q_per_kv)
+    out, lse = torch.empty((heads * q_per_kv, 128), device="cuda"), torch.empty(heads * q_per_kv, device="cuda")
+    exp, exp_lse = attend_decode(orc, 0, q.cpu().numpy(), 0, frames, 128.0 ** -0.5, q_per_kv=q_per_kv)
+    for mode, counts in ((1, (150, 90, 110)), (1, (0, 0, 0)), (1, (0, 0, 16)), (1, (576, 0, 0)), (0, (0, 0, 0)), (2, (10, 10, 10))):
+        ctx.set_tier_params(mode, k_fp16=counts[0], k_int8=counts[1], k_int4=counts[2])
+        out.fill_(7.0)
+        ctx.attend_decode_gqa(0, q, q_per_kv, 0, frames, 128.0 ** -0.5, out, lse)
+        err = np.abs(out.cpu().numpy() - exp).max() / np.abs(exp).max()
+        print(f"mode {mode} {counts}, {q_per_kv} queries: relative error {err:.1e}", flush=True)
+        assert err <= 1e-5
+        assert np.all(np.abs(lse.cpu().numpy() - exp_lse) <= 1e-5 * (1 + np.abs(exp_lse)))
+    ctx.close()
