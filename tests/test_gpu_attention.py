@@ -264,6 +264,7 @@ def test_attend_argument_checks():
     (3, 64, 5, (0, 65, 0)),          # one tier only
     (64, 10, 200, (3, 2, 2)),        # four parts of the range: a block looks up more than 64 frames
     (64, 40, 200, (33, 0, 1)),       # two parts, two query tiles
+    (129, 9, 5, (33, 2, 40)),        # more heads than half the compute units: three parts in two rounds
 ])
 def test_many_queries_shares_of_the_range_and_pointer_runs(heads, q_per_kv, frames, counts):
     """The matrix-core path where its split of the work has edges: tiles with few rows, blocks whose share
