@@ -146,11 +146,10 @@ struct PrepShared {
         } gray;
         uint32_t lbl[kTile * kTile];
     };
-    // blurred image; from the suppression on the classes
+    // blurred image
     union {
         uint32_t b[kRegB][kStripsB];
         uint8_t b8[kRegB][kRegB];
-        uint8_t cls[kTile][kTile];
     };
     __attribute__((aligned(16))) uint32_t grad[kRegM][kGradW];      // (gx, gy) as 16-bit halves
     __attribute__((aligned(16))) uint8_t lab[3][kRegB][kRegB];
@@ -181,7 +180,6 @@ __global__ __launch_bounds__(kPrepThreads) void k_prep(PrepBatch f, int h, int w
     unsigned long long* msum_clear = f.msum_clear[blockIdx.z];
     __shared__ PrepShared sh;
     uint32_t (&s_lbl)[kTile * kTile] = sh.lbl;
-    uint8_t (&s_cls)[kTile][kTile] = sh.cls;
 
     const int tid = threadIdx.x;
     const int x0 = blockIdx.x * kTile, y0 = blockIdx.y * kTile;
@@ -439,10 +437,8 @@ __global__ __launch_bounds__(kPrepThreads) void k_prep(PrepBatch f, int h, int w
             else step = -kGradW + 1;
             const int n1 = grad_m2(at[step]), n2 = grad_m2(at[-step]);
             if (m2 > n1 && m2 >= n2) cls[q] = m2 >= hi2 ? 2 : (m2 >= lo2 ? 1 : 0);
-
             cls_out[(size_t)gy * w + gx] = (uint8_t)cls[q];
         }
-        s_cls[ty][tx] = (uint8_t)cls[q];
     }
 
     // hysteresis, tile-local part: union-find in LDS over horizontal runs.
