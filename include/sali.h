@@ -258,8 +258,9 @@ int sali_step(sali_ctx* ctx, const uint8_t* d_rgb_t, const void* d_kv_t, int32_t
  * copies of its image scratch, so that many analyses can be in flight, and orders what must
  * be ordered (a frame's flow after its predecessor's expansion, tier assignment in frame
  * order, reuse of a scratch copy after its previous user) with device-side event waits.
- * sali_flow_score and sali_saliency_pool share one of the scratch copies: do not run them
- * while analyses are in flight on other streams.
+ * sali_saliency_pool uses one of the scratch copies: do not run it while analyses are in flight on
+ * other streams.  sali_flow_score has scratch of its own and may run next to analyses and to
+ * sali_saliency_pool; only calls of it on one context must not overlap each other.
  *
  * sali_store: packs `d_kv_fp16` into the pools according to the row that sali_analyze wrote.
  * Makes `stream` wait (on the device) for that frame's analysis if it ran on another stream.

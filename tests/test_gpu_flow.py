@@ -209,3 +209,56 @@ def test_updates_per_launch(h, w, levels, iters):
           f"{max(np.abs(uv[0] - d[..., 0]).max(), np.abs(uv[1] - d[..., 1]).max()):.2e}", flush=True)
     assert close(uv[0], d[..., 0]).all() and close(uv[1], d[..., 1]).all()
     ctx.close()
+
+
+def test_flow_score_next_to_analyses_on_another_stream():
+    """The stand-alone flow call has scratch of its own: next to batched analyses of the same context on another stream,
+    in either order of issue, both give the bits that they give alone."""
+    from paper_2602_14236_amd import binding
+    h, w, n = 200, 264, 8
+    ctx = binding.SaliContext(lib_config(params(h, w, max_frames=n)))
+    rng = np.random.default_rng(3)
+    base = np.kron(rng.integers(0, 256, (h // 4 + 4, w // 4 + 4, 3), dtype=np.uint8), np.ones((4, 4, 1), dtype=np.uint8))
+    rgb = [torch.from_numpy(base[t:t + h, 2 * t % 5:2 * t % 5 + w].copy()).cuda() for t in range(n)]
+    pairs = [(0, 1), (5, 2), (3, 7)]
+    a, b = torch.cuda.Stream(), torch.cuda.Stream()
+
+    def outputs():
+        return [(torch.full((2, h, w), 9.0, device="cuda"), torch.full((576,), 9.0, device="cuda"),
+                 torch.zeros(4, dtype=torch.int32, device="cuda")) for _ in pairs]
+
+    def flows(out):
+        with torch.cuda.stream(b):
+            for (i, j), o in zip(pairs, out):
+                ctx.flow_score(rgb[i], rgb[j], *o)
+
+    def analyses():
+        ctx.analyze_batch(rgb[:4], 0, a)
+        ctx.analyze_batch(rgb[4:], 4, a)
+
+    def analysed():
+        torch.cuda.synchronize()
+        return [ctx.read_analysis(t) for t in range(n)], [r.as_tuple() for r in ctx.read_frame_table(0, n)]
+
+    alone = outputs()
+    flows(alone)
+    torch.cuda.synchronize()
+    analyses()
+    ref, ref_rows = analysed()
+    for first in (flows, None):
+        for _ in range(4):
+            ctx.reset()
+            out = outputs()
+            torch.cuda.synchronize()
+            if first is not None:
+                flows(out)
+            analyses()
+            if first is None:
+                flows(out)
+            got, rows = analysed()
+            assert rows == ref_rows
+            for (dp, gate, sc), (dp0, gate0, sc0) in zip(got, ref):
+                assert np.array_equal(dp, dp0) and gate.n_static == gate0.n_static and not gate.redundant and np.array_equal(sc, sc0)
+            for x, y in zip(out, alone):
+                assert all(torch.equal(p, q) for p, q in zip(x, y))
+    ctx.close()
