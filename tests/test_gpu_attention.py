@@ -262,8 +262,9 @@ def test_attend_argument_checks():
     (1, 9, 1, (1, 0, 0)),            # fewer tiles than waves, one row
     (2, 33, 2, (31, 32, 33)),        # tile edges; a second query tile with one query
     (3, 64, 5, (0, 65, 0)),          # one tier only
-    (64, 10, 200, (3, 2, 2)),        # four parts of the range: a block looks up more than 64 frames
-    (64, 40, 200, (33, 0, 1)),       # two parts, two query tiles
+    (64, 10, 200, (3, 2, 2)),        # four parts of 50 frames
+    (64, 10, 264, (3, 2, 2)),        # four parts of 66: a block looks up frames twice, two the second time
+    (64, 40, 200, (33, 0, 1)),       # two parts of 100, two query tiles
     (129, 9, 5, (33, 2, 40)),        # more heads than half the compute units: three parts in two rounds
 ])
 def test_many_queries_shares_of_the_range_and_pointer_runs(heads, q_per_kv, frames, counts):
@@ -319,7 +320,8 @@ def test_many_queries_shares_of_the_range_and_pointer_runs(heads, q_per_kv, fram
 @pytest.mark.parametrize("q_per_kv", [1, 2, 4, 8])
 @pytest.mark.parametrize("frames,heads,counts", [
     (1, 1, (1, 0, 0)), (1, 3, (0, 0, 17)), (2, 2, (15, 16, 33)), (3, 1, (64, 65, 63)), (1, 2, (288, 144, 144)),   # groups of 16 rows
-    (30, 2, (200, 180, 196)), (12, 5, (63, 65, 128)),                                                              # groups of 64
+    (30, 2, (200, 180, 196)), (30, 5, (63, 65, 128)),                                                              # groups of 64
+    (12, 5, (63, 65, 128)),                                                                                        # of 16, and of 64 with 8 queries
 ])
 def test_few_queries_groups_of_rows(q_per_kv, frames, heads, counts):
     """The streaming kernel on both sides of its rule (groups of 16 rows for small ranges, of 64 otherwise) where
