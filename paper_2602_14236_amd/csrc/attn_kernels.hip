@@ -675,7 +675,9 @@ __device__ __forceinline__ int pf_list_frames(const sali_frame_row* __restrict__
 
 }  // namespace
 
-// grid (parts of the frame range, n_heads, ceil(q_per_kv / 32)), 512 threads
+// grid (parts of the frame range, n_heads, ceil(q_per_kv / 32)), 512 threads.  kLongRange: a stored frame of the
+// range may count more than 2^15 times, which takes more than 2^15 frames
+template <bool kLongRange>
 __global__ __launch_bounds__(64 * kPfWaves) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_attn_prefill(
     const sali_frame_row* __restrict__ rows, Pools pools, int layer, int n_heads, const _Float16* __restrict__ q,
     int q_per_kv, int frame_lo, int frame_hi, float softmax_scale, float* __restrict__ partial) {
@@ -789,7 +791,7 @@ __global__ __launch_bounds__(64 * kPfWaves) __attribute__((amdgpu_waves_per_eu(2
             // a weight times its count must stay an fp16 number (at most 65 504) for the second product: what a count
             // has above 2^15 raises the reference of the weights.  Up to there the counts stay out of the reference,
             // so that rows counted once next to a frame counted often keep their place above the fp16 subnormals
-            if (times > 32768.0f) tmax += __log2f(times) - 15.0f;
+            if constexpr (kLongRange) tmax += fmaxf(0.0f, __log2f(times) - 15.0f);
             const float mnew = fmaxf(mx, tmax);
             const float corr = __builtin_amdgcn_exp2f(mx - mnew);
             // the softmax weights in the order the second product wants them: step jj of two, element e of the
@@ -891,8 +893,13 @@ hipError_t launch_attend(const sali_frame_row* d_rows, Pools pools, int layer, i
         n_partials = parts < 1 ? 1 : parts;
         if (ev_start != nullptr && hipEventRecord(ev_start, s) != hipSuccess) return hipErrorUnknown;
         const dim3 grid(n_partials, n_heads, (q_per_kv + 31) / 32);
-        hipLaunchKernelGGL(k_attn_prefill, grid, dim3(64 * kPfWaves), 0, s, d_rows, pools, layer, n_heads,
-                           reinterpret_cast<const _Float16*>(d_q), q_per_kv, frame_lo, frame_hi, softmax_scale, d_partial);
+        // the general variant costs 0.7 % (32 heads x 32 queries x 20 frames 143.8 -> 144.8 us for four layers)
+        if (n_range > 32768)
+            hipLaunchKernelGGL(k_attn_prefill<true>, grid, dim3(64 * kPfWaves), 0, s, d_rows, pools, layer, n_heads,
+                               reinterpret_cast<const _Float16*>(d_q), q_per_kv, frame_lo, frame_hi, softmax_scale, d_partial);
+        else
+            hipLaunchKernelGGL(k_attn_prefill<false>, grid, dim3(64 * kPfWaves), 0, s, d_rows, pools, layer, n_heads,
+                               reinterpret_cast<const _Float16*>(d_q), q_per_kv, frame_lo, frame_hi, softmax_scale, d_partial);
         if (ev_stop != nullptr && hipEventRecord(ev_stop, s) != hipSuccess) return hipErrorUnknown;
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
