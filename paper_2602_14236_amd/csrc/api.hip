@@ -518,6 +518,9 @@ TierParams tier_params(const sali_config& cfg) {
     return tp;
 }
 
+// cache entries per video frame
+int tiles_of(const sali_config& cfg) { return cfg.tiles_per_frame > 1 ? cfg.tiles_per_frame : 1; }
+
 // rows that a stored frame keeps under the tier rule in force: exact with top-k counts, else as if it kept all
 // tokens in one tier
 RowsPerFrame kept_per_frame(const sali_config& cfg) {
@@ -843,7 +846,7 @@ int sali_attend_decode_gqa(sali_ctx* c, int32_t layer, const void* d_q_fp16, int
     hipStream_t s = static_cast<hipStream_t>(stream);
     hipEvent_t* ev = c->prof[SALI_PROF_ATTEND];
     const hipError_t e = launch_attend(c->rows(), c->pools, layer, c->cfg.n_heads, q_per_kv, d_q_fp16, frame_lo,
-                                       frame_hi, kept_per_frame(c->cfg), softmax_scale, c->sc<float>(c->sl.attn_partial), d_out,
+                                       frame_hi, tiles_of(c->cfg), kept_per_frame(c->cfg), softmax_scale, c->sc<float>(c->sl.attn_partial), d_out,
                                        d_lse_or_null, ev[0], ev[1], s);
     ev[0] = ev[1] = nullptr;
     return e == hipSuccess ? SALI_OK : SALI_ERR_HIP;
@@ -869,7 +872,7 @@ int sali_attend_decode_static(sali_ctx* c, int32_t layer, const void* d_q_fp16, 
     // every partial the merge kernel reads is written by the main kernel of the same call (one per
     // block, empty blocks included), so nothing of the previous call's contents has to be cleared
     const hipError_t e = launch_attend(c->rows(), c->pools, layer, c->cfg.n_heads, 1, d_q_fp16, frame_lo, frame_hi,
-                                       kept_per_frame(c->cfg), softmax_scale, c->static_scratch, d_out, d_lse_or_null, nullptr, nullptr,
+                                       tiles_of(c->cfg), kept_per_frame(c->cfg), softmax_scale, c->static_scratch, d_out, d_lse_or_null, nullptr, nullptr,
                                        static_cast<hipStream_t>(stream));
     return e == hipSuccess ? SALI_OK : SALI_ERR_HIP;
 }

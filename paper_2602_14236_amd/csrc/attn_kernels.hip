@@ -244,7 +244,7 @@ __device__ __forceinline__ int attend_tier(const Pools& pools, size_t plane_k, s
 template <int kQ, int kRowsPerStep>
 __global__ __launch_bounds__(256) void k_attn_partial(const sali_frame_row* __restrict__ rows, Pools pools, int layer,
                                                       int n_heads, const _Float16* __restrict__ q, int frame_lo,
-                                                      int frame_hi, int frames_per_chunk, int n_splits,
+                                                      int frame_hi, int tiles, int frames_per_chunk, int n_splits,
                                                       float softmax_scale, float* __restrict__ partial) {
     __shared__ float s_m[16], s_l[16];
     __shared__ float s_acc[16][kHeadDim];
@@ -283,19 +283,20 @@ __global__ __launch_bounds__(256) void k_attn_partial(const sali_frame_row* __re
         // Which stored frame does frame f bring in, and how many times?  A stored frame counts for
         // itself and for the redundant frames behind it (up to the next stored frame or the end of
         // the range); redundant frames at the head of the range, whose source lies before it, are
-        // counted at the first of them.  Every thread takes the same decision from the same
+        // counted at the first of them.  With `tiles` entries per video frame all of this goes by the entries
+        // of the same tile, which lie `tiles` apart.  Every thread takes the same decision from the same
         // (uniform) table reads.
         const sali_frame_row r = rows[f];
         bool leader = r.stored != 0;
         if (!leader && r.src >= 0 && r.src < frame_lo) {
             leader = true;
-            for (int t = frame_lo; t < f; ++t)
-                if (rows[t].src == r.src) leader = false;          // an earlier frame of the run counts them
+            for (int t = f - tiles; leader && t >= frame_lo; t -= tiles)
+                leader = rows[t].src != r.src;                     // an earlier frame of the run counts them
         }
         if (!leader) continue;
         const int src = r.src;
         int n_uses = 1;
-        for (int t = f + 1; t < frame_hi && rows[t].stored == 0; ++t)
+        for (int t = f + tiles; t < frame_hi && rows[t].stored == 0; t += tiles)
             if (rows[t].src == src) ++n_uses;
         const float mult = (float)n_uses;
         const sali_frame_row row = rows[src];
@@ -608,8 +609,8 @@ __device__ __forceinline__ half4_t pf_read_transposed(const _Float16* p) {
 // the blocks get equal work.
 // A stored frame counts for itself and for the redundant frames behind it (up to the next stored frame or
 // the end of the range); redundant frames at the head of the range, whose source lies before it, are
-// counted at the first of them.
-__device__ __forceinline__ int pf_list_frames(const sali_frame_row* __restrict__ rows, int frame_lo, int frame_hi, int g0,
+// counted at the first of them.  With `tiles` entries per video frame: the entries of the same tile, `tiles` apart.
+__device__ __forceinline__ int pf_list_frames(const sali_frame_row* __restrict__ rows, int frame_lo, int frame_hi, int tiles, int g0,
                                               int f_end, int part, int parts, int lane, int* s_src, PfFrame* list,
                                               int* n_tiles) {
     const int f = g0 + lane, g_end = min(f_end, g0 + kPfGroup);
@@ -625,17 +626,23 @@ __device__ __forceinline__ int pf_list_frames(const sali_frame_row* __restrict__
     const int src = row.src;
     if (valid && !stored && src >= 0 && src < frame_lo) {
         leader = true;
-        for (int t = frame_lo; t < f; ++t)
-            if (rows[t].src == src) leader = false;          // an earlier frame of the run counts them
+        for (int t = f - tiles; leader && t >= frame_lo; t -= tiles)
+            leader = rows[t].src != src;                     // an earlier frame of the run counts them
     }
     int n_uses = 1;
     if (leader) {
-        const unsigned long long behind = lane == 63 ? 0ull : stored_mask >> (lane + 1);
-        const int run_end = behind != 0ull ? f + 1 + __builtin_ctzll(behind) : g_end;
-        for (int t = f + 1; t < run_end; ++t)
+        unsigned long long behind = lane + tiles > 63 ? 0ull : stored_mask >> (lane + tiles);
+        if (tiles > 1) {
+            unsigned long long same = 0ull;                  // every tiles-th bit
+            for (int b = 0; b < 64; b += tiles) same |= 1ull << b;
+            behind &= same;
+        }
+        const int run_end = behind != 0ull ? f + tiles + __builtin_ctzll(behind) : g_end;
+        int t = f + tiles;
+        for (; t < run_end; t += tiles)
             if (s_src[t - g0] == src) ++n_uses;
         if (behind == 0ull)
-            for (int t = g_end; t < frame_hi && rows[t].stored == 0; ++t)
+            for (; t < frame_hi && rows[t].stored == 0; t += tiles)
                 if (rows[t].src == src) ++n_uses;
         if (!stored) row = rows[src];
     }
@@ -680,7 +687,7 @@ __device__ __forceinline__ int pf_list_frames(const sali_frame_row* __restrict__
 template <bool kLongRange>
 __global__ __launch_bounds__(64 * kPfWaves) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_attn_prefill(
     const sali_frame_row* __restrict__ rows, Pools pools, int layer, int n_heads, const _Float16* __restrict__ q,
-    int q_per_kv, int frame_lo, int frame_hi, float softmax_scale, float* __restrict__ partial) {
+    int q_per_kv, int frame_lo, int frame_hi, int tiles, float softmax_scale, float* __restrict__ partial) {
     __shared__ __align__(16) _Float16 s_tiles[kPfWaves][kPfTileHalves];     // a K^ and a V^ tile per wave; the results at the end
     __shared__ PfFrame s_list[kPfGroup];
     __shared__ int s_src[kPfGroup];
@@ -719,7 +726,7 @@ __global__ __launch_bounds__(64 * kPfWaves) __attribute__((amdgpu_waves_per_eu(2
         if (g0 != f_begin) __syncthreads();                 // every wave is through with the list
         if (wave == 0) {
             int n_tiles;
-            const int len = pf_list_frames(rows, frame_lo, frame_hi, g0, f_end, part, parts, lane, s_src, s_list, &n_tiles);
+            const int len = pf_list_frames(rows, frame_lo, frame_hi, tiles, g0, f_end, part, parts, lane, s_src, s_list, &n_tiles);
             if (lane == 0) {
                 s_n[0] = len;
                 s_n[1] = n_tiles;
@@ -872,7 +879,7 @@ __global__ __launch_bounds__(64 * kPfWaves) __attribute__((amdgpu_waves_per_eu(2
 }
 
 hipError_t launch_attend(const sali_frame_row* d_rows, Pools pools, int layer, int n_heads, int q_per_kv,
-                         const void* d_q, int frame_lo, int frame_hi, RowsPerFrame kept, float softmax_scale, float* d_partial,
+                         const void* d_q, int frame_lo, int frame_hi, int tiles, RowsPerFrame kept, float softmax_scale, float* d_partial,
                          float* d_out, float* d_lse_or_null, hipEvent_t ev_start, hipEvent_t ev_stop, hipStream_t s) {
     const int n_range = frame_hi - frame_lo;
     int n_partials = 0;
@@ -896,10 +903,10 @@ hipError_t launch_attend(const sali_frame_row* d_rows, Pools pools, int layer, i
         // the general variant costs 0.7 % (32 heads x 32 queries x 20 frames 143.8 -> 144.8 us for four layers)
         if (n_range > 32768)
             hipLaunchKernelGGL(k_attn_prefill<true>, grid, dim3(64 * kPfWaves), 0, s, d_rows, pools, layer, n_heads,
-                               reinterpret_cast<const _Float16*>(d_q), q_per_kv, frame_lo, frame_hi, softmax_scale, d_partial);
+                               reinterpret_cast<const _Float16*>(d_q), q_per_kv, frame_lo, frame_hi, tiles, softmax_scale, d_partial);
         else
             hipLaunchKernelGGL(k_attn_prefill<false>, grid, dim3(64 * kPfWaves), 0, s, d_rows, pools, layer, n_heads,
-                               reinterpret_cast<const _Float16*>(d_q), q_per_kv, frame_lo, frame_hi, softmax_scale, d_partial);
+                               reinterpret_cast<const _Float16*>(d_q), q_per_kv, frame_lo, frame_hi, tiles, softmax_scale, d_partial);
         if (ev_stop != nullptr && hipEventRecord(ev_stop, s) != hipSuccess) return hipErrorUnknown;
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
@@ -938,10 +945,10 @@ hipError_t launch_attend(const sali_frame_row* d_rows, Pools pools, int layer, i
     do {                                                                                                                  \
         if (small)                                                                                                        \
             hipLaunchKernelGGL((k_attn_partial<KQ, 1>), grid, dim3(256), 0, s, d_rows, pools, layer, n_heads, q, frame_lo, \
-                               frame_hi, fpc, n_splits, softmax_scale, d_partial);                                        \
+                               frame_hi, tiles, fpc, n_splits, softmax_scale, d_partial);                                        \
         else                                                                                                              \
             hipLaunchKernelGGL((k_attn_partial<KQ, 4>), grid, dim3(256), 0, s, d_rows, pools, layer, n_heads, q, frame_lo, \
-                               frame_hi, fpc, n_splits, softmax_scale, d_partial);                                        \
+                               frame_hi, tiles, fpc, n_splits, softmax_scale, d_partial);                                        \
     } while (0)
         switch (kq) {
             case 1: SALI_ATTN_LAUNCH(1); break;

@@ -4,10 +4,12 @@ import numpy as np
 import pytest
 import torch
 
+from oracle.attention import attend_decode
 from oracle.cache import SaliCacheOracle, step_tiles
 from paper_2602_14236_amd import synth
 
-from _util import FLOW_ATOL, FLOW_RTOL, assert_same, close, drift_frame, lib_config, oracle_config, params, pool_arrays
+from _util import (FLOW_ATOL, FLOW_RTOL, assert_same, close, drift_frame, fp16_operand_bounds, lib_config, oracle_config, params,
+                   pool_arrays)
 
 pytestmark = pytest.mark.gpu
 
@@ -125,4 +127,46 @@ def test_four_tiles_two_frames_per_call_workload_video():
     print("stored per frame:", stored, flush=True)
     assert stored == [1, 1, 0, 0, 1, 0]
     _compare(ctx, orc, T * n_frames)
+    ctx.close()
+
+
+@pytest.mark.parametrize("T,room", [(2, 99), (3, 99), (2, 5), (3, 8)])
+def test_attention_counts_pointer_entries_of_every_tile(T, room):
+    """Attention over tiled frames with pointer entries: an entry's uses are the pointer entries of the same tile, which lie
+    T apart, behind its frame's other tiles.  Whole range, ranges that begin inside a pointer run and inside a frame;
+    room: entries the pools hold (the last tile of the third stored frame overflows: its pointers then go on to
+    the second stored frame's).  Streaming path to 1e-5 of the largest output (fp32 sums of some thousand terms),
+    matrix cores to the bounds of their fp16 operands."""
+    from paper_2602_14236_amd import binding
+    counts, heads = (30, 45, 60), 2
+    seq = [0.0, 2.5, 2.5, 2.5, 5.0, 5.0]                    # frames 2, 3 and 5 repeat the frame before
+    p = params(96, 96, flow_levels=2, tier_mode=1, k_fp16=counts[0], k_int8=counts[1], k_int4=counts[2], n_layers=1, n_heads=heads,
+               cap_fp16=counts[0] * min(room, 3 * T), cap_int8=counts[1] * 3 * T, cap_int4=counts[2] * 3 * T,
+               max_frames=T * len(seq), tiles_per_frame=T)
+    ctx = binding.SaliContext(lib_config(p))
+    orc = SaliCacheOracle(oracle_config(p))
+    g = torch.Generator().manual_seed(T)
+    for t, shift in enumerate(seq):
+        rgbs = [drift_frame(shift + 0.8 * j) for j in range(T)]
+        kvs = [torch.randn((1, 2, heads, 576, 128), generator=g).to(torch.float16) for _ in range(T)]
+        ctx.step_batch([torch.from_numpy(r).cuda() for r in rgbs], [k.cuda() for k in kvs], t * T)
+        step_tiles(orc, rgbs, [k.numpy() for k in kvs], t)
+    n = T * len(seq)
+    assert [r.as_tuple() for r in ctx.read_frame_table(0, n)] == [orc.rows[e].as_tuple() for e in range(n)]
+    src = [orc.rows[e].src for e in range(n)]
+    assert src[2 * T:3 * T] == src[3 * T:4 * T] and any(s >= 0 and s < e for e, s in enumerate(src))
+    print("sources:", src, flush=True)
+    sm = 128.0 ** -0.5
+    for q_per_kv in (1, 4, 16):
+        q = torch.randn((heads * q_per_kv, 128), generator=g).to(torch.float16).cuda()
+        out, lse = torch.empty((heads * q_per_kv, 128), device="cuda"), torch.empty(heads * q_per_kv, device="cuda")
+        for lo, hi in ((0, n), (1, n), (2 * T, n), (2 * T + 1, 4 * T), (3 * T, n - 1), (T - 1, 3 * T + 1)):
+            ctx.attend_decode_gqa(0, q, q_per_kv, lo, hi, sm, out, lse)
+            exp, exp_lse = attend_decode(orc, 0, q.cpu().numpy(), lo, hi, sm, q_per_kv=q_per_kv)
+            if q_per_kv <= 8:
+                bound, lse_bound = 1e-5 * np.abs(exp).max(), 1e-5 * (1 + np.abs(exp_lse))
+            else:
+                bound, lse_bound = fp16_operand_bounds(orc, q.cpu().numpy(), lo, hi, sm, q_per_kv)
+            assert np.all(np.abs(out.cpu().numpy() - exp) <= bound), (q_per_kv, lo, hi)
+            assert np.all(np.abs(lse.cpu().numpy() - exp_lse) <= lse_bound), (q_per_kv, lo, hi)
     ctx.close()
