@@ -45,7 +45,7 @@ struct ScratchLayout {
 };
 
 struct TableLayout {
-    size_t lut, cursors, rows, tier, slot, order, total;      // lut = lin[256] followed by fl[4096]
+    size_t lut, cursors, rows, tier, slot, order, total;      // lut: the colour tables (kColourLutBytes)
 };
 
 struct LaneCounters {         // arrival counters, all self-resetting

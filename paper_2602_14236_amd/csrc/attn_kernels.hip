@@ -446,8 +446,8 @@ static void launch_merge(const float* d_partial, int n_partials, int slots, int 
 // the tests).  Accumulation, softmax state and partials are fp32; partials have the layout of the
 // single-query kernel and are merged by the same k_attn_merge.
 //
-// What bounds it: the trip to memory of a tile (waves wait for it about half their time), then the vector
-// instructions of a tile (600, conversions and softmax).  Hence: a tile's K^ and V^ rows are asked for a
+// What bounds it: the trip to memory of a tile (waves wait for 47 % of their time), then the vector
+// instructions of a tile (610, conversions and softmax).  Hence: a tile's K^ and V^ rows are asked for a
 // whole tile ahead, across tiers and frames; the launch is one block of eight waves per compute unit, forced
 // to one by its LDS, so that all start at once; and a block writes one partial instead of one per wave.
 // 32 heads x 32 queries over 20 frames (173 / 200 / 203 rows, 118 MB): 34.5 us + 4.6 us of merge.  The same
@@ -928,7 +928,7 @@ hipError_t launch_attend(const sali_frame_row* d_rows, Pools pools, int layer, i
         // Small ranges: with groups of 64 rows fewer than two blocks per compute unit would have any (at most
         // rows / 64 + 3 groups a frame), and each would be a chain of three tiers' loads and four rows'
         // arithmetic per lane group.  Groups of 16 rows then, one row per lane group, over up to twice the splits:
-        // 4 queries x 8 heads, 2 frames of 124 / 28 / 84 rows 11.3 -> 6.6 us, 1 query 6.3 -> 4.2.  No more splits
+        // 4 queries x 8 heads, 2 frames of 124 / 28 / 84 rows 11.3 -> 6.2 us, 1 query 6.3 -> 4.3.  No more splits
         // than a frame has groups: with eighteen for frames of 64 rows, fourteen of them empty, 40 heads x 8
         // queries x 2 frames took 17.6 us (groups of 64 rows: 12.4), and 8.0 with four.  Not fewer than four, for
         // frames stored under an earlier tier rule that kept more.

@@ -18,7 +18,7 @@
 //                into the first update of a level, so G/h fields never touch HBM.  The gather of
 //                the warped expansion is 82 % of a block's time (measured with the wall clock):
 //                a chain of dependent HBM round trips, not a throughput limit (vector ALU 78 %,
-//                texture addresser 75 % busy at 1920x1080);
+//                texture addresser 75 % busy at 1920x1080, three or more frames);
 //                tiles are handed to the XCDs in contiguous runs so that neighbours share an L2.
 //   k_flow_fused  three updates of a small level in one launch (halo recomputed)
 //   k_patch_motion, k_gate   per patch RMS flow magnitude (Eq. 5); static patches counted, the gate (Eq. 6).
@@ -717,7 +717,9 @@ __global__ __launch_bounds__(NT) void k_flow_iter(FlowBatch f, long long level_o
 // small that its blocks, one per compute unit, leave the chip idle and an update is a chain of
 // launch, trips to memory and window passes: 84x84 18.1 -> 11.5 us for three updates (tile 16x8), 168x168
 // 18.0 -> 12.4, two frames of it 18.1 -> 14.9 (16x16), 336x336 19.2 -> 17.5 (32x16).  With more than one
-// block per compute unit it loses (168x168 x 4: 21.5 against 27).  The results are the same numbers.
+// block per compute unit it loses (168x168 x 4: 21.5 against 27).  All of that on an idle chip, one launch after
+// the other; next to kernels that fill the wave slots a block of 1024 threads waits longer for room than the three
+// launches take.  The results are the same numbers.
 // Cells outside the image stand for the clamped coordinate, as in k_flow_iter.
 constexpr int kFusedUpdates = 3;
 constexpr int kFusedThreads = 1024;
@@ -946,8 +948,9 @@ hipError_t launch_expand(const ExpandBatch& f, int n, LevelGeom g, FlowWeights f
 
 hipError_t launch_flow_updates(const FlowBatch& f, int n, int64_t level_off, int h, int w, int ch, int cw,
                                int prior_mode, int wanted, int* done, FlowWeights fw, hipStream_t s) {
-    // three updates in one launch where the blocks of some tile fit one per compute unit, the smallest such tile (the
-    // largest, 32x16, also for batches: kept to single frames the batched clips were 0.5 to 5 % slower)
+    // three updates in one launch where the blocks of some tile fit one per compute unit, the smallest such tile, also
+    // for batches: of 100 clips with the image side next to K/V kernels three, of two frames a call, are 3 to 5 %
+    // slower than with single frames fused only, small frames up to 26 % faster, the median 1 % faster
     constexpr int kComputeUnits = 256;
     auto tiles = [&](int tx, int ty) { return (long long)((w + tx - 1) / tx) * ((h + ty - 1) / ty) * n; };
 #define SALI_FUSED_LAUNCH(TX, TY)                                                                                       \

@@ -241,15 +241,15 @@ hipError_t launch_unpack(const sali_frame_row* d_rows, int first_frame_id, const
                          const KvBatch& out, int n, uint8_t* d_valid_or_null, Cursors* d_cur, int n_planes,
                          hipStream_t s);
 
+struct RowsPerFrame {
+    int n16, n8, n4;
+};
 // attn_kernels.hip: single-query attention of one layer over frames [frame_lo, frame_hi) for
 // n_heads * q_per_kv queries (q_per_kv in {1, 2, 4, 8}: streaming kernel; 9 .. 64: matrix-core kernel); d_partial holds
 // n_heads * kAttnSlotsPerHead * kAttnPartialStride floats; tiles = cache entries per video frame (an entry's pointer
 // entries lie that far apart); kept = how many rows a stored frame is
 // expected to keep (it shapes the launch, any frame is read whole); the events (may be NULL) bracket
 // the main kernel
-struct RowsPerFrame {
-    int n16, n8, n4;
-};
 hipError_t launch_attend(const sali_frame_row* d_rows, Pools pools, int layer, int n_heads, int q_per_kv,
                          const void* d_q, int frame_lo, int frame_hi, int tiles, RowsPerFrame kept, float softmax_scale, float* d_partial,
                          float* d_out, float* d_lse_or_null, hipEvent_t ev_start, hipEvent_t ev_stop, hipStream_t s);

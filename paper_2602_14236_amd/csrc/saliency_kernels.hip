@@ -106,9 +106,9 @@ __device__ __forceinline__ bool frame_redundant(const float* const* dp, int b, c
 // bandwidth kernel of another stream keeps busy.
 //
 // Four 1920x1080 frames: 107 us, one 640x360 frame: 16; bound by the trips of a block's stages (image and tables
-// from memory, then LDS; 20 waves per compute unit), the vector ALU 60 % busy.  Taken tap by tap, byte
-// by byte, with clamped coordinates, the stencils were 612 instructions per pixel instead of 280, the ALU
-// 86 % busy, and the kernel took 150 and 24 us.  So each
+// from memory, then LDS; 20 waves per compute unit), the vector ALU 61 % busy.  Taken tap by tap, byte
+// by byte, with clamped coordinates, the stencils were 612 instructions per pixel instead of 305, the ALU
+// 90 % busy, and the kernel took 150 and 24 us.  So each
 // stage takes strips of four pixels as words: byte dot products along rows, packed 16-bit arithmetic down
 // columns, separable sums kept in LDS where neighbouring rows share them, gradients as 16-bit pairs whose
 // squared magnitude is one dot product.  No stage clamps coordinates: a cell outside the image holds what the
