@@ -1,9 +1,8 @@
 // Dense polynomial-expansion optical flow, per-patch motion and the redundancy gate for gfx950.
 //
 // Temporal Filtering via Optical Flow (Eq. 5, Eq. 6, reuse rule R_frame > theta_R) and
-// Implementation Details (Farneback's algorithm, pyramid scale 0.5).  Plain fp32 VALU work on
-// small images: no dense contraction here, so no MFMA; the design goal is few launches and no
-// spilled intermediates.
+// Implementation Details (Farneback's algorithm, pyramid scale 0.5).  fp32 throughout, on small
+// images; the design goal is few launches and no spilled intermediates.
 //
 //   k_expand     pyramid (5x5 binomial [1 4 6 4 1]/16, stride 2; level 0 is gray / 255) and
 //                polynomial expansion of up to three levels in ONE launch: 16x16 tiles, the pyramid
@@ -11,15 +10,13 @@
 //                closed-form solution of the 6-unknown weighted least-squares fit
 //   k_pyr_pair, k_polyexp   the same for more than three levels and larger frames: gray image and two
 //                pyramid levels per launch, the pyramid in HBM, then the expansion of all levels
-//   k_flow_iter  one displacement update: per cell of a tile (16x16 or 32x16, by level size) + 5-pixel
-//                halo, sample the new frame's expansion bilinearly at x + prior, build A^T A (3 values)
-//                and A^T db (2 values) in LDS, separable 11x11 Gaussian aggregation in LDS, 2x2 ridge
-//                solve.  The coarse-to-fine transfer (2 * bilinear of the coarser flow) is folded
-//                into the first update of a level, so G/h fields never touch HBM.  The gather of
-//                the warped expansion is 82 % of a block's time (measured with the wall clock):
-//                a chain of dependent HBM round trips, not a throughput limit (vector ALU 78 %,
-//                texture addresser 75 % busy at 1920x1080, three or more frames);
-//                tiles are handed to the XCDs in contiguous runs so that neighbours share an L2.
+//   k_flow_tile, k_flow_small   one displacement update: per cell of a tile (32x32, 32x16 or 16x16, whichever takes
+//                the fewest rounds of blocks) + 5-pixel halo, sample the new frame's expansion bilinearly at
+//                x + prior, build A^T A (3 values) and A^T db (2 values) in LDS, separable 11x11 Gaussian
+//                aggregation (on the matrix cores for the larger tiles), 2x2 ridge solve.  The coarse-to-fine
+//                transfer (2 * bilinear of the coarser flow) is folded into the first update of a level, so G/h
+//                fields never touch HBM.  Tiles are handed to the XCDs in contiguous runs so that neighbours share
+//                an L2.
 //   k_flow_fused  three updates of a small level in one launch (halo recomputed)
 //   k_patch_motion, k_gate   per patch RMS flow magnitude (Eq. 5); static patches counted, the gate (Eq. 6).
 //                Stand-alone flow call only: the chained step has them in its pooling kernels.
@@ -532,33 +529,34 @@ __device__ __forceinline__ float2 prior_at(const float2* __restrict__ d_in, int 
 }
 
 // A^T A (xx, xy, yy) and A^T db (x, y) of the pixel (gy, gx) with prior displacement dp: the old frame's
-// expansion there, the new frame's sampled at the pixel + dp
+// expansion there, the new frame's sampled at the pixel + dp.  The upper left of the four samples is clamped to the
+// last but one row and column (an image level has at least two of each; at the border the weight of the other
+// row or column is then exactly one), so that the others lie at fixed distances from it: no coordinates, products and
+// offsets of their own, and the two samples of a row of b in one load.
 __device__ __forceinline__ void flow_terms(const float4* __restrict__ A1, const float* __restrict__ b1,
                                            const float4* __restrict__ A2, const float* __restrict__ b2, int h, int w, int gy,
                                            int gx, float2 dp, float (&t)[5]) {
     const uint32_t gi = pix(gy, w, gx);
     const float4 a1 = ld_at(A1, gi);
-    const float2 bb1 = make_float2(a1.w, ld_at(b1, gi));
+    const float b1y = ld_at(b1, gi);
     const float sy = clampf((float)gy + dp.y, 0.0f, (float)(h - 1));
     const float sx = clampf((float)gx + dp.x, 0.0f, (float)(w - 1));
-    const float fy0 = floorf(sy), fx0 = floorf(sx);
-    const int iy0 = (int)fy0, ix0 = (int)fx0;
-    const int iy1 = min(iy0 + 1, h - 1), ix1 = min(ix0 + 1, w - 1);
-    const float wy = sy - fy0, wx = sx - fx0;
-    const uint32_t i00 = pix(iy0, w, ix0), i10 = pix(iy1, w, ix0);
-    const uint32_t i01 = i00 + (uint32_t)(ix1 - ix0), i11 = i10 + (uint32_t)(ix1 - ix0);
-    const float4 a00 = ld_at(A2, i00), a01 = ld_at(A2, i01), a10 = ld_at(A2, i10), a11 = ld_at(A2, i11);
-    const float2 c00 = make_float2(a00.w, ld_at(b2, i00)), c01 = make_float2(a01.w, ld_at(b2, i01));
-    const float2 c10 = make_float2(a10.w, ld_at(b2, i10)), c11 = make_float2(a11.w, ld_at(b2, i11));
+    const int iy0 = min((int)sy, h - 2), ix0 = min((int)sx, w - 2);
+    const float wy = sy - (float)iy0, wx = sx - (float)ix0;
+    const uint32_t i0 = pix(iy0, w, ix0), i1 = i0 + (uint32_t)w;
+    const float4 a00 = ld_at(A2, i0), a01 = ld_at(A2 + 1, i0), a10 = ld_at(A2, i1), a11 = ld_at(A2 + 1, i1);
+    float c0[2], c1[2];                      // four-byte alignment only
+    __builtin_memcpy(c0, reinterpret_cast<const char*>(b2) + i0 * 4u, 8);
+    __builtin_memcpy(c1, reinterpret_cast<const char*>(b2) + i1 * 4u, 8);
     const float w00 = (1.0f - wx) * (1.0f - wy), w01 = wx * (1.0f - wy), w10 = (1.0f - wx) * wy, w11 = wx * wy;
     const float a2xx = a00.x * w00 + a01.x * w01 + a10.x * w10 + a11.x * w11;
     const float a2xy = a00.y * w00 + a01.y * w01 + a10.y * w10 + a11.y * w11;
     const float a2yy = a00.z * w00 + a01.z * w01 + a10.z * w10 + a11.z * w11;
-    const float b2x = c00.x * w00 + c01.x * w01 + c10.x * w10 + c11.x * w11;
-    const float b2y = c00.y * w00 + c01.y * w01 + c10.y * w10 + c11.y * w11;
+    const float b2x = a00.w * w00 + a01.w * w01 + a10.w * w10 + a11.w * w11;
+    const float b2y = c0[0] * w00 + c0[1] * w01 + c1[0] * w10 + c1[1] * w11;
     const float axx = 0.5f * (a1.x + a2xx), axy = 0.5f * (a1.y + a2xy), ayy = 0.5f * (a1.z + a2yy);
-    const float dbx = -0.5f * (b2x - bb1.x) + axx * dp.x + axy * dp.y;
-    const float dby = -0.5f * (b2y - bb1.y) + axy * dp.x + ayy * dp.y;
+    const float dbx = -0.5f * (b2x - a1.w) + axx * dp.x + axy * dp.y;
+    const float dby = -0.5f * (b2y - b1y) + axy * dp.x + ayy * dp.y;
     t[0] = axx * axx + axy * axy;
     t[1] = axy * (axx + ayy);
     t[2] = axy * axy + ayy * ayy;
@@ -566,22 +564,116 @@ __device__ __forceinline__ void flow_terms(const float4* __restrict__ A1, const 
     t[4] = axy * dbx + ayy * dby;
 }
 
-// the displacement from the windowed sums of the terms and the prior (ridge term centred on the prior)
+// the displacement from the windowed sums of the terms and the prior (ridge term centred on the prior).  The two
+// quotients share one reciprocal, refined to the last place, and each gets a step of its own (at most half a unit in
+// the last place and a little more); the ridge term keeps the determinant above 1e-8, so nothing has to be scaled as
+// a general division does.
 __device__ __forceinline__ float2 flow_solve(float g11, float g12, float g22, float h1, float h2, float2 dp) {
     const float lam = kLamAbs + kLamRel * 0.5f * (g11 + g22);
     const float m11 = g11 + lam, m22 = g22 + lam, m12 = g12;
     const float r1 = h1 + lam * dp.x, r2 = h2 + lam * dp.y;
     const float det = m11 * m22 - m12 * m12;
-    return make_float2((m22 * r1 - m12 * r2) / det, (m11 * r2 - m12 * r1) / det);
+    float inv = __builtin_amdgcn_rcpf(det);
+    inv = __builtin_fmaf(__builtin_fmaf(-det, inv, 1.0f), inv, inv);
+    const float nx = m22 * r1 - m12 * r2, ny = m11 * r2 - m12 * r1;
+    const float qx = nx * inv, qy = ny * inv;
+    return make_float2(__builtin_fmaf(__builtin_fmaf(-det, qx, nx), inv, qx), __builtin_fmaf(__builtin_fmaf(-det, qy, ny), inv, qy));
 }
 
-// Row and column of item p of a window pass over n_rows rows of TX outputs; false = an idle lane.
-// TX = 32: row-major.  TX = 16: the 32 lanes of a group take rows r and r + 8 (first the whole blocks of 16
-// rows: groups 0..7 take rows (0,8) .. (7,15); of the rest, n_rows - 16 k <= 15 rows, those that have a
-// partner eight further on are paired, the others get a group of their own with its upper half idle).
-template <int TX>
-__device__ __forceinline__ bool window_item(int p, int n_rows, int& row, int& col) {
-    if constexpr (TX == 16) {
+// Window passes on the matrix cores.  v_mfma_f32_4x4x1f32 is sixteen independent outer products of four weights and
+// four values; with the lane's weight k of the window's row `lane % 4` as the one operand and a value of the
+// lane's own as the other, fourteen of them give every lane four neighbouring outputs of the eleven-tap window,
+//   out[i] = sum_k w[k - i] v[k],  i = 0..3,
+// from the fourteen values under them, in fp32, lane by lane: what 44 multiply-adds of the vector ALU do, which then
+// is free for the warped samples.  Lanes do not mix, but all 64 must be there: the weights come from all of a block of
+// four, so callers keep their control flow uniform over the wave and let idle lanes repeat an item.
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+constexpr int kFirOut = 4, kFirIn = 2 * kWinR + kFirOut;              // 14
+
+struct FirWeights {
+    float k[kFirIn];
+};
+constexpr int kFirTable = kFirIn + 3;
+// three zeros, the window, three zeros, in LDS (written by the first threads, one barrier before its use)
+__device__ __forceinline__ void fir_table(float* s_w, const FlowWeights& fw) {
+    if (threadIdx.x < kFirTable) {
+        float v = 0.0f;
+#pragma unroll
+        for (int k = 0; k <= 2 * kWinR; ++k) v = (int)threadIdx.x == 3 + k ? fw.win_g[k] : v;
+        s_w[threadIdx.x] = v;
+    }
+}
+__device__ __forceinline__ FirWeights fir_weights(const float* s_w) {
+    FirWeights w;
+#pragma unroll
+    for (int k = 0; k < kFirIn; ++k) w.k[k] = s_w[k + 3 - (threadIdx.x & 3)];
+    return w;
+}
+__device__ __forceinline__ f32x4 fir4(const FirWeights& w, const float* v) {
+    f32x4 acc = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+    for (int k = 0; k < kFirIn; ++k) acc = __builtin_amdgcn_mfma_f32_4x4x1f32(w.k[k], v[k], acc, 0, 0, 0);
+    return acc;
+}
+// four outputs of the row pass from sixteen floats at p (16-byte aligned; the last two count nothing, but have to be finite)
+__device__ __forceinline__ f32x4 fir4_row(const FirWeights& w, const float* p) {
+    float v[16];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) *reinterpret_cast<f32x4*>(v + 4 * i) = *reinterpret_cast<const f32x4*>(p + 4 * i);
+    return fir4(w, v);
+}
+// four outputs of the column pass, rows `stride` apart
+__device__ __forceinline__ f32x4 fir4_column(const FirWeights& w, const float* p, int stride) {
+    float v[kFirIn];
+#pragma unroll
+    for (int k = 0; k < kFirIn; ++k) v[k] = p[k * stride];
+    return fir4(w, v);
+}
+
+}  // namespace
+
+// One update of a small level: 16x16 tiles on 256 threads.  Here the block is a short chain and the chip is not full,
+// so the window passes stay on the vector ALU with one output per lane (84x84 x 4 frames 5.8 us a launch, with the
+// matrix cores' four outputs per lane 6.7: a quarter of the lanes at work, each on a serial chain).
+constexpr int kSmallTile = 16, kSmallThreads = 256;
+__global__ __launch_bounds__(kSmallThreads) void k_flow_small(FlowBatch f, long long level_off, int h, int w, int ch, int cw,
+                                                              int prior_mode, FlowWeights fw) {
+    // blk.z = frame of the batch, (blk.x, blk.y) = tile
+    const BlockId blk = xcd_block_id();
+    const float4* __restrict__ A1 = f.A1[blk.z] + level_off;
+    const float* __restrict__ b1 = f.b1[blk.z] + level_off;
+    const float4* __restrict__ A2 = f.A2[blk.z] + level_off;
+    const float* __restrict__ b2 = f.b2[blk.z] + level_off;
+    const float2* __restrict__ d_in = f.d_in[blk.z];
+    float2* __restrict__ d_out = f.d_out[blk.z];
+    constexpr int T = kSmallTile, NT = kSmallThreads, R = T + 2 * kWinR;       // 26: tile and halo
+    // A group of 32 lanes of a window pass reads two rows (16 lanes each), which must lie 16 banks apart.  The two
+    // rows of a group are eight apart (window_item) and the rows are unpadded: 8 * 26 = 16 mod 32; the pass that
+    // writes the terms then sees addresses linear in the thread index, and a block takes 16 KB, so that eight
+    // blocks fill every wave slot of a compute unit.
+    static_assert((8 * R) % 32 == 16, "rows eight apart sit 16 banks apart");
+    __shared__ float s_in[5][R][R];
+    __shared__ float2 s_dp[T][T];            // prior of the tile's own pixels, for the solve
+
+    const int tid = threadIdx.x;
+    const int x0 = blk.x * T, y0 = blk.y * T;
+
+    // per-cell A^T A and A^T db at the clamped coordinate of the cell
+#pragma unroll 2
+    for (int p = tid; p < R * R; p += NT) {
+        const int ry = p / R, rx = p % R;
+        const int gy = clampi(y0 - kWinR + ry, 0, h - 1), gx = clampi(x0 - kWinR + rx, 0, w - 1);
+        const float2 dp = prior_at(d_in, prior_mode, gy, gx, w, ch, cw);
+        if (ry >= kWinR && ry < kWinR + T && rx >= kWinR && rx < kWinR + T) s_dp[ry - kWinR][rx - kWinR] = dp;
+        float t[5];
+        flow_terms(A1, b1, A2, b2, h, w, gy, gx, dp, t);
+#pragma unroll
+        for (int c = 0; c < 5; ++c) s_in[c][ry][rx] = t[c];
+    }
+    __syncthreads();
+    // Item p of a pass over n_rows rows of 16 outputs: the 32 lanes of a group take rows r and r + 8, first the whole
+    // blocks of 16 rows, then the rest (ten rows in the row pass: two pairs, six rows with an idle half each).
+    auto window_item = [](int p, int n_rows, int& row, int& col) {
         const int g = p >> 5, half = (p >> 4) & 1;
         col = p & 15;
         const int full = n_rows / 16, base = 16 * full;
@@ -596,77 +688,17 @@ __device__ __forceinline__ bool window_item(int p, int n_rows, int& row, int& co
         }
         row = base + npair + (gg - npair);
         return half == 0 && row < base + (rest > 8 ? 8 : rest);
-    } else {
-        row = p / TX;
-        col = p % TX;
-        return row < n_rows;
-    }
-}
-// items (lanes, idle ones included) of such a pass
-template <int TX>
-constexpr int window_items(int n_rows) {
-    if (TX != 16) return n_rows * TX;
-    const int rest = n_rows % 16, npair = rest > 8 ? rest - 8 : 0;
-    return 32 * (8 * (n_rows / 16) + npair + ((rest > 8 ? 8 : rest) - npair));
-}
-
-}  // namespace
-
-// TX x TY = tile, NT = threads of the block.
-template <int TX, int TY, int NT>
-__global__ __launch_bounds__(NT) void k_flow_iter(FlowBatch f, long long level_off, int h, int w, int ch, int cw,
-                                                  int prior_mode, FlowWeights fw) {
-    // blk.z = frame of the batch, (blk.x, blk.y) = tile
-    const BlockId blk = xcd_block_id();
-    const float4* __restrict__ A1 = f.A1[blk.z] + level_off;
-    const float* __restrict__ b1 = f.b1[blk.z] + level_off;
-    const float4* __restrict__ A2 = f.A2[blk.z] + level_off;
-    const float* __restrict__ b2 = f.b2[blk.z] + level_off;
-    const float2* __restrict__ d_in = f.d_in[blk.z];
-    float2* __restrict__ d_out = f.d_out[blk.z];
-    constexpr int RX = TX + 2 * kWinR, RY = TY + 2 * kWinR;
-    // Row stride of the per-cell terms.  A group of 32 lanes of a window pass reads one row of a 32-wide
-    // tile but two rows (16 lanes each) of a 16-wide one, which must not share banks: their distance has
-    // to be 16 mod 32 floats.  With adjacent rows that takes a stride of 48 floats for 26 cells (25 KB a
-    // block, five blocks per compute unit; RX + 1 = 27 spent 37 % of the LDS cycles on bank conflicts).
-    // Instead the two rows of a group are eight apart (window_item) and the rows are unpadded: 8 * 26 = 16
-    // mod 32; the pass that writes the terms then sees addresses linear in the thread index, and a block
-    // takes 16 KB, so that eight blocks fill every wave slot of a compute unit.
-    constexpr int RXS = TX == 16 ? RX : RX + 1;
-    static_assert(TX != 16 || (8 * RXS) % 32 == 16, "rows eight apart sit 16 banks apart");
-    __shared__ float s_in[5][RY][RXS];
-    __shared__ float2 s_dp[TY][TX];          // prior of the tile's own pixels, for the solve
-
-    const int tid = threadIdx.x;
-    const int x0 = blk.x * TX, y0 = blk.y * TY;
-
-    // per-cell A^T A and A^T db at the clamped coordinate of the cell
-#pragma unroll 2
-    for (int p = tid; p < RX * RY; p += NT) {
-        const int ry = p / RX, rx = p % RX;
-        const int gy = clampi(y0 - kWinR + ry, 0, h - 1), gx = clampi(x0 - kWinR + rx, 0, w - 1);
-        const float2 dp = prior_at(d_in, prior_mode, gy, gx, w, ch, cw);
-        if (ry >= kWinR && ry < kWinR + TY && rx >= kWinR && rx < kWinR + TX) s_dp[ry - kWinR][rx - kWinR] = dp;
-        float t[5];
-        flow_terms(A1, b1, A2, b2, h, w, gy, gx, dp, t);
-#pragma unroll
-        for (int c = 0; c < 5; ++c) s_in[c][ry][rx] = t[c];
-    }
-    __syncthreads();
-
+    };
     {
-        // Row pass of the separable Gaussian window, in place: every thread keeps the sums of its (at most
-        // kRowItems) outputs in registers until all taps of all threads are read, then writes them over the
-        // terms at [ry][tx].  A second array for the row sums would cost 17 KB (32x16 tile): with it three
-        // blocks fit a compute unit, without it four, and next to the K/V kernels, where a block spends its
-        // time waiting for memory, the blocks in flight are what sets the kernel's speed.
-        constexpr int kRowItems = (window_items<TX>(RY) + NT - 1) / NT;
+        // Row pass of the separable Gaussian window, in place: every thread keeps the sums of its (at most two) outputs
+        // in registers until all taps of all threads are read, then writes them over the terms at [ry][tx].
+        constexpr int kRowItems = 2;
+        static_assert(32 * (8 + 2 + 6) <= kRowItems * NT, "26 rows: eight pairs, two pairs and six singles");
         float racc[kRowItems][5];
 #pragma unroll
         for (int q = 0; q < kRowItems; ++q) {
-            const int p = tid + q * NT;
             int ry, tx;
-            const bool mine = window_item<TX>(p, RY, ry, tx);
+            const bool mine = window_item(tid + q * NT, R, ry, tx);
 #pragma unroll
             for (int c = 0; c < 5; ++c) racc[q][c] = 0.0f;
             if (mine) {
@@ -681,9 +713,8 @@ __global__ __launch_bounds__(NT) void k_flow_iter(FlowBatch f, long long level_o
         __syncthreads();
 #pragma unroll
         for (int q = 0; q < kRowItems; ++q) {
-            const int p = tid + q * NT;
             int ry, tx;
-            if (window_item<TX>(p, RY, ry, tx)) {
+            if (window_item(tid + q * NT, R, ry, tx)) {
 #pragma unroll
                 for (int c = 0; c < 5; ++c) s_in[c][ry][tx] = racc[q][c];
             }
@@ -692,20 +723,116 @@ __global__ __launch_bounds__(NT) void k_flow_iter(FlowBatch f, long long level_o
     }
 
     // column pass + ridge solve
-    for (int p = tid; p < TX * TY; p += NT) {
-        int ty, tx;
-        window_item<TX>(p, TY, ty, tx);
-        const int gy = y0 + ty, gx = x0 + tx;
-        if (gy >= h || gx >= w) continue;
-        float acc[5] = {0, 0, 0, 0, 0};
+    int ty, tx;
+    window_item(tid, T, ty, tx);
+    const int gy = y0 + ty, gx = x0 + tx;
+    if (gy >= h || gx >= w) return;
+    float acc[5] = {0, 0, 0, 0, 0};
 #pragma unroll
-        for (int k = 0; k <= 2 * kWinR; ++k) {
-            const float wk = fw.win_g[k];
+    for (int k = 0; k <= 2 * kWinR; ++k) {
+        const float wk = fw.win_g[k];
 #pragma unroll
-            for (int c = 0; c < 5; ++c) acc[c] += wk * s_in[c][ty + k][tx];
+        for (int c = 0; c < 5; ++c) acc[c] += wk * s_in[c][ty + k][tx];
+    }
+    *reinterpret_cast<float2*>(reinterpret_cast<char*>(d_out) + pix(gy, w, gx) * 8u) =
+        flow_solve(acc[0], acc[1], acc[2], acc[3], acc[4], s_dp[ty][tx]);
+}
+
+// ---------------------------------------------------------------------------------------------
+// One update of a large level: tiles 32 wide on 512 threads, the window passes on the matrix cores.
+//
+// Three 1920x1080 frames: 81 us an update, one: 31, fifteen 640x360: 51.  With the windows on the vector ALU (110
+// multiply-adds and as many LDS reads a pixel and 1.6 rows of halo, 32x16 tiles, per-cell index arithmetic, divisions)
+// 518 vector instructions a pixel kept the ALU 91 % busy: 102, 37 and 59 us.  Now it is 60 % busy and the trips of
+// the warped samples bound the kernel: 12 000 of a block's 21 000 cycles, of which it takes 3.4 for a cell even when the
+// windows are left out.  Everything that costs a block or a wave shows: 16 waves a block (32x32 on 1024 threads)
+// 100 us, registers spilled under the 64 that eight waves per SIMD leave 94 to 140 (asking for all of a thread's
+// priors first, or marching down a strip while ten rows of sums stay in LDS), 48-wide tiles 104 to 121; 64x32 on 1024
+// threads is as fast but needs sixteen free wave slots on one compute unit.  The same windows as banded matrix products
+// (v_mfma_f32_16x16x4f32, the row pass's result the column pass's operand) took 100: 28 and 32 terms for eleven.
+constexpr int kTileX = 32, kTileThreads = 512;
+template <int TY>
+__global__ __launch_bounds__(kTileThreads, 8) void k_flow_tile(FlowBatch f, long long level_off, int h, int w, int ch, int cw,
+                                                               int prior_mode, FlowWeights fw) {
+    const BlockId blk = xcd_block_id();
+    const float4* __restrict__ A1 = f.A1[blk.z] + level_off;
+    const float* __restrict__ b1 = f.b1[blk.z] + level_off;
+    const float4* __restrict__ A2 = f.A2[blk.z] + level_off;
+    const float* __restrict__ b2 = f.b2[blk.z] + level_off;
+    const float2* __restrict__ d_in = f.d_in[blk.z];
+    float2* __restrict__ d_out = f.d_out[blk.z];
+    constexpr int TX = kTileX, NT = kTileThreads, RX = TX + 2 * kWinR, RY = TY + 2 * kWinR;
+    constexpr int P = (RX + 3) / 4 * 4;              // row stride: the row pass reads sixteen bytes at a time
+    __shared__ __align__(16) float s_in[5][RY * P];
+    __shared__ float s_w[kFirTable];
+    const int tid = threadIdx.x, wave0 = tid & ~63;
+    const int x0 = blk.x * TX, y0 = blk.y * TY;
+    fir_table(s_w, fw);
+    // columns RX .. P - 1 of the last group of a row: weight zero, but a number
+    if (tid < RY * (P - RX)) {
+#pragma unroll
+        for (int c = 0; c < 5; ++c) s_in[c][(tid / (P - RX)) * P + RX + tid % (P - RX)] = 0.0f;
+    }
+    {
+        // per-cell terms at the clamped coordinate of the cell: a thread stays in its column (of 504 threads, twelve
+        // rows at a time), so that only the row's coordinate changes
+        constexpr int kRows = NT / RX, kSteps = (RY + kRows - 1) / kRows;
+        const int rx = tid % RX, r0 = tid / RX;
+        const int gx = clampi(x0 - kWinR + rx, 0, w - 1);
+        if (r0 < kRows) {
+#pragma unroll
+            for (int k = 0; k < kSteps; ++k) {
+                const int ry = r0 + k * kRows;
+                if (k == kSteps - 1 && ry >= RY) continue;
+                const int gy = clampi(y0 - kWinR + ry, 0, h - 1);
+                float t[5];
+                flow_terms(A1, b1, A2, b2, h, w, gy, gx, prior_at(d_in, prior_mode, gy, gx, w, ch, cw), t);
+#pragma unroll
+                for (int c = 0; c < 5; ++c) s_in[c][ry * P + rx] = t[c];
+            }
         }
-        *reinterpret_cast<float2*>(reinterpret_cast<char*>(d_out) + pix(gy, w, gx) * 8u) =
-            flow_solve(acc[0], acc[1], acc[2], acc[3], acc[4], s_dp[ty][tx]);
+    }
+    __syncthreads();
+    const FirWeights wt = fir_weights(s_w);
+    // the priors of the four pixels the thread solves for, asked for again (they are in the cache) ahead of the row pass
+    constexpr int kSolve = TX * (TY / kFirOut);      // items of the column pass: whole waves
+    static_assert(kSolve <= NT && kSolve % 64 == 0, "one column item per thread, in whole waves");
+    const int tx = tid % TX, ty = kFirOut * (tid / TX);
+    const int gx = x0 + tx;
+    float2 dp[kFirOut];
+    if (wave0 < kSolve) {
+#pragma unroll
+        for (int i = 0; i < kFirOut; ++i) dp[i] = prior_at(d_in, prior_mode, min(y0 + ty + i, h - 1), min(gx, w - 1), w, ch, cw);
+    }
+    {
+        // Row pass, in place: the sums stay in registers until all of the block's taps are read.  A second array
+        // would cost a quarter of the blocks per compute unit.
+        constexpr int kItems = RY * (TX / kFirOut);
+        static_assert(kItems <= NT, "one row item per thread");
+        const int item = min(tid, kItems - 1);
+        const int at = (item / (TX / kFirOut)) * P + kFirOut * (item % (TX / kFirOut));
+        f32x4 r[5];
+        if (wave0 < kItems) {
+#pragma unroll
+            for (int c = 0; c < 5; ++c) r[c] = fir4_row(wt, &s_in[c][at]);
+        }
+        __syncthreads();
+        if (tid < kItems) {
+#pragma unroll
+            for (int c = 0; c < 5; ++c) *reinterpret_cast<f32x4*>(&s_in[c][at]) = r[c];
+        }
+        __syncthreads();
+    }
+    if (wave0 >= kSolve) return;
+    f32x4 acc[5];
+#pragma unroll
+    for (int c = 0; c < 5; ++c) acc[c] = fir4_column(wt, &s_in[c][ty * P + tx], P);
+#pragma unroll
+    for (int i = 0; i < kFirOut; ++i) {
+        const int gy = y0 + ty + i;
+        if (gy < h && gx < w)
+            *reinterpret_cast<float2*>(reinterpret_cast<char*>(d_out) + pix(gy, w, gx) * 8u) =
+                flow_solve(acc[0][i], acc[1][i], acc[2][i], acc[3][i], acc[4][i], dp[i]);
     }
 }
 
@@ -720,7 +847,7 @@ __global__ __launch_bounds__(NT) void k_flow_iter(FlowBatch f, long long level_o
 // block per compute unit it loses (168x168 x 4: 21.5 against 27).  All of that on an idle chip, one launch after
 // the other; next to kernels that fill the wave slots a block of 1024 threads waits longer for room than the three
 // launches take.  The results are the same numbers.
-// Cells outside the image stand for the clamped coordinate, as in k_flow_iter.
+// Cells outside the image stand for the clamped coordinate, as in k_flow_tile.
 constexpr int kFusedUpdates = 3;
 constexpr int kFusedThreads = 1024;
 
@@ -763,7 +890,7 @@ __device__ __forceinline__ void fused_update(FusedTile<TX, TY>& sh, float2* prio
     }
     __syncthreads();
     // Window passes, two outputs an item: twelve reads a field for two outputs; with one the passes
-    // wait for LDS, with four too few lanes have work.  Row pass in place, as in k_flow_iter.
+    // wait for LDS, with four too few lanes have work.  Row pass in place, as in k_flow_tile.
     {
         constexpr int kItems = RY * (DX / 2), kN = (kItems + NT - 1) / NT;
         static_assert(DX % 2 == 0 && DY % 2 == 0, "pairs");
@@ -967,24 +1094,21 @@ hipError_t launch_flow_updates(const FlowBatch& f, int n, int64_t level_off, int
     }
 #undef SALI_FUSED_LAUNCH
     *done = 1;
-    // Tile and block by level size:
-    //   below 40 000 pixels   16x16, 256 threads   (16 KB of LDS: eight blocks per compute unit)
-    //   above                 32x16, 512 threads   (26 KB: four blocks; 2.1 instead of 2.6 halo cells per output)
-    // A block is a chain of dependent HBM round trips (prior -> warped gather, once per cell a thread
-    // owns); with twice the threads a thread owns about two cells, taken together.  Both shapes fill every
-    // wave slot of a compute unit, which is what counts next to the K/V kernels, where a block mostly waits
-    // for memory.  A 32x32 tile on 1024 threads (1.7 halo cells per output, two blocks per compute unit,
-    // 64 registers) was used from 150 000 pixels up until the row pass went in place: alone on the GPU it
-    // is 1.5 % faster at 1920x1080 (235 against 239 us per frame), inside the pipeline 2 - 3 % slower
-    // (1080p 3 090 -> 3 160 frames/s, 640x360 32 150 -> 33 100): a block of 1024 threads needs sixteen free
-    // wave slots on one compute unit at once.  The same tile on 512 threads (84 registers, three blocks) is
-    // slower everywhere; 22x22 (one thread per cell), 64x16 and 32x16 on 1024 threads are slower as well.
-    const long long px = (long long)h * w;
-#define SALI_FLOW_LAUNCH(TX, TY, NT)                                                                         \
-    hipLaunchKernelGGL((k_flow_iter<TX, TY, NT>), dim3((w + TX - 1) / TX, (h + TY - 1) / TY, n), dim3(NT), 0, \
-                       s, f, (long long)level_off, h, w, ch, cw, prior_mode, fw)
-    if (px >= 40000) SALI_FLOW_LAUNCH(32, 16, 512);
-    else SALI_FLOW_LAUNCH(16, 16, 256);
+#define SALI_FLOW_LAUNCH(KERNEL, TX, TY, NT)                                                                      \
+    hipLaunchKernelGGL(KERNEL, dim3((w + TX - 1) / TX, (h + TY - 1) / TY, n), dim3(NT), 0, s, f, (long long)level_off, h, \
+                       w, ch, cw, prior_mode, fw)
+    // The shape whose rounds of blocks cost least.  A round is a block per compute unit; launches of 1, 2, 3 .. rounds
+    // measured over thirty levels (42x42 to 1920x1080, one to fifteen frames, an idle chip, in us) lie on a line each:
+    //   32x32 tiles   8.0  11.0  14.9 .. 30.6 (eight)      least work per pixel: 1.7 cells
+    //   32x16 tiles   6.9   8.6  10.4  12.2                2.1 cells
+    //   16x16 tiles   5.8   6.8   7.9   9.0  10.2          2.6 cells, the shortest block
+    // e.g. 640x360 8.3 / 8.7 / 9.1, two frames of 480x270 10.6 / 8.8 / 9.2, 168x168 x 8 frames 10.1 / 9.8 / 8.8.
+    auto rounds = [&](int tx, int ty) { return (tiles(tx, ty) + kComputeUnits - 1) / kComputeUnits; };
+    const long long cost32 = 100 + 60 * rounds(kTileX, 32), cost16 = 103 + 35 * rounds(kTileX, 16),
+                    cost_small = 94 + 22 * rounds(kSmallTile, kSmallTile);             // twentieths of a us
+    if (cost_small <= cost16 && cost_small <= cost32) SALI_FLOW_LAUNCH(k_flow_small, kSmallTile, kSmallTile, kSmallThreads);
+    else if (cost16 <= cost32) SALI_FLOW_LAUNCH(k_flow_tile<16>, kTileX, 16, kTileThreads);
+    else SALI_FLOW_LAUNCH(k_flow_tile<32>, kTileX, 32, kTileThreads);
 #undef SALI_FLOW_LAUNCH
     return hipGetLastError();
 }

@@ -214,6 +214,30 @@ def test_updates_per_launch(h, w, levels, iters):
     ctx.close()
 
 
+@pytest.mark.parametrize("h,w,shift", [
+    (353, 577, (0.9, -1.3)), (383, 607, (-2.6, 3.4)), (512, 481, (6.0, 5.0)),      # 32x32 tiles: one row and column over, ragged, exact rows
+    (270, 929, (0.9, -1.3)), (259, 947, (-2.6, 3.4)),                              # 32x16: a column over, three rows over
+    (480, 97, (3.0, -6.0)), (97, 480, (-6.0, 3.0)),                                # 16x16, a round and more
+])
+def test_single_updates_of_larger_levels(h, w, shift):
+    """Two updates, a launch each, in every tile shape, with windows and warped samples that reach past all four borders
+    (samples in the last row and column included), against the oracle."""
+    from paper_2602_14236_amd import binding
+    ctx = binding.SaliContext(lib_config(params(h, w, flow_levels=1, flow_iters=2)))
+    yy, xx = np.mgrid[0:h, 0:w].astype(np.float64)
+    rng = np.random.default_rng(h * w)
+    frames = []
+    for d in (0.0, 1.0):
+        x, y = xx - shift[0] * d, yy - shift[1] * d
+        img = 128 + 60 * np.sin(x / 9.1) * np.sin(y / 8.3) + 40 * np.sin((x - y) / 15.0)
+        frames.append(np.clip(np.rint(img[..., None] + rng.normal(0, 1, (h, w, 3))), 0, 255).astype(np.uint8))
+    uv, _, _ = _run(ctx, frames[0], frames[1])
+    d = of.flow(frames[0], frames[1], 1, 2)
+    print(f"{h}x{w}: largest error {max(np.abs(uv[0] - d[..., 0]).max(), np.abs(uv[1] - d[..., 1]).max()):.2e}", flush=True)
+    assert close(uv[0], d[..., 0]).all() and close(uv[1], d[..., 1]).all()
+    ctx.close()
+
+
 def test_flow_score_next_to_analyses_on_another_stream():
     """The stand-alone flow call has scratch of its own: next to batched analyses of the same context on another stream,
     in either order of issue, both give the bits that they give alone."""
