@@ -741,19 +741,23 @@ __global__ __launch_bounds__(kSmallThreads) void k_flow_small(FlowBatch f, long 
 // ---------------------------------------------------------------------------------------------
 // One update of a large level: tiles 32 wide on 512 threads, the window passes on the matrix cores.
 //
-// Three 1920x1080 frames: 81 us an update, one: 31, fifteen 640x360: 51.  With the windows on the vector ALU (110
+// Three 1920x1080 frames: 73 us an update, one: 28, fifteen 640x360: 45.  With the windows on the vector ALU (110
 // multiply-adds and as many LDS reads a pixel and 1.6 rows of halo, 32x16 tiles, per-cell index arithmetic, divisions)
 // 518 vector instructions a pixel kept the ALU 91 % busy: 102, 37 and 59 us.  Now it is 60 % busy and the trips of
-// the warped samples bound the kernel: 12 000 of a block's 21 000 cycles, of which it takes 3.4 for a cell even when the
-// windows are left out.  Everything that costs a block or a wave shows: 16 waves a block (32x32 on 1024 threads)
-// 100 us, registers spilled under the 64 that eight waves per SIMD leave 94 to 140 (asking for all of a thread's
-// priors first, or marching down a strip while ten rows of sums stay in LDS), 48-wide tiles 104 to 121; 64x32 on 1024
+// the warped samples bound the kernel: 12 000 of a block's 21 000 cycles.  Everything that costs a block or a wave shows: 16 waves a block (32x32 on 1024 threads)
+// 100 us, registers spilled under the 64 that eight waves per SIMD leave 94 to 140 (five fields' products in step,
+// or marching down a strip while ten rows of sums stay in LDS), 48-wide tiles 104 to 121; 64x32 on 1024
 // threads is as fast but needs sixteen free wave slots on one compute unit.  The same windows as banded matrix products
 // (v_mfma_f32_16x16x4f32, the row pass's result the column pass's operand) took 100: 28 and 32 terms for eleven.
 constexpr int kTileX = 32, kTileThreads = 512;
-template <int TY>
+//
+// kFirst: the first update of a level (prior_mode 0 or 1).  The others know that a prior is one load, and ask for those of
+// all the thread's cells before the first sample; a first update takes 81, 31 and 51 us.  The samples of the coarser flow that
+// a first update needs leave no registers for that.
+template <int TY, bool kFirst>
 __global__ __launch_bounds__(kTileThreads, 8) void k_flow_tile(FlowBatch f, long long level_off, int h, int w, int ch, int cw,
-                                                               int prior_mode, FlowWeights fw) {
+                                                               int first_mode, FlowWeights fw) {
+    const int prior_mode = kFirst ? first_mode : 2;
     const BlockId blk = xcd_block_id();
     const float4* __restrict__ A1 = f.A1[blk.z] + level_off;
     const float* __restrict__ b1 = f.b1[blk.z] + level_off;
@@ -780,13 +784,20 @@ __global__ __launch_bounds__(kTileThreads, 8) void k_flow_tile(FlowBatch f, long
         const int rx = tid % RX, r0 = tid / RX;
         const int gx = clampi(x0 - kWinR + rx, 0, w - 1);
         if (r0 < kRows) {
+            float2 prior[kSteps];
+            if constexpr (!kFirst) {
+#pragma unroll
+                for (int k = 0; k < kSteps; ++k)
+                    prior[k] = prior_at(d_in, 2, clampi(y0 - kWinR + min(r0 + k * kRows, RY - 1), 0, h - 1), gx, w, 0, 0);
+            }
 #pragma unroll
             for (int k = 0; k < kSteps; ++k) {
                 const int ry = r0 + k * kRows;
                 if (k == kSteps - 1 && ry >= RY) continue;
                 const int gy = clampi(y0 - kWinR + ry, 0, h - 1);
+                if constexpr (kFirst) prior[k] = prior_at(d_in, prior_mode, gy, gx, w, ch, cw);
                 float t[5];
-                flow_terms(A1, b1, A2, b2, h, w, gy, gx, prior_at(d_in, prior_mode, gy, gx, w, ch, cw), t);
+                flow_terms(A1, b1, A2, b2, h, w, gy, gx, prior[k], t);
 #pragma unroll
                 for (int c = 0; c < 5; ++c) s_in[c][ry * P + rx] = t[c];
             }
@@ -1098,17 +1109,20 @@ hipError_t launch_flow_updates(const FlowBatch& f, int n, int64_t level_off, int
     hipLaunchKernelGGL(KERNEL, dim3((w + TX - 1) / TX, (h + TY - 1) / TY, n), dim3(NT), 0, s, f, (long long)level_off, h, \
                        w, ch, cw, prior_mode, fw)
     // The shape whose rounds of blocks cost least.  A round is a block per compute unit; launches of 1, 2, 3 .. rounds
-    // measured over thirty levels (42x42 to 1920x1080, one to fifteen frames, an idle chip, in us) lie on a line each:
-    //   32x32 tiles   8.0  11.0  14.9 .. 30.6 (eight)      least work per pixel: 1.7 cells
-    //   32x16 tiles   6.9   8.6  10.4  12.2                2.1 cells
+    // measured over thirty levels (84x84 to 1920x1080, one to fifteen frames, an idle chip, in us, the first update of a
+    // level and the others averaged) lie on a line each:
+    //   32x32 tiles   7.7  10.6  14.2 .. 29 (eight)        least work per pixel: 1.7 cells
+    //   32x16 tiles   6.5   8.4  10.1  11.9                2.1 cells
     //   16x16 tiles   5.8   6.8   7.9   9.0  10.2          2.6 cells, the shortest block
-    // e.g. 640x360 8.3 / 8.7 / 9.1, two frames of 480x270 10.6 / 8.8 / 9.2, 168x168 x 8 frames 10.1 / 9.8 / 8.8.
+    // e.g. 640x360 7.8 / 8.5 / 9.1, two frames of 480x270 10.2 / 8.6 / 9.2, 168x168 x 8 frames 9.7 / 9.6 / 8.8.
     auto rounds = [&](int tx, int ty) { return (tiles(tx, ty) + kComputeUnits - 1) / kComputeUnits; };
-    const long long cost32 = 100 + 60 * rounds(kTileX, 32), cost16 = 103 + 35 * rounds(kTileX, 16),
+    const long long cost32 = 93 + 60 * rounds(kTileX, 32), cost16 = 95 + 36 * rounds(kTileX, 16),
                     cost_small = 94 + 22 * rounds(kSmallTile, kSmallTile);             // twentieths of a us
     if (cost_small <= cost16 && cost_small <= cost32) SALI_FLOW_LAUNCH(k_flow_small, kSmallTile, kSmallTile, kSmallThreads);
-    else if (cost16 <= cost32) SALI_FLOW_LAUNCH(k_flow_tile<16>, kTileX, 16, kTileThreads);
-    else SALI_FLOW_LAUNCH(k_flow_tile<32>, kTileX, 32, kTileThreads);
+    else if (cost16 <= cost32 && prior_mode != 2) SALI_FLOW_LAUNCH((k_flow_tile<16, true>), kTileX, 16, kTileThreads);
+    else if (cost16 <= cost32) SALI_FLOW_LAUNCH((k_flow_tile<16, false>), kTileX, 16, kTileThreads);
+    else if (prior_mode != 2) SALI_FLOW_LAUNCH((k_flow_tile<32, true>), kTileX, 32, kTileThreads);
+    else SALI_FLOW_LAUNCH((k_flow_tile<32, false>), kTileX, 32, kTileThreads);
 #undef SALI_FLOW_LAUNCH
     return hipGetLastError();
 }
