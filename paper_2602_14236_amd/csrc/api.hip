@@ -390,8 +390,9 @@ int enqueue_saliency(sali_ctx* c, const uint8_t* const* d_rgb, const BatchPlan& 
     return SALI_OK;
 }
 
-// gray image, pyramid and polynomial expansion of each frame, the last into its expansion slot
-int enqueue_expansion(sali_ctx* c, const uint8_t* const* d_rgb, const BatchPlan& bp, hipStream_t s) {
+// gray image, pyramid and polynomial expansion of each frame, the last into its expansion slot; `done` (may be NULL) is
+// recorded with the last launch
+int enqueue_expansion(sali_ctx* c, const uint8_t* const* d_rgb, const BatchPlan& bp, hipEvent_t done, hipStream_t s) {
     const LevelGeom& g = c->geom;
     if (fused_expansion(c, bp.n)) {
         const int rc = enqueue_gray(c, d_rgb, bp, s);
@@ -403,7 +404,7 @@ int enqueue_expansion(sali_ctx* c, const uint8_t* const* d_rgb, const BatchPlan&
             f.A[i] = c->sc<float4>(c->sl.expA[bp.slot[i]]);
             f.b[i] = c->sc<float>(c->sl.expB[bp.slot[i]]);
         }
-        SALI_TRY(launch_expand(f, bp.n, g, c->fw, s));
+        SALI_TRY(launch_expand(f, bp.n, g, c->fw, done, s));
         return SALI_OK;
     }
     PyrBatch f = {};
@@ -421,7 +422,7 @@ int enqueue_expansion(sali_ctx* c, const uint8_t* const* d_rgb, const BatchPlan&
     } else {
         SALI_TRY(launch_pyramid(f, bp.n, g, s));
     }
-    SALI_TRY(launch_polyexp(f, bp.n, g, c->fw, s));
+    SALI_TRY(launch_polyexp(f, bp.n, g, c->fw, done, s));
     return SALI_OK;
 }
 
@@ -495,13 +496,13 @@ int enqueue_motion(sali_ctx* c, const BatchPlan& bp, const float2* const* flow, 
 
 // Pooling of the batch's saliency pre-pass (Eq. 7).  With `tier` (the chained step) a second launch
 // evaluates the gates and writes the frame-table rows with tiers and compaction indices, in frame
-// order; redundant frames get no scores.  d_scores_or_null / d_salmap redirect the outputs of a
+// order; redundant frames get no scores; `done` (may be NULL) is recorded with it.  d_scores_or_null / d_salmap redirect the outputs of a
 // stand-alone single-frame call.
 int enqueue_pool(sali_ctx* c, const BatchPlan& bp, float* d_scores_or_null, uint8_t* d_salmap,
-                 const TierLaunch* tier, const float2* const* flow, hipStream_t s) {
+                 const TierLaunch* tier, const float2* const* flow, hipEvent_t done, hipStream_t s) {
     const PoolBatch f = pool_batch(c, bp, d_scores_or_null, flow);
     SALI_TRY(launch_pool(f, bp.n, c->cfg.src_h, c->cfg.src_w, d_salmap, tier, gate_params(c),
-                         &c->lane_ptrs(bp.lane[0]).counters->batch_done, s));
+                         &c->lane_ptrs(bp.lane[0]).counters->batch_done, done, s));
     return SALI_OK;
 }
 
@@ -564,6 +565,14 @@ int enqueue_pack(sali_ctx* c, const void* const* d_kv, int first_frame_id, int n
 int wait_unless_same(hipStream_t s, hipStream_t recorded_on, hipEvent_t ev) {
     if (recorded_on != s) SALI_TRY(hipStreamWaitEvent(s, ev, 0));
     return SALI_OK;
+}
+
+// May the events of an analysis ride on its launches?  Not while the stream is being captured: the dependence of another
+// stream's work on an event that a launch records does not become an edge of the graph (one recorded by a call does).
+// Where they may, sali_step frame by frame at 336x336 is 3.5 % faster (two packets of 3.4 us a frame).
+bool events_may_ride(hipStream_t s) {
+    hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+    return hipStreamIsCapturing(s, &status) == hipSuccess && status == hipStreamCaptureStatusNone;
 }
 
 // Device address of `scratch` on the current device, looked up once per device (with that device
@@ -772,7 +781,7 @@ int sali_flow_score(sali_ctx* c, const uint8_t* d_prev_rgb, const uint8_t* d_cur
     pair.prev_slot[0] = -1;
     pair.prev_slot[1] = kStepSlots;
     const uint8_t* const d_rgb[2] = {d_prev_rgb, d_cur_rgb};
-    int rc = enqueue_expansion(c, d_rgb, pair, s);
+    int rc = enqueue_expansion(c, d_rgb, pair, nullptr, s);
     if (rc != SALI_OK) return rc;
     const float2* flow[kMaxBatch];
     rc = enqueue_flow(c, pair, flow, s);
@@ -790,7 +799,7 @@ int sali_saliency_pool(sali_ctx* c, const uint8_t* d_rgb, uint8_t* d_salmap_or_n
     bp.n = 1;
     bp.parity[0] = c->lane_uses[0]++ & 1u;
     int rc = enqueue_saliency(c, &d_rgb, bp, nullptr, s);
-    if (rc == SALI_OK) rc = enqueue_pool(c, bp, d_scores576, d_salmap_or_null, nullptr, nullptr, s);
+    if (rc == SALI_OK) rc = enqueue_pool(c, bp, d_scores576, d_salmap_or_null, nullptr, nullptr, nullptr, s);
     return rc;
 }
 
@@ -912,12 +921,13 @@ int sali_analyze_batch(sali_ctx* c, const uint8_t* const* d_rgb_frames, int32_t 
         rc = wait_unless_same(s, old.stream, old.done);
         if (rc != SALI_OK) return rc;
     }
-    // the temporal filter first: gray, pyramid + expansion, flow, per-patch motion
-    rc = enqueue_expansion(c, d_rgb_frames, bp, s);
-    if (rc != SALI_OK) return rc;
     // the batch's events live in the ring entry of its last frame
     AnalysisRecord& rec = c->ring[n_last % kRing];
-    SALI_TRY(hipEventRecord(rec.exp_ready, s));
+    const bool ride = events_may_ride(s);
+    // the temporal filter first: gray, pyramid + expansion, flow, per-patch motion
+    rc = enqueue_expansion(c, d_rgb_frames, bp, ride ? rec.exp_ready : nullptr, s);
+    if (rc != SALI_OK) return rc;
+    if (!ride) SALI_TRY(hipEventRecord(rec.exp_ready, s));
     const float2* flow[kMaxBatch];
     if (prev != nullptr) {
         rc = wait_unless_same(s, prev->stream, prev->exp_ready);
@@ -936,9 +946,9 @@ int sali_analyze_batch(sali_ctx* c, const uint8_t* const* d_rgb_frames, int32_t 
     }
     // pooling, then gate and tiers
     const TierLaunch tl = tier_launch(c, first_frame_id);
-    rc = enqueue_pool(c, bp, nullptr, nullptr, &tl, flow, s);
+    rc = enqueue_pool(c, bp, nullptr, nullptr, &tl, flow, ride ? rec.done : nullptr, s);
     if (rc != SALI_OK) return rc;
-    SALI_TRY(hipEventRecord(rec.done, s));
+    if (!ride) SALI_TRY(hipEventRecord(rec.done, s));
     for (int i = 0; i < kRing; ++i)
         if (c->ring[i].frame_id >= first_frame_id && c->ring[i].frame_id < first_frame_id + n_frames)
             c->ring[i].frame_id = -1;      // an older analysis under the same id

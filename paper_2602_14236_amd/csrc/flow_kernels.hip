@@ -1064,12 +1064,12 @@ hipError_t launch_pyramid(const PyrBatch& f, int n, const LevelGeom& g, hipStrea
     return hipSuccess;
 }
 
-hipError_t launch_polyexp(const PyrBatch& f, int n, LevelGeom g, FlowWeights fw, hipStream_t s) {
-    hipLaunchKernelGGL(k_polyexp, dim3(g.tile_start[g.levels], n), dim3(256), 0, s, f, g, fw);
+hipError_t launch_polyexp(const PyrBatch& f, int n, LevelGeom g, FlowWeights fw, hipEvent_t done_or_null, hipStream_t s) {
+    launch_recording(done_or_null, k_polyexp, dim3(g.tile_start[g.levels], n), dim3(256), s, f, g, fw);
     return hipGetLastError();
 }
 
-hipError_t launch_expand(const ExpandBatch& f, int n, LevelGeom g, FlowWeights fw, hipStream_t s) {
+hipError_t launch_expand(const ExpandBatch& f, int n, LevelGeom g, FlowWeights fw, hipEvent_t done_or_null, hipStream_t s) {
     // up to three levels, 16x16 tiles, one launch
     int tx[3] = {1, 1, 1}, start[4] = {0, 0, 0, 0};
     for (int l = 0; l < 3; ++l) {
@@ -1080,7 +1080,7 @@ hipError_t launch_expand(const ExpandBatch& f, int n, LevelGeom g, FlowWeights f
         }
         start[l + 1] = start[l] + tiles;
     }
-    hipLaunchKernelGGL(k_expand, dim3(start[3], n), dim3(256), 0, s, f, g, start[1], start[2], tx[0], tx[1], tx[2], fw);
+    launch_recording(done_or_null, k_expand, dim3(start[3], n), dim3(256), s, f, g, start[1], start[2], tx[0], tx[1], tx[2], fw);
     return hipGetLastError();
 }
 

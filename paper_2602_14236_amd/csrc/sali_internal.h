@@ -2,6 +2,7 @@
 // gfx950 only; wave size 64.
 #pragma once
 
+#include <hip/hip_ext.h>
 #include <hip/hip_runtime.h>
 #include <stddef.h>
 #include <stdint.h>
@@ -228,6 +229,14 @@ __device__ __forceinline__ uint32_t gray_of_quad(const uint32_t* w) {
 }
 #endif
 
+// A launch that records `done` (may be NULL) when it has run.  The event rides on the launch's own completion signal:
+// recorded by a call of its own it is a packet of its own on the stream, and the next kernel starts 5 us later.
+template <typename... Params, typename... Args>
+inline void launch_recording(hipEvent_t done, void (*kernel)(Params...), dim3 grid, dim3 block, hipStream_t s, Args... args) {
+    if (done != nullptr) hipExtLaunchKernelGGL(kernel, grid, block, 0, s, nullptr, done, 0, static_cast<Params>(args)...);
+    else hipLaunchKernelGGL(kernel, grid, block, 0, s, static_cast<Params>(args)...);
+}
+
 // ---- launchers (each returns hipGetLastError()) ---------------------------------------------
 // kv_kernels.hip
 hipError_t launch_tier(const float* d_scores, const sali_gate* d_gate_or_null, TierParams tp, int frame_id,
@@ -266,16 +275,17 @@ hipError_t launch_union(const PrepBatch& f, int n, int h, int w, hipStream_t s);
 // launch_motion: Eq. 5, per-patch motion of every frame of the batch from its flow (0 without flow).
 // launch_pool: Eq. 7 scores (none for frames marked in f.skip);
 // d_salmap_or_null applies to frame 0 (stand-alone call); with `tier` a second small launch evaluates
-// the gate and assigns tiers for the n frames in order
+// the gate and assigns tiers for the n frames in order, and records done_or_null
 hipError_t launch_motion(const PoolBatch& f, int n, int h, int w, hipStream_t s);
 hipError_t launch_pool(const PoolBatch& f, int n, int h, int w, uint8_t* d_salmap_or_null,
-                       const TierLaunch* tier_or_null, GateParams gp, uint32_t* d_done_counter, hipStream_t s);
+                       const TierLaunch* tier_or_null, GateParams gp, uint32_t* d_done_counter, hipEvent_t done_or_null, hipStream_t s);
 
 // flow_kernels.hip
 // gray image and all pyramid levels (g.levels >= 2) from f.rgb
 hipError_t launch_pyramid(const PyrBatch& f, int n, const LevelGeom& g, hipStream_t s);
-hipError_t launch_polyexp(const PyrBatch& f, int n, LevelGeom g, FlowWeights fw, hipStream_t s);
-hipError_t launch_expand(const ExpandBatch& f, int n, LevelGeom g, FlowWeights fw, hipStream_t s);
+// the launches that complete the expansions; done_or_null is recorded then
+hipError_t launch_polyexp(const PyrBatch& f, int n, LevelGeom g, FlowWeights fw, hipEvent_t done_or_null, hipStream_t s);
+hipError_t launch_expand(const ExpandBatch& f, int n, LevelGeom g, FlowWeights fw, hipEvent_t done_or_null, hipStream_t s);
 // one launch of at most `wanted` (>= 1) updates of a level, as many as suit its size; *done = how many it makes
 hipError_t launch_flow_updates(const FlowBatch& f, int n, int64_t level_off, int h, int w, int ch, int cw,
                                int prior_mode, int wanted, int* done, FlowWeights fw, hipStream_t s);

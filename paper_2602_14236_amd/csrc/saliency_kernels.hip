@@ -823,7 +823,7 @@ hipError_t launch_motion(const PoolBatch& f, int n, int h, int w, hipStream_t s)
 }
 
 hipError_t launch_pool(const PoolBatch& f, int n, int h, int w, uint8_t* d_salmap_or_null,
-                       const TierLaunch* tier_or_null, GateParams gp, uint32_t* d_done_counter, hipStream_t s) {
+                       const TierLaunch* tier_or_null, GateParams gp, uint32_t* d_done_counter, hipEvent_t done_or_null, hipStream_t s) {
     TierLaunch t = {};
     if (tier_or_null != nullptr) t = *tier_or_null;
     if ((long long)h * w <= 1024ll * kTokens) {
@@ -834,7 +834,7 @@ hipError_t launch_pool(const PoolBatch& f, int n, int h, int w, uint8_t* d_salma
     if (tier_or_null != nullptr) {
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
-        hipLaunchKernelGGL(k_pool_tail, dim3(n), dim3(kTierThreads), 0, s, f, gp.tau_t, gp.theta_r, t, d_done_counter);
+        launch_recording(done_or_null, k_pool_tail, dim3(n), dim3(kTierThreads), s, f, gp.tau_t, gp.theta_r, t, d_done_counter);
     }
     return hipGetLastError();
 }

@@ -401,3 +401,56 @@ def test_random_batch_schedules_equal_the_one_stream_path():
             assert torch.equal(pools[k][:, :used[k]], ref_pools[k][:, :used[k]]), f"pool {k}"
         ctx.close()
     ref.close()
+
+
+def test_captured_calls_on_several_streams_replay():
+    """Analyses on two image streams and the stores on a third, captured into one graph: the dependences between the
+    streams (a batch's flow on the expansions before it, a store on its analysis) must be edges of the graph.  Replayed with
+    eager passes in between; every replay leaves the rows and pools of the eager pass."""
+    from paper_2602_14236_amd import binding
+    wl = synth.WORKLOADS[5]
+    n = 6
+    v = synth.video(5, 32)
+    p = workload_params(wl, frames=n, n_layers=1, n_heads=2)
+    scale = synth.kv_channel_scale(wl, 1, 2)
+    rgbs = [torch.from_numpy(v.frame(t)).cuda() for t in range(n)]
+    kvs = [synth.kv_frame(wl, t, device="cuda", n_layers=1, n_heads=2, scale=scale) for t in range(n)]
+    ctx = binding.SaliContext(lib_config(p))
+    images, kv_stream, main = [torch.cuda.Stream(), torch.cuda.Stream()], torch.cuda.Stream(), torch.cuda.Stream()
+
+    def one_pass():
+        here = torch.cuda.current_stream()
+        ctx.reset()
+        for s in images + [kv_stream]:
+            s.wait_stream(here)
+        for b in range(2):
+            ctx.analyze_batch(rgbs[3 * b:3 * b + 3], 3 * b, images[b])
+        for b in range(2):
+            ctx.store_batch(kvs[3 * b:3 * b + 3], 3 * b, kv_stream)
+        for s in images + [kv_stream]:
+            here.wait_stream(s)
+
+    def left():
+        torch.cuda.synchronize()
+        rows = [r.as_tuple() for r in ctx.read_frame_table(0, n)]
+        return rows, {k: a.clone() for k, a in ctx.pool_views_flat().items()}
+
+    ctx.pools.zero_()
+    with torch.cuda.stream(main):
+        one_pass()
+    ref_rows, ref_pools = left()
+    assert sum(r[2] for r in ref_rows) > 1
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=main):
+        one_pass()
+    for replay in range(3):
+        ctx.pools.zero_()
+        torch.cuda.synchronize()
+        graph.replay()
+        rows, pools = left()
+        assert rows == ref_rows, f"replay {replay}"
+        assert all(torch.equal(pools[k], ref_pools[k]) for k in ref_pools), f"replay {replay}"
+        with torch.cuda.stream(main):
+            one_pass()
+        assert left()[0] == ref_rows
+    ctx.close()
