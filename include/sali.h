@@ -240,10 +240,12 @@ int sali_kv_decompress(sali_ctx* ctx, int32_t frame_id, void* d_kv_fp16_out,
  * was stored) -> gate; a redundant frame becomes a pointer row to the last stored frame: no
  * ranking, no tiers, no K/V read or written; otherwise saliency -> tiers -> storage as in
  * sali_kv_compress.  The first call after create/reset has no previous frame and always
- * stores.  No host synchronisation: the gate lives in device memory and later kernels
- * test it: the temporal filter runs first (gray, pyramid, expansion, flow, per-patch motion), and the
- * kernels of the spatial filter go by the reuse rule evaluated from the motions and leave at once for
- * a redundant frame, so such a frame costs its temporal filter and nothing else (Algorithm 1). */
+ * stores.  No host synchronisation: the gate lives in device memory and later kernels test it.  For
+ * larger batches the temporal filter runs first (gray, pyramid, expansion, flow, per-patch motion), and the kernels of
+ * the spatial filter go by the reuse rule evaluated from the motions and leave at once for a redundant
+ * frame, so such a frame costs its temporal filter and nothing else (Algorithm 1).  Small batches (up to 512 tiles of
+ * 32x32 pixels, 256 a frame) leave the GPU idle behind every launch: there the spatial filter runs next to the
+ * temporal filter, and what it finds for a redundant frame is not used. */
 int sali_step(sali_ctx* ctx, const uint8_t* d_rgb_t, const void* d_kv_t, int32_t frame_id,
               void* stream);
 

@@ -7,6 +7,7 @@
 #include <new>
 #include <string.h>
 
+#include "hysteresis.h"
 #include "sali_internal.h"
 #include "tier_body.h"
 
@@ -392,9 +393,40 @@ int enqueue_saliency(sali_ctx* c, const uint8_t* const* d_rgb, const BatchPlan& 
     return SALI_OK;
 }
 
-// gray image, pyramid and polynomial expansion of each frame, the last into its expansion slot; `done` (may be NULL) is
-// recorded with the last launch
-int enqueue_expansion(sali_ctx* c, const uint8_t* const* d_rgb, const BatchPlan& bp, hipEvent_t done, hipStream_t s) {
+// Does the spatial filter of a batch ride on the launches of its temporal filter, before the gate has spoken?  The two need
+// nothing of each other until then, and where a batch is a chain of launches that leave the chip idle the pre-pass next to
+// the expansions, the hysteresis next to the coarsest flow updates and the scores next to the following ones cost a
+// third of what they cost behind the flow (one 336x336 frame: 8 of 29 us; sali_step 680 -> 608 us for eight frames, of
+// which three are redundant).  Redundant frames get scores that nobody uses.  So it is done up to two tiles of the
+// pre-pass per compute unit in a batch, one in a frame; K/V kernels next to it or not, eight to sixteen frames:
+//   336x336 x 4: 3 redundant of 8 426 -> 410 us, none 438 -> 418; with 16 layers 760 -> 732, 992 -> 953
+//   640x360 x 2: 769 -> 755, none redundant 919 -> 861; 427x241 x 3: 447 -> 406; 270x480, none: 837 -> 680
+//   800x600 (475 tiles, not done): 3 redundant of 8 1173 -> 1209, none 1333 -> 1232
+bool saliency_rides(const sali_ctx* c, int n_frames) {
+    constexpr long long kComputeUnits = 256;
+    const long long tiles = (long long)((c->cfg.src_w + kTile - 1) / kTile) * ((c->cfg.src_h + kTile - 1) / kTile);
+    return tiles <= kComputeUnits && tiles * n_frames <= 2 * kComputeUnits;
+}
+
+PrepRide prep_ride(const sali_ctx* c, const PrepBatch& f, int n) {
+    const sali_config& cfg = c->cfg;
+    PrepRide r;
+    r.f = f;
+    r.lut = c->tb<uint32_t>(c->tl.lut);
+    r.h = cfg.src_h;
+    r.w = cfg.src_w;
+    r.tiles_x = (cfg.src_w + kTile - 1) / kTile;
+    r.tiles_y = (cfg.src_h + kTile - 1) / kTile;
+    r.blocks = r.tiles_x * r.tiles_y * n;
+    r.lo2 = cfg.canny_lo * cfg.canny_lo;
+    r.hi2 = cfg.canny_hi * cfg.canny_hi;
+    return r;
+}
+
+// gray image, pyramid and polynomial expansion of each frame, the last into its expansion slot; `ride` (may be
+// NULL) goes with the last launch, which records `done` (may be NULL)
+int enqueue_expansion(sali_ctx* c, const uint8_t* const* d_rgb, const BatchPlan& bp, const PrepRide* ride, hipEvent_t done,
+                      hipStream_t s) {
     const LevelGeom& g = c->geom;
     if (fused_expansion(c, bp.n)) {
         const int rc = enqueue_gray(c, d_rgb, bp, s);
@@ -406,7 +438,7 @@ int enqueue_expansion(sali_ctx* c, const uint8_t* const* d_rgb, const BatchPlan&
             f.A[i] = c->sc<float4>(c->sl.expA[bp.slot[i]]);
             f.b[i] = c->sc<float>(c->sl.expB[bp.slot[i]]);
         }
-        SALI_TRY(launch_expand(f, bp.n, g, c->fw, done, s));
+        SALI_TRY(launch_expand(f, bp.n, g, c->fw, ride, done, s));
         return SALI_OK;
     }
     PyrBatch f = {};
@@ -424,13 +456,15 @@ int enqueue_expansion(sali_ctx* c, const uint8_t* const* d_rgb, const BatchPlan&
     } else {
         SALI_TRY(launch_pyramid(f, bp.n, g, s));
     }
-    SALI_TRY(launch_polyexp(f, bp.n, g, c->fw, done, s));
+    SALI_TRY(launch_polyexp(f, bp.n, g, c->fw, ride, done, s));
     return SALI_OK;
 }
 
 // coarse-to-fine displacement estimation of every frame of the batch that has a predecessor;
-// flow[i] = the frame's result (NULL without predecessor)
-int enqueue_flow(sali_ctx* c, const BatchPlan& bp, const float2** flow, hipStream_t s) {
+// flow[i] = the frame's result (NULL without predecessor).  riders (may be NULL): pieces of the spatial filter that may ride on
+// the launches; *united_out, *scored_out say which did (untouched if there was no launch)
+int enqueue_flow(sali_ctx* c, const BatchPlan& bp, const float2** flow, const FlowRiders* riders, bool* united_out, bool* scored_out,
+                 hipStream_t s) {
     const LevelGeom& g = c->geom;
     FlowBatch f[2] = {};            // [which of the two flow buffers is read]
     int idx[kMaxBatch];
@@ -450,16 +484,29 @@ int enqueue_flow(sali_ctx* c, const BatchPlan& bp, const float2** flow, hipStrea
         idx[m++] = i;
     }
     if (m == 0) return SALI_OK;
+    // The riders' launches: hysteresis on the first, the scores on the first after it that can carry them.
+    const int iters = c->cfg.flow_iters;
+    int scores_level = -1;
+    bool united = false;
+    if (riders != nullptr && flow_launch_carries(FlowRider::hysteresis, *riders, m, g.h[g.levels - 1], g.w[g.levels - 1], iters)) {
+        united = true;
+        for (int l = g.levels - 2; l >= 0 && scores_level < 0; --l)
+            if (flow_launch_carries(FlowRider::scores, *riders, m, g.h[l], g.w[l], iters)) scores_level = l;
+    }
+    if (united_out != nullptr) *united_out = united;
+    if (scored_out != nullptr) *scored_out = scores_level >= 0;
     int cur = 0;            // buffer holding the latest estimate
     bool have = false;
     for (int l = g.levels - 1; l >= 0; --l) {
-        for (int it = 0; it < c->cfg.flow_iters;) {
+        for (int it = 0; it < iters;) {
             int mode, done = 1;
             int ch = 0, cw = 0;
             if (it > 0) mode = 2;
             else if (!have) mode = 0;
             else { mode = 1; ch = g.h[l + 1]; cw = g.w[l + 1]; }
-            SALI_TRY(launch_flow_updates(f[cur], m, g.off[l], g.h[l], g.w[l], ch, cw, mode, c->cfg.flow_iters - it, &done, c->fw, s));
+            const FlowRider rider = it > 0 ? FlowRider::none : (!have && united) ? FlowRider::hysteresis
+                                    : l == scores_level ? FlowRider::scores : FlowRider::none;
+            SALI_TRY(launch_flow_updates(f[cur], m, g.off[l], g.h[l], g.w[l], ch, cw, mode, iters - it, &done, c->fw, rider, riders, s));
             it += done;
             cur ^= 1;
             have = true;
@@ -496,15 +543,19 @@ int enqueue_motion(sali_ctx* c, const BatchPlan& bp, const float2* const* flow, 
     return SALI_OK;
 }
 
-// Pooling of the batch's saliency pre-pass (Eq. 7).  With `tier` (the chained step) a second launch
-// evaluates the gates and writes the frame-table rows with tiers and compaction indices, in frame
-// order; redundant frames get no scores; `done` (may be NULL) is recorded with it.  d_scores_or_null / d_salmap redirect the outputs of a
-// stand-alone single-frame call.
-int enqueue_pool(sali_ctx* c, const BatchPlan& bp, float* d_scores_or_null, uint8_t* d_salmap,
-                 const TierLaunch* tier, const float2* const* flow, hipEvent_t done, hipStream_t s) {
-    const PoolBatch f = pool_batch(c, bp, d_scores_or_null, flow);
-    SALI_TRY(launch_pool(f, bp.n, c->cfg.src_h, c->cfg.src_w, d_salmap, tier, gate_params(c),
-                         &c->lane_ptrs(bp.lane[0]).counters->batch_done, done, s));
+// Pooling of the batch's saliency pre-pass (Eq. 7); frames that it found redundant get no scores.  d_scores_or_null /
+// d_salmap redirect the outputs of a stand-alone single-frame call.
+int enqueue_scores(sali_ctx* c, const BatchPlan& bp, float* d_scores_or_null, uint8_t* d_salmap, hipStream_t s) {
+    const PoolBatch f = pool_batch(c, bp, d_scores_or_null, nullptr);
+    SALI_TRY(launch_scores(f, bp.n, c->cfg.src_h, c->cfg.src_w, d_salmap, s));
+    return SALI_OK;
+}
+
+// The gates, and the frame-table rows with tiers and compaction indices, in frame order; `done` (may be NULL) is recorded
+// with it.
+int enqueue_tail(sali_ctx* c, const BatchPlan& bp, const TierLaunch& tier, const float2* const* flow, hipEvent_t done, hipStream_t s) {
+    const PoolBatch f = pool_batch(c, bp, nullptr, flow);
+    SALI_TRY(launch_tail(f, bp.n, tier, gate_params(c), &c->lane_ptrs(bp.lane[0]).counters->batch_done, done, s));
     return SALI_OK;
 }
 
@@ -569,10 +620,10 @@ int wait_unless_same(hipStream_t s, hipStream_t recorded_on, hipEvent_t ev) {
     return SALI_OK;
 }
 
-// May the events of an analysis ride on its launches?  Not while the stream is being captured: the dependence of another
+// May the events of an analysis be recorded by its launches?  Not while the stream is being captured: the dependence of another
 // stream's work on an event that a launch records does not become an edge of the graph (one recorded by a call does).
 // Where they may, sali_step frame by frame at 336x336 is 3.5 % faster (two packets of 3.4 us a frame).
-bool events_may_ride(hipStream_t s) {
+bool events_may_attach(hipStream_t s) {
     hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
     return hipStreamIsCapturing(s, &status) == hipSuccess && status == hipStreamCaptureStatusNone;
 }
@@ -783,10 +834,10 @@ int sali_flow_score(sali_ctx* c, const uint8_t* d_prev_rgb, const uint8_t* d_cur
     pair.prev_slot[0] = -1;
     pair.prev_slot[1] = kStepSlots;
     const uint8_t* const d_rgb[2] = {d_prev_rgb, d_cur_rgb};
-    int rc = enqueue_expansion(c, d_rgb, pair, nullptr, s);
+    int rc = enqueue_expansion(c, d_rgb, pair, nullptr, nullptr, s);
     if (rc != SALI_OK) return rc;
     const float2* flow[kMaxBatch];
-    rc = enqueue_flow(c, pair, flow, s);
+    rc = enqueue_flow(c, pair, flow, nullptr, nullptr, nullptr, s);
     if (rc != SALI_OK) return rc;
     SALI_TRY(launch_patch_gate(flow[1], c->cfg.src_h, c->cfg.src_w, c->cfg.tau_t, c->cfg.theta_r, d_patch_motion576,
                                d_gate_out, d_flow_uv_or_null, s));
@@ -801,7 +852,7 @@ int sali_saliency_pool(sali_ctx* c, const uint8_t* d_rgb, uint8_t* d_salmap_or_n
     bp.n = 1;
     bp.parity[0] = c->lane_uses[0]++ & 1u;
     int rc = enqueue_saliency(c, &d_rgb, bp, nullptr, s);
-    if (rc == SALI_OK) rc = enqueue_pool(c, bp, d_scores576, d_salmap_or_null, nullptr, nullptr, nullptr, s);
+    if (rc == SALI_OK) rc = enqueue_scores(c, bp, d_scores576, d_salmap_or_null, s);
     return rc;
 }
 
@@ -925,32 +976,52 @@ int sali_analyze_batch(sali_ctx* c, const uint8_t* const* d_rgb_frames, int32_t 
     }
     // the batch's events live in the ring entry of its last frame
     AnalysisRecord& rec = c->ring[n_last % kRing];
-    const bool ride = events_may_ride(s);
-    // the temporal filter first: gray, pyramid + expansion, flow, per-patch motion
-    rc = enqueue_expansion(c, d_rgb_frames, bp, ride ? rec.exp_ready : nullptr, s);
+    const bool attach = events_may_attach(s);
+    // the temporal filter first: gray, pyramid + expansion, flow, per-patch motion.  Where the spatial filter rides along its
+    // frames are all taken as not redundant (no motions yet).
+    const bool rides = saliency_rides(c, n_frames);
+    PrepBatch prep = {};
+    PoolBatch pool = {};
+    PrepRide ride;
+    FlowRiders riders = {};
+    if (rides) {
+        prep = prep_batch(c, d_rgb_frames, bp, true, nullptr);
+        pool = pool_batch(c, bp, nullptr, nullptr);
+        ride = prep_ride(c, prep, n_frames);
+        riders = {&prep, &pool, n_frames, c->cfg.src_h, c->cfg.src_w};
+    }
+    rc = enqueue_expansion(c, d_rgb_frames, bp, rides ? &ride : nullptr, attach ? rec.exp_ready : nullptr, s);
     if (rc != SALI_OK) return rc;
-    if (!ride) SALI_TRY(hipEventRecord(rec.exp_ready, s));
+    if (!attach) SALI_TRY(hipEventRecord(rec.exp_ready, s));
     const float2* flow[kMaxBatch];
     if (prev != nullptr) {
         rc = wait_unless_same(s, prev->stream, prev->exp_ready);
         if (rc != SALI_OK) return rc;
     }
-    rc = enqueue_flow(c, bp, flow, s);
+    bool united = false, scored = false;
+    rc = enqueue_flow(c, bp, flow, rides ? &riders : nullptr, &united, &scored, s);
     if (rc == SALI_OK) rc = enqueue_motion(c, bp, flow, s);
-    // then the spatial filter, for the frames the reuse rule does not find redundant (Algorithm 1: a
-    // redundant frame bypasses it): every kernel from here on evaluates the rule from the motions
-    if (rc == SALI_OK) rc = enqueue_saliency(c, d_rgb_frames, bp, flow, s);
     if (rc != SALI_OK) return rc;
+    if (rides) {
+        // what found no launch to ride on
+        if (!united) SALI_TRY(launch_union(prep, n_frames, c->cfg.src_h, c->cfg.src_w, s));
+        if (!scored) SALI_TRY(launch_scores(pool, n_frames, c->cfg.src_h, c->cfg.src_w, nullptr, s));
+    } else {
+        // then the spatial filter, for the frames the reuse rule does not find redundant (Algorithm 1: a
+        // redundant frame bypasses it): every kernel from here on evaluates the rule from the motions
+        rc = enqueue_saliency(c, d_rgb_frames, bp, flow, s);
+        if (rc == SALI_OK) rc = enqueue_scores(c, bp, nullptr, nullptr, s);
+        if (rc != SALI_OK) return rc;
+    }
     if (prev != nullptr) {
         // tiers are handed out in frame order: the cursors must have seen the previous frame
         rc = wait_unless_same(s, prev->stream, prev->done);
         if (rc != SALI_OK) return rc;
     }
-    // pooling, then gate and tiers
-    const TierLaunch tl = tier_launch(c, first_frame_id);
-    rc = enqueue_pool(c, bp, nullptr, nullptr, &tl, flow, ride ? rec.done : nullptr, s);
+    // gate and tiers
+    rc = enqueue_tail(c, bp, tier_launch(c, first_frame_id), flow, attach ? rec.done : nullptr, s);
     if (rc != SALI_OK) return rc;
-    if (!ride) SALI_TRY(hipEventRecord(rec.done, s));
+    if (!attach) SALI_TRY(hipEventRecord(rec.done, s));
     for (int i = 0; i < kRing; ++i)
         if (c->ring[i].frame_id >= first_frame_id && c->ring[i].frame_id < first_frame_id + n_frames)
             c->ring[i].frame_id = -1;      // an older analysis under the same id

@@ -26,6 +26,7 @@
 #include <type_traits>
 
 #include "sali_internal.h"
+#include "saliency_body.h"
 
 namespace sali {
 
@@ -34,7 +35,6 @@ namespace {
 constexpr int kT = 32;                       // tile side of the expansion kernel
 constexpr int kPR = kT + 2 * kPolyN;         // 38
 
-__device__ __forceinline__ int clampi(int v, int lo, int hi) { return v < lo ? lo : (v > hi ? hi : v); }
 __device__ __forceinline__ float clampf(float v, float lo, float hi) { return fminf(fmaxf(v, lo), hi); }
 
 // Element i of an array whose base is uniform over the wave: base + 32-bit byte offset (an image level
@@ -178,21 +178,66 @@ __global__ __launch_bounds__(256) void k_pyr_pair(PyrBatch f, LevelGeom g, int l
 // With separable symmetric weights (sum 1, second moment m2, fourth moment m4) the normal
 // equations decouple:  b = (sx, sy) / m2,  A_xx = (sxx - m2 s0) / (m4 - m2^2),  A_yy likewise,
 // A_xy = sxy / (2 m2^2), where s* are the weighted correlations of f with 1, x, y, x^2, y^2, xy.
-__global__ __launch_bounds__(256) void k_polyexp(PyrBatch f, LevelGeom g, FlowWeights fw) {
-    // blockIdx.y = frame of the batch
-    const uint8_t* __restrict__ y8 = f.y8[blockIdx.y];
-    const float* __restrict__ pyr = f.pyr[blockIdx.y];
-    float4* __restrict__ A_out = f.A[blockIdx.y];
-    float* __restrict__ b_out = f.b[blockIdx.y];
+//
+// The launch that completes the expansions may carry the saliency pre-pass of its frames (Ride = PrepRide): blocks
+// 0 .. ride.blocks - 1, so that these, the longest, start first.  Neither needs anything of the other.
+namespace {
+struct PolyexpShared {
+    float f[kPR][kPR], v[3][kT][kPR];
+};
+// LDS of a block that is either kind
+template <typename Own, typename Ride>
+struct WithPrep {
+    union {
+        Own own;
+        PrepShared prep;
+    };
+};
+template <typename Own>
+struct WithPrep<Own, NoRide> {
+    Own own;
+};
+// Is this block one of the riders?  Then it does its tile; the others get their number among the launch's own blocks (per_frame
+// a frame, frame by frame).  Without riders the grid is (per_frame, frames).
+template <typename Shared>
+__device__ __forceinline__ bool ride_prep(Shared& sh, const PrepRide& ride, int& block) {
+    block = (int)blockIdx.x - ride.blocks;
+    if (block >= 0) return false;
+    const int tiles = ride.tiles_x * ride.tiles_y, frame = (int)blockIdx.x / tiles, t = (int)blockIdx.x - frame * tiles;
+    prep_tile<false>(sh.prep, ride.f, t % ride.tiles_x, t / ride.tiles_x, frame, ride.h, ride.w, GateParams{}, ride.lut, ride.lo2, ride.hi2);
+    return true;
+}
+template <typename Shared>
+__device__ __forceinline__ bool ride_prep(Shared&, const NoRide&, int& block) {
+    block = (int)blockIdx.x + (int)gridDim.x * (int)blockIdx.y;
+    return false;
+}
+}  // namespace
+
+template <typename Ride>
+__global__ __launch_bounds__(256) void k_polyexp(PyrBatch f, LevelGeom g, FlowWeights fw, Ride ride) {
+    __shared__ WithPrep<PolyexpShared, Ride> sh;
+    int block;
+    if (ride_prep(sh, ride, block)) return;
+    int frame = (int)blockIdx.y, tile = (int)blockIdx.x;
+    if constexpr (!std::is_same_v<Ride, NoRide>) {
+        const int tiles = g.tile_start[g.levels];
+        frame = block / tiles;
+        tile = block - frame * tiles;
+    }
+    const uint8_t* __restrict__ y8 = f.y8[frame];
+    const float* __restrict__ pyr = f.pyr[frame];
+    float4* __restrict__ A_out = f.A[frame];
+    float* __restrict__ b_out = f.b[frame];
     // unpadded rows: the passes that write and read these arrays column-wise address them linearly
     // in the thread index (with a pad of one float, a group of 32 lanes that straddles two rows has
     // two lanes on one bank: 23 % of the kernel's LDS cycles were bank conflicts)
-    __shared__ float s_f[kPR][kPR];
-    __shared__ float s_v[3][kT][kPR];
+    float (&s_f)[kPR][kPR] = sh.own.f;
+    float (&s_v)[3][kT][kPR] = sh.own.v;
 
     int lvl = 0;
-    while (lvl + 1 < g.levels && (int)blockIdx.x >= g.tile_start[lvl + 1]) ++lvl;
-    const int t = blockIdx.x - g.tile_start[lvl];
+    while (lvl + 1 < g.levels && tile >= g.tile_start[lvl + 1]) ++lvl;
+    const int t = tile - g.tile_start[lvl];
     const int h = g.h[lvl], w = g.w[lvl];
     const int x0 = (t % g.tiles_x[lvl]) * kT, y0 = (t / g.tiles_x[lvl]) * kT;
     const float* src = pyr + g.off[lvl];
@@ -386,18 +431,28 @@ __device__ __forceinline__ void pyr_level_from_bytes(const uint8_t* src, int o_s
     }
 }
 
+struct ExpandShared {
+    uint32_t qb[kEQ * (kEQB / 4)];      // gray patch of a level-2 block, bytes
+    float p[kEP * kEPS];                // level-1 patch of a level-2 block; gray patch of a level-1 block
+    // unpadded rows: both the pass that writes these arrays and the pass that reads them then see
+    // addresses linear in the thread index (the horizontal pass pairs rows eight apart, see below)
+    float f[kER][kER];
+};
+
 }  // namespace
 
-__global__ __launch_bounds__(256) void k_expand(ExpandBatch f, LevelGeom g, int t1, int t2, int tx0, int tx1, int tx2,
-                                                FlowWeights fw) {
+// t1, t2, t3: a frame's tiles of level 0, of levels 0 and 1, of all levels
+template <typename Ride>
+__global__ __launch_bounds__(256) void k_expand(ExpandBatch f, LevelGeom g, int n_frames, int t1, int t2, int t3, int tx0, int tx1,
+                                                int tx2, FlowWeights fw, Ride ride) {
+    __shared__ WithPrep<ExpandShared, Ride> sh;
+    int idx;
+    if (ride_prep(sh, ride, idx)) return;
     // Work order.  A level-2 tile costs about ten times a level-0 tile (97 x 97 gray pixels, two pyramid
     // stages) and there are sixteen level-0 tiles for each: with the tiles of a frame in level order the
     // heavy ones start last and the launch ends with a few of them on an idle chip (22 us per four
     // 336x336 frames, 10 of them that tail).  So the linear block id is cut into runs, heaviest first,
     // each run over all frames of the batch: level-2 tiles, level-1 tiles, level-0 tiles.
-    const int n_frames = (int)gridDim.y;
-    const int t3 = (int)gridDim.x;                  // tiles of a frame over all levels
-    int idx = (int)blockIdx.x + (int)gridDim.x * (int)blockIdx.y;
     int lvl, t, frame;
     if (idx < n_frames * (t3 - t2)) {
         lvl = 2;
@@ -416,11 +471,9 @@ __global__ __launch_bounds__(256) void k_expand(ExpandBatch f, LevelGeom g, int 
     const uint8_t* __restrict__ y8 = f.y8[frame];
     float4* __restrict__ A_out = f.A[frame];
     float* __restrict__ b_out = f.b[frame];
-    __shared__ uint32_t s_qb[kEQ * (kEQB / 4)];     // gray patch of a level-2 block, bytes
-    __shared__ float s_p[kEP * kEPS];               // level-1 patch of a level-2 block; gray patch of a level-1 block
-    // unpadded rows: both the pass that writes these arrays and the pass that reads them then see
-    // addresses linear in the thread index (the horizontal pass pairs rows eight apart, see below)
-    __shared__ float s_f[kER][kER];
+    uint32_t (&s_qb)[kEQ * (kEQB / 4)] = sh.own.qb;
+    float (&s_p)[kEP * kEPS] = sh.own.p;
+    float (&s_f)[kER][kER] = sh.own.f;
     // the vertical moments reuse the 47-wide patch's memory: every path has a barrier between its last
     // read of s_p and the pass that writes them
     float (*s_v)[kET][kER] = reinterpret_cast<float (*)[kET][kER]>(s_p);
@@ -968,10 +1021,34 @@ __device__ __forceinline__ void fused_update(FusedTile<TX, TY>& sh, float2* prio
     if constexpr (kLeft > 0) __syncthreads();
 }
 
-template <int TX, int TY>
+// Riders of a launch, its blocks after the flow's: a border pixel per thread, or a patch per wave.  At 336x336 the flow
+// leaves room for them: its own blocks are at most one per compute unit.
+namespace {
+__device__ __forceinline__ void ride_flow(const UnionRide& r, int block) {
+    const int b = block / r.blocks_per_frame;
+    union_item(r.f, b, r.h, r.w, (block - b * r.blocks_per_frame) * kFusedThreads + (int)threadIdx.x, r.n_items);
+}
+__device__ __forceinline__ void ride_flow(const ScoreRide& r, int block) {
+    const int b = block / r.blocks_per_frame;
+    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    score_by_wave(r.f, b, (block - b * r.blocks_per_frame) * (kFusedThreads / 64) + wave, r.h, r.w, nullptr);
+}
+}  // namespace
+
+// gx x gy tiles of n frames: the grid, or the first blocks of a one-dimensional grid that ends with the riders
+template <int TX, int TY, typename Ride>
 __global__ __launch_bounds__(kFusedThreads) void k_flow_fused(FlowBatch f, long long level_off, int h, int w, int ch, int cw,
-                                                              int prior_mode, FlowWeights fw) {
-    const BlockId blk = xcd_block_id();
+                                                              int prior_mode, FlowWeights fw, int gx, int gy, int n, Ride ride) {
+    BlockId blk;
+    if constexpr (std::is_same_v<Ride, NoRide>) {
+        blk = xcd_block_id();
+    } else {
+        if ((int)blockIdx.x >= gx * gy * n) {
+            ride_flow(ride, (int)blockIdx.x - gx * gy * n);
+            return;
+        }
+        blk = xcd_block_id((int)blockIdx.x, gx, gy, n);
+    }
     const float4* __restrict__ A1 = f.A1[blk.z] + level_off;
     const float* __restrict__ b1 = f.b1[blk.z] + level_off;
     const float4* __restrict__ A2 = f.A2[blk.z] + level_off;
@@ -1064,12 +1141,18 @@ hipError_t launch_pyramid(const PyrBatch& f, int n, const LevelGeom& g, hipStrea
     return hipSuccess;
 }
 
-hipError_t launch_polyexp(const PyrBatch& f, int n, LevelGeom g, FlowWeights fw, hipEvent_t done_or_null, hipStream_t s) {
-    launch_recording(done_or_null, k_polyexp, dim3(g.tile_start[g.levels], n), dim3(256), s, f, g, fw);
+hipError_t launch_polyexp(const PyrBatch& f, int n, LevelGeom g, FlowWeights fw, const PrepRide* ride_or_null, hipEvent_t done_or_null,
+                          hipStream_t s) {
+    const int own = g.tile_start[g.levels] * n;
+    if (ride_or_null != nullptr)
+        launch_recording(done_or_null, k_polyexp<PrepRide>, dim3(ride_or_null->blocks + own), dim3(256), s, f, g, fw, *ride_or_null);
+    else
+        launch_recording(done_or_null, k_polyexp<NoRide>, dim3(g.tile_start[g.levels], n), dim3(256), s, f, g, fw, NoRide{});
     return hipGetLastError();
 }
 
-hipError_t launch_expand(const ExpandBatch& f, int n, LevelGeom g, FlowWeights fw, hipEvent_t done_or_null, hipStream_t s) {
+hipError_t launch_expand(const ExpandBatch& f, int n, LevelGeom g, FlowWeights fw, const PrepRide* ride_or_null, hipEvent_t done_or_null,
+                         hipStream_t s) {
     // up to three levels, 16x16 tiles, one launch
     int tx[3] = {1, 1, 1}, start[4] = {0, 0, 0, 0};
     for (int l = 0; l < 3; ++l) {
@@ -1080,30 +1163,78 @@ hipError_t launch_expand(const ExpandBatch& f, int n, LevelGeom g, FlowWeights f
         }
         start[l + 1] = start[l] + tiles;
     }
-    launch_recording(done_or_null, k_expand, dim3(start[3], n), dim3(256), s, f, g, start[1], start[2], tx[0], tx[1], tx[2], fw);
+    const int own = start[3] * n;
+    if (ride_or_null != nullptr)
+        launch_recording(done_or_null, k_expand<PrepRide>, dim3(ride_or_null->blocks + own), dim3(256), s, f, g, n, start[1], start[2],
+                         start[3], tx[0], tx[1], tx[2], fw, *ride_or_null);
+    else
+        launch_recording(done_or_null, k_expand<NoRide>, dim3(start[3], n), dim3(256), s, f, g, n, start[1], start[2], start[3], tx[0], tx[1],
+                         tx[2], fw, NoRide{});
     return hipGetLastError();
 }
 
-hipError_t launch_flow_updates(const FlowBatch& f, int n, int64_t level_off, int h, int w, int ch, int cw,
-                               int prior_mode, int wanted, int* done, FlowWeights fw, hipStream_t s) {
-    // three updates in one launch where the blocks of some tile fit one per compute unit, the smallest such tile, also
-    // for batches: of 100 clips with the image side next to K/V kernels three, of two frames a call, are 3 to 5 %
-    // slower than with single frames fused only, small frames up to 26 % faster, the median 1 % faster
-    constexpr int kComputeUnits = 256;
-    auto tiles = [&](int tx, int ty) { return (long long)((w + tx - 1) / tx) * ((h + ty - 1) / ty) * n; };
-#define SALI_FUSED_LAUNCH(TX, TY)                                                                                       \
-    do {                                                                                                                \
-        hipLaunchKernelGGL((k_flow_fused<TX, TY>), dim3((w + TX - 1) / TX, (h + TY - 1) / TY, n), dim3(kFusedThreads), 0, \
-                           s, f, (long long)level_off, h, w, ch, cw, prior_mode, fw);                                   \
-        *done = kFusedUpdates;                                                                                          \
-        return hipGetLastError();                                                                                       \
-    } while (0)
-    if (wanted >= kFusedUpdates) {
-        if (tiles(16, 8) <= kComputeUnits) SALI_FUSED_LAUNCH(16, 8);
-        if (tiles(16, 16) <= kComputeUnits) SALI_FUSED_LAUNCH(16, 16);
-        if (tiles(32, 16) <= kComputeUnits) SALI_FUSED_LAUNCH(32, 16);
+namespace {
+
+constexpr int kComputeUnits = 256;
+
+long long tiles_of(int tx, int ty, int n, int h, int w) { return (long long)((w + tx - 1) / tx) * ((h + ty - 1) / ty) * n; }
+
+// Tile of the launch that makes three updates of a level at once: the smallest whose blocks fit one per compute unit.
+// Also for batches: of 100 clips with the image side next to K/V kernels three, of two frames a call, are 3 to 5 %
+// slower than with single frames fused only, small frames up to 26 % faster, the median 1 % faster.
+enum class Fused { no, t16x8, t16x16, t32x16 };
+Fused fused_tile(int n, int h, int w, int wanted) {
+    if (wanted < kFusedUpdates) return Fused::no;
+    if (tiles_of(16, 8, n, h, w) <= kComputeUnits) return Fused::t16x8;
+    if (tiles_of(16, 16, n, h, w) <= kComputeUnits) return Fused::t16x16;
+    return tiles_of(32, 16, n, h, w) <= kComputeUnits ? Fused::t32x16 : Fused::no;
+}
+
+// blocks that a piece of the spatial filter takes per frame as a rider
+int rider_blocks(FlowRider rider, const FlowRiders& r) {
+    return rider == FlowRider::hysteresis ? (border_items(r.h, r.w) + kFusedThreads - 1) / kFusedThreads : kTokens / (kFusedThreads / 64);
+}
+
+template <int TX, int TY>
+hipError_t launch_fused(const FlowBatch& f, int n, int64_t level_off, int h, int w, int ch, int cw, int prior_mode, FlowWeights fw,
+                        FlowRider rider, const FlowRiders* r, hipStream_t s) {
+    const int gx = (w + TX - 1) / TX, gy = (h + TY - 1) / TY, own = gx * gy * n;
+    auto go = [&](const auto& ride, dim3 grid) {
+        hipLaunchKernelGGL((k_flow_fused<TX, TY, std::decay_t<decltype(ride)>>), grid, dim3(kFusedThreads), 0, s, f,
+                           (long long)level_off, h, w, ch, cw, prior_mode, fw, gx, gy, n, ride);
+        return hipGetLastError();
+    };
+    if (rider == FlowRider::none) return go(NoRide{}, dim3(gx, gy, n));
+    const int per = rider_blocks(rider, *r), blocks = per * r->n;
+    if (rider == FlowRider::hysteresis) return go(UnionRide{*r->prep, r->h, r->w, border_items(r->h, r->w), per, blocks}, dim3(own + blocks));
+    return go(ScoreRide{*r->pool, r->h, r->w, per, blocks}, dim3(own + blocks));
+}
+
+}  // namespace
+
+// A fused launch carries a piece if the compute units that its own blocks (one each, by registers or LDS) leave take the
+// riders in two rounds: a rider takes 3 to 5 us, a flow block 10 and more.
+bool flow_launch_carries(FlowRider rider, const FlowRiders& riders, int n, int h, int w, int wanted) {
+    long long own = 0;
+    switch (fused_tile(n, h, w, wanted)) {
+        case Fused::no: return false;
+        case Fused::t16x8: own = tiles_of(16, 8, n, h, w); break;
+        case Fused::t16x16: own = tiles_of(16, 16, n, h, w); break;
+        case Fused::t32x16: own = tiles_of(32, 16, n, h, w); break;
     }
-#undef SALI_FUSED_LAUNCH
+    return (long long)rider_blocks(rider, riders) * riders.n <= 2 * (kComputeUnits - own);
+}
+
+hipError_t launch_flow_updates(const FlowBatch& f, int n, int64_t level_off, int h, int w, int ch, int cw,
+                               int prior_mode, int wanted, int* done, FlowWeights fw, FlowRider rider, const FlowRiders* riders,
+                               hipStream_t s) {
+    *done = kFusedUpdates;
+    switch (fused_tile(n, h, w, wanted)) {
+        case Fused::no: break;
+        case Fused::t16x8: return launch_fused<16, 8>(f, n, level_off, h, w, ch, cw, prior_mode, fw, rider, riders, s);
+        case Fused::t16x16: return launch_fused<16, 16>(f, n, level_off, h, w, ch, cw, prior_mode, fw, rider, riders, s);
+        case Fused::t32x16: return launch_fused<32, 16>(f, n, level_off, h, w, ch, cw, prior_mode, fw, rider, riders, s);
+    }
     *done = 1;
 #define SALI_FLOW_LAUNCH(KERNEL, TX, TY, NT)                                                                      \
     hipLaunchKernelGGL(KERNEL, dim3((w + TX - 1) / TX, (h + TY - 1) / TY, n), dim3(NT), 0, s, f, (long long)level_off, h, \
@@ -1115,7 +1246,7 @@ hipError_t launch_flow_updates(const FlowBatch& f, int n, int64_t level_off, int
     //   32x16 tiles   6.5   8.4  10.1  11.9                2.1 cells
     //   16x16 tiles   5.8   6.8   7.9   9.0  10.2          2.6 cells, the shortest block
     // e.g. 640x360 7.8 / 8.5 / 9.1, two frames of 480x270 10.2 / 8.6 / 9.2, 168x168 x 8 frames 9.7 / 9.6 / 8.8.
-    auto rounds = [&](int tx, int ty) { return (tiles(tx, ty) + kComputeUnits - 1) / kComputeUnits; };
+    auto rounds = [&](int tx, int ty) { return (tiles_of(tx, ty, n, h, w) + kComputeUnits - 1) / kComputeUnits; };
     const long long cost32 = 93 + 60 * rounds(kTileX, 32), cost16 = 95 + 36 * rounds(kTileX, 16),
                     cost_small = 94 + 22 * rounds(kSmallTile, kSmallTile);             // twentieths of a us
     if (cost_small <= cost16 && cost_small <= cost32) SALI_FLOW_LAUNCH(k_flow_small, kSmallTile, kSmallTile, kSmallThreads);

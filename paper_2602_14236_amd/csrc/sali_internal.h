@@ -176,6 +176,29 @@ struct PoolBatch {
     struct TierCounts* tcounts[kMaxBatch];        // hand-over from the frame's ranking to the row writer
 };
 
+// Work of the spatial filter that rides on launches of the temporal filter: extra blocks of theirs.
+struct NoRide {};
+struct PrepRide {                                 // the pre-pass, on the launch that makes the expansions
+    PrepBatch f;
+    const uint32_t* lut;
+    int32_t h, w, tiles_x, tiles_y, blocks, lo2, hi2;
+};
+struct UnionRide {                                // hysteresis across tiles, on the first flow update
+    PrepBatch f;
+    int32_t h, w, n_items, blocks_per_frame, blocks;
+};
+struct ScoreRide {                                // patch scores, on the update after it
+    PoolBatch f;
+    int32_t h, w, blocks_per_frame, blocks;
+};
+// a piece of the spatial filter that a flow launch is asked to carry
+enum class FlowRider { none, hysteresis, scores };
+struct FlowRiders {
+    const PrepBatch* prep;
+    const PoolBatch* pool;
+    int n, h, w;                                  // frames, their size
+};
+
 struct KvBatch {
     void* kv[kMaxBatch];
 };
@@ -198,11 +221,9 @@ struct BlockId {
     int x, y, z;
 };
 #ifdef __HIPCC__
-__device__ __forceinline__ BlockId xcd_block_id() {
+__device__ __forceinline__ BlockId xcd_block_id(int linear, int gx, int gy, int gz) {
     constexpr int kXcds = 8;
-    const int gx = (int)gridDim.x, gy = (int)gridDim.y;
-    const int total = gx * gy * (int)gridDim.z;
-    const int linear = (int)blockIdx.x + gx * ((int)blockIdx.y + gy * (int)blockIdx.z);
+    const int total = gx * gy * gz;
     const int q = total / kXcds, r = total % kXcds;
     const int xcd = linear % kXcds, slot = linear / kXcds;
     const int logical = xcd * q + (xcd < r ? xcd : r) + slot;      // XCDs 0..r-1 hold q + 1 blocks
@@ -213,9 +234,15 @@ __device__ __forceinline__ BlockId xcd_block_id() {
     b.x = rem - b.y * gx;
     return b;
 }
+__device__ __forceinline__ BlockId xcd_block_id() {
+    const int gx = (int)gridDim.x, gy = (int)gridDim.y;
+    return xcd_block_id((int)blockIdx.x + gx * ((int)blockIdx.y + gy * (int)blockIdx.z), gx, gy, (int)gridDim.z);
+}
 #endif
 
 #ifdef __HIPCC__
+__device__ __forceinline__ int clampi(int v, int lo, int hi) { return v < lo ? lo : (v > hi ? hi : v); }
+
 // Y8 of one pixel, and of four pixels in three words (bytes RGBR GBRG BRGB)
 __device__ __forceinline__ uint32_t gray_of(uint32_t r, uint32_t g, uint32_t b) {
     return (77u * r + 150u * g + 29u * b + 128u) >> 8;
@@ -273,22 +300,27 @@ hipError_t launch_prep(const PrepBatch& f, int n, int h, int w, GateParams gp, c
                        int lo2, int hi2, hipStream_t s);
 hipError_t launch_union(const PrepBatch& f, int n, int h, int w, hipStream_t s);
 // launch_motion: Eq. 5, per-patch motion of every frame of the batch from its flow (0 without flow).
-// launch_pool: Eq. 7 scores (none for frames marked in f.skip);
-// d_salmap_or_null applies to frame 0 (stand-alone call); with `tier` a second small launch evaluates
-// the gate and assigns tiers for the n frames in order, and records done_or_null
+// launch_scores: Eq. 7 scores (none for frames marked in f.skip); d_salmap_or_null applies to frame 0 (stand-alone call).
+// launch_tail: evaluates the gate and assigns tiers for the n frames in order, and records done_or_null.
 hipError_t launch_motion(const PoolBatch& f, int n, int h, int w, hipStream_t s);
-hipError_t launch_pool(const PoolBatch& f, int n, int h, int w, uint8_t* d_salmap_or_null,
-                       const TierLaunch* tier_or_null, GateParams gp, uint32_t* d_done_counter, hipEvent_t done_or_null, hipStream_t s);
+hipError_t launch_scores(const PoolBatch& f, int n, int h, int w, uint8_t* d_salmap_or_null, hipStream_t s);
+hipError_t launch_tail(const PoolBatch& f, int n, const TierLaunch& tier, GateParams gp, uint32_t* d_done_counter,
+                       hipEvent_t done_or_null, hipStream_t s);
 
 // flow_kernels.hip
 // gray image and all pyramid levels (g.levels >= 2) from f.rgb
 hipError_t launch_pyramid(const PyrBatch& f, int n, const LevelGeom& g, hipStream_t s);
-// the launches that complete the expansions; done_or_null is recorded then
-hipError_t launch_polyexp(const PyrBatch& f, int n, LevelGeom g, FlowWeights fw, hipEvent_t done_or_null, hipStream_t s);
-hipError_t launch_expand(const ExpandBatch& f, int n, LevelGeom g, FlowWeights fw, hipEvent_t done_or_null, hipStream_t s);
+// the launches that complete the expansions; ride_or_null rides on them, done_or_null is recorded then
+hipError_t launch_polyexp(const PyrBatch& f, int n, LevelGeom g, FlowWeights fw, const PrepRide* ride_or_null, hipEvent_t done_or_null,
+                          hipStream_t s);
+hipError_t launch_expand(const ExpandBatch& f, int n, LevelGeom g, FlowWeights fw, const PrepRide* ride_or_null, hipEvent_t done_or_null,
+                         hipStream_t s);
 // one launch of at most `wanted` (>= 1) updates of a level, as many as suit its size; *done = how many it makes
 hipError_t launch_flow_updates(const FlowBatch& f, int n, int64_t level_off, int h, int w, int ch, int cw,
-                               int prior_mode, int wanted, int* done, FlowWeights fw, hipStream_t s);
+                               int prior_mode, int wanted, int* done, FlowWeights fw, FlowRider rider, const FlowRiders* riders,
+                               hipStream_t s);
+// has the launch for `wanted` updates of an h x w level of n frames room for that piece?
+bool flow_launch_carries(FlowRider rider, const FlowRiders& riders, int n, int h, int w, int wanted);
 hipError_t launch_patch_gate(const float2* d_flow, int h, int w, float tau_t, float theta_r, float* d_dp,
                              sali_gate* d_gate, float* d_flow_uv_or_null, hipStream_t s);
 

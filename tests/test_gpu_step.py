@@ -9,7 +9,7 @@ import torch
 from oracle.cache import SaliCacheOracle
 from paper_2602_14236_amd import synth
 
-from _util import FLOW_ATOL, FLOW_RTOL, assert_same, close, lib_config, oracle_config, pool_arrays, workload_params
+from _util import FLOW_ATOL, FLOW_RTOL, assert_same, close, lib_config, oracle_config, params, pool_arrays, workload_params
 
 pytestmark = pytest.mark.gpu
 
@@ -401,6 +401,42 @@ def test_random_batch_schedules_equal_the_one_stream_path():
             assert torch.equal(pools[k][:, :used[k]], ref_pools[k][:, :used[k]]), f"pool {k}"
         ctx.close()
     ref.close()
+
+
+@pytest.mark.parametrize("h,w,levels,iters,n", [
+    (336, 336, 3, 3, 1), (336, 336, 3, 3, 4), (97, 131, 3, 3, 2),              # all pieces ride: 16x8 updates, 32x16, ragged
+    (241, 427, 4, 3, 3), (360, 640, 3, 3, 2), (512, 512, 3, 3, 1),             # pyramid in pairs; one tile per compute unit
+    (200, 264, 1, 3, 2), (100, 90, 3, 1, 3), (40, 33, 1, 2, 1), (24, 24, 1, 3, 16),      # pieces that find no launch; a single tile
+    (513, 512, 3, 3, 1), (336, 336, 3, 3, 5),                                  # too many tiles: behind the flow
+])
+def test_spatial_filter_next_to_the_temporal_filter(h, w, levels, iters, n):
+    """Small batches run the pre-pass, the hysteresis and the scores on launches of the temporal filter: scores and motions
+    of every frame must be those of the stand-alone calls (the scores bit by bit), also for the first, which has no flow."""
+    from paper_2602_14236_amd import binding
+    rng = np.random.default_rng(h * 7 + w + n)
+    yy, xx = np.mgrid[0:h, 0:w].astype(np.float64)
+    rgbs = []
+    for t in range(2 * n):
+        x, y = xx - 1.7 * t, yy + 1.1 * t
+        img = 120 + 60 * np.sin(x / 4.1) * np.sin(y / 5.3) + 50 * np.sin((x - y) / 3.0)
+        img = img[..., None] * np.array([1.0, 0.8, 0.6]) + rng.normal(0, 2, (h, w, 3))
+        rgbs.append(torch.from_numpy(np.clip(np.rint(img), 0, 255).astype(np.uint8)).cuda())
+    cfg = lib_config(params(h, w, flow_levels=levels, flow_iters=iters, max_frames=2 * n))
+    ctx, alone = binding.SaliContext(cfg), binding.SaliContext(cfg)
+    for first in (0, n):
+        ctx.analyze_batch(rgbs[first:first + n], first)
+    uv = torch.empty((2, h, w), device="cuda")
+    for t in range(2 * n):
+        dp, gate, scores = ctx.read_analysis(t)
+        ref_scores, ref_dp = torch.empty(576, device="cuda"), torch.zeros(576, device="cuda")
+        alone.saliency_pool(rgbs[t], None, ref_scores)
+        if t > 0:
+            alone.flow_score(rgbs[t - 1], rgbs[t], uv, ref_dp, torch.zeros(4, dtype=torch.int32, device="cuda"))
+        assert not gate.redundant
+        assert np.array_equal(scores, ref_scores.cpu().numpy()), f"frame {t}"
+        assert close(dp, ref_dp.cpu().numpy()).all(), f"frame {t}"          # batches take other tiles: sums in another order
+    ctx.close()
+    alone.close()
 
 
 def test_captured_calls_on_several_streams_replay():
