@@ -395,9 +395,9 @@ int enqueue_saliency(sali_ctx* c, const uint8_t* const* d_rgb, const BatchPlan& 
 
 // Does the spatial filter of a batch ride on the launches of its temporal filter, before the gate has spoken?  The two need
 // nothing of each other until then, and where a batch is a chain of launches that leave the chip idle the pre-pass next to
-// the expansions, the hysteresis next to the coarsest flow updates and the scores next to the following ones cost a
-// third of what they cost behind the flow (one 336x336 frame: 8 of 29 us; sali_step 680 -> 608 us for eight frames, of
-// which three are redundant).  Redundant frames get scores that nobody uses.  So it is done up to two tiles of the
+// the coarsest flow updates (or, with no room there, the expansions), the hysteresis next to the updates after them and the
+// scores next to the last cost little of what they cost behind the flow (29 us of 85 for one 336x336 frame; sali_step
+// 680 -> 568 us for eight frames, of which three are redundant).  Redundant frames get scores that nobody uses.  So it is done up to two tiles of the
 // pre-pass per compute unit in a batch, one in a frame; K/V kernels next to it or not, eight to sixteen frames:
 //   336x336 x 4: 3 redundant of 8 426 -> 410 us, none 438 -> 418; with 16 layers 760 -> 732, 992 -> 953
 //   640x360 x 2: 769 -> 755, none redundant 919 -> 861; 427x241 x 3: 447 -> 406; 270x480, none: 837 -> 680
@@ -460,11 +460,24 @@ int enqueue_expansion(sali_ctx* c, const uint8_t* const* d_rgb, const BatchPlan&
     return SALI_OK;
 }
 
+// Which piece of the spatial filter goes with a level's first launch: they depend on one another, so each takes the first
+// level after its predecessor's that has room for it (m frames with flow), starting with *next, which ends as the first piece
+// that found none.
+void plan_riders(const sali_ctx* c, int m, const FlowRiders* riders, FlowRider* next, FlowRider* rider_of) {
+    const LevelGeom& g = c->geom;
+    for (int l = g.levels - 1; l >= 0; --l) {
+        rider_of[l] = FlowRider::none;
+        if (riders == nullptr || *next == FlowRider::none) continue;
+        if (!flow_launch_carries(*next, *riders, m, g.h[l], g.w[l], c->cfg.flow_iters)) continue;
+        rider_of[l] = *next;
+        *next = *next == FlowRider::prepass ? FlowRider::hysteresis : *next == FlowRider::hysteresis ? FlowRider::scores : FlowRider::none;
+    }
+}
+
 // coarse-to-fine displacement estimation of every frame of the batch that has a predecessor;
-// flow[i] = the frame's result (NULL without predecessor).  riders (may be NULL): pieces of the spatial filter that may ride on
-// the launches; *united_out, *scored_out say which did (untouched if there was no launch)
-int enqueue_flow(sali_ctx* c, const BatchPlan& bp, const float2** flow, const FlowRiders* riders, bool* united_out, bool* scored_out,
-                 hipStream_t s) {
+// flow[i] = the frame's result (NULL without predecessor).  riders (may be NULL): the spatial filter, whose piece *next and those
+// after it go with the launches that have room; *next is the first that found none (none: all are done).
+int enqueue_flow(sali_ctx* c, const BatchPlan& bp, const float2** flow, const FlowRiders* riders, FlowRider* next, hipStream_t s) {
     const LevelGeom& g = c->geom;
     FlowBatch f[2] = {};            // [which of the two flow buffers is read]
     int idx[kMaxBatch];
@@ -484,17 +497,9 @@ int enqueue_flow(sali_ctx* c, const BatchPlan& bp, const float2** flow, const Fl
         idx[m++] = i;
     }
     if (m == 0) return SALI_OK;
-    // The riders' launches: hysteresis on the first, the scores on the first after it that can carry them.
     const int iters = c->cfg.flow_iters;
-    int scores_level = -1;
-    bool united = false;
-    if (riders != nullptr && flow_launch_carries(FlowRider::hysteresis, *riders, m, g.h[g.levels - 1], g.w[g.levels - 1], iters)) {
-        united = true;
-        for (int l = g.levels - 2; l >= 0 && scores_level < 0; --l)
-            if (flow_launch_carries(FlowRider::scores, *riders, m, g.h[l], g.w[l], iters)) scores_level = l;
-    }
-    if (united_out != nullptr) *united_out = united;
-    if (scored_out != nullptr) *scored_out = scores_level >= 0;
+    FlowRider rider_of[kMaxLevels];
+    plan_riders(c, m, riders, next, rider_of);
     int cur = 0;            // buffer holding the latest estimate
     bool have = false;
     for (int l = g.levels - 1; l >= 0; --l) {
@@ -504,9 +509,8 @@ int enqueue_flow(sali_ctx* c, const BatchPlan& bp, const float2** flow, const Fl
             if (it > 0) mode = 2;
             else if (!have) mode = 0;
             else { mode = 1; ch = g.h[l + 1]; cw = g.w[l + 1]; }
-            const FlowRider rider = it > 0 ? FlowRider::none : (!have && united) ? FlowRider::hysteresis
-                                    : l == scores_level ? FlowRider::scores : FlowRider::none;
-            SALI_TRY(launch_flow_updates(f[cur], m, g.off[l], g.h[l], g.w[l], ch, cw, mode, iters - it, &done, c->fw, rider, riders, s));
+            SALI_TRY(launch_flow_updates(f[cur], m, g.off[l], g.h[l], g.w[l], ch, cw, mode, iters - it, &done, c->fw,
+                                         it > 0 ? FlowRider::none : rider_of[l], riders, s));
             it += done;
             cur ^= 1;
             have = true;
@@ -837,7 +841,7 @@ int sali_flow_score(sali_ctx* c, const uint8_t* d_prev_rgb, const uint8_t* d_cur
     int rc = enqueue_expansion(c, d_rgb, pair, nullptr, nullptr, s);
     if (rc != SALI_OK) return rc;
     const float2* flow[kMaxBatch];
-    rc = enqueue_flow(c, pair, flow, nullptr, nullptr, nullptr, s);
+    rc = enqueue_flow(c, pair, flow, nullptr, nullptr, s);
     if (rc != SALI_OK) return rc;
     SALI_TRY(launch_patch_gate(flow[1], c->cfg.src_h, c->cfg.src_w, c->cfg.tau_t, c->cfg.theta_r, d_patch_motion576,
                                d_gate_out, d_flow_uv_or_null, s));
@@ -978,19 +982,24 @@ int sali_analyze_batch(sali_ctx* c, const uint8_t* const* d_rgb_frames, int32_t 
     AnalysisRecord& rec = c->ring[n_last % kRing];
     const bool attach = events_may_attach(s);
     // the temporal filter first: gray, pyramid + expansion, flow, per-patch motion.  Where the spatial filter rides along its
-    // frames are all taken as not redundant (no motions yet).
+    // frames are all taken as not redundant (no motions yet).  Its pre-pass goes with the coarsest flow updates where the two
+    // fit one block per compute unit, else with the expansions.
     const bool rides = saliency_rides(c, n_frames);
-    PrepBatch prep = {};
     PoolBatch pool = {};
-    PrepRide ride;
+    PrepRide prep;
     FlowRiders riders = {};
+    FlowRider next = FlowRider::none;
     if (rides) {
-        prep = prep_batch(c, d_rgb_frames, bp, true, nullptr);
+        prep = prep_ride(c, prep_batch(c, d_rgb_frames, bp, true, nullptr), n_frames);
         pool = pool_batch(c, bp, nullptr, nullptr);
-        ride = prep_ride(c, prep, n_frames);
         riders = {&prep, &pool, n_frames, c->cfg.src_h, c->cfg.src_w};
+        int m = 0;
+        for (int i = 0; i < n_frames; ++i) m += bp.prev_slot[i] >= 0 ? 1 : 0;
+        const LevelGeom& g = c->geom;
+        next = m > 0 && flow_launch_carries(FlowRider::prepass, riders, m, g.h[g.levels - 1], g.w[g.levels - 1], c->cfg.flow_iters)
+                   ? FlowRider::prepass : FlowRider::hysteresis;
     }
-    rc = enqueue_expansion(c, d_rgb_frames, bp, rides ? &ride : nullptr, attach ? rec.exp_ready : nullptr, s);
+    rc = enqueue_expansion(c, d_rgb_frames, bp, next == FlowRider::hysteresis ? &prep : nullptr, attach ? rec.exp_ready : nullptr, s);
     if (rc != SALI_OK) return rc;
     if (!attach) SALI_TRY(hipEventRecord(rec.exp_ready, s));
     const float2* flow[kMaxBatch];
@@ -998,14 +1007,13 @@ int sali_analyze_batch(sali_ctx* c, const uint8_t* const* d_rgb_frames, int32_t 
         rc = wait_unless_same(s, prev->stream, prev->exp_ready);
         if (rc != SALI_OK) return rc;
     }
-    bool united = false, scored = false;
-    rc = enqueue_flow(c, bp, flow, rides ? &riders : nullptr, &united, &scored, s);
+    rc = enqueue_flow(c, bp, flow, rides ? &riders : nullptr, &next, s);
     if (rc == SALI_OK) rc = enqueue_motion(c, bp, flow, s);
     if (rc != SALI_OK) return rc;
     if (rides) {
         // what found no launch to ride on
-        if (!united) SALI_TRY(launch_union(prep, n_frames, c->cfg.src_h, c->cfg.src_w, s));
-        if (!scored) SALI_TRY(launch_scores(pool, n_frames, c->cfg.src_h, c->cfg.src_w, nullptr, s));
+        if (next == FlowRider::hysteresis) SALI_TRY(launch_union(prep.f, n_frames, c->cfg.src_h, c->cfg.src_w, s));
+        if (next != FlowRider::none) SALI_TRY(launch_scores(pool, n_frames, c->cfg.src_h, c->cfg.src_w, nullptr, s));
     } else {
         // then the spatial filter, for the frames the reuse rule does not find redundant (Algorithm 1: a
         // redundant frame bypasses it): every kernel from here on evaluates the rule from the motions

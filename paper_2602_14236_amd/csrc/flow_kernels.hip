@@ -204,7 +204,7 @@ __device__ __forceinline__ bool ride_prep(Shared& sh, const PrepRide& ride, int&
     block = (int)blockIdx.x - ride.blocks;
     if (block >= 0) return false;
     const int tiles = ride.tiles_x * ride.tiles_y, frame = (int)blockIdx.x / tiles, t = (int)blockIdx.x - frame * tiles;
-    prep_tile<false>(sh.prep, ride.f, t % ride.tiles_x, t / ride.tiles_x, frame, ride.h, ride.w, GateParams{}, ride.lut, ride.lo2, ride.hi2);
+    prep_tile<false, kPrepThreads>(sh.prep, ride.f, t % ride.tiles_x, t / ride.tiles_x, frame, ride.h, ride.w, GateParams{}, ride.lut, ride.lo2, ride.hi2);
     return true;
 }
 template <typename Shared>
@@ -1021,30 +1021,43 @@ __device__ __forceinline__ void fused_update(FusedTile<TX, TY>& sh, float2* prio
     if constexpr (kLeft > 0) __syncthreads();
 }
 
-// Riders of a launch, its blocks after the flow's: a border pixel per thread, or a patch per wave.  At 336x336 the flow
-// leaves room for them: its own blocks are at most one per compute unit.
+// Riders of a launch, its blocks after the flow's: a tile of the pre-pass per block, a border pixel per thread, or a patch per
+// wave.  At 336x336 the flow leaves room for them: its own blocks are at most one per compute unit.
 namespace {
-__device__ __forceinline__ void ride_flow(const UnionRide& r, int block) {
+template <typename Shared>
+__device__ __forceinline__ void ride_flow(Shared& sh, const PrepRide& r, int block) {
+    const int tiles = r.tiles_x * r.tiles_y, b = block / tiles, t = block - b * tiles;
+    prep_tile<false, kFusedThreads>(sh.prep, r.f, t % r.tiles_x, t / r.tiles_x, b, r.h, r.w, GateParams{}, r.lut, r.lo2, r.hi2);
+}
+template <typename Shared>
+__device__ __forceinline__ void ride_flow(Shared&, const UnionRide& r, int block) {
     const int b = block / r.blocks_per_frame;
     union_item(r.f, b, r.h, r.w, (block - b * r.blocks_per_frame) * kFusedThreads + (int)threadIdx.x, r.n_items);
 }
-__device__ __forceinline__ void ride_flow(const ScoreRide& r, int block) {
+template <typename Shared>
+__device__ __forceinline__ void ride_flow(Shared&, const ScoreRide& r, int block) {
     const int b = block / r.blocks_per_frame;
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     score_by_wave(r.f, b, (block - b * r.blocks_per_frame) * (kFusedThreads / 64) + wave, r.h, r.w, nullptr);
 }
+// LDS: the pre-pass needs some of its own, the other riders none
+template <typename Own, typename Ride>
+struct FlowShared : WithPrep<Own, NoRide> {};
+template <typename Own>
+struct FlowShared<Own, PrepRide> : WithPrep<Own, PrepRide> {};
 }  // namespace
 
 // gx x gy tiles of n frames: the grid, or the first blocks of a one-dimensional grid that ends with the riders
 template <int TX, int TY, typename Ride>
 __global__ __launch_bounds__(kFusedThreads) void k_flow_fused(FlowBatch f, long long level_off, int h, int w, int ch, int cw,
                                                               int prior_mode, FlowWeights fw, int gx, int gy, int n, Ride ride) {
+    __shared__ FlowShared<FusedTile<TX, TY>, Ride> lds;
     BlockId blk;
     if constexpr (std::is_same_v<Ride, NoRide>) {
         blk = xcd_block_id();
     } else {
         if ((int)blockIdx.x >= gx * gy * n) {
-            ride_flow(ride, (int)blockIdx.x - gx * gy * n);
+            ride_flow(lds, ride, (int)blockIdx.x - gx * gy * n);
             return;
         }
         blk = xcd_block_id((int)blockIdx.x, gx, gy, n);
@@ -1055,7 +1068,7 @@ __global__ __launch_bounds__(kFusedThreads) void k_flow_fused(FlowBatch f, long 
     const float* __restrict__ b2 = f.b2[blk.z] + level_off;
     const float2* __restrict__ d_in = f.d_in[blk.z];
     float2* __restrict__ d_out = f.d_out[blk.z];
-    __shared__ FusedTile<TX, TY> sh;
+    FusedTile<TX, TY>& sh = lds.own;
     const int x0 = blk.x * TX, y0 = blk.y * TY;
     fused_update<TX, TY, 0>(sh, sh.p, sh.q, A1, b1, A2, b2, d_in, d_out, h, w, ch, cw, prior_mode, x0, y0, fw);
     fused_update<TX, TY, 1>(sh, sh.q, sh.p, A1, b1, A2, b2, d_in, d_out, h, w, ch, cw, prior_mode, x0, y0, fw);
@@ -1192,6 +1205,7 @@ Fused fused_tile(int n, int h, int w, int wanted) {
 
 // blocks that a piece of the spatial filter takes per frame as a rider
 int rider_blocks(FlowRider rider, const FlowRiders& r) {
+    if (rider == FlowRider::prepass) return r.prep->tiles_x * r.prep->tiles_y;
     return rider == FlowRider::hysteresis ? (border_items(r.h, r.w) + kFusedThreads - 1) / kFusedThreads : kTokens / (kFusedThreads / 64);
 }
 
@@ -1206,14 +1220,16 @@ hipError_t launch_fused(const FlowBatch& f, int n, int64_t level_off, int h, int
     };
     if (rider == FlowRider::none) return go(NoRide{}, dim3(gx, gy, n));
     const int per = rider_blocks(rider, *r), blocks = per * r->n;
-    if (rider == FlowRider::hysteresis) return go(UnionRide{*r->prep, r->h, r->w, border_items(r->h, r->w), per, blocks}, dim3(own + blocks));
+    if (rider == FlowRider::prepass) return go(*r->prep, dim3(own + blocks));
+    if (rider == FlowRider::hysteresis) return go(UnionRide{r->prep->f, r->h, r->w, border_items(r->h, r->w), per, blocks}, dim3(own + blocks));
     return go(ScoreRide{*r->pool, r->h, r->w, per, blocks}, dim3(own + blocks));
 }
 
 }  // namespace
 
 // A fused launch carries a piece if the compute units that its own blocks (one each, by registers or LDS) leave take the
-// riders in two rounds: a rider takes 3 to 5 us, a flow block 10 and more.
+// riders, those of the pre-pass at once, the others in two rounds: a tile of the pre-pass takes as long as a flow block, 10 us,
+// the others 3 to 5.
 bool flow_launch_carries(FlowRider rider, const FlowRiders& riders, int n, int h, int w, int wanted) {
     long long own = 0;
     switch (fused_tile(n, h, w, wanted)) {
@@ -1222,7 +1238,7 @@ bool flow_launch_carries(FlowRider rider, const FlowRiders& riders, int n, int h
         case Fused::t16x16: own = tiles_of(16, 16, n, h, w); break;
         case Fused::t32x16: own = tiles_of(32, 16, n, h, w); break;
     }
-    return (long long)rider_blocks(rider, riders) * riders.n <= 2 * (kComputeUnits - own);
+    return (long long)rider_blocks(rider, riders) * riders.n <= (rider == FlowRider::prepass ? 1 : 2) * (kComputeUnits - own);
 }
 
 hipError_t launch_flow_updates(const FlowBatch& f, int n, int64_t level_off, int h, int w, int ch, int cw,

@@ -178,23 +178,23 @@ struct PoolBatch {
 
 // Work of the spatial filter that rides on launches of the temporal filter: extra blocks of theirs.
 struct NoRide {};
-struct PrepRide {                                 // the pre-pass, on the launch that makes the expansions
+struct PrepRide {                                 // the pre-pass, on the launch that makes the expansions or a flow update
     PrepBatch f;
     const uint32_t* lut;
     int32_t h, w, tiles_x, tiles_y, blocks, lo2, hi2;
 };
-struct UnionRide {                                // hysteresis across tiles, on the first flow update
+struct UnionRide {                                // hysteresis across tiles, on a flow update after it
     PrepBatch f;
     int32_t h, w, n_items, blocks_per_frame, blocks;
 };
-struct ScoreRide {                                // patch scores, on the update after it
+struct ScoreRide {                                // patch scores, on an update after that
     PoolBatch f;
     int32_t h, w, blocks_per_frame, blocks;
 };
 // a piece of the spatial filter that a flow launch is asked to carry
-enum class FlowRider { none, hysteresis, scores };
+enum class FlowRider { none, prepass, hysteresis, scores };
 struct FlowRiders {
-    const PrepBatch* prep;
+    const PrepRide* prep;
     const PoolBatch* pool;
     int n, h, w;                                  // frames, their size
 };

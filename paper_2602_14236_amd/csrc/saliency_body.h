@@ -15,40 +15,48 @@ constexpr int kRegB = kTile + 4;               // 36: blur / LAB region (halo 2)
 constexpr int kRegM = kTile + 2;               // 34: gradient-magnitude region (halo 1)
 
 
-// #{dP_i < tau_t} over the thread's share of one image's 576 patch motions (block of 256 threads); the
+// #{dP_i < tau_t} over the thread's share of one image's 576 patch motions (block of NT threads); the
 // loads are independent and issued together
+template <int NT>
 __device__ __forceinline__ int count_static(const float* dp, float tau_t) {
-    float v[3];
+    constexpr int kPer = (kTokens + NT - 1) / NT;
+    float v[kPer];
 #pragma unroll
-    for (int k = 0; k < 3; ++k) {
-        const int i = (int)threadIdx.x + 256 * k;
+    for (int k = 0; k < kPer; ++k) {
+        const int i = (int)threadIdx.x + NT * k;
         v[k] = i < kTokens ? __hip_atomic_load(dp + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : tau_t;
     }
-    return (v[0] < tau_t ? 1 : 0) + (v[1] < tau_t ? 1 : 0) + (v[2] < tau_t ? 1 : 0);
+    int n = 0;
+#pragma unroll
+    for (int k = 0; k < kPer; ++k) n += v[k] < tau_t ? 1 : 0;
+    return n;
 }
 
-// Eq. 6 and the reuse rule for frame b of a launch, evaluated by a whole block of 256 threads from the
+// Eq. 6 and the reuse rule for frame b of a launch, evaluated by a whole block of NT threads from the
 // per-patch motions that an earlier kernel left (dp[b] NULL: no predecessor, never redundant): the
 // kernels of the spatial filter ask this first and leave at once for a redundant frame (Algorithm 1
 // skips its saliency).  Same counts and the same fp32 quotient as the tail kernel that writes the gate,
-// so all of them take the same decision.  s_cnt: four ints of LDS.
+// so all of them take the same decision.  s_cnt: NT / 64 ints of LDS.
+template <int NT>
 __device__ __forceinline__ bool frame_redundant(const float* const* dp, int b, const GateParams& gp, int* s_cnt) {
     const int b0 = b - b % gp.tiles;
     if (dp[b0] == nullptr) return false;
     int n = 0;
-    for (int j = 0; j < gp.tiles; ++j) n += count_static(dp[b0 + j], gp.tau_t);
+    for (int j = 0; j < gp.tiles; ++j) n += count_static<NT>(dp[b0 + j], gp.tau_t);
     for (int off = 32; off > 0; off >>= 1) n += __shfl_down(n, off);
     if ((threadIdx.x & 63) == 0) s_cnt[threadIdx.x >> 6] = n;
     __syncthreads();
-    const int n_static = s_cnt[0] + s_cnt[1] + s_cnt[2] + s_cnt[3];
+    int n_static = 0;
+#pragma unroll
+    for (int k = 0; k < NT / 64; ++k) n_static += s_cnt[k];
     __syncthreads();
     return (float)n_static / (float)(kTokens * gp.tiles) > gp.theta_r;
 }
 
-// 256 threads per 32x32 tile.  Workgroups are kept this small so that they find room on compute units that a
-// bandwidth kernel of another stream keeps busy.
+// A block per 32x32 tile: 256 threads in the chained step, so that blocks find room on compute units that a bandwidth
+// kernel of another stream keeps busy; 512 or 1024 in the stand-alone call and where it rides on blocks of that size.
 //
-// Four 1920x1080 frames: 107 us, one 640x360 frame: 16; bound by the trips of a block's stages (image and tables
+// Four 1920x1080 frames: 107 us, one 640x360 frame: 16 (11 on 1024 threads); bound by the trips of a block's stages (image and tables
 // from memory, then LDS; 20 waves per compute unit), the vector ALU 61 % busy.  Taken tap by tap, byte
 // by byte, with clamped coordinates, the stencils were 612 instructions per pixel instead of 305, the ALU
 // 90 % busy, and the kernel took 150 and 24 us.  So each
@@ -57,14 +65,11 @@ __device__ __forceinline__ bool frame_redundant(const float* const* dp, int b, c
 // squared magnitude is one dot product.  No stage clamps coordinates: a cell outside the image holds what the
 // definition wants to see there (gray and colour of the clamped coordinate as loaded; blurred values copied
 // from the clamped cell, gradient 0), which only blocks on the image border have to arrange.
-constexpr int kPrepThreads = 256;
-constexpr int kPrepPx = kTile * kTile / kPrepThreads;                          // 4
+constexpr int kPrepThreads = 256, kPrepMaxThreads = 1024;
 constexpr int kQuadsY = kReg / 4;                                              // 10 quads of a gray row
-constexpr int kPrepQuads = (kReg * kQuadsY + kPrepThreads - 1) / kPrepThreads; // 2 per thread
 constexpr int kStripsB = kRegB / 4;                                            // 9 strips of a blurred row
 constexpr int kGradW = 36;                                                     // gradient row: 34 cells, whole strips
 constexpr int kLutWords = kColourLutBytes / 4;
-constexpr int kLutQuads = (kLutWords / 4 + kPrepThreads - 1) / kPrepThreads;
 static_assert(kLutWords % 4 == 0, "tables are copied sixteen bytes at a time");
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 typedef short short2_t __attribute__((ext_vector_type(2)));
@@ -96,8 +101,8 @@ struct PrepShared {
     };
     __attribute__((aligned(16))) uint32_t grad[kRegM][kGradW];      // (gx, gy) as 16-bit halves
     __attribute__((aligned(16))) uint8_t lab[3][kRegB][kRegB];
-    unsigned long long sum[kPrepThreads / 64];
-    int gate[4];
+    unsigned long long sum[kPrepMaxThreads / 64];
+    int gate[kPrepMaxThreads / 64];
     uint32_t row[kTile];        // a tile row's edge candidates, a bit each
     uint32_t n_contacts;
 };
@@ -114,7 +119,7 @@ __device__ __forceinline__ int grad_m2(uint32_t g) {
 
 // Tile (bx, by) of frame bz of the batch, by a block of 256 threads.  kGated: frames that the reuse rule finds redundant are
 // left out; without it (a launch that runs before the flow) all are done.
-template <bool kGated>
+template <bool kGated, int NT>
 __device__ __forceinline__ void prep_tile(PrepShared& sh, const PrepBatch& f, int bx, int by, int bz, int h, int w, const GateParams& gp,
                                           const uint32_t* __restrict__ lut_words, int lo2, int hi2) {
     const uint8_t* __restrict__ rgb = f.rgb[bz];
@@ -123,6 +128,9 @@ __device__ __forceinline__ void prep_tile(PrepShared& sh, const PrepBatch& f, in
     uint32_t* __restrict__ parent_out = f.parent[bz];
     unsigned long long* msum_acc = f.msum_acc[bz];
     unsigned long long* msum_clear = f.msum_clear[bz];
+    constexpr int kPrepPx = kTile * kTile / NT;                          // pixels of the tile per thread
+    constexpr int kPrepQuads = (kReg * kQuadsY + NT - 1) / NT;           // quads of the region per thread
+    constexpr int kLutQuads = (kLutWords / 4 + NT - 1) / NT;
     uint32_t (&s_lbl)[kTile * kTile] = sh.lbl;
 
     const int tid = threadIdx.x;
@@ -137,7 +145,7 @@ __device__ __forceinline__ void prep_tile(PrepShared& sh, const PrepBatch& f, in
     uint32_t crgb[kPrepQuads][3];
 #pragma unroll
     for (int k = 0; k < kPrepQuads; ++k) {
-        const int p = min(tid + k * kPrepThreads, kReg * kQuadsY - 1);
+        const int p = min(tid + k * NT, kReg * kQuadsY - 1);
         const int x = x0 - kHalo + 4 * (p % kQuadsY);
         const uint8_t* row = rgb + (size_t)clampi(y0 - kHalo + p / kQuadsY, 0, h - 1) * w * 3;
         if (x >= 0 && x + 3 < w) {
@@ -153,24 +161,24 @@ __device__ __forceinline__ void prep_tile(PrepShared& sh, const PrepBatch& f, in
     u32x4 lut[kLutQuads];
 #pragma unroll
     for (int k = 0; k < kLutQuads; ++k)
-        lut[k] = reinterpret_cast<const u32x4*>(lut_words)[min(tid + k * kPrepThreads, kLutWords / 4 - 1)];
+        lut[k] = reinterpret_cast<const u32x4*>(lut_words)[min(tid + k * NT, kLutWords / 4 - 1)];
     {
         // no saliency for a redundant frame; the frame's first block leaves the decision for the kernels
         // after this one, whose blocks are too small to count 576 patches each
         bool skip = false;
-        if constexpr (kGated) skip = frame_redundant(f.dp, bz, gp, sh.gate);
+        if constexpr (kGated) skip = frame_redundant<NT>(f.dp, bz, gp, sh.gate);
         if (bx == 0 && by == 0 && tid == 0) *f.skip[bz] = skip ? 1u : 0u;
         if (skip) return;
     }
     // colour tables -> LDS, gray of the region
 #pragma unroll
     for (int k = 0; k < kLutQuads; ++k) {
-        const int i = tid + k * kPrepThreads;
+        const int i = tid + k * NT;
         if (i < kLutWords / 4) reinterpret_cast<u32x4*>(sh.lut)[i] = lut[k];
     }
 #pragma unroll
     for (int k = 0; k < kPrepQuads; ++k) {
-        const int p = tid + k * kPrepThreads;
+        const int p = tid + k * NT;
         if (p < kReg * kQuadsY) sh.gray.y[p / kQuadsY][p % kQuadsY] = gray_of_quad(crgb[k]);
     }
     __syncthreads();
@@ -182,7 +190,7 @@ __device__ __forceinline__ void prep_tile(PrepShared& sh, const PrepBatch& f, in
         const uint8_t* s_l8 = reinterpret_cast<const uint8_t*>(s_fl + 4096);
 #pragma unroll
         for (int k = 0; k < kPrepQuads; ++k) {
-            const int p = tid + k * kPrepThreads;
+            const int p = tid + k * NT;
             const int ry = p / kQuadsY - 2, quad = p % kQuadsY;          // row of the region, cells 4 quad - 2 ..
             if (ry < 0 || ry >= kRegB) continue;
             uint32_t lab[3] = {0u, 0u, 0u};                              // four pixels, a byte each
@@ -209,7 +217,7 @@ __device__ __forceinline__ void prep_tile(PrepShared& sh, const PrepBatch& f, in
     // Region arrays: cell i of the gray region is image coordinate x0 - 4 + i, of the blurred and the colour
     // region x0 - 2 + i, of the gradient region x0 - 1 + i (rows alike).
     // stage 2: 5x5 binomial blur, (sum + 128) >> 8; along the rows (weights 1 4 6 4 as a byte dot product)
-    for (int p = tid; p < kReg * kStripsB; p += kPrepThreads) {
+    for (int p = tid; p < kReg * kStripsB; p += NT) {
         const int ry = p / kStripsB, sx = p % kStripsB;
         const uint32_t w0 = sh.gray.y[ry][sx], w1 = sh.gray.y[ry][sx + 1];
         uint32_t v[4];
@@ -220,7 +228,7 @@ __device__ __forceinline__ void prep_tile(PrepShared& sh, const PrepBatch& f, in
     }
     __syncthreads();
     // ... and down the columns, two pixels per packed operation (sums stay below 2^16)
-    for (int p = tid; p < kRegB * kStripsB; p += kPrepThreads) {
+    for (int p = tid; p < kRegB * kStripsB; p += NT) {
         const int ry = p / kStripsB, sx = p % kStripsB;
         uint2 r[5];
 #pragma unroll
@@ -236,7 +244,7 @@ __device__ __forceinline__ void prep_tile(PrepShared& sh, const PrepBatch& f, in
     }
     // stage 4a: colour variance, 25 * sum v^2 - (sum v)^2 over 5x5 per channel: sums over the five cells of a row
     // (the tables are done with: their memory holds these)
-    for (int p = tid; p < kRegB * (kTile / 4); p += kPrepThreads) {
+    for (int p = tid; p < kRegB * (kTile / 4); p += NT) {
         const int ry = p / (kTile / 4), sx = p % (kTile / 4);
         uint32_t sq[4] = {0u, 0u, 0u, 0u};
 #pragma unroll
@@ -258,7 +266,7 @@ __device__ __forceinline__ void prep_tile(PrepShared& sh, const PrepBatch& f, in
     __syncthreads();
     if (border) {
         // blurred cells outside the image: the value at the clamped coordinate
-        for (int p = tid; p < kRegB * kRegB; p += kPrepThreads) {
+        for (int p = tid; p < kRegB * kRegB; p += NT) {
             const int ry = p / kRegB, rx = p % kRegB;
             const int cy = clampi(y0 - 2 + ry, 0, h - 1) - (y0 - 2), cx = clampi(x0 - 2 + rx, 0, w - 1) - (x0 - 2);
             if (cy != ry || cx != rx) sh.b8[ry][rx] = sh.b8[cy][cx];
@@ -268,7 +276,7 @@ __device__ __forceinline__ void prep_tile(PrepShared& sh, const PrepBatch& f, in
 
     // stage 3: Sobel gradients of the 34x34 region; cells outside the image hold 0 (that is what
     // non-maximum suppression wants to see there)
-    for (int p = tid; p < kRegM * kStripsB; p += kPrepThreads) {
+    for (int p = tid; p < kRegM * kStripsB; p += NT) {
         const int ry = p / kStripsB, sx = p % kStripsB;
         short2_t gx[2], gy[2];
         short2_t d[3][2], sm[3][2];
@@ -303,7 +311,7 @@ __device__ __forceinline__ void prep_tile(PrepShared& sh, const PrepBatch& f, in
     }
     // stage 4b: the variance of four pixels from five rows of sums
     unsigned long long local_sum = 0ull;
-    {
+    if (tid < kTile * kTile / 4) {
         const int vy = tid >> 3, sx = tid & 7;
         const int gy = y0 + vy, gx0 = x0 + 4 * sx;
         uint32_t sq[4] = {0u, 0u, 0u, 0u};
@@ -354,7 +362,7 @@ __device__ __forceinline__ void prep_tile(PrepShared& sh, const PrepBatch& f, in
     // block sum of V -> one atomic
     if (tid == 0) {
         unsigned long long t = 0ull;
-        for (int k = 0; k < kPrepThreads / 64; ++k) t += sh.sum[k];
+        for (int k = 0; k < NT / 64; ++k) t += sh.sum[k];
         atomicAdd(msum_acc, t);
     }
 
@@ -365,7 +373,7 @@ __device__ __forceinline__ void prep_tile(PrepShared& sh, const PrepBatch& f, in
     int cls[kPrepPx];
 #pragma unroll
     for (int q = 0; q < kPrepPx; ++q) {
-        const int ty = (tid + q * kPrepThreads) / kTile;
+        const int ty = (tid + q * NT) / kTile;
         const int gy = y0 + ty;
         cls[q] = 0;
         if (gy < h && gx < w) {
@@ -394,7 +402,7 @@ __device__ __forceinline__ void prep_tile(PrepShared& sh, const PrepBatch& f, in
     if (tid == 0) sh.n_contacts = 0u;
 #pragma unroll
     for (int q = 0; q < kPrepPx; ++q) {
-        const int p = tid + q * kPrepThreads;
+        const int p = tid + q * NT;
         const int ty = p / kTile;
         const unsigned long long cand64 = __ballot(cls[q] != 0);
         const unsigned long long strong64 = __ballot(cls[q] == 2);
@@ -429,7 +437,7 @@ __device__ __forceinline__ void prep_tile(PrepShared& sh, const PrepBatch& f, in
         uint32_t total = 0u;
 #pragma unroll
         for (int q = 0; q < kPrepPx; ++q) {
-            const int ty = (tid + q * kPrepThreads) / kTile;
+            const int ty = (tid + q * NT) / kTile;
             const bool inner = ty + 1 < kTile;
             const unsigned long long row_below = (unsigned long long)(inner ? sh.row[ty + 1] : 0u) << 1;
             const uint32_t near = cls[q] != 0 ? (uint32_t)(row_below >> tx) & 7u : 0u;      // SW, S, SE
@@ -462,7 +470,7 @@ __device__ __forceinline__ void prep_tile(PrepShared& sh, const PrepBatch& f, in
             }
     }
     __syncthreads();
-    for (uint32_t i = tid; i < sh.n_contacts; i += kPrepThreads) {
+    for (uint32_t i = tid; i < sh.n_contacts; i += NT) {
         const uint32_t c = sh.contact[i];
         auto unpack = [](uint32_t v) { return (v & 0x3FFu) | (v << 21 & kWeakBit); };
         uf_spread_strong<__HIP_MEMORY_SCOPE_WORKGROUP>(s_lbl, unpack(c & 0xFFFFu), unpack(c >> 16));
@@ -475,7 +483,7 @@ __device__ __forceinline__ void prep_tile(PrepShared& sh, const PrepBatch& f, in
     // once, so what a walk meets has been shortened as often as itself (no root changes any more).
     uint32_t root[kPrepPx];
 #pragma unroll
-    for (int q = 0; q < kPrepPx; ++q) root[q] = cls[q] != 0 ? head_key[q] : (uint32_t)(tid + q * kPrepThreads);
+    for (int q = 0; q < kPrepPx; ++q) root[q] = cls[q] != 0 ? head_key[q] : (uint32_t)(tid + q * NT);
     for (;;) {
         uint32_t up[kPrepPx];
         bool moved = false;
@@ -486,13 +494,13 @@ __device__ __forceinline__ void prep_tile(PrepShared& sh, const PrepBatch& f, in
             if ((root[q] & kWeakBit) == 0u || up[q] == root[q]) continue;
             moved = true;
             root[q] = up[q];
-            __hip_atomic_store(&s_lbl[tid + q * kPrepThreads], up[q], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+            __hip_atomic_store(&s_lbl[tid + q * NT], up[q], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
         }
         if (!moved) break;
     }
 #pragma unroll
     for (int q = 0; q < kPrepPx; ++q) {
-        const int ty = (tid + q * kPrepThreads) / kTile;
+        const int ty = (tid + q * NT) / kTile;
         if (y0 + ty >= h || gx >= w) continue;
         const uint32_t rl = root[q] & ~kWeakBit;
         const size_t rg = (size_t)(y0 + (int)(rl / kTile)) * w + (x0 + (int)(rl % kTile));

@@ -60,11 +60,12 @@ __global__ __launch_bounds__(256) void k_gray(PrepBatch f, int n) {
     }
 }
 
-__global__ __launch_bounds__(kPrepThreads) void k_prep(PrepBatch f, int h, int w, GateParams gp,
-                                                       const uint32_t* __restrict__ lut_words, int lo2, int hi2) {
+template <bool kGated, int NT>
+__global__ __launch_bounds__(NT) void k_prep(PrepBatch f, int h, int w, GateParams gp, const uint32_t* __restrict__ lut_words, int lo2,
+                                             int hi2) {
     // blockIdx.z = frame of the batch
     __shared__ PrepShared sh;
-    prep_tile<true>(sh, f, (int)blockIdx.x, (int)blockIdx.y, (int)blockIdx.z, h, w, gp, lut_words, lo2, hi2);
+    prep_tile<kGated, NT>(sh, f, (int)blockIdx.x, (int)blockIdx.y, (int)blockIdx.z, h, w, gp, lut_words, lo2, hi2);
 }
 
 // hysteresis, cross-tile part; blockIdx.y = frame of the batch.  A thread per border pixel: with a thread per
@@ -95,7 +96,7 @@ __device__ __forceinline__ void pool_tail(TierShared& sh, int* s_cnt, const Pool
     const int b0 = b - b % tiles;
     int n = 0;
     if (have_flow)
-        for (int j = 0; j < tiles; ++j) n += count_static(f.dp[b0 + j], tau_t);
+        for (int j = 0; j < tiles; ++j) n += count_static<kTierThreads>(f.dp[b0 + j], tau_t);
     for (int off = 32; off > 0; off >>= 1) n += __shfl_down(n, off);
     if (lane == 0) s_cnt[wave] = n;
     __syncthreads();
@@ -274,8 +275,16 @@ hipError_t launch_gray(const PrepBatch& f, int n, int h, int w, hipStream_t s) {
 hipError_t launch_prep(const PrepBatch& f, int n, int h, int w, GateParams gp, const void* d_lut,
                        int lo2, int hi2, hipStream_t s) {
     dim3 grid((w + kTile - 1) / kTile, (h + kTile - 1) / kTile, n);
-    hipLaunchKernelGGL(k_prep, grid, dim3(kPrepThreads), 0, s, f, h, w, gp,
-                       static_cast<const uint32_t*>(d_lut), lo2, hi2);
+    const uint32_t* lut = static_cast<const uint32_t*>(d_lut);
+    bool gated = false;
+    for (int i = 0; i < n; ++i) gated = gated || f.dp[i] != nullptr;
+    // Batches (the chained step, behind its flow) on 256 threads: next to K/V kernels small blocks find room, 640x360 clips are
+    // 0.5 to 1 % slower with 512.  The stand-alone call on 512, or on 1024 if every tile has a compute unit to itself: a stage of
+    // 300 to 400 strips is one pass instead of two, the whole call at 640x360 37.7 -> 32.6 us (512 threads 33.2), at
+    // 1920x1080 96.3 -> 92.9 (1024 threads 95.4).
+    if (gated) hipLaunchKernelGGL((k_prep<true, kPrepThreads>), grid, dim3(kPrepThreads), 0, s, f, h, w, gp, lut, lo2, hi2);
+    else if ((long long)grid.x * grid.y * n <= 256) hipLaunchKernelGGL((k_prep<false, 1024>), grid, dim3(1024), 0, s, f, h, w, gp, lut, lo2, hi2);
+    else hipLaunchKernelGGL((k_prep<false, 512>), grid, dim3(512), 0, s, f, h, w, gp, lut, lo2, hi2);
     return hipGetLastError();
 }
 

@@ -117,3 +117,17 @@ def test_weak_chains_across_tile_borders_and_corners(h, w):
         m = _check(ctx, np.stack([img, img, img], axis=-1), 1, hi)
         print(f"{h}x{w} grain {grain}: {int((m >= 1).sum())} edge pixels", flush=True)
         ctx.close()
+
+
+@pytest.mark.parametrize("h,w", [(512, 512), (513, 480), (545, 610)])
+def test_block_sizes_of_the_pre_pass(h, w):
+    """A tile per compute unit (256 tiles, the last size on 1024 threads), one row more and ragged (512 threads): textured
+    halves, and pure noise with a low threshold, whose tiles are full of weak chains."""
+    from paper_2602_14236_amd import binding
+    ctx = binding.SaliContext(lib_config(params(h, w, flow_levels=1, canny_lo=8, canny_hi=120)))
+    rng = np.random.default_rng(h + w)
+    img = rng.integers(0, 256, (h, w, 3))
+    yy, xx = np.mgrid[0:h, 0:w]
+    img[:, : w // 2] = (128 + 60 * np.sin(xx / 3.3) * np.sin(yy / 4.7) + rng.normal(0, 3, (h, w)))[:, : w // 2, None]
+    _check(ctx, np.clip(img, 0, 255).astype(np.uint8), 8, 120)
+    ctx.close()
