@@ -1038,7 +1038,9 @@ template <typename Shared>
 __device__ __forceinline__ void ride_flow(Shared&, const ScoreRide& r, int block) {
     const int b = block / r.blocks_per_frame;
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-    score_by_wave(r.f, b, (block - b * r.blocks_per_frame) * (kFusedThreads / 64) + wave, r.h, r.w, nullptr);
+    for (int token = (block - b * r.blocks_per_frame) * (kFusedThreads / 64) + wave; token < kTokens;
+         token += r.blocks_per_frame * (kFusedThreads / 64))
+        score_by_wave(r.f, b, token, r.h, r.w, nullptr);
 }
 // LDS: the pre-pass needs some of its own, the other riders none
 template <typename Own, typename Ride>
@@ -1203,10 +1205,17 @@ Fused fused_tile(int n, int h, int w, int wanted) {
     return tiles_of(32, 16, n, h, w) <= kComputeUnits ? Fused::t32x16 : Fused::no;
 }
 
-// blocks that a piece of the spatial filter takes per frame as a rider
-int rider_blocks(FlowRider rider, const FlowRiders& r) {
-    if (rider == FlowRider::prepass) return r.prep->tiles_x * r.prep->tiles_y;
-    return rider == FlowRider::hysteresis ? (border_items(r.h, r.w) + kFusedThreads - 1) / kFusedThreads : kTokens / (kFusedThreads / 64);
+// Blocks per frame that a piece of the spatial filter gets beside `own` blocks of the flow's, 0: no room.  The flow's blocks fit
+// a compute unit each, by registers or LDS, and take 10 us and more; the riders get the other units, all at once.  A tile of
+// the pre-pass (one per block) takes 10 us, a block of border pixels 5, a patch of a wave's 5: up to three per wave.
+// (In two rounds of blocks, 36 a frame on 25 units, the scores made the flow's launch at 336x336 5 us longer.)
+int rider_blocks(FlowRider rider, const FlowRiders& r, long long own) {
+    const long long room = own < kComputeUnits ? (kComputeUnits - own) / r.n : 0;
+    constexpr int kAll = kTokens / (kFusedThreads / 64);
+    if (rider == FlowRider::scores) return room >= kAll ? kAll : (room >= kAll / 3 ? (int)room : 0);
+    const int want = rider == FlowRider::prepass ? r.prep->tiles_x * r.prep->tiles_y
+                                                 : (border_items(r.h, r.w) + kFusedThreads - 1) / kFusedThreads;
+    return want <= room ? want : 0;
 }
 
 template <int TX, int TY>
@@ -1219,7 +1228,7 @@ hipError_t launch_fused(const FlowBatch& f, int n, int64_t level_off, int h, int
         return hipGetLastError();
     };
     if (rider == FlowRider::none) return go(NoRide{}, dim3(gx, gy, n));
-    const int per = rider_blocks(rider, *r), blocks = per * r->n;
+    const int per = rider_blocks(rider, *r, own), blocks = per * r->n;
     if (rider == FlowRider::prepass) return go(*r->prep, dim3(own + blocks));
     if (rider == FlowRider::hysteresis) return go(UnionRide{r->prep->f, r->h, r->w, border_items(r->h, r->w), per, blocks}, dim3(own + blocks));
     return go(ScoreRide{*r->pool, r->h, r->w, per, blocks}, dim3(own + blocks));
@@ -1227,9 +1236,6 @@ hipError_t launch_fused(const FlowBatch& f, int n, int64_t level_off, int h, int
 
 }  // namespace
 
-// A fused launch carries a piece if the compute units that its own blocks (one each, by registers or LDS) leave take the
-// riders, those of the pre-pass at once, the others in two rounds: a tile of the pre-pass takes as long as a flow block, 10 us,
-// the others 3 to 5.
 bool flow_launch_carries(FlowRider rider, const FlowRiders& riders, int n, int h, int w, int wanted) {
     long long own = 0;
     switch (fused_tile(n, h, w, wanted)) {
@@ -1238,7 +1244,7 @@ bool flow_launch_carries(FlowRider rider, const FlowRiders& riders, int n, int h
         case Fused::t16x16: own = tiles_of(16, 16, n, h, w); break;
         case Fused::t32x16: own = tiles_of(32, 16, n, h, w); break;
     }
-    return (long long)rider_blocks(rider, riders) * riders.n <= (rider == FlowRider::prepass ? 1 : 2) * (kComputeUnits - own);
+    return rider_blocks(rider, riders, own) > 0;
 }
 
 hipError_t launch_flow_updates(const FlowBatch& f, int n, int64_t level_off, int h, int w, int ch, int cw,
