@@ -429,12 +429,9 @@ int enqueue_expansion(sali_ctx* c, const uint8_t* const* d_rgb, const BatchPlan&
                       hipStream_t s) {
     const LevelGeom& g = c->geom;
     if (fused_expansion(c, bp.n)) {
-        const int rc = enqueue_gray(c, d_rgb, bp, s);
-        if (rc != SALI_OK) return rc;
         ExpandBatch f = {};
         for (int i = 0; i < bp.n; ++i) {
-            const LaneLayout& L = c->sl.lane[bp.lane[i]];
-            f.y8[i] = c->sc<uint8_t>(L.y8);
+            f.rgb[i] = d_rgb[i];
             f.A[i] = c->sc<float4>(c->sl.expA[bp.slot[i]]);
             f.b[i] = c->sc<float>(c->sl.expB[bp.slot[i]]);
         }

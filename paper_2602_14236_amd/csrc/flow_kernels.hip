@@ -87,16 +87,7 @@ __global__ __launch_bounds__(256) void k_pyr_pair(PyrBatch f, LevelGeom g, int l
         for (int k = 0; k < kN; ++k) {
             const int p = min(tid + 256 * k, kItems - 1);
             const int x = qx + 4 * (p % kQuads);
-            const uint8_t* row = rgb + (size_t)clampi(qy + p / kQuads, 0, sh - 1) * sw * 3;
-            if (x >= 0 && x + 3 < sw) {
-                __builtin_memcpy(v[k], row + 3 * x, 12);
-            } else {
-                uint32_t c[12];
-#pragma unroll
-                for (int i = 0; i < 12; ++i) c[i] = row[3 * clampi(x + i / 3, 0, sw - 1) + i % 3];
-#pragma unroll
-                for (int i = 0; i < 3; ++i) v[k][i] = c[4 * i] | (c[4 * i + 1] << 8) | (c[4 * i + 2] << 16) | (c[4 * i + 3] << 24);
-            }
+            load_rgb_quad(rgb + (size_t)clampi(qy + p / kQuads, 0, sh - 1) * sw * 3, x, sw, v[k]);
         }
 #pragma unroll
         for (int k = 0; k < kN; ++k) {
@@ -353,58 +344,42 @@ __device__ __forceinline__ void pyr_level_lds(const float* src, int o_src_y, int
         dst[ry * kDstStride + lds_col<kDstEven>(rx)] = acc;
     }
 }
-// Gray patch of kSide x kSide pixels with origin (qy, qx) (coordinates clamped to the image) into LDS
-// as gray / 255, row stride kStride, columns laid out by lds_col<kEven>.  All of a thread's loads are
-// issued before the first one is used: written as one loop the compiler waits for every byte in turn,
-// up to 37 dependent round trips, and next to a kernel that saturates the memory system each of them
-// takes microseconds.
-template <int kSide, int kStride, int kEven>
-__device__ __forceinline__ void load_gray_patch(const uint8_t* __restrict__ y8, int h0, int w0, int qy, int qx,
-                                                float* __restrict__ dst) {
-    constexpr int kN = (kSide * kSide + 255) / 256;
-    uint8_t v[kN];
+// Patch of kSide x kSide pixels with origin (qy, qx) (coordinates clamped to the image) as gray, straight from the frame: a
+// gray image of its own would be a launch before this one that nothing else reads.  put(row, column, four gray bytes) for
+// every quad of columns.  All of a thread's loads are issued before the first one is used: written as one loop the
+// compiler waits for every one in turn, and next to a kernel that saturates the memory system each takes
+// microseconds.
+template <int kSide, typename Put>
+__device__ __forceinline__ void load_gray_patch(const uint8_t* __restrict__ rgb, int h0, int w0, int qy, int qx, Put put) {
+    constexpr int kQuads = (kSide + 3) / 4, kItems = kSide * kQuads, kN = (kItems + 255) / 256;
+    uint32_t v[kN][3];
 #pragma unroll
     for (int k = 0; k < kN; ++k) {
-        const int p = (int)threadIdx.x + 256 * k;
-        const int pp = p < kSide * kSide ? p : 0;
-        const int ry = pp / kSide, rx = pp % kSide;
-        const int gy = clampi(qy + ry, 0, h0 - 1), gx = clampi(qx + rx, 0, w0 - 1);
-        v[k] = y8[(size_t)gy * w0 + gx];
+        const int p = min((int)threadIdx.x + 256 * k, kItems - 1);
+        load_rgb_quad(rgb + (size_t)clampi(qy + p / kQuads, 0, h0 - 1) * w0 * 3, qx + 4 * (p % kQuads), w0, v[k]);
     }
 #pragma unroll
     for (int k = 0; k < kN; ++k) {
         const int p = (int)threadIdx.x + 256 * k;
-        if (p < kSide * kSide) dst[(p / kSide) * kStride + lds_col<kEven>(p % kSide)] = (float)v[k] / 255.0f;
+        if (p < kItems) put(p / kQuads, 4 * (p % kQuads), gray_of_quad(v[k]));
     }
 }
-
-// The 97 x 97 gray patch of a level-2 tile, origin (qy, qx), coordinates clamped to the image, as bytes:
-// a thread takes four columns at a time (one 32-bit LDS write; one 32-bit load where the four lie inside the
-// image, the compiler is told nothing about its alignment) and has all its loads in flight before the
-// first is used.  As floats the patch took 40 KB and the block 52: three blocks per compute unit, also for
-// the level-0 and level-1 tiles of the same launch, which need none of it; in bytes the block takes 24 KB.
-__device__ __forceinline__ void load_gray_patch_bytes(const uint8_t* __restrict__ y8, int h0, int w0, int qy, int qx,
-                                                      uint32_t* __restrict__ dst) {
-    constexpr int kQuads = (kEQ + 3) / 4, kItems = kEQ * kQuads, kN = (kItems + 255) / 256;
-    uint32_t v[kN];
+// as gray / 255, row stride kStride, columns laid out by lds_col<kEven>
+template <int kSide, int kStride, int kEven>
+__device__ __forceinline__ void load_gray_floats(const uint8_t* __restrict__ rgb, int h0, int w0, int qy, int qx,
+                                                 float* __restrict__ dst) {
+    load_gray_patch<kSide>(rgb, h0, w0, qy, qx, [&](int row, int col, uint32_t quad) {
 #pragma unroll
-    for (int k = 0; k < kN; ++k) {
-        const int p = (int)threadIdx.x + 256 * k;
-        const int pp = p < kItems ? p : 0;
-        const int ry = pp / kQuads, x = qx + 4 * (pp % kQuads);
-        const uint8_t* row = y8 + (size_t)clampi(qy + ry, 0, h0 - 1) * w0;
-        if (x >= 0 && x + 3 < w0) {
-            __builtin_memcpy(&v[k], row + x, 4);
-        } else {
-            v[k] = (uint32_t)row[clampi(x, 0, w0 - 1)] | ((uint32_t)row[clampi(x + 1, 0, w0 - 1)] << 8) |
-                   ((uint32_t)row[clampi(x + 2, 0, w0 - 1)] << 16) | ((uint32_t)row[clampi(x + 3, 0, w0 - 1)] << 24);
-        }
-    }
-#pragma unroll
-    for (int k = 0; k < kN; ++k) {
-        const int p = (int)threadIdx.x + 256 * k;
-        if (p < kItems) dst[(p / kQuads) * (kEQB / 4) + p % kQuads] = v[k];
-    }
+        for (int i = 0; i < 4; ++i)
+            if (col + i < kSide) dst[row * kStride + lds_col<kEven>(col + i)] = (float)((quad >> (8 * i)) & 0xFFu) / 255.0f;
+    });
+}
+// The 97 x 97 patch of a level-2 tile, as bytes.  As floats it took 40 KB and the block 52: three blocks per
+// compute unit, also for the level-0 and level-1 tiles of the same launch, which need none of it; in bytes the block
+// takes 24 KB.
+__device__ __forceinline__ void load_gray_bytes(const uint8_t* __restrict__ rgb, int h0, int w0, int qy, int qx,
+                                                uint32_t* __restrict__ dst) {
+    load_gray_patch<kEQ>(rgb, h0, w0, qy, qx, [&](int row, int col, uint32_t quad) { dst[row * (kEQB / 4) + col / 4] = quad; });
 }
 
 // First pyramid level of a level-2 tile from the byte patch: the 5x5 binomial sum in integers (weights
@@ -468,7 +443,7 @@ __global__ __launch_bounds__(256) void k_expand(ExpandBatch f, LevelGeom g, int 
         frame = idx / t1;
         t = idx - frame * t1;
     }
-    const uint8_t* __restrict__ y8 = f.y8[frame];
+    const uint8_t* __restrict__ rgb = f.rgb[frame];
     float4* __restrict__ A_out = f.A[frame];
     float* __restrict__ b_out = f.b[frame];
     uint32_t (&s_qb)[kEQ * (kEQB / 4)] = sh.own.qb;
@@ -487,17 +462,17 @@ __global__ __launch_bounds__(256) void k_expand(ExpandBatch f, LevelGeom g, int 
     const int h0 = g.h[0], w0 = g.w[0];
 
     if (lvl == 0) {
-        load_gray_patch<kER, kER, 0>(y8, h, w, oy, ox, &s_f[0][0]);
+        load_gray_floats<kER, kER, 0>(rgb, h, w, oy, ox, &s_f[0][0]);
     } else if (lvl == 1) {
         const int qy = 2 * oy - 2, qx = 2 * ox - 2;              // origin of the gray patch (47 x 47)
-        load_gray_patch<kEP, kEPS, kEvenP>(y8, h0, w0, qy, qx, s_p);
+        load_gray_floats<kEP, kEPS, kEvenP>(rgb, h0, w0, qy, qx, s_p);
         __syncthreads();
         pyr_level_lds<kEPS, kEvenP, kER, 0, kER, kER>(s_p, qy, qx, &s_f[0][0], oy, ox, h, w);
     } else {
         const int h1 = g.h[1], w1 = g.w[1];
         const int py = 2 * oy - 2, px = 2 * ox - 2;              // origin of the level-1 patch (47 x 47)
         const int qy = 2 * py - 2, qx = 2 * px - 2;              // origin of the gray patch (97 x 97)
-        load_gray_patch_bytes(y8, h0, w0, qy, qx, s_qb);
+        load_gray_bytes(rgb, h0, w0, qy, qx, s_qb);
         __syncthreads();
         pyr_level_from_bytes<kEPS, kEvenP, kEP, kEP + 1>(reinterpret_cast<const uint8_t*>(s_qb), qy, qx, s_p, py, px, h1,
                                                          w1);

@@ -140,7 +140,7 @@ struct GateParams {
 // updates re-read both frames' expansions once per update: at 1920x1080 that is most of the image
 // side's HBM traffic).
 struct ExpandBatch {
-    const uint8_t* y8[kMaxBatch];
+    const uint8_t* rgb[kMaxBatch];
     float4* A[kMaxBatch];
     float* b[kMaxBatch];
 };
@@ -253,6 +253,19 @@ __device__ __forceinline__ uint32_t gray_of_quad(const uint32_t* w) {
     const uint32_t g2 = gray_of((w[1] >> 16) & 0xFF, w[1] >> 24, w[2] & 0xFF);
     const uint32_t g3 = gray_of((w[2] >> 8) & 0xFF, (w[2] >> 16) & 0xFF, w[2] >> 24);
     return g0 | (g1 << 8) | (g2 << 16) | (g3 << 24);
+}
+// the four pixels from column x of an image row of w pixels, coordinates clamped: twelve bytes at any address, as one load
+// where they lie inside the row
+__device__ __forceinline__ void load_rgb_quad(const uint8_t* __restrict__ row, int x, int w, uint32_t (&v)[3]) {
+    if (x >= 0 && x + 3 < w) {
+        __builtin_memcpy(v, row + 3 * x, 12);
+    } else {
+        uint32_t c[12];
+#pragma unroll
+        for (int i = 0; i < 12; ++i) c[i] = row[3 * clampi(x + i / 3, 0, w - 1) + i % 3];
+#pragma unroll
+        for (int i = 0; i < 3; ++i) v[i] = c[4 * i] | (c[4 * i + 1] << 8) | (c[4 * i + 2] << 16) | (c[4 * i + 3] << 24);
+    }
 }
 #endif
 

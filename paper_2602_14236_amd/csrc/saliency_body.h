@@ -147,16 +147,7 @@ __device__ __forceinline__ void prep_tile(PrepShared& sh, const PrepBatch& f, in
     for (int k = 0; k < kPrepQuads; ++k) {
         const int p = min(tid + k * NT, kReg * kQuadsY - 1);
         const int x = x0 - kHalo + 4 * (p % kQuadsY);
-        const uint8_t* row = rgb + (size_t)clampi(y0 - kHalo + p / kQuadsY, 0, h - 1) * w * 3;
-        if (x >= 0 && x + 3 < w) {
-            __builtin_memcpy(crgb[k], row + 3 * x, 12);
-        } else {
-            uint32_t c[12];
-#pragma unroll
-            for (int i = 0; i < 12; ++i) c[i] = row[3 * clampi(x + i / 3, 0, w - 1) + i % 3];
-#pragma unroll
-            for (int i = 0; i < 3; ++i) crgb[k][i] = c[4 * i] | (c[4 * i + 1] << 8) | (c[4 * i + 2] << 16) | (c[4 * i + 3] << 24);
-        }
+        load_rgb_quad(rgb + (size_t)clampi(y0 - kHalo + p / kQuadsY, 0, h - 1) * w * 3, x, w, crgb[k]);
     }
     u32x4 lut[kLutQuads];
 #pragma unroll
