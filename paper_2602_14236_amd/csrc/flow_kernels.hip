@@ -771,11 +771,12 @@ __global__ __launch_bounds__(kSmallThreads) void k_flow_small(FlowBatch f, long 
 //
 // Three 1920x1080 frames: 73 us an update, one: 28, fifteen 640x360: 45.  With the windows on the vector ALU (110
 // multiply-adds and as many LDS reads a pixel and 1.6 rows of halo, 32x16 tiles, per-cell index arithmetic, divisions)
-// 518 vector instructions a pixel kept the ALU 91 % busy: 102, 37 and 59 us.  Now it is 60 % busy and the trips of
-// the warped samples bound the kernel: 12 000 of a block's 21 000 cycles.  Everything that costs a block or a wave shows: 16 waves a block (32x32 on 1024 threads)
-// 100 us, registers spilled under the 64 that eight waves per SIMD leave 94 to 140 (five fields' products in step,
-// or marching down a strip while ten rows of sums stay in LDS), 48-wide tiles 104 to 121; 64x32 on 1024
-// threads is as fast but needs sixteen free wave slots on one compute unit.  The same windows as banded matrix products
+// 518 vector instructions a pixel kept the ALU 91 % busy: 102, 37 and 59 us.  Now it is 45 % busy (260 instructions)
+// and the trips of the warped samples bound the kernel: 12 000 of a block's 21 000 cycles.  Everything that costs a block
+// or a wave shows: 16 waves a block (32x32 on 1024 threads) 100 us, registers spilled under the 64 that eight waves per
+// SIMD leave 94 to 140 (five fields' products in step, or marching down a strip while ten rows of sums stay in LDS),
+// 48-wide tiles 104 to 121; 64x32 on 1024 threads is as fast but needs sixteen free wave slots on one compute unit.  The
+// same windows as banded matrix products
 // (v_mfma_f32_16x16x4f32, the row pass's result the column pass's operand) took 100: 28 and 32 terms for eleven.
 constexpr int kTileX = 32, kTileThreads = 512;
 //

@@ -34,8 +34,8 @@
 
 namespace sali {
 
-// gray only, blockIdx.y = frame of the batch: what the flow needs of a frame.  The rest of the spatial
-// filter waits until the reuse rule has spoken.  Sixteen pixels per thread (48 bytes in, 16 out) where
+// gray only, blockIdx.y = frame of the batch: what the flow needs of a frame with a single, large level (elsewhere the
+// kernels that read gray values convert them).  Sixteen pixels per thread (48 bytes in, 16 out) where
 // the caller's image is 16-byte aligned, else pixel by pixel.
 __global__ __launch_bounds__(256) void k_gray(PrepBatch f, int n) {
     const uint8_t* __restrict__ rgb = f.rgb[blockIdx.y];

@@ -68,7 +68,7 @@ def test_identical_frames_are_exactly_static():
     ctx.close()
 
 
-# with three updates a level: 360x640 is too large for updates in one launch and takes 32x16 tiles; 300x500 does so with
+# with three updates a level: 360x640 is too large for updates in one launch and takes 32x32 tiles; 300x500 does so with
 # ragged ones; the other levels fit the chip and have their three updates in one launch, 200x200 and 200x264 with ragged
 # 16x16 tiles, the smaller ones with 16x8 (test_updates_per_launch goes along both rules)
 @pytest.mark.parametrize("h,w,levels", [(24, 24, 1), (50, 77, 2), (97, 131, 3), (360, 640, 3), (200, 264, 5),
@@ -192,7 +192,7 @@ def test_pyramid_in_pairs_of_levels(h, w, levels, shift):
     (24, 25, 1, 3), (49, 33, 2, 3), (128, 129, 1, 4), (170, 168, 2, 3),                       # three in one: 16x8 tiles
     (181, 243, 1, 3), (240, 433, 2, 3),                                                       # 16x16; 32x16, then 16x8
     (100, 90, 3, 1), (100, 90, 3, 2), (100, 90, 3, 7), (430, 440, 1, 3),                      # single updates, both mixed, too large
-    (199, 200, 1, 2), (200, 200, 1, 2), (200, 264, 2, 1), (211, 199, 1, 2),                   # a launch each: 16x16 below 40 000 pixels, 32x16 from there
+    (199, 200, 1, 2), (200, 200, 1, 2), (200, 264, 2, 1), (211, 199, 1, 2),                   # a launch each: 16x16 tiles (the larger tiles: test_single_updates_of_larger_levels)
 ])
 def test_updates_per_launch(h, w, levels, iters):
     """Three updates of a small level in one launch, over its tile shapes, ragged tiles, frames smaller than the
