@@ -626,7 +626,11 @@ int wait_unless_same(hipStream_t s, hipStream_t recorded_on, hipEvent_t ev) {
 // Where they may, sali_step frame by frame at 336x336 is 3.5 % faster (two packets of 3.4 us a frame).
 bool events_may_attach(hipStream_t s) {
     hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
-    return hipStreamIsCapturing(s, &status) == hipSuccess && status == hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(s, &status) != hipSuccess) {
+        (void)hipGetLastError();            // the question's failure, not the next launch's
+        return false;
+    }
+    return status == hipStreamCaptureStatusNone;
 }
 
 // Device address of `scratch` on the current device, looked up once per device (with that device
