@@ -26,11 +26,11 @@ inline size_t align_up(size_t v) { return (v + kAlign - 1) / kAlign * kAlign; }
 
 // Image-side scratch exists in kLanes copies (one per frame in flight) so that the analyses of
 // many frames can be in flight at once, in one batch or on different streams; polynomial expansions
-// live in a ring one longer than that (a frame's flow reads its predecessor's expansion), plus two
-// slots for the stand-alone flow call.
+// live in a ring that is longer by the tiles of a video frame (an analysis' flow reads the expansion of the
+// same tile of the frame before, so many analyses back, and a batch waits only for the analysis kLanes back), plus
+// two slots for the stand-alone flow call.
 constexpr int kLanes = SALI_ANALYSIS_LANES;
-constexpr int kStepSlots = kLanes + 1;
-constexpr int kExpSlots = kStepSlots + 2;
+constexpr int kExpSlots = kLanes + kMaxTiles + 2;      // at most: step_slots() + 2 are used
 constexpr int kRing = 2 * kLanes;     // bookkeeping of the most recent analyses
 static_assert(kLanes >= 2 * kMaxBatch, "two batches in flight");
 
@@ -44,6 +44,12 @@ struct ScratchLayout {
     size_t attn_partial;
     size_t total;
 };
+
+// cache entries (images) per video frame
+int tiles_of(const sali_config& cfg) { return cfg.tiles_per_frame > 1 ? cfg.tiles_per_frame : 1; }
+
+// expansion slots of the analyses; the two of the stand-alone flow call follow
+int step_slots(const sali_config& cfg) { return kLanes + tiles_of(cfg); }
 
 struct TableLayout {
     size_t lut, cursors, rows, tier, slot, order, total;      // lut: the colour tables (kColourLutBytes)
@@ -177,7 +183,7 @@ ScratchLayout scratch_layout(const sali_config& c, const LevelGeom& g) {
             L.flow[1] = take(hw * sizeof(float2));
         }
     }
-    for (int i = 0; i < kExpSlots; ++i) {
+    for (int i = 0; i < step_slots(c) + 2; ++i) {
         s.expA[i] = take(px * sizeof(float4));
         s.expB[i] = take(px * sizeof(float));
     }
@@ -573,9 +579,6 @@ TierParams tier_params(const sali_config& cfg) {
     return tp;
 }
 
-// cache entries per video frame
-int tiles_of(const sali_config& cfg) { return cfg.tiles_per_frame > 1 ? cfg.tiles_per_frame : 1; }
-
 // rows that a stored frame keeps under the tier rule in force: exact with top-k counts, else as if it kept all
 // tokens in one tier
 RowsPerFrame kept_per_frame(const sali_config& cfg) {
@@ -834,10 +837,10 @@ int sali_flow_score(sali_ctx* c, const uint8_t* d_prev_rgb, const uint8_t* d_cur
     pair.n = 2;
     for (int i = 0; i < 2; ++i) {
         pair.lane[i] = kLanes + i;
-        pair.slot[i] = kStepSlots + i;
+        pair.slot[i] = step_slots(c->cfg) + i;
     }
     pair.prev_slot[0] = -1;
-    pair.prev_slot[1] = kStepSlots;
+    pair.prev_slot[1] = pair.slot[0];
     const uint8_t* const d_rgb[2] = {d_prev_rgb, d_cur_rgb};
     int rc = enqueue_expansion(c, d_rgb, pair, nullptr, nullptr, s);
     if (rc != SALI_OK) return rc;
@@ -954,7 +957,7 @@ int sali_analyze_batch(sali_ctx* c, const uint8_t* const* d_rgb_frames, int32_t 
     if (c->cfg.budget_tokens > 0 && first_frame_id <= c->last_frame_id) return SALI_ERR_STATE;
     // tiled frames come whole: entries t T .. t T + T - 1 in one call, and analysis number = entry number
     // modulo T, so that an entry's predecessor (the same tile of the frame before) is T analyses back
-    const int tiles = c->cfg.tiles_per_frame > 1 ? c->cfg.tiles_per_frame : 1;
+    const int tiles = tiles_of(c->cfg);
     if (first_frame_id % tiles != 0 || n_frames % tiles != 0) return SALI_ERR_SHAPE;
     if (first_frame_id + n_frames - 1 > c->last_frame_id) c->last_frame_id = first_frame_id + n_frames - 1;
     hipStream_t s = static_cast<hipStream_t>(stream);
@@ -962,18 +965,19 @@ int sali_analyze_batch(sali_ctx* c, const uint8_t* const* d_rgb_frames, int32_t 
     const unsigned n_last = n0 + (unsigned)n_frames - 1u;
     BatchPlan bp = {};
     bp.n = n_frames;
+    const unsigned slots = (unsigned)step_slots(c->cfg);
     for (int i = 0; i < n_frames; ++i) {
         const unsigned n = n0 + (unsigned)i;
         bp.lane[i] = (int)(n % kLanes);
-        bp.slot[i] = (int)(n % kStepSlots);
-        bp.prev_slot[i] = n >= (unsigned)tiles ? (int)((n - (unsigned)tiles) % kStepSlots) : -1;
+        bp.slot[i] = (int)(n % slots);
+        bp.prev_slot[i] = n >= (unsigned)tiles ? (int)((n - (unsigned)tiles) % slots) : -1;
         bp.parity[i] = c->lane_uses[bp.lane[i]]++ & 1u;      // alternates per saliency pass in the lane
     }
     const AnalysisRecord* prev = n0 >= 1 ? &c->ring[c->ring[(n0 - 1) % kRing].batch_last] : nullptr;
     int rc;
-    // A lane's scratch and expansion slot were last used by the analysis kLanes before (the slot
-    // was read last by that one's successor's flow, which finished before it in tier order); tier
-    // order also means the latest of them finishing implies that the others have.
+    // A lane's scratch was last used by the analysis kLanes before.  An expansion slot was written by the analysis
+    // kLanes + tiles before and read last by the flow of the same tile of the next frame, tiles later: the analysis
+    // kLanes before again.  Tier order means that the latest of them finishing implies that the others have.
     if (n_last >= (unsigned)kLanes) {
         const AnalysisRecord& old = c->ring[c->ring[(n_last - kLanes) % kRing].batch_last];
         rc = wait_unless_same(s, old.stream, old.done);

@@ -170,3 +170,34 @@ def test_attention_counts_pointer_entries_of_every_tile(T, room):
             assert np.all(np.abs(out.cpu().numpy() - exp) <= bound), (q_per_kv, lo, hi)
             assert np.all(np.abs(lse.cpu().numpy() - exp_lse) <= lse_bound), (q_per_kv, lo, hi)
     ctx.close()
+
+
+@pytest.mark.parametrize("T,entries", [(2, 16), (8, 8), (3, 15), (8, 16)])
+def test_tiled_frames_on_several_streams_equal_the_one_stream_path(T, entries):
+    """More entries than there are scratch copies, `entries` a call in turn on three image streams: the frame-table rows of
+    every entry and the motions and gates of the last 30 or 32 are those of the same calls on one stream."""
+    from paper_2602_14236_amd import binding
+    n = (4 * 32 // entries) * entries
+    p = params(96, 96, flow_levels=2, tier_mode=1, k_fp16=100, k_int8=200, k_int4=100, n_layers=1, n_heads=1,
+               cap_fp16=100 * n, cap_int8=200 * n, cap_int4=100 * n, max_frames=n, tiles_per_frame=T)
+    rgbs = [torch.from_numpy(drift_frame(0.37 * (e // T) * (1 + e % T))).cuda() for e in range(n)]
+    streams = [torch.cuda.Stream() for _ in range(3)]
+
+    def analysed(streams):
+        ctx = binding.SaliContext(lib_config(p))
+        torch.cuda.synchronize()
+        for k, lo in enumerate(range(0, n, entries)):
+            ctx.analyze_batch(rgbs[lo:lo + entries], lo, streams[k % len(streams)])
+        torch.cuda.synchronize()
+        left = [ctx.read_analysis(e) for e in range(n - 32 // entries * entries, n)]
+        rows = [r.as_tuple() for r in ctx.read_frame_table(0, n)]
+        assert ctx.get_status() == 0
+        ctx.close()
+        return rows, [(dp.tobytes(), (g.n_static, g.r_frame, g.redundant)) for dp, g, _ in left]
+
+    rows, left = analysed(streams[:1])
+    print(f"stored {sum(r[2] for r in rows)} of {n}", flush=True)
+    for _ in range(3):
+        got_rows, got = analysed(streams)
+        assert got_rows == rows
+        assert got == left
