@@ -263,6 +263,11 @@ int sali_step(sali_ctx* ctx, const uint8_t* d_rgb_t, const void* d_kv_t, int32_t
  * sali_saliency_pool uses one of the scratch copies: do not run it while analyses are in flight on
  * other streams.  sali_flow_score has scratch of its own and may run next to analyses and to
  * sali_saliency_pool; only calls of it on one context must not overlap each other.
+ * Under stream capture the streams of a context's calls must not wait on each other in both directions (the runtime does
+ * not survive the end of such a capture): the call that would close the circle, for instance the third of three analyses
+ * that alternate over two streams, or a store on the first of them of a frame that was analysed on the second, is refused with
+ * SALI_ERR_STATE, and that call has changed and enqueued nothing (of sali_step_pipelined: the half that would wait).  Go on from the stream that was changed to, and store on
+ * that one or on a stream of its own.
  *
  * sali_store: packs `d_kv_fp16` into the pools according to the row that sali_analyze wrote.
  * Makes `stream` wait (on the device) for that frame's analysis if it ran on another stream.

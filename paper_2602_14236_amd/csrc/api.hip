@@ -5,6 +5,7 @@
 #include <math.h>
 #include <mutex>
 #include <new>
+#include <stdlib.h>
 #include <string.h>
 
 #include "hysteresis.h"
@@ -285,6 +286,17 @@ struct AnalysisRecord {
     int batch_last;           // ring entry whose events cover this frame (the last frame of its batch)
 };
 
+// which stream of a capture the library has made wait on which, for the capture that it saw last
+struct CaptureWaits {
+    struct Pair {
+        hipStream_t stream, on;
+        bool followed;
+    };
+    unsigned long long id;
+    int n, room;
+    Pair* pair;               // malloc'ed, room entries
+};
+
 struct sali_ctx {
     sali_config cfg;
     LevelGeom geom;
@@ -299,6 +311,7 @@ struct sali_ctx {
     unsigned n_analysed;      // analyses since create / reset; analysis n uses lane n % kLanes
     unsigned lane_uses[kLanes];   // saliency passes run in each lane; the parity selects the frame-sum accumulator
     AnalysisRecord ring[kRing];
+    CaptureWaits capture;
     hipEvent_t prof[3][2];    // [SALI_PROF_*][start, stop], armed for one launch
     int device;               // the GPU that was current in sali_create (the buffers live there)
     float* static_scratch;    // that GPU's copy of the library's own partial-result array
@@ -624,6 +637,59 @@ int wait_unless_same(hipStream_t s, hipStream_t recorded_on, hipEvent_t ev) {
     return SALI_OK;
 }
 
+// does `stream` wait on `on`, directly or through other streams?
+bool waits_on(CaptureWaits& w, hipStream_t stream, hipStream_t on) {
+    for (int i = 0; i < w.n; ++i) w.pair[i].followed = false;
+    auto reached = [&](hipStream_t x) {
+        if (x == stream) return true;
+        for (int i = 0; i < w.n; ++i)
+            if (w.pair[i].followed && w.pair[i].on == x) return true;
+        return false;
+    };
+    for (bool more = true; more;) {
+        more = false;
+        for (int i = 0; i < w.n; ++i)
+            if (!w.pair[i].followed && reached(w.pair[i].stream)) w.pair[i].followed = more = true;
+    }
+    return reached(on);
+}
+
+// May stream `s` be made to wait on the n streams on[]?  Not while it is being captured and one of them waits on it, directly
+// or through others: hipStreamEndCapture has ended in a segmentation fault where streams of a capture waited on each other in
+// both directions (analyses that alternate over two streams, from the third batch on).  Asked before a call changes or enqueues
+// anything; eager calls with one stream ask nothing of the runtime.
+int check_capture_waits(sali_ctx* c, hipStream_t s, const hipStream_t* on, int n) {
+    bool other = false;
+    for (int i = 0; i < n; ++i) other = other || on[i] != s;
+    if (!other) return SALI_OK;
+    hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+    unsigned long long id = 0;
+    if (hipStreamGetCaptureInfo(s, &status, &id) != hipSuccess) {
+        (void)hipGetLastError();            // not to be asked: not a stream that is captured
+        return SALI_OK;
+    }
+    if (status != hipStreamCaptureStatusActive) return SALI_OK;
+    CaptureWaits& w = c->capture;
+    if (w.id != id) w.n = 0;
+    w.id = id;
+    for (int i = 0; i < n; ++i)
+        if (on[i] != s && waits_on(w, on[i], s)) return SALI_ERR_STATE;
+    for (int i = 0; i < n; ++i) {
+        bool known = on[i] == s;
+        for (int k = 0; k < w.n; ++k) known = known || (w.pair[k].stream == s && w.pair[k].on == on[i]);
+        if (known) continue;
+        if (w.n == w.room) {
+            const int room = w.room == 0 ? 16 : 2 * w.room;
+            void* p = realloc(w.pair, (size_t)room * sizeof(CaptureWaits::Pair));
+            if (p == nullptr) return SALI_ERR_STATE;
+            w.pair = static_cast<CaptureWaits::Pair*>(p);
+            w.room = room;
+        }
+        w.pair[w.n++] = {s, on[i], false};
+    }
+    return SALI_OK;
+}
+
 // May the events of an analysis be recorded by its launches?  Not while the stream is being captured: the dependence of another
 // stream's work on an event that a launch records does not become an edge of the graph (one recorded by a call does).
 // Where they may, sali_step frame by frame at 336x336 is 3.5 % faster (two packets of 3.4 us a frame).
@@ -780,6 +846,7 @@ int sali_create(const sali_config* cfg, void* d_scratch, void* d_pools, void* d_
 void sali_destroy(sali_ctx* ctx) {
     if (ctx == nullptr) return;
     destroy_events(ctx);
+    free(ctx->capture.pair);
     delete ctx;
 }
 
@@ -959,10 +1026,19 @@ int sali_analyze_batch(sali_ctx* c, const uint8_t* const* d_rgb_frames, int32_t 
     // modulo T, so that an entry's predecessor (the same tile of the frame before) is T analyses back
     const int tiles = tiles_of(c->cfg);
     if (first_frame_id % tiles != 0 || n_frames % tiles != 0) return SALI_ERR_SHAPE;
-    if (first_frame_id + n_frames - 1 > c->last_frame_id) c->last_frame_id = first_frame_id + n_frames - 1;
     hipStream_t s = static_cast<hipStream_t>(stream);
     const unsigned n0 = c->n_analysed;                  // analysis number of the batch's first frame
     const unsigned n_last = n0 + (unsigned)n_frames - 1u;
+    // the batch before, and the one that used the same scratch last (see below)
+    const AnalysisRecord* prev = n0 >= 1 ? &c->ring[c->ring[(n0 - 1) % kRing].batch_last] : nullptr;
+    const AnalysisRecord* old = n_last >= (unsigned)kLanes ? &c->ring[c->ring[(n_last - kLanes) % kRing].batch_last] : nullptr;
+    int rc;
+    {
+        const hipStream_t on[2] = {prev != nullptr ? prev->stream : s, old != nullptr ? old->stream : s};
+        rc = check_capture_waits(c, s, on, 2);
+        if (rc != SALI_OK) return rc;
+    }
+    if (first_frame_id + n_frames - 1 > c->last_frame_id) c->last_frame_id = first_frame_id + n_frames - 1;
     BatchPlan bp = {};
     bp.n = n_frames;
     const unsigned slots = (unsigned)step_slots(c->cfg);
@@ -973,14 +1049,11 @@ int sali_analyze_batch(sali_ctx* c, const uint8_t* const* d_rgb_frames, int32_t 
         bp.prev_slot[i] = n >= (unsigned)tiles ? (int)((n - (unsigned)tiles) % slots) : -1;
         bp.parity[i] = c->lane_uses[bp.lane[i]]++ & 1u;      // alternates per saliency pass in the lane
     }
-    const AnalysisRecord* prev = n0 >= 1 ? &c->ring[c->ring[(n0 - 1) % kRing].batch_last] : nullptr;
-    int rc;
     // A lane's scratch was last used by the analysis kLanes before.  An expansion slot was written by the analysis
     // kLanes + tiles before and read last by the flow of the same tile of the next frame, tiles later: the analysis
     // kLanes before again.  Tier order means that the latest of them finishing implies that the others have.
-    if (n_last >= (unsigned)kLanes) {
-        const AnalysisRecord& old = c->ring[c->ring[(n_last - kLanes) % kRing].batch_last];
-        rc = wait_unless_same(s, old.stream, old.done);
+    if (old != nullptr) {
+        rc = wait_unless_same(s, old->stream, old->done);
         if (rc != SALI_OK) return rc;
     }
     // the batch's events live in the ring entry of its last frame
@@ -1065,6 +1138,7 @@ int sali_store_batch(sali_ctx* c, const void* const* d_kv_frames, int32_t first_
     hipStream_t s = static_cast<hipStream_t>(stream);
     // every frame must have been analysed recently; wait once per batch of analyses
     const AnalysisRecord* waits[kMaxBatch];
+    hipStream_t on[kMaxBatch];
     int n_waits = 0;
     for (int f = 0; f < n_frames; ++f) {
         const AnalysisRecord* rec = nullptr;
@@ -1072,10 +1146,15 @@ int sali_store_batch(sali_ctx* c, const void* const* d_kv_frames, int32_t first_
             if (c->ring[i].frame_id == first_frame_id + f) rec = &c->ring[i];
         if (rec == nullptr) return SALI_ERR_STATE;      // not analysed (or too long ago)
         const AnalysisRecord* ev = &c->ring[rec->batch_last];
-        if (n_waits == 0 || waits[n_waits - 1] != ev) waits[n_waits++] = ev;
+        if (n_waits == 0 || waits[n_waits - 1] != ev) {
+            on[n_waits] = ev->stream;
+            waits[n_waits++] = ev;
+        }
     }
+    int rc = check_capture_waits(c, s, on, n_waits);
+    if (rc != SALI_OK) return rc;
     for (int i = 0; i < n_waits; ++i) {
-        const int rc = wait_unless_same(s, waits[i]->stream, waits[i]->done);
+        rc = wait_unless_same(s, waits[i]->stream, waits[i]->done);
         if (rc != SALI_OK) return rc;
     }
     return enqueue_pack(c, d_kv_frames, first_frame_id, n_frames, s);
@@ -1167,7 +1246,8 @@ int sali_read_analysis(sali_ctx* c, int32_t frame_id, float* h_patch_motion576, 
     const unsigned n = last - ((last + (unsigned)kRing - (unsigned)slot) % (unsigned)kRing);
     if (c->n_analysed - n > (unsigned)kLanes) return SALI_ERR_STATE;
     const AnalysisRecord& ev = c->ring[c->ring[slot].batch_last];
-    const int rc = wait_unless_same(s, ev.stream, ev.done);
+    int rc = check_capture_waits(c, s, &ev.stream, 1);
+    if (rc == SALI_OK) rc = wait_unless_same(s, ev.stream, ev.done);
     if (rc != SALI_OK) return rc;
     const LanePtrs lp = c->lane_ptrs((int)(n % kLanes));
     if (h_patch_motion576 != nullptr)

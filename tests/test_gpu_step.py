@@ -490,3 +490,64 @@ def test_captured_calls_on_several_streams_replay():
             one_pass()
         assert left()[0] == ref_rows
     ctx.close()
+
+
+def test_capture_refuses_streams_that_wait_on_each_other():
+    """Three analyses that alternate over two streams under capture, and a store on the first stream of a frame analysed on
+    the second: each would make the streams wait on each other in both directions, and is refused with nothing changed, so
+    that the capture goes on on the stream that was changed to and the graph leaves what the same eager calls leave.  The
+    same calls are taken without capture, and by the next capture."""
+    from paper_2602_14236_amd import binding
+    wl = synth.WORKLOADS[5]
+    n = 9
+    v = synth.video(5, 32)
+    p = workload_params(wl, frames=n, n_layers=1, n_heads=2)
+    scale = synth.kv_channel_scale(wl, 1, 2)
+    rgbs = [torch.from_numpy(v.frame(t)).cuda() for t in range(n)]
+    kvs = [synth.kv_frame(wl, t, device="cuda", n_layers=1, n_heads=2, scale=scale) for t in range(n)]
+    ctx = binding.SaliContext(lib_config(p))
+    images, kv_stream, main = [torch.cuda.Stream(), torch.cuda.Stream()], torch.cuda.Stream(), torch.cuda.Stream()
+
+    def one_pass(order, refused=()):
+        here = torch.cuda.current_stream()
+        ctx.reset()
+        for s in images + [kv_stream]:
+            s.wait_stream(here)
+        for b in range(3):
+            if b in refused:
+                with pytest.raises(binding.SaliError) as e:
+                    ctx.analyze_batch(rgbs[3 * b:3 * b + 3], 3 * b, images[0])
+                assert e.value.code == -5
+                with pytest.raises(binding.SaliError) as e:
+                    ctx.store_batch(kvs[3:6], 3, images[0])
+                assert e.value.code == -5
+            ctx.analyze_batch(rgbs[3 * b:3 * b + 3], 3 * b, images[order[b]])
+        for b in range(3):
+            ctx.store_batch(kvs[3 * b:3 * b + 3], 3 * b, kv_stream)
+        for s in images + [kv_stream]:
+            here.wait_stream(s)
+
+    def left():
+        torch.cuda.synchronize()
+        return [r.as_tuple() for r in ctx.read_frame_table(0, n)], {k: a.clone() for k, a in ctx.pool_views_flat().items()}
+
+    ctx.pools.zero_()
+    with torch.cuda.stream(main):
+        one_pass((0, 1, 0))
+    ref_rows, ref_pools = left()
+    for first in (0, 1):                                    # the second capture starts from the other stream
+        images = images[::-1] if first else images
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=main):
+            one_pass((0, 1, 1), refused=(2,))
+        for replay in range(3):
+            ctx.pools.zero_()
+            torch.cuda.synchronize()
+            graph.replay()
+            rows, pools = left()
+            assert rows == ref_rows, f"replay {replay}"
+            assert all(torch.equal(pools[k], ref_pools[k]) for k in ref_pools), f"replay {replay}"
+            with torch.cuda.stream(main):
+                one_pass((0, 1, 0))
+            assert left()[0] == ref_rows
+    ctx.close()
