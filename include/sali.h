@@ -245,7 +245,8 @@ int sali_kv_decompress(sali_ctx* ctx, int32_t frame_id, void* d_kv_fp16_out,
  * the spatial filter go by the reuse rule evaluated from the motions and leave at once for a redundant
  * frame, so such a frame costs its temporal filter and nothing else (Algorithm 1).  Small batches (up to 512 tiles of
  * 32x32 pixels, 256 a frame) leave the GPU idle behind every launch: there the spatial filter runs next to the
- * temporal filter, and what it finds for a redundant frame is not used. */
+ * temporal filter as far as it finds room, what it finds for a redundant frame is not used, and only the rest of it
+ * is left out for such a frame. */
 int sali_step(sali_ctx* ctx, const uint8_t* d_rgb_t, const void* d_kv_t, int32_t frame_id,
               void* stream);
 

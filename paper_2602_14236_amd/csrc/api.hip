@@ -408,19 +408,22 @@ int enqueue_saliency(sali_ctx* c, const uint8_t* const* d_rgb, const BatchPlan& 
     const GateParams gp = gate_params(c);
     SALI_TRY(launch_prep(f, bp.n, cfg.src_h, cfg.src_w, gp, c->tb<uint8_t>(c->tl.lut),
                          cfg.canny_lo * cfg.canny_lo, cfg.canny_hi * cfg.canny_hi, s));
-    SALI_TRY(launch_union(f, bp.n, cfg.src_h, cfg.src_w, s));
+    SALI_TRY(launch_union(f, bp.n, cfg.src_h, cfg.src_w, nullptr, s));
     return SALI_OK;
 }
 
 // Does the spatial filter of a batch ride on the launches of its temporal filter, before the gate has spoken?  The two need
 // nothing of each other until then, and where a batch is a chain of launches that leave the chip idle the pre-pass next to
 // the coarsest flow updates (or, with no room there, the expansions), the hysteresis next to the updates after them and the
-// scores next to the last cost little of what they cost behind the flow (29 us of 85 for one 336x336 frame; sali_step
-// 680 -> 568 us for eight frames, of which three are redundant).  Redundant frames get scores that nobody uses.  So it is done up to two tiles of the
-// pre-pass per compute unit in a batch, one in a frame; K/V kernels next to it or not, eight to sixteen frames:
-//   336x336 x 4: 3 redundant of 8 426 -> 410 us, none 438 -> 418; with 16 layers 760 -> 732, 992 -> 953
-//   640x360 x 2: 769 -> 755, none redundant 919 -> 861; 427x241 x 3: 447 -> 406; 270x480, none: 837 -> 680
-//   800x600 (475 tiles, not done): 3 redundant of 8 1173 -> 1209, none 1333 -> 1232
+// scores next to the last cost little of what they cost behind the flow (29 us of 85 for one 336x336 frame).  Redundant
+// frames get scores that nobody uses; pieces that found no launch run behind the flow and leave such frames out.  Done up to
+// two tiles of the pre-pass per compute unit in a batch, one in a frame.  Sixteen frames (clips 32), one layer of 32 heads, us,
+// with seven of eight frames redundant / three / none, all behind the flow -> riding:
+//   frame by frame  336x336 1183 / 1436 / 1625 -> 1070 / 1131 / 1179, one update a level 888 / 1147 / 1331 -> 912 / 1054 / 1172
+//                   512x512 1429 / 1746 / 1982 -> 1492 / 1641 / 1759, 640x360 1430 / 1756 / 1976 -> 1581 / 1652 / 1691
+//   clips           336x336 x 4 682 / 756 / 777 -> 689 / 710 / 719, 640x360 x 2 1309 / 1469 / 1644 -> 1369 / 1473 / 1562
+// so a stream of 640x360 loses by it if more than three frames of four are redundant (its pre-pass finds room on the
+// expansions only and lengthens them: 9 us a redundant frame).  800x600 (475 tiles, not done): three redundant of eight, eight frames 1173 -> 1209.
 bool saliency_rides(const sali_ctx* c, int n_frames) {
     constexpr long long kComputeUnits = 256;
     const long long tiles = (long long)((c->cfg.src_w + kTile - 1) / kTile) * ((c->cfg.src_h + kTile - 1) / kTile);
@@ -567,7 +570,7 @@ int enqueue_motion(sali_ctx* c, const BatchPlan& bp, const float2* const* flow, 
 // d_salmap redirect the outputs of a stand-alone single-frame call.
 int enqueue_scores(sali_ctx* c, const BatchPlan& bp, float* d_scores_or_null, uint8_t* d_salmap, hipStream_t s) {
     const PoolBatch f = pool_batch(c, bp, d_scores_or_null, nullptr);
-    SALI_TRY(launch_scores(f, bp.n, c->cfg.src_h, c->cfg.src_w, d_salmap, s));
+    SALI_TRY(launch_scores(f, bp.n, c->cfg.src_h, c->cfg.src_w, d_salmap, nullptr, s));
     return SALI_OK;
 }
 
@@ -1089,9 +1092,12 @@ int sali_analyze_batch(sali_ctx* c, const uint8_t* const* d_rgb_frames, int32_t 
     if (rc == SALI_OK) rc = enqueue_motion(c, bp, flow, s);
     if (rc != SALI_OK) return rc;
     if (rides) {
-        // what found no launch to ride on
-        if (next == FlowRider::hysteresis) SALI_TRY(launch_union(prep.f, n_frames, c->cfg.src_h, c->cfg.src_w, s));
-        if (next != FlowRider::none) SALI_TRY(launch_scores(pool, n_frames, c->cfg.src_h, c->cfg.src_w, nullptr, s));
+        // what found no launch to ride on; the motions are known now, so not for redundant frames
+        const GateParams gp = gate_params(c);
+        if (next == FlowRider::hysteresis)
+            SALI_TRY(launch_union(prep_batch(c, d_rgb_frames, bp, true, flow), n_frames, c->cfg.src_h, c->cfg.src_w, &gp, s));
+        if (next != FlowRider::none)
+            SALI_TRY(launch_scores(pool_batch(c, bp, nullptr, flow), n_frames, c->cfg.src_h, c->cfg.src_w, nullptr, &gp, s));
     } else {
         // then the spatial filter, for the frames the reuse rule does not find redundant (Algorithm 1: a
         // redundant frame bypasses it): every kernel from here on evaluates the rule from the motions

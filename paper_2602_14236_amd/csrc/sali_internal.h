@@ -307,16 +307,18 @@ hipError_t launch_attend(const sali_frame_row* d_rows, Pools pools, int layer, i
 // n = frames in the batch (1..kMaxBatch).  launch_gray: RGB -> gray only.  launch_prep: the edge / colour
 // variance pre-pass; frames that the reuse rule finds redundant from
 // f.dp are skipped (Algorithm 1: their saliency is not computed) and marked in f.skip, which launch_union
-// and launch_pool go by.
+// and launch_scores go by.  With a gate these two evaluate the rule from f.dp themselves (behind a pre-pass that ran
+// ahead of the flow).
 hipError_t launch_gray(const PrepBatch& f, int n, int h, int w, hipStream_t s);
 hipError_t launch_prep(const PrepBatch& f, int n, int h, int w, GateParams gp, const void* d_lut,
                        int lo2, int hi2, hipStream_t s);
-hipError_t launch_union(const PrepBatch& f, int n, int h, int w, hipStream_t s);
+hipError_t launch_union(const PrepBatch& f, int n, int h, int w, const GateParams* gate_or_null, hipStream_t s);
 // launch_motion: Eq. 5, per-patch motion of every frame of the batch from its flow (0 without flow).
-// launch_scores: Eq. 7 scores (none for frames marked in f.skip); d_salmap_or_null applies to frame 0 (stand-alone call).
+// launch_scores: Eq. 7 scores (none for redundant frames); d_salmap_or_null applies to frame 0 (stand-alone call).
 // launch_tail: evaluates the gate and assigns tiers for the n frames in order, and records done_or_null.
 hipError_t launch_motion(const PoolBatch& f, int n, int h, int w, hipStream_t s);
-hipError_t launch_scores(const PoolBatch& f, int n, int h, int w, uint8_t* d_salmap_or_null, hipStream_t s);
+hipError_t launch_scores(const PoolBatch& f, int n, int h, int w, uint8_t* d_salmap_or_null, const GateParams* gate_or_null,
+                         hipStream_t s);
 hipError_t launch_tail(const PoolBatch& f, int n, const TierLaunch& tier, GateParams gp, uint32_t* d_done_counter,
                        hipEvent_t done_or_null, hipStream_t s);
 

@@ -71,8 +71,15 @@ __global__ __launch_bounds__(NT) void k_prep(PrepBatch f, int h, int w, GatePara
 // hysteresis, cross-tile part; blockIdx.y = frame of the batch.  A thread per border pixel: with a thread per
 // image pixel, nearly all of them idle, and walks to the root also between strong components sixteen 640x360
 // frames took 44 us in the pipeline, one frame alone 16.8; now 23.5 and 9.6 (chains of trips past the L2).
-__global__ __launch_bounds__(256) void k_union(PrepBatch f, int h, int w, int n_items) {
-    if (*f.skip[blockIdx.y] != 0u) return;          // redundant frame, says the pre-pass
+// kGated: the pre-pass ran ahead of the flow and could not ask the reuse rule; it is evaluated here, from the motions.
+template <bool kGated>
+__global__ __launch_bounds__(256) void k_union(PrepBatch f, int h, int w, int n_items, GateParams gp) {
+    if constexpr (kGated) {
+        __shared__ int s_cnt[4];
+        if (frame_redundant<256>(f.dp, (int)blockIdx.y, gp, s_cnt)) return;
+    } else {
+        if (*f.skip[blockIdx.y] != 0u) return;      // redundant frame, says the pre-pass
+    }
     union_item(f, (int)blockIdx.y, h, w, (int)(blockIdx.x * 256 + threadIdx.x), n_items);
 }
 
@@ -202,8 +209,9 @@ __device__ __forceinline__ void pool_tail(TierShared& sh, int* s_cnt, const Pool
 // such a fence writes back and invalidates the issuing XCD's L2: with 144 blocks per frame it made the
 // K/V kernels running next to it 7 % slower (5 400 -> 5 700 frames/s without), and at 1920x1080 (576
 // blocks per frame) it cost the pooling kernel itself 110 us per four-frame launch against 33 us of work.
-template <int kWaves, bool kMotion>
-__global__ __launch_bounds__(kTierThreads) void k_pool(PoolBatch f, int h, int w, uint8_t* __restrict__ salmap) {
+// kGated: as in k_union.
+template <int kWaves, bool kMotion, bool kGated>
+__global__ __launch_bounds__(kTierThreads) void k_pool(PoolBatch f, int h, int w, uint8_t* __restrict__ salmap, GateParams gp) {
     static_assert(kTierThreads == 256, "four waves, one patch each");
     static_assert(kWaves == 1 || kWaves == 4, "");
     const int b = blockIdx.y;                               // frame of the batch
@@ -213,7 +221,12 @@ __global__ __launch_bounds__(kTierThreads) void k_pool(PoolBatch f, int h, int w
     constexpr int kStride = 64 * kWaves;
     if constexpr (!kMotion) {
         __shared__ uint32_t s_pq[kTierThreads / 64];
-        if (*f.skip[b] != 0u) return;                       // redundant frame, says the pre-pass
+        if constexpr (kGated) {
+            __shared__ int s_cnt[kTierThreads / 64];
+            if (frame_redundant<kTierThreads>(f.dp, b, gp, s_cnt)) return;
+        } else {
+            if (*f.skip[b] != 0u) return;                   // redundant frame, says the pre-pass
+        }
         if constexpr (kWaves == 1) {
             score_by_wave(f, b, token, h, w, salmap);
         } else {
@@ -288,30 +301,35 @@ hipError_t launch_prep(const PrepBatch& f, int n, int h, int w, GateParams gp, c
     return hipGetLastError();
 }
 
-hipError_t launch_union(const PrepBatch& f, int n, int h, int w, hipStream_t s) {
+hipError_t launch_union(const PrepBatch& f, int n, int h, int w, const GateParams* gate_or_null, hipStream_t s) {
     const int items = border_items(h, w);
     if (items == 0) return hipSuccess;              // a single tile
-    hipLaunchKernelGGL(k_union, dim3((items + 255) / 256, n), dim3(256), 0, s, f, h, w, items);
+    const dim3 grid((items + 255) / 256, n);
+    if (gate_or_null != nullptr) hipLaunchKernelGGL(k_union<true>, grid, dim3(256), 0, s, f, h, w, items, *gate_or_null);
+    else hipLaunchKernelGGL(k_union<false>, grid, dim3(256), 0, s, f, h, w, items, GateParams{});
     return hipGetLastError();
 }
+
+namespace {
+// patches of up to 1024 pixels: one wave each
+template <bool kMotion, bool kGated>
+hipError_t launch_patches(const PoolBatch& f, int n, int h, int w, uint8_t* d_salmap, const GateParams& gp, hipStream_t s) {
+    if ((long long)h * w <= 1024ll * kTokens)
+        hipLaunchKernelGGL((k_pool<1, kMotion, kGated>), dim3(kTokens / 4, n), dim3(kTierThreads), 0, s, f, h, w, d_salmap, gp);
+    else
+        hipLaunchKernelGGL((k_pool<4, kMotion, kGated>), dim3(kTokens, n), dim3(kTierThreads), 0, s, f, h, w, d_salmap, gp);
+    return hipGetLastError();
+}
+}  // namespace
 
 hipError_t launch_motion(const PoolBatch& f, int n, int h, int w, hipStream_t s) {
-    // patches of up to 1024 pixels: one wave each
-    if ((long long)h * w <= 1024ll * kTokens) {
-        hipLaunchKernelGGL((k_pool<1, true>), dim3(kTokens / 4, n), dim3(kTierThreads), 0, s, f, h, w, nullptr);
-    } else {
-        hipLaunchKernelGGL((k_pool<4, true>), dim3(kTokens, n), dim3(kTierThreads), 0, s, f, h, w, nullptr);
-    }
-    return hipGetLastError();
+    return launch_patches<true, false>(f, n, h, w, nullptr, GateParams{}, s);
 }
 
-hipError_t launch_scores(const PoolBatch& f, int n, int h, int w, uint8_t* d_salmap_or_null, hipStream_t s) {
-    if ((long long)h * w <= 1024ll * kTokens) {
-        hipLaunchKernelGGL((k_pool<1, false>), dim3(kTokens / 4, n), dim3(kTierThreads), 0, s, f, h, w, d_salmap_or_null);
-    } else {
-        hipLaunchKernelGGL((k_pool<4, false>), dim3(kTokens, n), dim3(kTierThreads), 0, s, f, h, w, d_salmap_or_null);
-    }
-    return hipGetLastError();
+hipError_t launch_scores(const PoolBatch& f, int n, int h, int w, uint8_t* d_salmap_or_null, const GateParams* gate_or_null,
+                         hipStream_t s) {
+    return gate_or_null != nullptr ? launch_patches<false, true>(f, n, h, w, d_salmap_or_null, *gate_or_null, s)
+                                   : launch_patches<false, false>(f, n, h, w, d_salmap_or_null, GateParams{}, s);
 }
 
 hipError_t launch_tail(const PoolBatch& f, int n, const TierLaunch& tier, GateParams gp, uint32_t* d_done_counter,
