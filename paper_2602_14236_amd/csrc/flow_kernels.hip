@@ -886,7 +886,8 @@ __global__ __launch_bounds__(kTileThreads, 8) void k_flow_tile(FlowBatch f, long
 // 18.0 -> 12.4, two frames of it 18.1 -> 14.9 (16x16), 336x336 19.2 -> 17.5 (32x16).  With more than one
 // block per compute unit it loses (168x168 x 4: 21.5 against 27).  All of that on an idle chip, one launch after
 // the other; next to kernels that fill the wave slots a block of 1024 threads waits longer for room than the three
-// launches take.  The results are the same numbers.
+// launches take.  The results are the same bits (tests/test_gpu_step.py: calls of one to sixteen frames, whose levels take other
+// kernels).
 // Cells outside the image stand for the clamped coordinate, as in k_flow_tile.
 constexpr int kFusedUpdates = 3;
 constexpr int kFusedThreads = 1024;

@@ -434,9 +434,45 @@ def test_spatial_filter_next_to_the_temporal_filter(h, w, levels, iters, n):
             alone.flow_score(rgbs[t - 1], rgbs[t], uv, ref_dp, torch.zeros(4, dtype=torch.int32, device="cuda"))
         assert not gate.redundant
         assert np.array_equal(scores, ref_scores.cpu().numpy()), f"frame {t}"
-        assert close(dp, ref_dp.cpu().numpy()).all(), f"frame {t}"          # batches take other tiles: sums in another order
+        assert close(dp, ref_dp.cpu().numpy()).all(), f"frame {t}"          # the stand-alone call sums a patch's pixels in another order
     ctx.close()
     alone.close()
+
+
+@pytest.mark.parametrize("h,w,levels,iters", [
+    (84, 84, 1, 1), (200, 264, 1, 2),                                          # 16x16, 32x16 and 32x32 tiles, a launch an update
+    (97, 131, 3, 3), (270, 480, 3, 3),                                         # three updates a launch in each of its tiles, or one
+    (241, 427, 4, 7), (360, 640, 3, 3),                                        # both mixed; too large for three in one
+])
+def test_motions_do_not_depend_on_the_batch_size(h, w, levels, iters):
+    """The number of frames in a call decides which kernels and tiles make the updates of a level, on the vector ALU or the matrix
+    cores: motions, gates and scores of a frame are the same bits in calls of 1, 2, 4, 8 and 16.  The texture moves by a tenth of
+    a pixel at the left and more than one at the right, so that patches lie on both sides of the threshold and next to it."""
+    from paper_2602_14236_amd import binding
+    rng = np.random.default_rng(h * 7 + w)
+    yy, xx = np.mgrid[0:h, 0:w].astype(np.float64)
+    rgbs = []
+    for t in range(16):
+        x, y = xx - (0.1 + 1.2 * xx / w) * t, yy + 0.1 * t
+        img = 120 + 60 * np.sin(x / 4.1) * np.sin(y / 5.3) + 50 * np.sin((x - y) / 3.0)
+        img = img[..., None] * np.array([1.0, 0.8, 0.6]) + rng.normal(0, 2, (h, w, 3))
+        rgbs.append(torch.from_numpy(np.clip(np.rint(img), 0, 255).astype(np.uint8)).cuda())
+    cfg = lib_config(params(h, w, flow_levels=levels, flow_iters=iters, max_frames=16))
+    ref = None
+    for n in (1, 2, 4, 8, 16):
+        ctx = binding.SaliContext(cfg)
+        for lo in range(0, 16, n):
+            ctx.analyze_batch(rgbs[lo:lo + n], lo)
+        got = []
+        for t in range(16):
+            dp, gate, scores = ctx.read_analysis(t)
+            got.append((dp.tobytes(), gate.n_static, gate.r_frame, gate.redundant, None if gate.redundant else scores.tobytes()))
+        ctx.close()
+        if ref is None:
+            ref = got
+            print(f"{h}x{w}: static patches {[g[1] for g in got]}", flush=True)
+            assert all(0 < g[1] < 576 for g in got[1:])
+        assert got == ref, f"{n} frames a call: frames {[t for t in range(16) if got[t] != ref[t]]} differ"
 
 
 @pytest.mark.parametrize("h,w,levels,iters,n,tiles", [
