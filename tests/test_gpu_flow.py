@@ -217,7 +217,7 @@ def test_updates_per_launch(h, w, levels, iters):
 @pytest.mark.parametrize("h,w,shift", [
     (353, 577, (0.9, -1.3)), (383, 607, (-2.6, 3.4)), (512, 481, (6.0, 5.0)),      # 32x32 tiles: one row and column over, ragged, exact rows
     (270, 929, (0.9, -1.3)), (259, 947, (-2.6, 3.4)),                              # 32x16: a column over, three rows over
-    (480, 97, (3.0, -6.0)), (97, 480, (-6.0, 3.0)),                                # 16x16, a round and more
+    (480, 97, (3.0, -6.0)), (97, 480, (-6.0, 3.0)), (2050, 43, (0.9, -1.3)),       # 16x16, 210 blocks; 387, a round and a half
 ])
 def test_single_updates_of_larger_levels(h, w, shift):
     """Two updates, a launch each, in every tile shape, with windows and warped samples that reach past all four borders

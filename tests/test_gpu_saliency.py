@@ -119,10 +119,10 @@ def test_weak_chains_across_tile_borders_and_corners(h, w):
         ctx.close()
 
 
-@pytest.mark.parametrize("h,w", [(512, 512), (513, 480), (545, 610)])
+@pytest.mark.parametrize("h,w", [(512, 512), (513, 480), (513, 512), (545, 610)])
 def test_block_sizes_of_the_pre_pass(h, w):
-    """A tile per compute unit (256 tiles, the last size on 1024 threads), one row more and ragged (512 threads): textured
-    halves, and pure noise with a low threshold, whose tiles are full of weak chains."""
+    """A tile per compute unit (256 tiles, the last count on 1024 threads; 255 with ragged ones), the next row of tiles (272, on 512
+    threads) and more: textured halves, and pure noise with a low threshold, whose tiles are full of weak chains."""
     from paper_2602_14236_amd import binding
     ctx = binding.SaliContext(lib_config(params(h, w, flow_levels=1, canny_lo=8, canny_hi=120)))
     rng = np.random.default_rng(h + w)
