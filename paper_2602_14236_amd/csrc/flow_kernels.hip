@@ -643,7 +643,7 @@ __device__ __forceinline__ f32x4 fir4(const FirWeights& w, const float* v) {
     for (int k = 0; k < kFirIn; ++k) acc = __builtin_amdgcn_mfma_f32_4x4x1f32(w.k[k], v[k], acc, 0, 0, 0);
     return acc;
 }
-// four outputs of the row pass from sixteen floats at p (16-byte aligned; the last two count nothing, but have to be finite)
+// four outputs of the row pass from sixteen floats at p (16-byte aligned; the last two come with the fourth load and are not used)
 __device__ __forceinline__ f32x4 fir4_row(const FirWeights& w, const float* p) {
     float v[16];
 #pragma unroll
@@ -801,11 +801,6 @@ __global__ __launch_bounds__(kTileThreads, 8) void k_flow_tile(FlowBatch f, long
     const int tid = threadIdx.x, wave0 = tid & ~63;
     const int x0 = blk.x * TX, y0 = blk.y * TY;
     fir_table(s_w, fw);
-    // columns RX .. P - 1 of the last group of a row: weight zero, but a number
-    if (tid < RY * (P - RX)) {
-#pragma unroll
-        for (int c = 0; c < 5; ++c) s_in[c][(tid / (P - RX)) * P + RX + tid % (P - RX)] = 0.0f;
-    }
     {
         // per-cell terms at the clamped coordinate of the cell: a thread stays in its column (of 504 threads, twelve
         // rows at a time), so that only the row's coordinate changes
