@@ -352,7 +352,7 @@ struct BatchPlan {
 };
 
 // Pyramid and polynomial expansion in one launch (k_expand: every tile rebuilds the pyramid values it
-// needs from the gray image in LDS) or in steps (k_pyr_pair per two levels, then k_polyexp).  The fused
+// needs from the RGB frame in LDS) or in steps (k_pyr_pair per two levels, then k_polyexp).  The fused
 // launch saves two dependent launches, but does several times the work per
 // pixel (a 16x16 tile of level 2 reads a 97x97 gray patch), so it is the choice only while the launch
 // chain, not the work, bounds a batch: up to three levels and small frames.  Measured in the pipeline,
@@ -1064,7 +1064,8 @@ int sali_analyze_batch(sali_ctx* c, const uint8_t* const* d_rgb_frames, int32_t 
     const bool attach = events_may_attach(s);
     // the temporal filter first: gray, pyramid + expansion, flow, per-patch motion.  Where the spatial filter rides along its
     // frames are all taken as not redundant (no motions yet).  Its pre-pass goes with the coarsest flow updates where the two
-    // fit one block per compute unit, else with the expansions.
+    // fit one block per compute unit, else with the expansions, whose event then covers it too (the flow of a next batch on another
+    // stream starts behind it).
     const bool rides = saliency_rides(c, n_frames);
     PoolBatch pool = {};
     PrepRide prep;

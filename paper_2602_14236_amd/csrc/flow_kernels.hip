@@ -6,7 +6,7 @@
 //
 //   k_expand     pyramid (5x5 binomial [1 4 6 4 1]/16, stride 2; level 0 is gray / 255) and
 //                polynomial expansion of up to three levels in ONE launch: 16x16 tiles, the pyramid
-//                values a tile needs are rebuilt from the gray image in LDS; separable moments,
+//                values a tile needs are rebuilt from the RGB frame in LDS; separable moments,
 //                closed-form solution of the 6-unknown weighted least-squares fit
 //   k_pyr_pair, k_polyexp   the same for more than three levels and larger frames: gray image and two
 //                pyramid levels per launch, the pyramid in HBM, then the expansion of all levels
@@ -289,7 +289,7 @@ __global__ __launch_bounds__(256) void k_polyexp(PyrBatch f, LevelGeom g, FlowWe
 
 // ---------------------------------------------------------------------------------------------
 // Pyramid + expansion in one launch for up to three levels: a block owns one 16x16 tile of one
-// level and rebuilds the pyramid values it needs from the gray image in LDS (level 1 from a 47x47
+// level and rebuilds the pyramid values it needs from the RGB frame in LDS (level 1 from a 47x47
 // gray patch, level 2 from a 47x47 level-1 patch built from a 97x97 gray patch).  This recomputes
 // some pyramid pixels but removes two dependent launches and all pyramid traffic.
 namespace {

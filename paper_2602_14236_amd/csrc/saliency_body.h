@@ -117,7 +117,7 @@ __device__ __forceinline__ int grad_m2(uint32_t g) {
     return __builtin_amdgcn_sdot2(v, v, 0, false);
 }
 
-// Tile (bx, by) of frame bz of the batch, by a block of 256 threads.  kGated: frames that the reuse rule finds redundant are
+// Tile (bx, by) of frame bz of the batch, by a block of NT (256, 512 or 1024) threads.  kGated: frames that the reuse rule finds redundant are
 // left out; without it (a launch that runs before the flow) all are done.
 template <bool kGated, int NT>
 __device__ __forceinline__ void prep_tile(PrepShared& sh, const PrepBatch& f, int bx, int by, int bz, int h, int w, const GateParams& gp,
@@ -357,8 +357,8 @@ __device__ __forceinline__ void prep_tile(PrepShared& sh, const PrepBatch& f, in
         atomicAdd(msum_acc, t);
     }
 
-    // stage 5: non-maximum suppression + class.  Four pixels per thread: pixel p = tid + 256 q sits in tile row
-    // p / 32, so a wave always holds two complete tile rows.
+    // stage 5: non-maximum suppression + class.  kPrepPx pixels per thread (four of 256 threads, one of 1024): pixel
+    // p = tid + NT q sits in tile row p / 32, so a wave always holds two complete tile rows.
     const int tx = tid % kTile;
     const int gx = x0 + tx;
     int cls[kPrepPx];
@@ -469,8 +469,8 @@ __device__ __forceinline__ void prep_tile(PrepShared& sh, const PrepBatch& f, in
     __syncthreads();
     // each pixel's global link: the global key of a strong pixel of its component or, without one, of the
     // component's smallest key in this tile (itself for pixels that are no edge candidates).  Tile-local
-    // row-major order agrees with image row-major order, so "smallest" means the same in both.  The four
-    // walks of a thread go in step, and every pixel's link follows its walk: all walks of the tile move at
+    // row-major order agrees with image row-major order, so "smallest" means the same in both.  The
+    // walks of a thread's pixels go in step, and every pixel's link follows its walk: all walks of the tile move at
     // once, so what a walk meets has been shortened as often as itself (no root changes any more).
     uint32_t root[kPrepPx];
 #pragma unroll
