@@ -643,6 +643,17 @@ __device__ __forceinline__ f32x4 fir4(const FirWeights& w, const float* v) {
     for (int k = 0; k < kFirIn; ++k) acc = __builtin_amdgcn_mfma_f32_4x4x1f32(w.k[k], v[k], acc, 0, 0, 0);
     return acc;
 }
+// N windows abreast: consecutive products do not wait for one another (one window's follow each other every four cycles at best)
+template <int N>
+__device__ __forceinline__ void fir4_abreast(const FirWeights& w, const float (&v)[N][16], f32x4* acc) {
+    __builtin_amdgcn_sched_barrier(0);      // all reads ahead of the products: taken as they go they cost an LDS trip every few
+#pragma unroll
+    for (int n = 0; n < N; ++n) acc[n] = (f32x4){0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+    for (int k = 0; k < kFirIn; ++k)
+#pragma unroll
+        for (int n = 0; n < N; ++n) acc[n] = __builtin_amdgcn_mfma_f32_4x4x1f32(w.k[k], v[n][k], acc[n], 0, 0, 0);
+}
 // four outputs of the row pass from sixteen floats at p (16-byte aligned; the last two come with the fourth load and are not used)
 __device__ __forceinline__ f32x4 fir4_row(const FirWeights& w, const float* p) {
     float v[16];
@@ -891,78 +902,88 @@ template <int TX, int TY>
 struct FusedTile {
     static constexpr int SX = TX + 10 * kFusedUpdates, SY = TY + 10 * kFusedUpdates;      // the first update's terms
     static constexpr int PX = SX - 10, PY = SY - 10;                                      // the first update's results
-    float in[5][SY][SX];
+    static constexpr int SP = (SX + 3) / 4 * 4, kFloats = 5 * SY * SP;
+    alignas(16) float in[kFloats];
     float2 p[SY * SX];          // priors of the first update, then of the third
     float2 q[PY * PX];          // priors of the second update
+    float w[kFirTable];
 };
 
 // Update I of the block: terms of its region plus five cells all round, window passes, solve; the priors
 // (region of the terms, row-major) come from `prior`, the results go to `next` or, the last ones, to d_out.
+// The row pass runs on the matrix cores, as in k_flow_tile, over quads of outputs of one field, dealt to all waves: 1.5 -> 1.2, 0.92 ->
+// 0.76 and 0.56 -> 0.32 us of a 168x168 level's three updates.  The column pass stays on the vector ALU, two outputs an item: on the
+// matrix cores, five fields and four outputs a lane, it is a chain of 70 products and four solves on a quarter of the waves (0.6 -> 0.84 us
+// of the last update).  A region that is no multiple of four has outputs past its end, which nothing uses, and the zero weights of its last outputs meet cells past its end.  Those must
+// be finite: terms of other cells or of an earlier update, or the padding of the first update's rows, which is cleared.
 template <int TX, int TY, int I>
 __device__ __forceinline__ void fused_update(FusedTile<TX, TY>& sh, float2* prior, float2* next, const float4* __restrict__ A1,
                                              const float* __restrict__ b1, const float4* __restrict__ A2,
                                              const float* __restrict__ b2, const float2* __restrict__ d_in,
                                              float2* __restrict__ d_out, int h, int w, int ch, int cw, int prior_mode, int x0,
-                                             int y0, const FlowWeights& fw) {
+                                             int y0, FirWeights& wt, const FlowWeights& fw) {
     constexpr int kLeft = kFusedUpdates - 1 - I, NT = kFusedThreads;
     constexpr int DX = TX + 10 * kLeft, DY = TY + 10 * kLeft, RX = DX + 10, RY = DY + 10;
-    const int tid = threadIdx.x;
+    constexpr int P = (RX + 3) / 4 * 4;             // row stride: the row pass reads sixteen bytes at a time
+    const int tid = threadIdx.x, wave0 = tid & ~63;
     const int ox = x0 - 5 * (kLeft + 1), oy = y0 - 5 * (kLeft + 1);
-#pragma unroll 2
-    for (int p = tid; p < RX * RY; p += NT) {
-        const int ry = p / RX, rx = p % RX;
-        const int gy = clampi(oy + ry, 0, h - 1), gx = clampi(ox + rx, 0, w - 1);
-        float2 dp;
-        if constexpr (I == 0) {
-            dp = prior_at(d_in, prior_mode, gy, gx, w, ch, cw);
-            prior[p] = dp;
-        } else {
-            dp = prior[(gy - oy) * RX + (gx - ox)];         // the clamped cell lies in the region: the tile meets the image
-        }
-        float t[5];
-        flow_terms(A1, b1, A2, b2, h, w, gy, gx, dp, t);
+    {
+        // a thread stays in its column, kRows rows at a time, and asks for the priors of all its cells before the first sample
+        constexpr int kRows = NT / RX, kSteps = (RY + kRows - 1) / kRows;
+        const int rx = tid % RX, r0 = tid / RX;
+        const int gx = clampi(ox + rx, 0, w - 1);
+        if (r0 < kRows) {
+            float2 dp[kSteps];
 #pragma unroll
-        for (int c = 0; c < 5; ++c) sh.in[c][ry][rx] = t[c];
+            for (int k = 0; k < kSteps; ++k) {
+                const int ry = min(r0 + k * kRows, RY - 1), gy = clampi(oy + ry, 0, h - 1);
+                if constexpr (I == 0) dp[k] = prior_at(d_in, prior_mode, gy, gx, w, ch, cw);
+                else dp[k] = prior[(gy - oy) * RX + (gx - ox)];     // the clamped cell lies in the region: the tile meets the image
+            }
+#pragma unroll
+            for (int k = 0; k < kSteps; ++k) {
+                const int ry = r0 + k * kRows;
+                if (k == kSteps - 1 && ry >= RY) continue;
+                const int gy = clampi(oy + ry, 0, h - 1);
+                if constexpr (I == 0) prior[ry * RX + rx] = dp[k];
+                float t[5];
+                flow_terms(A1, b1, A2, b2, h, w, gy, gx, dp[k], t);
+#pragma unroll
+                for (int c = 0; c < 5; ++c) sh.in[(c * RY + ry) * P + rx] = t[c];
+            }
+        }
     }
     __syncthreads();
-    // Window passes, two outputs an item: twelve reads a field for two outputs; with one the passes
-    // wait for LDS, with four too few lanes have work.  Row pass in place, as in k_flow_tile.
+    if constexpr (I == 0) wt = fir_weights(sh.w);
     {
-        constexpr int kItems = RY * (DX / 2), kN = (kItems + NT - 1) / NT;
-        static_assert(DX % 2 == 0 && DY % 2 == 0, "pairs");
-        float acc[kN][5][2];
+        // Row pass in place, as in k_flow_tile, an item four outputs of one field: the rows of the five fields follow one another.
+        constexpr int kQuads = (DX + 3) / 4, kItems = 5 * RY * kQuads, kN = (kItems + NT - 1) / NT;
+        static_assert((5 * RY - 1) * P + 4 * (kQuads - 1) + 16 <= FusedTile<TX, TY>::kFloats, "reads end inside the array");
+        f32x4 r[kN];
+        auto rows = [&](auto count) {
+            float v[count()][16];
 #pragma unroll
-        for (int n = 0; n < kN; ++n) {
-            const int p = tid + n * NT;
-            if (p >= kItems) continue;
-            const int ry = p / (DX / 2), cx = 2 * (p % (DX / 2));
+            for (int n = 0; n < count(); ++n) {
+                const int item = min(tid + n * NT, kItems - 1);
+                const float* p = &sh.in[(item / kQuads) * P + 4 * (item % kQuads)];
 #pragma unroll
-            for (int c = 0; c < 5; ++c) {
-                float v[12];
-#pragma unroll
-                for (int k = 0; k < 12; ++k) v[k] = sh.in[c][ry][cx + k];
-                acc[n][c][0] = acc[n][c][1] = 0.0f;
-#pragma unroll
-                for (int k = 0; k <= 2 * kWinR; ++k) {
-                    acc[n][c][0] += fw.win_g[k] * v[k];
-                    acc[n][c][1] += fw.win_g[k] * v[k + 1];
-                }
+                for (int i = 0; i < 4; ++i) *reinterpret_cast<f32x4*>(v[n] + 4 * i) = *reinterpret_cast<const f32x4*>(p + 4 * i);
             }
-        }
+            fir4_abreast<count()>(wt, v, r);
+        };
+        // whole waves have either all of their kN items or all but the last
+        if (wave0 + (kN - 1) * NT < kItems) rows(std::integral_constant<int, kN>{});
+        else if constexpr (kN > 1) rows(std::integral_constant<int, kN - 1>{});
         __syncthreads();
 #pragma unroll
         for (int n = 0; n < kN; ++n) {
-            const int p = tid + n * NT;
-            if (p >= kItems) continue;
-            const int ry = p / (DX / 2), cx = 2 * (p % (DX / 2));
-#pragma unroll
-            for (int c = 0; c < 5; ++c) {
-                sh.in[c][ry][cx] = acc[n][c][0];
-                sh.in[c][ry][cx + 1] = acc[n][c][1];
-            }
+            const int item = tid + n * NT;
+            if (item < kItems) *reinterpret_cast<f32x4*>(&sh.in[(item / kQuads) * P + 4 * (item % kQuads)]) = r[n];
         }
         __syncthreads();
     }
+    // Column pass, two outputs an item: twelve reads a field for two outputs
+    static_assert(DY % 2 == 0, "pairs");
     for (int p = tid; p < (DY / 2) * DX; p += NT) {
         const int ty0 = 2 * (p / DX), tx = p % DX;
         float acc[5][2];
@@ -970,7 +991,7 @@ __device__ __forceinline__ void fused_update(FusedTile<TX, TY>& sh, float2* prio
         for (int c = 0; c < 5; ++c) {
             float v[12];
 #pragma unroll
-            for (int k = 0; k < 12; ++k) v[k] = sh.in[c][ty0 + k][tx];
+            for (int k = 0; k < 12; ++k) v[k] = sh.in[(c * RY + ty0 + k) * P + tx];
             acc[c][0] = acc[c][1] = 0.0f;
 #pragma unroll
             for (int k = 0; k <= 2 * kWinR; ++k) {
@@ -1044,9 +1065,16 @@ __global__ __launch_bounds__(kFusedThreads) void k_flow_fused(FlowBatch f, long 
     float2* __restrict__ d_out = f.d_out[blk.z];
     FusedTile<TX, TY>& sh = lds.own;
     const int x0 = blk.x * TX, y0 = blk.y * TY;
-    fused_update<TX, TY, 0>(sh, sh.p, sh.q, A1, b1, A2, b2, d_in, d_out, h, w, ch, cw, prior_mode, x0, y0, fw);
-    fused_update<TX, TY, 1>(sh, sh.q, sh.p, A1, b1, A2, b2, d_in, d_out, h, w, ch, cw, prior_mode, x0, y0, fw);
-    fused_update<TX, TY, 2>(sh, sh.p, sh.q, A1, b1, A2, b2, d_in, d_out, h, w, ch, cw, prior_mode, x0, y0, fw);
+    fir_table(sh.w, fw);
+    constexpr int kPad = FusedTile<TX, TY>::SP - FusedTile<TX, TY>::SX;
+    if constexpr (kPad > 0) {
+        for (int p = threadIdx.x; p < 5 * FusedTile<TX, TY>::SY * kPad; p += kFusedThreads)
+            sh.in[(p / kPad + 1) * FusedTile<TX, TY>::SP - 1 - p % kPad] = 0.0f;
+    }
+    FirWeights wt;
+    fused_update<TX, TY, 0>(sh, sh.p, sh.q, A1, b1, A2, b2, d_in, d_out, h, w, ch, cw, prior_mode, x0, y0, wt, fw);
+    fused_update<TX, TY, 1>(sh, sh.q, sh.p, A1, b1, A2, b2, d_in, d_out, h, w, ch, cw, prior_mode, x0, y0, wt, fw);
+    fused_update<TX, TY, 2>(sh, sh.p, sh.q, A1, b1, A2, b2, d_in, d_out, h, w, ch, cw, prior_mode, x0, y0, wt, fw);
 }
 
 // ---------------------------------------------------------------------------------------------
