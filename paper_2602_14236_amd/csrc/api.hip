@@ -376,16 +376,16 @@ PrepBatch prep_batch(sali_ctx* c, const uint8_t* const* d_rgb, const BatchPlan& 
     for (int i = 0; i < bp.n; ++i) {
         const LaneLayout& L = c->sl.lane[bp.lane[i]];
         unsigned long long* msum = c->sc<unsigned long long>(L.msum);
-        f.rgb[i] = d_rgb[i];
-        f.y8[i] = c->sc<uint8_t>(L.y8);
-        f.cls[i] = c->sc<uint8_t>(L.cls);
-        f.var[i] = c->sc<uint32_t>(L.var);
-        f.parent[i] = c->sc<uint32_t>(L.parent);
-        f.msum_acc[i] = with_saliency ? msum + (bp.parity[i] & 1u) : nullptr;
-        f.msum_clear[i] = with_saliency ? msum + ((bp.parity[i] + 1u) & 1u) : nullptr;
+        f.frame[i].rgb = d_rgb[i];
+        f.frame[i].y8 = c->sc<uint8_t>(L.y8);
+        f.frame[i].cls = c->sc<uint8_t>(L.cls);
+        f.frame[i].var = c->sc<uint32_t>(L.var);
+        f.frame[i].parent = c->sc<uint32_t>(L.parent);
+        f.frame[i].msum_acc = with_saliency ? msum + (bp.parity[i] & 1u) : nullptr;
+        f.frame[i].msum_clear = with_saliency ? msum + ((bp.parity[i] + 1u) & 1u) : nullptr;
         // a frame with a predecessor has per-patch motions by the time the pre-pass runs: the reuse rule applies
-        f.dp[i] = (flow_or_null != nullptr && flow_or_null[i] != nullptr) ? c->lane_ptrs(bp.lane[i]).dp : nullptr;
-        f.skip[i] = &c->lane_ptrs(bp.lane[i]).counters->skip;
+        f.frame[i].dp = (flow_or_null != nullptr && flow_or_null[i] != nullptr) ? c->lane_ptrs(bp.lane[i]).dp : nullptr;
+        f.frame[i].skip = &c->lane_ptrs(bp.lane[i]).counters->skip;
     }
     return f;
 }
@@ -453,9 +453,9 @@ int enqueue_expansion(sali_ctx* c, const uint8_t* const* d_rgb, const BatchPlan&
     if (fused_expansion(c, bp.n)) {
         ExpandBatch f = {};
         for (int i = 0; i < bp.n; ++i) {
-            f.rgb[i] = d_rgb[i];
-            f.A[i] = c->sc<float4>(c->sl.expA[bp.slot[i]]);
-            f.b[i] = c->sc<float>(c->sl.expB[bp.slot[i]]);
+            f.frame[i].rgb = d_rgb[i];
+            f.frame[i].A = c->sc<float4>(c->sl.expA[bp.slot[i]]);
+            f.frame[i].b = c->sc<float>(c->sl.expB[bp.slot[i]]);
         }
         SALI_TRY(launch_expand(f, bp.n, g, c->fw, ride, done, s));
         return SALI_OK;
@@ -463,11 +463,11 @@ int enqueue_expansion(sali_ctx* c, const uint8_t* const* d_rgb, const BatchPlan&
     PyrBatch f = {};
     for (int i = 0; i < bp.n; ++i) {
         const LaneLayout& L = c->sl.lane[bp.lane[i]];
-        f.rgb[i] = d_rgb[i];
-        f.y8[i] = c->sc<uint8_t>(L.y8);
-        f.pyr[i] = c->sc<float>(L.pyr);
-        f.A[i] = c->sc<float4>(c->sl.expA[bp.slot[i]]);
-        f.b[i] = c->sc<float>(c->sl.expB[bp.slot[i]]);
+        f.frame[i].rgb = d_rgb[i];
+        f.frame[i].y8 = c->sc<uint8_t>(L.y8);
+        f.frame[i].pyr = c->sc<float>(L.pyr);
+        f.frame[i].A = c->sc<float4>(c->sl.expA[bp.slot[i]]);
+        f.frame[i].b = c->sc<float>(c->sl.expB[bp.slot[i]]);
     }
     if (g.levels == 1) {
         const int rc = enqueue_gray(c, d_rgb, bp, s);
@@ -506,12 +506,13 @@ int enqueue_flow(sali_ctx* c, const BatchPlan& bp, const float2** flow, const Fl
         if (bp.prev_slot[i] < 0) continue;
         const LaneLayout& L = c->sl.lane[bp.lane[i]];
         for (int k = 0; k < 2; ++k) {
-            f[k].A1[m] = c->sc<float4>(c->sl.expA[bp.prev_slot[i]]);
-            f[k].b1[m] = c->sc<float>(c->sl.expB[bp.prev_slot[i]]);
-            f[k].A2[m] = c->sc<float4>(c->sl.expA[bp.slot[i]]);
-            f[k].b2[m] = c->sc<float>(c->sl.expB[bp.slot[i]]);
-            f[k].d_in[m] = c->sc<float2>(L.flow[k]);
-            f[k].d_out[m] = c->sc<float2>(L.flow[k ^ 1]);
+            FlowFrame& at = f[k].frame[m];
+            at.A1 = c->sc<float4>(c->sl.expA[bp.prev_slot[i]]);
+            at.b1 = c->sc<float>(c->sl.expB[bp.prev_slot[i]]);
+            at.A2 = c->sc<float4>(c->sl.expA[bp.slot[i]]);
+            at.b2 = c->sc<float>(c->sl.expB[bp.slot[i]]);
+            at.d_in = c->sc<float2>(L.flow[k]);
+            at.d_out = c->sc<float2>(L.flow[k ^ 1]);
         }
         idx[m++] = i;
     }
@@ -544,17 +545,17 @@ PoolBatch pool_batch(sali_ctx* c, const BatchPlan& bp, float* d_scores_or_null, 
     for (int i = 0; i < bp.n; ++i) {
         const LaneLayout& L = c->sl.lane[bp.lane[i]];
         const LanePtrs lp = c->lane_ptrs(bp.lane[i]);
-        f.cls[i] = c->sc<uint8_t>(L.cls);
-        f.parent[i] = c->sc<uint32_t>(L.parent);
-        f.var[i] = c->sc<uint32_t>(L.var);
-        f.msum[i] = lp.msum + (bp.parity[i] & 1u);
-        f.scores[i] = d_scores_or_null != nullptr ? d_scores_or_null : lp.scores;
-        f.flow[i] = flow != nullptr ? flow[i] : nullptr;
-        f.dp_out[i] = lp.dp;
-        f.dp[i] = f.flow[i] != nullptr ? lp.dp : nullptr;
-        f.skip[i] = &lp.counters->skip;
-        f.gate[i] = lp.gate;
-        f.tcounts[i] = c->sc<TierCounts>(L.tcounts);
+        f.frame[i].cls = c->sc<uint8_t>(L.cls);
+        f.frame[i].parent = c->sc<uint32_t>(L.parent);
+        f.frame[i].var = c->sc<uint32_t>(L.var);
+        f.frame[i].msum = lp.msum + (bp.parity[i] & 1u);
+        f.frame[i].scores = d_scores_or_null != nullptr ? d_scores_or_null : lp.scores;
+        f.frame[i].flow = flow != nullptr ? flow[i] : nullptr;
+        f.frame[i].dp_out = lp.dp;
+        f.frame[i].dp = f.frame[i].flow != nullptr ? lp.dp : nullptr;
+        f.frame[i].skip = &lp.counters->skip;
+        f.frame[i].gate = lp.gate;
+        f.frame[i].tcounts = c->sc<TierCounts>(L.tcounts);
     }
     return f;
 }

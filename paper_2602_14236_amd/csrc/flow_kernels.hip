@@ -35,8 +35,6 @@ namespace {
 constexpr int kT = 32;                       // tile side of the expansion kernel
 constexpr int kPR = kT + 2 * kPolyN;         // 38
 
-__device__ __forceinline__ float clampf(float v, float lo, float hi) { return fminf(fmaxf(v, lo), hi); }
-
 // Element i of an array whose base is uniform over the wave: base + 32-bit byte offset (an image level
 // has fewer than 2^28 pixels, so i * 16 fits), which the hardware adds itself; with 64-bit indices a
 // quarter of the gather's vector instructions were address arithmetic.
@@ -66,22 +64,24 @@ constexpr int kPyrCols = 76;                    // source columns: from 64 bx - 
 }  // namespace
 
 template <bool kRgb>
-__global__ __launch_bounds__(256) void k_pyr_pair(PyrBatch f, LevelGeom g, int lvl) {
+__global__ __launch_bounds__(256) void k_pyr_pair(int tiles_x, int tiles_y, int n, int lvl, LevelGeom g, PyrBatch f) {
     using Cell = typename std::conditional<kRgb, uint8_t, float>::type;
     using Sum = typename std::conditional<kRgb, uint16_t, float>::type;
     __shared__ __align__(16) Cell s_src[kPyrRows][kPyrCols];
     __shared__ Sum s_h[kPyrRows][kPyrR + 1];            // horizontal sums
     __shared__ float s_l1[kPyrR][kPyrR + 1];
-    const BlockId blk = xcd_block_id();
-    const int tid = threadIdx.x;
+    const BlockId blk = xcd_block_id(tiles_x, tiles_y, n);
+    const PyrFrame& frame = f.frame[blk.z];
     const int sh = g.h[lvl - 1], sw = g.w[lvl - 1], h1 = g.h[lvl], w1 = g.w[lvl];
-    float* __restrict__ pyr = f.pyr[blk.z];
+    float* __restrict__ pyr = frame.pyr;
+    together(sh, sw, h1, w1, frame.rgb, frame.y8, pyr, g.off[lvl - 1], g.off[lvl], g.levels);
+    const int tid = threadIdx.x;
     const int qy = 64 * blk.y - 6, qx = 64 * blk.x - 8;         // origin of the patch
     constexpr int kQuads = kPyrCols / 4, kItems = kPyrRows * kQuads, kN = (kItems + 255) / 256;
     if constexpr (kRgb) {
         // a thread takes four pixels (twelve bytes, the compiler is told nothing about their alignment) at a
         // time and has all its loads in flight before the first is used
-        const uint8_t* __restrict__ rgb = f.rgb[blk.z];
+        const uint8_t* __restrict__ rgb = frame.rgb;
         uint32_t v[kN][3];
 #pragma unroll
         for (int k = 0; k < kN; ++k) {
@@ -105,7 +105,7 @@ __global__ __launch_bounds__(256) void k_pyr_pair(PyrBatch f, LevelGeom g, int l
     }
     __syncthreads();
     if constexpr (kRgb) {
-        uint8_t* __restrict__ y8 = f.y8[blk.z];
+        uint8_t* __restrict__ y8 = frame.y8;
 #pragma unroll
         for (int k = 0; k < 4; ++k) {                           // 64 rows of sixteen quads
             const int p = tid + 256 * k;
@@ -188,38 +188,39 @@ template <typename Own>
 struct WithPrep<Own, NoRide> {
     Own own;
 };
-// Is this block one of the riders?  Then it does its tile; the others get their number among the launch's own blocks (per_frame
+// Is this block one of the `riders`?  Then it does its tile; the others get their number among the launch's own blocks (per_frame
 // a frame, frame by frame).  Without riders the grid is (per_frame, frames).
 template <typename Shared>
-__device__ __forceinline__ bool ride_prep(Shared& sh, const PrepRide& ride, int& block) {
-    block = (int)blockIdx.x - ride.blocks;
+__device__ __forceinline__ bool ride_prep(Shared& sh, const PrepRide& ride, int riders, int, int& block) {
+    block = (int)blockIdx.x - riders;
     if (block >= 0) return false;
     const int tiles = ride.tiles_x * ride.tiles_y, frame = (int)blockIdx.x / tiles, t = (int)blockIdx.x - frame * tiles;
     prep_tile<false, kPrepThreads>(sh.prep, ride.f, t % ride.tiles_x, t / ride.tiles_x, frame, ride.h, ride.w, GateParams{}, ride.lut, ride.lo2, ride.hi2);
     return true;
 }
 template <typename Shared>
-__device__ __forceinline__ bool ride_prep(Shared&, const NoRide&, int& block) {
-    block = (int)blockIdx.x + (int)gridDim.x * (int)blockIdx.y;
+__device__ __forceinline__ bool ride_prep(Shared&, const NoRide&, int, int per_frame, int& block) {
+    block = (int)blockIdx.x + per_frame * (int)blockIdx.y;
     return false;
 }
 }  // namespace
 
 template <typename Ride>
-__global__ __launch_bounds__(256) void k_polyexp(PyrBatch f, LevelGeom g, FlowWeights fw, Ride ride) {
+__global__ __launch_bounds__(256) void k_polyexp(int riders, int per_frame, LevelGeom g, FlowWeights fw, PyrBatch f, Ride ride) {
     __shared__ WithPrep<PolyexpShared, Ride> sh;
     int block;
-    if (ride_prep(sh, ride, block)) return;
+    if (ride_prep(sh, ride, riders, per_frame, block)) return;
     int frame = (int)blockIdx.y, tile = (int)blockIdx.x;
     if constexpr (!std::is_same_v<Ride, NoRide>) {
-        const int tiles = g.tile_start[g.levels];
-        frame = block / tiles;
-        tile = block - frame * tiles;
+        frame = block / per_frame;
+        tile = block - frame * per_frame;
     }
-    const uint8_t* __restrict__ y8 = f.y8[frame];
-    const float* __restrict__ pyr = f.pyr[frame];
-    float4* __restrict__ A_out = f.A[frame];
-    float* __restrict__ b_out = f.b[frame];
+    const PyrFrame& fr = f.frame[frame];
+    const uint8_t* __restrict__ y8 = fr.y8;
+    const float* __restrict__ pyr = fr.pyr;
+    float4* __restrict__ A_out = fr.A;
+    float* __restrict__ b_out = fr.b;
+    together(y8, pyr, A_out, b_out);
     // unpadded rows: the passes that write and read these arrays column-wise address them linearly
     // in the thread index (with a pad of one float, a group of 32 lanes that straddles two rows has
     // two lanes on one bank: 23 % of the kernel's LDS cycles were bank conflicts)
@@ -228,8 +229,9 @@ __global__ __launch_bounds__(256) void k_polyexp(PyrBatch f, LevelGeom g, FlowWe
 
     int lvl = 0;
     while (lvl + 1 < g.levels && tile >= g.tile_start[lvl + 1]) ++lvl;
-    const int t = tile - g.tile_start[lvl];
     const int h = g.h[lvl], w = g.w[lvl];
+    together(h, w, g.tile_start[lvl], g.tiles_x[lvl], g.off[lvl]);
+    const int t = tile - g.tile_start[lvl];
     const int x0 = (t % g.tiles_x[lvl]) * kT, y0 = (t / g.tiles_x[lvl]) * kT;
     const float* src = pyr + g.off[lvl];
     const int tid = threadIdx.x;
@@ -418,11 +420,11 @@ struct ExpandShared {
 
 // t1, t2, t3: a frame's tiles of level 0, of levels 0 and 1, of all levels
 template <typename Ride>
-__global__ __launch_bounds__(256) void k_expand(ExpandBatch f, LevelGeom g, int n_frames, int t1, int t2, int t3, int tx0, int tx1,
-                                                int tx2, FlowWeights fw, Ride ride) {
+__global__ __launch_bounds__(256) void k_expand(int riders, int n_frames, int t1, int t2, int t3, int tx0, int tx1, int tx2,
+                                                LevelGeom g, FlowWeights fw, ExpandBatch f, Ride ride) {
     __shared__ WithPrep<ExpandShared, Ride> sh;
     int idx;
-    if (ride_prep(sh, ride, idx)) return;
+    if (ride_prep(sh, ride, riders, t3, idx)) return;
     // Work order.  A level-2 tile costs about ten times a level-0 tile (97 x 97 gray pixels, two pyramid
     // stages) and there are sixteen level-0 tiles for each: with the tiles of a frame in level order the
     // heavy ones start last and the launch ends with a few of them on an idle chip (22 us per four
@@ -443,9 +445,11 @@ __global__ __launch_bounds__(256) void k_expand(ExpandBatch f, LevelGeom g, int 
         frame = idx / t1;
         t = idx - frame * t1;
     }
-    const uint8_t* __restrict__ rgb = f.rgb[frame];
-    float4* __restrict__ A_out = f.A[frame];
-    float* __restrict__ b_out = f.b[frame];
+    const ExpandFrame& fr = f.frame[frame];
+    const uint8_t* __restrict__ rgb = fr.rgb;
+    float4* __restrict__ A_out = fr.A;
+    float* __restrict__ b_out = fr.b;
+    together(rgb, A_out, b_out, g.h[0], g.w[0], g.h[1], g.w[1], g.h[2], g.w[2], g.off[1], g.off[2]);
     uint32_t (&s_qb)[kEQ * (kEQB / 4)] = sh.own.qb;
     float (&s_p)[kEP * kEPS] = sh.own.p;
     float (&s_f)[kER][kER] = sh.own.f;
@@ -455,7 +459,8 @@ __global__ __launch_bounds__(256) void k_expand(ExpandBatch f, LevelGeom g, int 
     static_assert(3 * kET * kER <= kEP * kEPS, "moments fit into the 47-wide patch");
 
     const int tiles_x = lvl == 0 ? tx0 : (lvl == 1 ? tx1 : tx2);
-    const int h = g.h[lvl], w = g.w[lvl];
+    const int h = lvl == 0 ? g.h[0] : (lvl == 1 ? g.h[1] : g.h[2]), w = lvl == 0 ? g.w[0] : (lvl == 1 ? g.w[1] : g.w[2]);
+    const int64_t level_off = lvl == 0 ? 0 : (lvl == 1 ? g.off[1] : g.off[2]);
     const int x0 = (t % tiles_x) * kET, y0 = (t / tiles_x) * kET;
     const int oy = y0 - kPolyN, ox = x0 - kPolyN;   // origin of s_f in this level's coordinates
     const int tid = threadIdx.x;
@@ -518,7 +523,7 @@ __global__ __launch_bounds__(256) void k_expand(ExpandBatch f, LevelGeom g, int 
                 sxy += a1 * (float)k;
                 syy += a2;
             }
-            const size_t gi = g.off[lvl] + (size_t)gy * w + gx;
+            const size_t gi = level_off + (size_t)gy * w + gx;
             A_out[gi] = make_float4((sxx - fw.m2 * s0) * fw.inv_den, sxy * fw.inv_2m2sq, (syy - fw.m2 * s0) * fw.inv_den,
                                     sx * fw.inv_m2);
             b_out[gi] = sy * fw.inv_m2;
@@ -529,19 +534,16 @@ __global__ __launch_bounds__(256) void k_expand(ExpandBatch f, LevelGeom g, int 
 // ---------------------------------------------------------------------------------------------
 namespace {
 
-// bilinear sample of a float2 field at real (y, x), coordinates clamped to the image
-__device__ __forceinline__ float2 bilerp2(const float2* __restrict__ f, int h, int w, float y, float x) {
-    y = clampf(y, 0.0f, (float)(h - 1));
-    x = clampf(x, 0.0f, (float)(w - 1));
-    const float fy0 = floorf(y), fx0 = floorf(x);
-    const int y0 = (int)fy0, x0 = (int)fx0;
-    const int y1 = min(y0 + 1, h - 1), x1 = min(x0 + 1, w - 1);
-    const float wy = y - fy0, wx = x - fx0;
-    const float2 a = ld_at(f, pix(y0, w, x0)), b = ld_at(f, pix(y0, w, x1));
-    const float2 c = ld_at(f, pix(y1, w, x0)), d = ld_at(f, pix(y1, w, x1));
-    const float tx = a.x * (1.0f - wx) + b.x * wx, ty = a.y * (1.0f - wx) + b.y * wx;
-    const float bx = c.x * (1.0f - wx) + d.x * wx, by = c.y * (1.0f - wx) + d.y * wx;
-    return make_float2(tx * (1.0f - wy) + bx * wy, ty * (1.0f - wy) + by * wy);
+// 2 * the coarser flow at (y / 2, x / 2), bilinear, coordinates clamped to it.  The weights are 1 and 0 or both a half, and past the
+// last row or column (an odd pixel of an even size) both samples are the last one.
+__device__ __forceinline__ float2 transfer_at(const float2* __restrict__ coarse, int gy, int gx, int ch, int cw) {
+    const int y0 = gy >> 1, x0 = gx >> 1, y1 = min(y0 + (gy & 1), ch - 1), x1 = min(x0 + (gx & 1), cw - 1);
+    const uint32_t r0 = pix(y0, cw, 0), r1 = pix(y1, cw, 0);
+    const float2 a = ld_at(coarse, r0 + (uint32_t)x0), b = ld_at(coarse, r0 + (uint32_t)x1);
+    const float2 c = ld_at(coarse, r1 + (uint32_t)x0), d = ld_at(coarse, r1 + (uint32_t)x1);
+    // each pair's mean is exact but for one rounding of the sum, as is 2 * the mean of the two
+    const float tx = 0.5f * (a.x + b.x), ty = 0.5f * (a.y + b.y), bx = 0.5f * (c.x + d.x), by = 0.5f * (c.y + d.y);
+    return make_float2(tx + bx, ty + by);
 }
 
 // prior displacement of a pixel: 0 (coarsest level), 2 * bilinear(coarser flow; y/2, x/2) for
@@ -549,26 +551,43 @@ __device__ __forceinline__ float2 bilerp2(const float2* __restrict__ f, int h, i
 __device__ __forceinline__ float2 prior_at(const float2* __restrict__ d_in, int mode, int gy, int gx, int w, int ch,
                                            int cw) {
     if (mode == 0) return make_float2(0.0f, 0.0f);
-    if (mode == 1) {
-        const float2 c = bilerp2(d_in, ch, cw, 0.5f * (float)gy, 0.5f * (float)gx);
-        return make_float2(2.0f * c.x, 2.0f * c.y);
-    }
+    if (mode == 1) return transfer_at(d_in, gy, gx, ch, cw);
     return ld_at(d_in, pix(gy, w, gx));
+}
+
+// size of a level and the coordinates of its last row and column, in scalar registers
+struct Extent {
+    int h, w;
+    float last_y, last_x;
+};
+__device__ __forceinline__ Extent extent_of(int h, int w) {
+    auto uniform = [](float v) { return __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, v))); };
+    return {h, w, uniform((float)(h - 1)), uniform((float)(w - 1))};
+}
+
+// the old frame's expansion at a pixel
+struct OldCell {
+    float4 A;
+    float by;
+};
+__device__ __forceinline__ OldCell old_cell(const float4* __restrict__ A1, const float* __restrict__ b1, uint32_t gi) {
+    return {ld_at(A1, gi), ld_at(b1, gi)};
 }
 
 // A^T A (xx, xy, yy) and A^T db (x, y) of the pixel (gy, gx) with prior displacement dp: the old frame's
 // expansion there, the new frame's sampled at the pixel + dp.  The upper left of the four samples is clamped to the
 // last but one row and column (an image level has at least two of each; at the border the weight of the other
 // row or column is then exactly one), so that the others lie at fixed distances from it: no coordinates, products and
-// offsets of their own, and the two samples of a row of b in one load.
-__device__ __forceinline__ void flow_terms(const float4* __restrict__ A1, const float* __restrict__ b1,
-                                           const float4* __restrict__ A2, const float* __restrict__ b2, int h, int w, int gy,
-                                           int gx, float2 dp, float (&t)[5]) {
-    const uint32_t gi = pix(gy, w, gx);
-    const float4 a1 = ld_at(A1, gi);
-    const float b1y = ld_at(b1, gi);
-    const float sy = clampf((float)gy + dp.y, 0.0f, (float)(h - 1));
-    const float sx = clampf((float)gx + dp.x, 0.0f, (float)(w - 1));
+// offsets of their own, and the two samples of a row of b in one load.  Which sums are fused is written out, here and in
+// flow_solve: left to the compiler it depended on the code around, and kernels for other sizes of the same level must agree bit by bit.
+__device__ __forceinline__ void flow_terms(const OldCell& old, const float4* __restrict__ A2, const float* __restrict__ b2, const Extent& e,
+                                           int gy, int gx, float2 dp, float (&t)[5]) {
+#pragma clang fp contract(off)
+    const int h = e.h, w = e.w;
+    const float4 a1 = old.A;
+    const float b1y = old.by;
+    const float sy = __builtin_amdgcn_fmed3f((float)gy + dp.y, 0.0f, e.last_y);       // not a number: 0
+    const float sx = __builtin_amdgcn_fmed3f((float)gx + dp.x, 0.0f, e.last_x);
     const int iy0 = min((int)sy, h - 2), ix0 = min((int)sx, w - 2);
     const float wy = sy - (float)iy0, wx = sx - (float)ix0;
     const uint32_t i0 = pix(iy0, w, ix0), i1 = i0 + (uint32_t)w;
@@ -577,19 +596,20 @@ __device__ __forceinline__ void flow_terms(const float4* __restrict__ A1, const 
     __builtin_memcpy(c0, reinterpret_cast<const char*>(b2) + i0 * 4u, 8);
     __builtin_memcpy(c1, reinterpret_cast<const char*>(b2) + i1 * 4u, 8);
     const float w00 = (1.0f - wx) * (1.0f - wy), w01 = wx * (1.0f - wy), w10 = (1.0f - wx) * wy, w11 = wx * wy;
-    const float a2xx = a00.x * w00 + a01.x * w01 + a10.x * w10 + a11.x * w11;
-    const float a2xy = a00.y * w00 + a01.y * w01 + a10.y * w10 + a11.y * w11;
-    const float a2yy = a00.z * w00 + a01.z * w01 + a10.z * w10 + a11.z * w11;
-    const float b2x = a00.w * w00 + a01.w * w01 + a10.w * w10 + a11.w * w11;
-    const float b2y = c0[0] * w00 + c0[1] * w01 + c1[0] * w10 + c1[1] * w11;
+    auto sampled = [&](float v00, float v01, float v10, float v11) {
+        return __builtin_fmaf(v11, w11, __builtin_fmaf(v10, w10, __builtin_fmaf(v01, w01, v00 * w00)));
+    };
+    const float a2xx = sampled(a00.x, a01.x, a10.x, a11.x), a2xy = sampled(a00.y, a01.y, a10.y, a11.y);
+    const float a2yy = sampled(a00.z, a01.z, a10.z, a11.z), b2x = sampled(a00.w, a01.w, a10.w, a11.w);
+    const float b2y = sampled(c0[0], c0[1], c1[0], c1[1]);
     const float axx = 0.5f * (a1.x + a2xx), axy = 0.5f * (a1.y + a2xy), ayy = 0.5f * (a1.z + a2yy);
-    const float dbx = -0.5f * (b2x - a1.w) + axx * dp.x + axy * dp.y;
-    const float dby = -0.5f * (b2y - b1y) + axy * dp.x + ayy * dp.y;
-    t[0] = axx * axx + axy * axy;
+    const float dbx = __builtin_fmaf(axy, dp.y, __builtin_fmaf(axx, dp.x, -0.5f * (b2x - a1.w)));
+    const float dby = __builtin_fmaf(ayy, dp.y, __builtin_fmaf(axy, dp.x, -0.5f * (b2y - b1y)));
+    t[0] = __builtin_fmaf(axx, axx, axy * axy);
     t[1] = axy * (axx + ayy);
-    t[2] = axy * axy + ayy * ayy;
-    t[3] = axx * dbx + axy * dby;
-    t[4] = axy * dbx + ayy * dby;
+    t[2] = __builtin_fmaf(ayy, ayy, axy * axy);
+    t[3] = __builtin_fmaf(axx, dbx, axy * dby);
+    t[4] = __builtin_fmaf(axy, dbx, ayy * dby);
 }
 
 // the displacement from the windowed sums of the terms and the prior (ridge term centred on the prior).  The two
@@ -597,13 +617,14 @@ __device__ __forceinline__ void flow_terms(const float4* __restrict__ A1, const 
 // the last place and a little more); the ridge term keeps the determinant above 1e-8, so nothing has to be scaled as
 // a general division does.
 __device__ __forceinline__ float2 flow_solve(float g11, float g12, float g22, float h1, float h2, float2 dp) {
-    const float lam = kLamAbs + kLamRel * 0.5f * (g11 + g22);
-    const float m11 = g11 + lam, m22 = g22 + lam, m12 = g12;
-    const float r1 = h1 + lam * dp.x, r2 = h2 + lam * dp.y;
-    const float det = m11 * m22 - m12 * m12;
+#pragma clang fp contract(off)
+    const float lam = __builtin_fmaf(kLamRel * 0.5f, g11 + g22, kLamAbs);
+    const float m11 = g11 + lam, m22 = g22 + lam;
+    const float r1 = __builtin_fmaf(lam, dp.x, h1), r2 = __builtin_fmaf(lam, dp.y, h2);
+    const float det = __builtin_fmaf(m11, m22, -(g12 * g12));
     float inv = __builtin_amdgcn_rcpf(det);
     inv = __builtin_fmaf(__builtin_fmaf(-det, inv, 1.0f), inv, inv);
-    const float nx = m22 * r1 - m12 * r2, ny = m11 * r2 - m12 * r1;
+    const float nx = __builtin_fmaf(m22, r1, -(g12 * r2)), ny = __builtin_fmaf(m11, r2, -(g12 * r1));
     const float qx = nx * inv, qy = ny * inv;
     return make_float2(__builtin_fmaf(__builtin_fmaf(-det, qx, nx), inv, qx), __builtin_fmaf(__builtin_fmaf(-det, qy, ny), inv, qy));
 }
@@ -675,16 +696,13 @@ __device__ __forceinline__ f32x4 fir4_column(const FirWeights& w, const float* p
 // so the window passes stay on the vector ALU with one output per lane (84x84 x 4 frames 5.8 us a launch, with the
 // matrix cores' four outputs per lane 6.7: a quarter of the lanes at work, each on a serial chain).
 constexpr int kSmallTile = 16, kSmallThreads = 256;
-__global__ __launch_bounds__(kSmallThreads) void k_flow_small(FlowBatch f, long long level_off, int h, int w, int ch, int cw,
-                                                              int prior_mode, FlowWeights fw) {
+__global__ __launch_bounds__(kSmallThreads) void k_flow_small(int tiles_x, int tiles_y, int n, int h, int w, int ch, int cw, int prior_mode,
+                                                              FlowWeights fw, FlowBatch f) {
     // blk.z = frame of the batch, (blk.x, blk.y) = tile
-    const BlockId blk = xcd_block_id();
-    const float4* __restrict__ A1 = f.A1[blk.z] + level_off;
-    const float* __restrict__ b1 = f.b1[blk.z] + level_off;
-    const float4* __restrict__ A2 = f.A2[blk.z] + level_off;
-    const float* __restrict__ b2 = f.b2[blk.z] + level_off;
-    const float2* __restrict__ d_in = f.d_in[blk.z];
-    float2* __restrict__ d_out = f.d_out[blk.z];
+    const BlockId blk = xcd_block_id(tiles_x, tiles_y, n);
+    const FlowFrame fr = f.frame[blk.z];
+    together(fr.A1, fr.A2, fr.b1, fr.b2, fr.d_in, fr.d_out);
+    const Extent extent = extent_of(h, w);
     constexpr int T = kSmallTile, NT = kSmallThreads, R = T + 2 * kWinR;       // 26: tile and halo
     // A group of 32 lanes of a window pass reads two rows (16 lanes each), which must lie 16 banks apart.  The two
     // rows of a group are eight apart (window_item) and the rows are unpadded: 8 * 26 = 16 mod 32; the pass that
@@ -702,10 +720,11 @@ __global__ __launch_bounds__(kSmallThreads) void k_flow_small(FlowBatch f, long 
     for (int p = tid; p < R * R; p += NT) {
         const int ry = p / R, rx = p % R;
         const int gy = clampi(y0 - kWinR + ry, 0, h - 1), gx = clampi(x0 - kWinR + rx, 0, w - 1);
-        const float2 dp = prior_at(d_in, prior_mode, gy, gx, w, ch, cw);
+        const OldCell old = old_cell(fr.A1, fr.b1, pix(gy, w, gx));
+        const float2 dp = prior_at(fr.d_in, prior_mode, gy, gx, w, ch, cw);
         if (ry >= kWinR && ry < kWinR + T && rx >= kWinR && rx < kWinR + T) s_dp[ry - kWinR][rx - kWinR] = dp;
         float t[5];
-        flow_terms(A1, b1, A2, b2, h, w, gy, gx, dp, t);
+        flow_terms(old, fr.A2, fr.b2, extent, gy, gx, dp, t);
 #pragma unroll
         for (int c = 0; c < 5; ++c) s_in[c][ry][rx] = t[c];
     }
@@ -773,7 +792,7 @@ __global__ __launch_bounds__(kSmallThreads) void k_flow_small(FlowBatch f, long 
 #pragma unroll
         for (int c = 0; c < 5; ++c) acc[c] += wk * s_in[c][ty + k][tx];
     }
-    *reinterpret_cast<float2*>(reinterpret_cast<char*>(d_out) + pix(gy, w, gx) * 8u) =
+    *reinterpret_cast<float2*>(reinterpret_cast<char*>(fr.d_out) + pix(gy, w, gx) * 8u) =
         flow_solve(acc[0], acc[1], acc[2], acc[3], acc[4], s_dp[ty][tx]);
 }
 
@@ -795,16 +814,15 @@ constexpr int kTileX = 32, kTileThreads = 512;
 // all the thread's cells before the first sample; a first update takes 81, 31 and 51 us.  The samples of the coarser flow that
 // a first update needs leave no registers for that.
 template <int TY, bool kFirst>
-__global__ __launch_bounds__(kTileThreads, 8) void k_flow_tile(FlowBatch f, long long level_off, int h, int w, int ch, int cw,
-                                                               int first_mode, FlowWeights fw) {
+__global__ __launch_bounds__(kTileThreads, 8) void k_flow_tile(int tiles_x, int tiles_y, int n, int h, int w, int ch, int cw, int first_mode,
+                                                               FlowWeights fw, FlowBatch f) {
     const int prior_mode = kFirst ? first_mode : 2;
-    const BlockId blk = xcd_block_id();
-    const float4* __restrict__ A1 = f.A1[blk.z] + level_off;
-    const float* __restrict__ b1 = f.b1[blk.z] + level_off;
-    const float4* __restrict__ A2 = f.A2[blk.z] + level_off;
-    const float* __restrict__ b2 = f.b2[blk.z] + level_off;
-    const float2* __restrict__ d_in = f.d_in[blk.z];
-    float2* __restrict__ d_out = f.d_out[blk.z];
+    const BlockId blk = xcd_block_id(tiles_x, tiles_y, n);
+    const FlowFrame fr = f.frame[blk.z];
+    together(fr.A1, fr.A2, fr.b1, fr.b2, fr.d_in, fr.d_out);
+    const Extent extent = extent_of(h, w);
+    const float2* __restrict__ d_in = fr.d_in;
+    float2* __restrict__ d_out = fr.d_out;
     constexpr int TX = kTileX, NT = kTileThreads, RX = TX + 2 * kWinR, RY = TY + 2 * kWinR;
     constexpr int P = (RX + 3) / 4 * 4;              // row stride: the row pass reads sixteen bytes at a time
     __shared__ __align__(16) float s_in[5][RY * P];
@@ -830,9 +848,10 @@ __global__ __launch_bounds__(kTileThreads, 8) void k_flow_tile(FlowBatch f, long
                 const int ry = r0 + k * kRows;
                 if (k == kSteps - 1 && ry >= RY) continue;
                 const int gy = clampi(y0 - kWinR + ry, 0, h - 1);
+                __builtin_amdgcn_sched_barrier(0);      // cell by cell: two interleaved need more registers than there are
                 if constexpr (kFirst) prior[k] = prior_at(d_in, prior_mode, gy, gx, w, ch, cw);
                 float t[5];
-                flow_terms(A1, b1, A2, b2, h, w, gy, gx, prior[k], t);
+                flow_terms(old_cell(fr.A1, fr.b1, pix(gy, w, gx)), fr.A2, fr.b2, extent, gy, gx, prior[k], t);
 #pragma unroll
                 for (int c = 0; c < 5; ++c) s_in[c][ry * P + rx] = t[c];
             }
@@ -914,40 +933,43 @@ struct FusedTile {
 // The row pass runs on the matrix cores, as in k_flow_tile, over quads of outputs of one field, dealt to all waves: 1.5 -> 1.2, 0.92 ->
 // 0.76 and 0.56 -> 0.32 us of a 168x168 level's three updates.  The column pass stays on the vector ALU, two outputs an item: on the
 // matrix cores, five fields and four outputs a lane, it is a chain of 70 products and four solves on a quarter of the waves (0.6 -> 0.84 us
-// of the last update).  A region that is no multiple of four has outputs past its end, which nothing uses, and the zero weights of its last outputs meet cells past its end.  Those must
-// be finite: terms of other cells or of an earlier update, or the padding of the first update's rows, which is cleared.
+// of the last update).  A region that is no multiple of four has outputs past its end, which nothing uses, and the zero weights of its
+// last outputs meet cells past its end.  Those must be finite: terms of other cells or of an earlier update, or the padding of the first update's rows, which is cleared.
 template <int TX, int TY, int I>
-__device__ __forceinline__ void fused_update(FusedTile<TX, TY>& sh, float2* prior, float2* next, const float4* __restrict__ A1,
-                                             const float* __restrict__ b1, const float4* __restrict__ A2,
-                                             const float* __restrict__ b2, const float2* __restrict__ d_in,
-                                             float2* __restrict__ d_out, int h, int w, int ch, int cw, int prior_mode, int x0,
-                                             int y0, FirWeights& wt, const FlowWeights& fw) {
+__device__ __forceinline__ void fused_update(FusedTile<TX, TY>& sh, float2* prior, float2* next, const FlowFrame& f,
+                                             const Extent& extent, int ch, int cw, int prior_mode, int x0, int y0, FirWeights& wt, const FlowWeights& fw) {
     constexpr int kLeft = kFusedUpdates - 1 - I, NT = kFusedThreads;
     constexpr int DX = TX + 10 * kLeft, DY = TY + 10 * kLeft, RX = DX + 10, RY = DY + 10;
     constexpr int P = (RX + 3) / 4 * 4;             // row stride: the row pass reads sixteen bytes at a time
     const int tid = threadIdx.x, wave0 = tid & ~63;
-    const int ox = x0 - 5 * (kLeft + 1), oy = y0 - 5 * (kLeft + 1);
+    const int ox = x0 - 5 * (kLeft + 1), oy = y0 - 5 * (kLeft + 1), h = extent.h, w = extent.w;
     {
-        // a thread stays in its column, kRows rows at a time, and asks for the priors of all its cells before the first sample
+        // a thread stays in its column, kRows rows at a time, and asks for all that does not depend on the prior first, then
+        // for the priors of all its cells
         constexpr int kRows = NT / RX, kSteps = (RY + kRows - 1) / kRows;
         const int rx = tid % RX, r0 = tid / RX;
         const int gx = clampi(ox + rx, 0, w - 1);
         if (r0 < kRows) {
+            OldCell old[kSteps];
             float2 dp[kSteps];
 #pragma unroll
-            for (int k = 0; k < kSteps; ++k) {
-                const int ry = min(r0 + k * kRows, RY - 1), gy = clampi(oy + ry, 0, h - 1);
-                if constexpr (I == 0) dp[k] = prior_at(d_in, prior_mode, gy, gx, w, ch, cw);
-                else dp[k] = prior[(gy - oy) * RX + (gx - ox)];     // the clamped cell lies in the region: the tile meets the image
-            }
+            for (int k = 0; k < kSteps; ++k)
+                old[k] = old_cell(f.A1, f.b1, pix(clampi(oy + min(r0 + k * kRows, RY - 1), 0, h - 1), w, gx));
+            auto priors = [&](auto of) {
+#pragma unroll
+                for (int k = 0; k < kSteps; ++k) dp[k] = of(clampi(oy + min(r0 + k * kRows, RY - 1), 0, h - 1));
+            };
+            if constexpr (I > 0) priors([&](int gy) { return prior[(gy - oy) * RX + (gx - ox)]; });   // in the region: the tile meets the image
+            else if (prior_mode == 0) priors([](int) { return make_float2(0.0f, 0.0f); });
+            else if (prior_mode == 1) priors([&](int gy) { return transfer_at(f.d_in, gy, gx, ch, cw); });
+            else priors([&](int gy) { return ld_at(f.d_in, pix(gy, w, gx)); });
 #pragma unroll
             for (int k = 0; k < kSteps; ++k) {
                 const int ry = r0 + k * kRows;
                 if (k == kSteps - 1 && ry >= RY) continue;
-                const int gy = clampi(oy + ry, 0, h - 1);
                 if constexpr (I == 0) prior[ry * RX + rx] = dp[k];
                 float t[5];
-                flow_terms(A1, b1, A2, b2, h, w, gy, gx, dp[k], t);
+                flow_terms(old[k], f.A2, f.b2, extent, clampi(oy + ry, 0, h - 1), gx, dp[k], t);
 #pragma unroll
                 for (int c = 0; c < 5; ++c) sh.in[(c * RY + ry) * P + rx] = t[c];
             }
@@ -1005,7 +1027,7 @@ __device__ __forceinline__ void fused_update(FusedTile<TX, TY>& sh, float2* prio
             const float2 d = flow_solve(acc[0][j], acc[1][j], acc[2][j], acc[3][j], acc[4][j], prior[(ty + kWinR) * RX + tx + kWinR]);
             if constexpr (kLeft == 0) {
                 const int gy = y0 + ty, gx = x0 + tx;
-                if (gy < h && gx < w) *reinterpret_cast<float2*>(reinterpret_cast<char*>(d_out) + pix(gy, w, gx) * 8u) = d;
+                if (gy < h && gx < w) *reinterpret_cast<float2*>(reinterpret_cast<char*>(f.d_out) + pix(gy, w, gx) * 8u) = d;
             } else {
                 next[ty * DX + tx] = d;
             }
@@ -1042,27 +1064,25 @@ template <typename Own>
 struct FlowShared<Own, PrepRide> : WithPrep<Own, PrepRide> {};
 }  // namespace
 
-// gx x gy tiles of n frames: the grid, or the first blocks of a one-dimensional grid that ends with the riders
+// tiles_x x tiles_y tiles of n frames: the grid, or the first blocks of a one-dimensional grid that ends with the riders
 template <int TX, int TY, typename Ride>
-__global__ __launch_bounds__(kFusedThreads) void k_flow_fused(FlowBatch f, long long level_off, int h, int w, int ch, int cw,
-                                                              int prior_mode, FlowWeights fw, int gx, int gy, int n, Ride ride) {
+__global__ __launch_bounds__(kFusedThreads) void k_flow_fused(int tiles_x, int tiles_y, int n, int h, int w, int ch, int cw, int prior_mode,
+                                                              FlowWeights fw, FlowBatch f, Ride ride) {
     __shared__ FlowShared<FusedTile<TX, TY>, Ride> lds;
     BlockId blk;
     if constexpr (std::is_same_v<Ride, NoRide>) {
-        blk = xcd_block_id();
+        blk = xcd_block_id(tiles_x, tiles_y, n);
     } else {
-        if ((int)blockIdx.x >= gx * gy * n) {
-            ride_flow(lds, ride, (int)blockIdx.x - gx * gy * n);
+        const int own = tiles_x * tiles_y * n;
+        if ((int)blockIdx.x >= own) {
+            ride_flow(lds, ride, (int)blockIdx.x - own);
             return;
         }
-        blk = xcd_block_id((int)blockIdx.x, gx, gy, n);
+        blk = xcd_block_id((int)blockIdx.x, tiles_x, tiles_y, n);
     }
-    const float4* __restrict__ A1 = f.A1[blk.z] + level_off;
-    const float* __restrict__ b1 = f.b1[blk.z] + level_off;
-    const float4* __restrict__ A2 = f.A2[blk.z] + level_off;
-    const float* __restrict__ b2 = f.b2[blk.z] + level_off;
-    const float2* __restrict__ d_in = f.d_in[blk.z];
-    float2* __restrict__ d_out = f.d_out[blk.z];
+    const FlowFrame fr = f.frame[blk.z];
+    together(fr.A1, fr.A2, fr.b1, fr.b2, fr.d_in, fr.d_out);
+    const Extent extent = extent_of(h, w);
     FusedTile<TX, TY>& sh = lds.own;
     const int x0 = blk.x * TX, y0 = blk.y * TY;
     fir_table(sh.w, fw);
@@ -1072,9 +1092,9 @@ __global__ __launch_bounds__(kFusedThreads) void k_flow_fused(FlowBatch f, long 
             sh.in[(p / kPad + 1) * FusedTile<TX, TY>::SP - 1 - p % kPad] = 0.0f;
     }
     FirWeights wt;
-    fused_update<TX, TY, 0>(sh, sh.p, sh.q, A1, b1, A2, b2, d_in, d_out, h, w, ch, cw, prior_mode, x0, y0, wt, fw);
-    fused_update<TX, TY, 1>(sh, sh.q, sh.p, A1, b1, A2, b2, d_in, d_out, h, w, ch, cw, prior_mode, x0, y0, wt, fw);
-    fused_update<TX, TY, 2>(sh, sh.p, sh.q, A1, b1, A2, b2, d_in, d_out, h, w, ch, cw, prior_mode, x0, y0, wt, fw);
+    fused_update<TX, TY, 0>(sh, sh.p, sh.q, fr, extent, ch, cw, prior_mode, x0, y0, wt, fw);
+    fused_update<TX, TY, 1>(sh, sh.q, sh.p, fr, extent, ch, cw, prior_mode, x0, y0, wt, fw);
+    fused_update<TX, TY, 2>(sh, sh.p, sh.q, fr, extent, ch, cw, prior_mode, x0, y0, wt, fw);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -1148,8 +1168,9 @@ __global__ __launch_bounds__(256) void k_gate(const float* __restrict__ dp, floa
 hipError_t launch_pyramid(const PyrBatch& f, int n, const LevelGeom& g, hipStream_t s) {
     for (int lvl = 1; lvl < g.levels; lvl += 2) {
         const dim3 grid((g.w[lvl] + kPyrT - 1) / kPyrT, (g.h[lvl] + kPyrT - 1) / kPyrT, n);
-        if (lvl == 1) hipLaunchKernelGGL(k_pyr_pair<true>, grid, dim3(256), 0, s, f, g, lvl);
-        else hipLaunchKernelGGL(k_pyr_pair<false>, grid, dim3(256), 0, s, f, g, lvl);
+        const int sharing = frames_sharing_runs((int)grid.x, (int)grid.y, n);
+        if (lvl == 1) hipLaunchKernelGGL(k_pyr_pair<true>, grid, dim3(256), 0, s, (int)grid.x, (int)grid.y, sharing, lvl, g, f);
+        else hipLaunchKernelGGL(k_pyr_pair<false>, grid, dim3(256), 0, s, (int)grid.x, (int)grid.y, sharing, lvl, g, f);
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
@@ -1158,11 +1179,12 @@ hipError_t launch_pyramid(const PyrBatch& f, int n, const LevelGeom& g, hipStrea
 
 hipError_t launch_polyexp(const PyrBatch& f, int n, LevelGeom g, FlowWeights fw, const PrepRide* ride_or_null, hipEvent_t done_or_null,
                           hipStream_t s) {
-    const int own = g.tile_start[g.levels] * n;
+    const int per_frame = g.tile_start[g.levels];
     if (ride_or_null != nullptr)
-        launch_recording(done_or_null, k_polyexp<PrepRide>, dim3(ride_or_null->blocks + own), dim3(256), s, f, g, fw, *ride_or_null);
+        launch_recording(done_or_null, k_polyexp<PrepRide>, dim3(ride_or_null->blocks + per_frame * n), dim3(256), s, ride_or_null->blocks,
+                         per_frame, g, fw, f, *ride_or_null);
     else
-        launch_recording(done_or_null, k_polyexp<NoRide>, dim3(g.tile_start[g.levels], n), dim3(256), s, f, g, fw, NoRide{});
+        launch_recording(done_or_null, k_polyexp<NoRide>, dim3(per_frame, n), dim3(256), s, 0, per_frame, g, fw, f, NoRide{});
     return hipGetLastError();
 }
 
@@ -1178,13 +1200,12 @@ hipError_t launch_expand(const ExpandBatch& f, int n, LevelGeom g, FlowWeights f
         }
         start[l + 1] = start[l] + tiles;
     }
-    const int own = start[3] * n;
     if (ride_or_null != nullptr)
-        launch_recording(done_or_null, k_expand<PrepRide>, dim3(ride_or_null->blocks + own), dim3(256), s, f, g, n, start[1], start[2],
-                         start[3], tx[0], tx[1], tx[2], fw, *ride_or_null);
+        launch_recording(done_or_null, k_expand<PrepRide>, dim3(ride_or_null->blocks + start[3] * n), dim3(256), s, ride_or_null->blocks, n,
+                         start[1], start[2], start[3], tx[0], tx[1], tx[2], g, fw, f, *ride_or_null);
     else
-        launch_recording(done_or_null, k_expand<NoRide>, dim3(start[3], n), dim3(256), s, f, g, n, start[1], start[2], start[3], tx[0], tx[1],
-                         tx[2], fw, NoRide{});
+        launch_recording(done_or_null, k_expand<NoRide>, dim3(start[3], n), dim3(256), s, 0, n, start[1], start[2], start[3], tx[0], tx[1],
+                         tx[2], g, fw, f, NoRide{});
     return hipGetLastError();
 }
 
@@ -1219,19 +1240,19 @@ int rider_blocks(FlowRider rider, const FlowRiders& r, long long own) {
 }
 
 template <int TX, int TY>
-hipError_t launch_fused(const FlowBatch& f, int n, int64_t level_off, int h, int w, int ch, int cw, int prior_mode, FlowWeights fw,
-                        FlowRider rider, const FlowRiders* r, hipStream_t s) {
+hipError_t launch_fused(const FlowBatch& f, int n, int h, int w, int ch, int cw, int prior_mode, const FlowWeights& fw, FlowRider rider,
+                        const FlowRiders* r, hipStream_t s) {
     const int gx = (w + TX - 1) / TX, gy = (h + TY - 1) / TY, own = gx * gy * n;
     auto go = [&](const auto& ride, dim3 grid) {
-        hipLaunchKernelGGL((k_flow_fused<TX, TY, std::decay_t<decltype(ride)>>), grid, dim3(kFusedThreads), 0, s, f,
-                           (long long)level_off, h, w, ch, cw, prior_mode, fw, gx, gy, n, ride);
+        hipLaunchKernelGGL((k_flow_fused<TX, TY, std::decay_t<decltype(ride)>>), grid, dim3(kFusedThreads), 0, s, gx, gy, n, h, w, ch, cw,
+                           prior_mode, fw, f, ride);
         return hipGetLastError();
     };
     if (rider == FlowRider::none) return go(NoRide{}, dim3(gx, gy, n));
     const int per = rider_blocks(rider, *r, own), blocks = per * r->n;
     if (rider == FlowRider::prepass) return go(*r->prep, dim3(own + blocks));
-    if (rider == FlowRider::hysteresis) return go(UnionRide{r->prep->f, r->h, r->w, border_items(r->h, r->w), per, blocks}, dim3(own + blocks));
-    return go(ScoreRide{*r->pool, r->h, r->w, per, blocks}, dim3(own + blocks));
+    if (rider == FlowRider::hysteresis) return go(UnionRide{blocks, r->h, r->w, border_items(r->h, r->w), per, r->prep->f}, dim3(own + blocks));
+    return go(ScoreRide{blocks, r->h, r->w, per, *r->pool}, dim3(own + blocks));
 }
 
 }  // namespace
@@ -1247,20 +1268,28 @@ bool flow_launch_carries(FlowRider rider, const FlowRiders& riders, int n, int h
     return rider_blocks(rider, riders, own) > 0;
 }
 
-hipError_t launch_flow_updates(const FlowBatch& f, int n, int64_t level_off, int h, int w, int ch, int cw,
-                               int prior_mode, int wanted, int* done, FlowWeights fw, FlowRider rider, const FlowRiders* riders,
+hipError_t launch_flow_updates(const FlowBatch& level0, int n, int64_t level_off, int h, int w, int ch, int cw,
+                               int prior_mode, int wanted, int* done, const FlowWeights& fw, FlowRider rider, const FlowRiders* riders,
                                hipStream_t s) {
+    FlowBatch f = {};
+    for (int i = 0; i < n; ++i) {
+        f.frame[i] = level0.frame[i];
+        f.frame[i].A1 += level_off;
+        f.frame[i].A2 += level_off;
+        f.frame[i].b1 += level_off;
+        f.frame[i].b2 += level_off;
+    }
     *done = kFusedUpdates;
     switch (fused_tile(n, h, w, wanted)) {
         case Fused::no: break;
-        case Fused::t16x8: return launch_fused<16, 8>(f, n, level_off, h, w, ch, cw, prior_mode, fw, rider, riders, s);
-        case Fused::t16x16: return launch_fused<16, 16>(f, n, level_off, h, w, ch, cw, prior_mode, fw, rider, riders, s);
-        case Fused::t32x16: return launch_fused<32, 16>(f, n, level_off, h, w, ch, cw, prior_mode, fw, rider, riders, s);
+        case Fused::t16x8: return launch_fused<16, 8>(f, n, h, w, ch, cw, prior_mode, fw, rider, riders, s);
+        case Fused::t16x16: return launch_fused<16, 16>(f, n, h, w, ch, cw, prior_mode, fw, rider, riders, s);
+        case Fused::t32x16: return launch_fused<32, 16>(f, n, h, w, ch, cw, prior_mode, fw, rider, riders, s);
     }
     *done = 1;
-#define SALI_FLOW_LAUNCH(KERNEL, TX, TY, NT)                                                                      \
-    hipLaunchKernelGGL(KERNEL, dim3((w + TX - 1) / TX, (h + TY - 1) / TY, n), dim3(NT), 0, s, f, (long long)level_off, h, \
-                       w, ch, cw, prior_mode, fw)
+#define SALI_FLOW_LAUNCH(KERNEL, TX, TY, NT)                                                                              \
+    hipLaunchKernelGGL(KERNEL, dim3((w + TX - 1) / TX, (h + TY - 1) / TY, n), dim3(NT), 0, s, (w + TX - 1) / TX, (h + TY - 1) / TY, \
+                       frames_sharing_runs((w + TX - 1) / TX, (h + TY - 1) / TY, n), h, w, ch, cw, prior_mode, fw, f)
     // The shape whose rounds of blocks cost least.  A round is a block per compute unit; launches of 1, 2, 3 .. rounds
     // measured over thirty levels (84x84 to 1920x1080, one to fifteen frames, an idle chip, in us, the first update of a
     // level and the others averaged) lie on a line each:

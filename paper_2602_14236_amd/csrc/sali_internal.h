@@ -115,17 +115,21 @@ struct LevelGeom {
     int32_t levels;
 };
 
-// Per-frame operands of the batched image kernels: entry i belongs to frame i of the batch.
+// Per-frame operands of the batched image kernels: entry i belongs to frame i of the batch.  A frame's pointers lie side by
+// side, so that a block finds its own in one or two cache lines of the kernel's arguments.
+struct PrepFrame {
+    const uint8_t* rgb;
+    uint8_t* y8;
+    uint8_t* cls;
+    uint32_t* var;
+    uint32_t* parent;
+    unsigned long long* msum_acc;      // frame sum of the colour variance, accumulated
+    unsigned long long* msum_clear;    // the accumulator of the lane's next use, cleared
+    const float* dp;                   // the frame's per-patch motions, for the reuse rule; NULL: never redundant
+    uint32_t* skip;                    // the pre-pass leaves the rule's answer here (1: redundant, no saliency)
+};
 struct PrepBatch {
-    const uint8_t* rgb[kMaxBatch];
-    uint8_t* y8[kMaxBatch];
-    uint8_t* cls[kMaxBatch];
-    uint32_t* var[kMaxBatch];
-    uint32_t* parent[kMaxBatch];
-    unsigned long long* msum_acc[kMaxBatch];      // frame sum of the colour variance, accumulated
-    unsigned long long* msum_clear[kMaxBatch];    // the accumulator of the lane's next use, cleared
-    const float* dp[kMaxBatch];                   // the frame's per-patch motions, for the reuse rule; NULL: never redundant
-    uint32_t* skip[kMaxBatch];                    // the pre-pass leaves the rule's answer here (1: redundant, no saliency)
+    PrepFrame frame[kMaxBatch];
 };
 
 // The reuse rule (Eq. 6, R_frame > theta_R) as the kernels that come after the flow evaluate it for
@@ -139,57 +143,69 @@ struct GateParams {
 // by = b_y (a float4 for A plus a float2 for b would be 24, a fifth of it padding, and the flow
 // updates re-read both frames' expansions once per update: at 1920x1080 that is most of the image
 // side's HBM traffic).
+struct ExpandFrame {
+    const uint8_t* rgb;
+    float4* A;
+    float* b;
+};
 struct ExpandBatch {
-    const uint8_t* rgb[kMaxBatch];
-    float4* A[kMaxBatch];
-    float* b[kMaxBatch];
+    ExpandFrame frame[kMaxBatch];
 };
 
-struct PyrBatch {                                 // per-level path (more than three levels, larger frames)
-    const uint8_t* rgb[kMaxBatch];
-    uint8_t* y8[kMaxBatch];
-    float* pyr[kMaxBatch];                        // all levels of the frame's pyramid, LevelGeom offsets
-    float4* A[kMaxBatch];
-    float* b[kMaxBatch];
+struct PyrFrame {                                 // per-level path (more than three levels, larger frames)
+    const uint8_t* rgb;
+    uint8_t* y8;
+    float* pyr;                                   // all levels of the frame's pyramid, LevelGeom offsets
+    float4* A;
+    float* b;
+};
+struct PyrBatch {
+    PyrFrame frame[kMaxBatch];
 };
 
-struct FlowBatch {                                // expansions at level 0; the launcher adds the level offset
-    const float4* A1[kMaxBatch];
-    const float* b1[kMaxBatch];
-    const float4* A2[kMaxBatch];
-    const float* b2[kMaxBatch];
-    const float2* d_in[kMaxBatch];
-    float2* d_out[kMaxBatch];
+struct FlowFrame {                                // expansions at level 0; the launcher adds the level offset
+    const float4* A1;
+    const float4* A2;
+    const float* b1;
+    const float* b2;
+    const float2* d_in;
+    float2* d_out;
+};
+struct FlowBatch {
+    FlowFrame frame[kMaxBatch];
 };
 
+struct PoolFrame {
+    const uint8_t* cls;
+    const uint32_t* parent;
+    const uint32_t* var;
+    const unsigned long long* msum;
+    float* scores;
+    const float2* flow;                           // NULL: no predecessor (never redundant)
+    float* dp_out;                                // per-patch motion, written by the motion launch
+    const float* dp;                              // the same for the reuse rule; NULL: never redundant
+    const uint32_t* skip;                         // what the pre-pass found (1: redundant, no scores)
+    sali_gate* gate;
+    struct TierCounts* tcounts;                   // hand-over from the frame's ranking to the row writer
+};
 struct PoolBatch {
-    const uint8_t* cls[kMaxBatch];
-    const uint32_t* parent[kMaxBatch];
-    const uint32_t* var[kMaxBatch];
-    const unsigned long long* msum[kMaxBatch];
-    float* scores[kMaxBatch];
-    const float2* flow[kMaxBatch];                // NULL: no predecessor (never redundant)
-    float* dp_out[kMaxBatch];                     // per-patch motion, written by the motion launch
-    const float* dp[kMaxBatch];                   // the same for the reuse rule; NULL: never redundant
-    const uint32_t* skip[kMaxBatch];              // what the pre-pass found (1: redundant, no scores)
-    sali_gate* gate[kMaxBatch];
-    struct TierCounts* tcounts[kMaxBatch];        // hand-over from the frame's ranking to the row writer
+    PoolFrame frame[kMaxBatch];
 };
 
 // Work of the spatial filter that rides on launches of the temporal filter: extra blocks of theirs.
 struct NoRide {};
 struct PrepRide {                                 // the pre-pass, on the launch that makes the expansions or a flow update
-    PrepBatch f;
+    int32_t blocks, h, w, tiles_x, tiles_y, lo2, hi2;
     const uint32_t* lut;
-    int32_t h, w, tiles_x, tiles_y, blocks, lo2, hi2;
+    PrepBatch f;
 };
 struct UnionRide {                                // hysteresis across tiles, on a flow update after it
+    int32_t blocks, h, w, n_items, blocks_per_frame;
     PrepBatch f;
-    int32_t h, w, n_items, blocks_per_frame, blocks;
 };
 struct ScoreRide {                                // patch scores, on an update after that
+    int32_t blocks, h, w, blocks_per_frame;
     PoolBatch f;
-    int32_t h, w, blocks_per_frame, blocks;
 };
 // a piece of the spatial filter that a flow launch is asked to carry
 enum class FlowRider { none, prepass, hysteresis, scores };
@@ -216,27 +232,42 @@ struct FlowWeights {
 // in linear-id order (x fastest), and every XCD has an L2 of its own: with the plain order
 // neighbouring tiles land on different XCDs and every L2 ends up holding every frame.  This maps
 // the hardware id to a logical (x, y, z) such that each XCD works through one contiguous run of the
-// (z, y, x) order: tiles that share halos share an L2, and an L2 holds an eighth of the data.
+// (z, y, x) order: tiles that share halos share an L2, and an L2 holds an eighth of the data.  Large frames are cut into eight
+// runs each instead (gz = 0) and so go one after the other, which leaves the expansion that two flows share in the last-level
+// cache: flow updates of three 1920x1080 frames 1 % faster, 15 x 320x180 4 % slower (more tiles have neighbours elsewhere), 15 x
+// 640x360 (240 tiles) the same.
+// The grid comes as arguments: the leading ones are in registers when a block starts, the launch's own record is not.
 struct BlockId {
     int x, y, z;
 };
+constexpr int kTilesOwnRuns = 480;
+inline int frames_sharing_runs(int tiles_x, int tiles_y, int n) { return tiles_x * tiles_y >= kTilesOwnRuns ? 0 : n; }
 #ifdef __HIPCC__
 __device__ __forceinline__ BlockId xcd_block_id(int linear, int gx, int gy, int gz) {
-    constexpr int kXcds = 8;
-    const int total = gx * gy * gz;
-    const int q = total / kXcds, r = total % kXcds;
-    const int xcd = linear % kXcds, slot = linear / kXcds;
-    const int logical = xcd * q + (xcd < r ? xcd : r) + slot;      // XCDs 0..r-1 hold q + 1 blocks
-    BlockId b;
-    b.z = logical / (gx * gy);
-    const int rem = logical - b.z * (gx * gy);
-    b.y = rem / gx;
-    b.x = rem - b.y * gx;
-    return b;
+    constexpr uint32_t kXcds = 8;
+    const uint32_t plane = (uint32_t)(gx * gy), total = plane * (uint32_t)gz;
+    const uint32_t q = total / kXcds, r = total % kXcds;
+    const uint32_t xcd = (uint32_t)linear % kXcds, slot = (uint32_t)linear / kXcds;
+    const uint32_t logical = xcd * q + (xcd < r ? xcd : r) + slot;      // XCDs 0..r-1 hold q + 1 blocks
+    const uint32_t z = gz == 1 ? 0u : logical / plane, rem = logical - z * plane;
+    const uint32_t y = rem / (uint32_t)gx;
+    return {(int)(rem - y * (uint32_t)gx), (int)y, (int)z};
 }
-__device__ __forceinline__ BlockId xcd_block_id() {
-    const int gx = (int)gridDim.x, gy = (int)gridDim.y;
-    return xcd_block_id((int)blockIdx.x + gx * ((int)blockIdx.y + gy * (int)blockIdx.z), gx, gy, (int)gridDim.z);
+__device__ __forceinline__ BlockId xcd_block_id(int gx, int gy, int gz) {
+    const int in_frame = (int)blockIdx.x + gx * (int)blockIdx.y;
+    if (gz > 0) return xcd_block_id(in_frame + gx * gy * (int)blockIdx.z, gx, gy, gz);
+    const BlockId b = xcd_block_id(in_frame, gx, gy, 1);
+    return {b.x, b.y, (int)blockIdx.z};
+}
+
+// What a block needs of its kernel's arguments is asked for at once: an empty use of all of it, ahead of the work.  Left to the
+// compiler the pieces are loaded where they are needed first, one trip of the scalar cache behind the other (a miss each:
+// arguments come from memory), and five or six such trips were 1.5 us of a launch of 5 to 12.
+__device__ __forceinline__ void together() {}
+template <typename T, typename... Rest>
+__device__ __forceinline__ void together(const T& first, const Rest&... rest) {
+    asm volatile("" : : "s"(first));
+    together(rest...);
 }
 #endif
 
@@ -332,7 +363,7 @@ hipError_t launch_expand(const ExpandBatch& f, int n, LevelGeom g, FlowWeights f
                          hipStream_t s);
 // one launch of at most `wanted` (>= 1) updates of a level, as many as suit its size; *done = how many it makes
 hipError_t launch_flow_updates(const FlowBatch& f, int n, int64_t level_off, int h, int w, int ch, int cw,
-                               int prior_mode, int wanted, int* done, FlowWeights fw, FlowRider rider, const FlowRiders* riders,
+                               int prior_mode, int wanted, int* done, const FlowWeights& fw, FlowRider rider, const FlowRiders* riders,
                                hipStream_t s);
 // has the launch for `wanted` updates of an h x w level of n frames room for that piece?
 bool flow_launch_carries(FlowRider rider, const FlowRiders& riders, int n, int h, int w, int wanted);

@@ -33,16 +33,16 @@ __device__ __forceinline__ int count_static(const float* dp, float tau_t) {
 }
 
 // Eq. 6 and the reuse rule for frame b of a launch, evaluated by a whole block of NT threads from the
-// per-patch motions that an earlier kernel left (dp[b] NULL: no predecessor, never redundant): the
+// per-patch motions that an earlier kernel left (frames[b].dp NULL: no predecessor, never redundant): the
 // kernels of the spatial filter ask this first and leave at once for a redundant frame (Algorithm 1
 // skips its saliency).  Same counts and the same fp32 quotient as the tail kernel that writes the gate,
 // so all of them take the same decision.  s_cnt: NT / 64 ints of LDS.
-template <int NT>
-__device__ __forceinline__ bool frame_redundant(const float* const* dp, int b, const GateParams& gp, int* s_cnt) {
+template <int NT, typename Frame>
+__device__ __forceinline__ bool frame_redundant(const Frame* frames, int b, const GateParams& gp, int* s_cnt) {
     const int b0 = b - b % gp.tiles;
-    if (dp[b0] == nullptr) return false;
+    if (frames[b0].dp == nullptr) return false;
     int n = 0;
-    for (int j = 0; j < gp.tiles; ++j) n += count_static<NT>(dp[b0 + j], gp.tau_t);
+    for (int j = 0; j < gp.tiles; ++j) n += count_static<NT>(frames[b0 + j].dp, gp.tau_t);
     for (int off = 32; off > 0; off >>= 1) n += __shfl_down(n, off);
     if ((threadIdx.x & 63) == 0) s_cnt[threadIdx.x >> 6] = n;
     __syncthreads();
@@ -122,12 +122,13 @@ __device__ __forceinline__ int grad_m2(uint32_t g) {
 template <bool kGated, int NT>
 __device__ __forceinline__ void prep_tile(PrepShared& sh, const PrepBatch& f, int bx, int by, int bz, int h, int w, const GateParams& gp,
                                           const uint32_t* __restrict__ lut_words, int lo2, int hi2) {
-    const uint8_t* __restrict__ rgb = f.rgb[bz];
-    uint8_t* __restrict__ cls_out = f.cls[bz];
-    uint32_t* __restrict__ var_out = f.var[bz];
-    uint32_t* __restrict__ parent_out = f.parent[bz];
-    unsigned long long* msum_acc = f.msum_acc[bz];
-    unsigned long long* msum_clear = f.msum_clear[bz];
+    const PrepFrame& frame = f.frame[bz];
+    const uint8_t* __restrict__ rgb = frame.rgb;
+    uint8_t* __restrict__ cls_out = frame.cls;
+    uint32_t* __restrict__ var_out = frame.var;
+    uint32_t* __restrict__ parent_out = frame.parent;
+    unsigned long long* msum_acc = frame.msum_acc;
+    unsigned long long* msum_clear = frame.msum_clear;
     constexpr int kPrepPx = kTile * kTile / NT;                          // pixels of the tile per thread
     constexpr int kPrepQuads = (kReg * kQuadsY + NT - 1) / NT;           // quads of the region per thread
     constexpr int kLutQuads = (kLutWords / 4 + NT - 1) / NT;
@@ -157,8 +158,8 @@ __device__ __forceinline__ void prep_tile(PrepShared& sh, const PrepBatch& f, in
         // no saliency for a redundant frame; the frame's first block leaves the decision for the kernels
         // after this one, whose blocks are too small to count 576 patches each
         bool skip = false;
-        if constexpr (kGated) skip = frame_redundant<NT>(f.dp, bz, gp, sh.gate);
-        if (bx == 0 && by == 0 && tid == 0) *f.skip[bz] = skip ? 1u : 0u;
+        if constexpr (kGated) skip = frame_redundant<NT>(f.frame, bz, gp, sh.gate);
+        if (bx == 0 && by == 0 && tid == 0) *frame.skip = skip ? 1u : 0u;
         if (skip) return;
     }
     // colour tables -> LDS, gray of the region
@@ -501,7 +502,7 @@ __device__ __forceinline__ void prep_tile(PrepShared& sh, const PrepBatch& f, in
 
 // Hysteresis across tiles, item = border pixel of frame b
 __device__ __forceinline__ void union_item(const PrepBatch& f, int b, int h, int w, int item, int n_items) {
-    if (item < n_items) union_border(f.cls[b], f.parent[b], h, w, item);
+    if (item < n_items) union_border(f.frame[b].cls, f.frame[b].parent, h, w, item);
 }
 
 // Eq. 7 for the pixels of one patch that fall to a lane, pixels p0, p0 + kStride, ...: sum of E + C
@@ -517,10 +518,12 @@ __device__ __forceinline__ PatchBox patch_box(int token, int h, int w) {
 template <int kStride>
 __device__ __forceinline__ uint32_t patch_sum(const PoolBatch& f, int b, const PatchBox& box, int p_first, int h, int w,
                                               uint8_t* __restrict__ salmap) {
-    const uint8_t* __restrict__ cls = f.cls[b];
-    const uint32_t* __restrict__ parent = f.parent[b];
-    const uint32_t* __restrict__ var = f.var[b];
-    const unsigned long long m = *f.msum[b];
+    const PoolFrame& frame = f.frame[b];
+    const uint8_t* __restrict__ cls = frame.cls;
+    const uint32_t* __restrict__ parent = frame.parent;
+    const uint32_t* __restrict__ var = frame.var;
+    together(cls, parent, var, frame.msum, frame.scores, salmap);
+    const unsigned long long m = *frame.msum;
     const unsigned long long hw = (unsigned long long)h * (unsigned long long)w;
     uint32_t q = 0;
     // four pixels per pass, all their loads issued before any is used (the loop is bound by
@@ -557,7 +560,7 @@ __device__ __forceinline__ uint32_t patch_sum(const PoolBatch& f, int b, const P
 __device__ __forceinline__ void store_score(const PoolBatch& f, int b, int token, uint32_t q, int area) {
     const uint32_t s_fix = (uint32_t)(((unsigned long long)q << 15) / (unsigned long long)area);
     const float score = (float)s_fix * (1.0f / 65536.0f);      // exact: s_fix <= 2^16
-    __hip_atomic_store(f.scores[b] + token, score, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __hip_atomic_store(f.frame[b].scores + token, score, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 // one patch by one wave
 __device__ __forceinline__ void score_by_wave(const PoolBatch& f, int b, int token, int h, int w, uint8_t* __restrict__ salmap) {

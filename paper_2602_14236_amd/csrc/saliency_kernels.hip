@@ -37,9 +37,9 @@ namespace sali {
 // gray only, blockIdx.y = frame of the batch: what the flow needs of a frame with a single, large level (elsewhere the
 // kernels that read gray values convert them).  Sixteen pixels per thread (48 bytes in, 16 out) where
 // the caller's image is 16-byte aligned, else pixel by pixel.
-__global__ __launch_bounds__(256) void k_gray(PrepBatch f, int n) {
-    const uint8_t* __restrict__ rgb = f.rgb[blockIdx.y];
-    uint8_t* __restrict__ y8 = f.y8[blockIdx.y];
+__global__ __launch_bounds__(256) void k_gray(int n, PrepBatch f) {
+    const uint8_t* __restrict__ rgb = f.frame[blockIdx.y].rgb;
+    uint8_t* __restrict__ y8 = f.frame[blockIdx.y].y8;
     const int i0 = (blockIdx.x * 256 + threadIdx.x) * 16;
     if (i0 >= n) return;
     if (i0 + 16 <= n && (reinterpret_cast<uintptr_t>(rgb) & 15u) == 0) {
@@ -61,8 +61,8 @@ __global__ __launch_bounds__(256) void k_gray(PrepBatch f, int n) {
 }
 
 template <bool kGated, int NT>
-__global__ __launch_bounds__(NT) void k_prep(PrepBatch f, int h, int w, GateParams gp, const uint32_t* __restrict__ lut_words, int lo2,
-                                             int hi2) {
+__global__ __launch_bounds__(NT) void k_prep(const uint32_t* __restrict__ lut_words, int h, int w, int lo2, int hi2, GateParams gp,
+                                             PrepBatch f) {
     // blockIdx.z = frame of the batch
     __shared__ PrepShared sh;
     prep_tile<kGated, NT>(sh, f, (int)blockIdx.x, (int)blockIdx.y, (int)blockIdx.z, h, w, gp, lut_words, lo2, hi2);
@@ -73,12 +73,14 @@ __global__ __launch_bounds__(NT) void k_prep(PrepBatch f, int h, int w, GatePara
 // frames took 44 us in the pipeline, one frame alone 16.8; now 23.5 and 9.6 (chains of trips past the L2).
 // kGated: the pre-pass ran ahead of the flow and could not ask the reuse rule; it is evaluated here, from the motions.
 template <bool kGated>
-__global__ __launch_bounds__(256) void k_union(PrepBatch f, int h, int w, int n_items, GateParams gp) {
+__global__ __launch_bounds__(256) void k_union(int h, int w, int n_items, GateParams gp, PrepBatch f) {
     if constexpr (kGated) {
         __shared__ int s_cnt[4];
-        if (frame_redundant<256>(f.dp, (int)blockIdx.y, gp, s_cnt)) return;
+        if (frame_redundant<256>(f.frame, (int)blockIdx.y, gp, s_cnt)) return;
     } else {
-        if (*f.skip[blockIdx.y] != 0u) return;      // redundant frame, says the pre-pass
+        const PrepFrame& frame = f.frame[blockIdx.y];
+        together(frame.skip, frame.cls, frame.parent);
+        if (*frame.skip != 0u) return;              // redundant frame, says the pre-pass
     }
     union_item(f, (int)blockIdx.y, h, w, (int)(blockIdx.x * 256 + threadIdx.x), n_items);
 }
@@ -93,17 +95,17 @@ __device__ __forceinline__ void pool_tail(TierShared& sh, int* s_cnt, const Pool
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
     // gate: n_static = #{dP_i < tau_t}, R = n_static / 576, redundant iff R > theta_R; a frame
     // without predecessor (no flow) is never redundant
-    const bool have_flow = f.flow[b] != nullptr;
+    const bool have_flow = f.frame[b].flow != nullptr;
     // the scores are asked for now, with the patch motions: one memory round trip instead of two on the
     // critical path of the batch (a redundant frame does not use them)
-    const TierScores scores = tier_load_scores(f.scores[b]);
+    const TierScores scores = tier_load_scores(f.frame[b].scores);
     // a tiled frame's patches are those of all its tiles (entries b0 .. b0 + tiles - 1 of the launch): the
     // block of every tile counts them all and so reaches the frame's one decision on its own
     const int tiles = tl.tiles;
     const int b0 = b - b % tiles;
     int n = 0;
     if (have_flow)
-        for (int j = 0; j < tiles; ++j) n += count_static<kTierThreads>(f.dp[b0 + j], tau_t);
+        for (int j = 0; j < tiles; ++j) n += count_static<kTierThreads>(f.frame[b0 + j].dp, tau_t);
     for (int off = 32; off > 0; off >>= 1) n += __shfl_down(n, off);
     if (lane == 0) s_cnt[wave] = n;
     __syncthreads();
@@ -122,8 +124,8 @@ __device__ __forceinline__ void pool_tail(TierShared& sh, int* s_cnt, const Pool
         gt.r_frame = have_flow ? r : 0.0f;
         gt.redundant = redundant ? 1 : 0;
         gt.reserved = 0;
-        *f.gate[b] = gt;
-        int32_t* out = reinterpret_cast<int32_t*>(f.tcounts[b]);
+        *f.frame[b].gate = gt;
+        int32_t* out = reinterpret_cast<int32_t*>(f.frame[b].tcounts);
         __hip_atomic_store(out + 0, tc.state, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 #pragma unroll
         for (int t = 0; t < 4; ++t)
@@ -148,7 +150,7 @@ __device__ __forceinline__ void pool_tail(TierShared& sh, int* s_cnt, const Pool
         TierCounts* all = reinterpret_cast<TierCounts*>(&sh);
         static_assert(sizeof(TierCounts) * kMaxBatch <= sizeof(TierShared), "records fit the ranking's memory");
         if ((int)threadIdx.x < n_frames) {
-            const int32_t* in = reinterpret_cast<const int32_t*>(f.tcounts[threadIdx.x]);
+            const int32_t* in = reinterpret_cast<const int32_t*>(f.frame[threadIdx.x].tcounts);
             TierCounts rec = {};
             rec.state = __hip_atomic_load(in + 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 #pragma unroll
@@ -175,7 +177,7 @@ __device__ __forceinline__ void pool_tail(TierShared& sh, int* s_cnt, const Pool
     __syncthreads();
     for (int i = 0; i < n_frames; ++i) {
         // the frame's hand-over record, the same words for every thread
-        const int32_t* in = reinterpret_cast<const int32_t*>(f.tcounts[i]);
+        const int32_t* in = reinterpret_cast<const int32_t*>(f.frame[i].tcounts);
         TierCounts tci = {};
         tci.state = __hip_atomic_load(in + 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         int q[3];
@@ -183,7 +185,7 @@ __device__ __forceinline__ void pool_tail(TierShared& sh, int* s_cnt, const Pool
         for (int j = 0; j < 3; ++j) q[j] = __hip_atomic_load(in + 5 + j, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         const bool ranked = tci.state == 3;
         if (ranked)
-            tci = tier_assign_adaptive(sh, tier_load_scores(f.scores[i]), tl.tier + (size_t)i * kTokens,
+            tci = tier_assign_adaptive(sh, tier_load_scores(f.frame[i].scores), tl.tier + (size_t)i * kTokens,
                                        tl.slot + (size_t)i * kTokens, tl.order + (size_t)i * kTokens);
         __syncthreads();
         if (threadIdx.x == 0) {
@@ -211,7 +213,7 @@ __device__ __forceinline__ void pool_tail(TierShared& sh, int* s_cnt, const Pool
 // blocks per frame) it cost the pooling kernel itself 110 us per four-frame launch against 33 us of work.
 // kGated: as in k_union.
 template <int kWaves, bool kMotion, bool kGated>
-__global__ __launch_bounds__(kTierThreads) void k_pool(PoolBatch f, int h, int w, uint8_t* __restrict__ salmap, GateParams gp) {
+__global__ __launch_bounds__(kTierThreads) void k_pool(uint8_t* __restrict__ salmap, int h, int w, GateParams gp, PoolBatch f) {
     static_assert(kTierThreads == 256, "four waves, one patch each");
     static_assert(kWaves == 1 || kWaves == 4, "");
     const int b = blockIdx.y;                               // frame of the batch
@@ -223,9 +225,11 @@ __global__ __launch_bounds__(kTierThreads) void k_pool(PoolBatch f, int h, int w
         __shared__ uint32_t s_pq[kTierThreads / 64];
         if constexpr (kGated) {
             __shared__ int s_cnt[kTierThreads / 64];
-            if (frame_redundant<kTierThreads>(f.dp, b, gp, s_cnt)) return;
+            if (frame_redundant<kTierThreads>(f.frame, b, gp, s_cnt)) return;
         } else {
-            if (*f.skip[b] != 0u) return;                   // redundant frame, says the pre-pass
+            const PoolFrame& frame = f.frame[b];
+            together(frame.skip, frame.cls, frame.parent, frame.var, frame.msum, frame.scores);
+            if (*frame.skip != 0u) return;                  // redundant frame, says the pre-pass
         }
         if constexpr (kWaves == 1) {
             score_by_wave(f, b, token, h, w, salmap);
@@ -239,10 +243,12 @@ __global__ __launch_bounds__(kTierThreads) void k_pool(PoolBatch f, int h, int w
         }
     } else {
         __shared__ float s_pm[kTierThreads / 64];
-        const float2* __restrict__ flow = f.flow[b];
+        const float2* __restrict__ flow = f.frame[b].flow;
+        float* dp_out = f.frame[b].dp_out;
+        together(flow, dp_out);
         if (flow == nullptr) {                              // no predecessor: no motion
             if (lane == 0 && (kWaves == 1 || wave == 0))
-                __hip_atomic_store(f.dp_out[b] + token, 0.0f, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                __hip_atomic_store(dp_out + token, 0.0f, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             return;
         }
         const PatchBox box = patch_box(token, h, w);
@@ -266,13 +272,13 @@ __global__ __launch_bounds__(kTierThreads) void k_pool(PoolBatch f, int h, int w
             mag = (s_pm[0] + s_pm[1]) + (s_pm[2] + s_pm[3]);
         }
         if (lane == 0 && (kWaves == 1 || wave == 0))
-            __hip_atomic_store(f.dp_out[b] + token, sqrtf(mag / (float)box.area), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            __hip_atomic_store(dp_out + token, sqrtf(mag / (float)box.area), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
 }
 
 // the tail as a launch of its own: one block per frame
-__global__ __launch_bounds__(kTierThreads) void k_pool_tail(PoolBatch f, float tau_t, float theta_r, TierLaunch tl,
-                                                            uint32_t* batch_done) {
+__global__ __launch_bounds__(kTierThreads) void k_pool_tail(uint32_t* batch_done, float tau_t, float theta_r, TierLaunch tl,
+                                                            PoolBatch f) {
     __shared__ TierShared sh;
     __shared__ int s_cnt[kTierThreads / 64];
     pool_tail(sh, s_cnt, f, (int)blockIdx.x, (int)gridDim.x, tau_t, theta_r, tl, batch_done);
@@ -281,7 +287,7 @@ __global__ __launch_bounds__(kTierThreads) void k_pool_tail(PoolBatch f, float t
 // ---------------------------------------------------------------------------------------------
 hipError_t launch_gray(const PrepBatch& f, int n, int h, int w, hipStream_t s) {
     const int px = h * w;
-    hipLaunchKernelGGL(k_gray, dim3((px + 4095) / 4096, n), dim3(256), 0, s, f, px);
+    hipLaunchKernelGGL(k_gray, dim3((px + 4095) / 4096, n), dim3(256), 0, s, px, f);
     return hipGetLastError();
 }
 
@@ -290,14 +296,14 @@ hipError_t launch_prep(const PrepBatch& f, int n, int h, int w, GateParams gp, c
     dim3 grid((w + kTile - 1) / kTile, (h + kTile - 1) / kTile, n);
     const uint32_t* lut = static_cast<const uint32_t*>(d_lut);
     bool gated = false;
-    for (int i = 0; i < n; ++i) gated = gated || f.dp[i] != nullptr;
+    for (int i = 0; i < n; ++i) gated = gated || f.frame[i].dp != nullptr;
     // Batches (the chained step, behind its flow) on 256 threads: next to K/V kernels small blocks find room, 640x360 clips are
     // 0.5 to 1 % slower with 512.  The stand-alone call on 512, or on 1024 if every tile has a compute unit to itself: a stage of
     // 300 to 400 strips is one pass instead of two, the whole call at 640x360 37.7 -> 32.6 us (512 threads 33.2), at
     // 1920x1080 96.3 -> 92.9 (1024 threads 95.4).
-    if (gated) hipLaunchKernelGGL((k_prep<true, kPrepThreads>), grid, dim3(kPrepThreads), 0, s, f, h, w, gp, lut, lo2, hi2);
-    else if ((long long)grid.x * grid.y * n <= 256) hipLaunchKernelGGL((k_prep<false, 1024>), grid, dim3(1024), 0, s, f, h, w, gp, lut, lo2, hi2);
-    else hipLaunchKernelGGL((k_prep<false, 512>), grid, dim3(512), 0, s, f, h, w, gp, lut, lo2, hi2);
+    if (gated) hipLaunchKernelGGL((k_prep<true, kPrepThreads>), grid, dim3(kPrepThreads), 0, s, lut, h, w, lo2, hi2, gp, f);
+    else if ((long long)grid.x * grid.y * n <= 256) hipLaunchKernelGGL((k_prep<false, 1024>), grid, dim3(1024), 0, s, lut, h, w, lo2, hi2, gp, f);
+    else hipLaunchKernelGGL((k_prep<false, 512>), grid, dim3(512), 0, s, lut, h, w, lo2, hi2, gp, f);
     return hipGetLastError();
 }
 
@@ -305,8 +311,8 @@ hipError_t launch_union(const PrepBatch& f, int n, int h, int w, const GateParam
     const int items = border_items(h, w);
     if (items == 0) return hipSuccess;              // a single tile
     const dim3 grid((items + 255) / 256, n);
-    if (gate_or_null != nullptr) hipLaunchKernelGGL(k_union<true>, grid, dim3(256), 0, s, f, h, w, items, *gate_or_null);
-    else hipLaunchKernelGGL(k_union<false>, grid, dim3(256), 0, s, f, h, w, items, GateParams{});
+    if (gate_or_null != nullptr) hipLaunchKernelGGL(k_union<true>, grid, dim3(256), 0, s, h, w, items, *gate_or_null, f);
+    else hipLaunchKernelGGL(k_union<false>, grid, dim3(256), 0, s, h, w, items, GateParams{}, f);
     return hipGetLastError();
 }
 
@@ -315,9 +321,9 @@ namespace {
 template <bool kMotion, bool kGated>
 hipError_t launch_patches(const PoolBatch& f, int n, int h, int w, uint8_t* d_salmap, const GateParams& gp, hipStream_t s) {
     if ((long long)h * w <= 1024ll * kTokens)
-        hipLaunchKernelGGL((k_pool<1, kMotion, kGated>), dim3(kTokens / 4, n), dim3(kTierThreads), 0, s, f, h, w, d_salmap, gp);
+        hipLaunchKernelGGL((k_pool<1, kMotion, kGated>), dim3(kTokens / 4, n), dim3(kTierThreads), 0, s, d_salmap, h, w, gp, f);
     else
-        hipLaunchKernelGGL((k_pool<4, kMotion, kGated>), dim3(kTokens, n), dim3(kTierThreads), 0, s, f, h, w, d_salmap, gp);
+        hipLaunchKernelGGL((k_pool<4, kMotion, kGated>), dim3(kTokens, n), dim3(kTierThreads), 0, s, d_salmap, h, w, gp, f);
     return hipGetLastError();
 }
 }  // namespace
@@ -334,7 +340,7 @@ hipError_t launch_scores(const PoolBatch& f, int n, int h, int w, uint8_t* d_sal
 
 hipError_t launch_tail(const PoolBatch& f, int n, const TierLaunch& tier, GateParams gp, uint32_t* d_done_counter,
                        hipEvent_t done_or_null, hipStream_t s) {
-    launch_recording(done_or_null, k_pool_tail, dim3(n), dim3(kTierThreads), s, f, gp.tau_t, gp.theta_r, tier, d_done_counter);
+    launch_recording(done_or_null, k_pool_tail, dim3(n), dim3(kTierThreads), s, d_done_counter, gp.tau_t, gp.theta_r, tier, f);
     return hipGetLastError();
 }
 

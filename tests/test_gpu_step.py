@@ -475,6 +475,28 @@ def test_motions_do_not_depend_on_the_batch_size(h, w, levels, iters):
         assert got == ref, f"{n} frames a call: frames {[t for t in range(16) if got[t] != ref[t]]} differ"
 
 
+@pytest.mark.parametrize("h,w", [(640, 736), (641, 705), (992, 1000)])      # 460, 483 and 992 tiles of 32x32
+def test_flow_of_levels_that_are_cut_into_runs_by_frames(h, w):
+    """From 480 tiles on the blocks of a batch are dealt to the chip frame by frame instead of all together: every tile of every
+    frame is made once, so motions of a batch are those of single frames, bit by bit."""
+    from paper_2602_14236_amd import binding
+    rng = np.random.default_rng(h)
+    yy, xx = np.mgrid[0:h, 0:w].astype(np.float64)
+    rgbs = []
+    for t in range(4):
+        img = 120 + 60 * np.sin((xx - 1.3 * t) / 4.1) * np.sin((yy + 0.7 * t) / 5.3)
+        img = img[..., None] * np.array([1.0, 0.8, 0.6]) + rng.normal(0, 2, (h, w, 3))
+        rgbs.append(torch.from_numpy(np.clip(np.rint(img), 0, 255).astype(np.uint8)).cuda())
+    got = []
+    for n in (1, 4):
+        ctx = binding.SaliContext(lib_config(params(h, w, flow_levels=2, flow_iters=2, max_frames=4)))
+        for lo in range(0, 4, n):
+            ctx.analyze_batch(rgbs[lo:lo + n], lo)
+        got.append([ctx.read_analysis(t)[0].tobytes() for t in range(4)])
+        ctx.close()
+    assert len(set(got[0])) == 4 and got[0] == got[1]
+
+
 @pytest.mark.parametrize("h,w,levels,iters,n,tiles", [
     (336, 336, 3, 1, 1, 1), (336, 336, 3, 2, 4, 1), (32, 32, 1, 1, 4, 1),      # hysteresis and scores behind the flow; a single tile
     (336, 336, 3, 3, 4, 1), (512, 512, 3, 3, 1, 1),                            # the scores only
