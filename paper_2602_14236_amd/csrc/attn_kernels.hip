@@ -19,8 +19,8 @@
 // 8 consecutive head-dim values each, a 32-value quantisation group is one lane quad, the dot
 // product is reduced over the 16 lanes with four DPP moves.  Every lane group keeps an
 // online-softmax state (running max, sum and 8 output values per lane); a block merges its 16 lane
-// groups through LDS and writes one partial (max, sum, 128 values); a second small kernel merges
-// the partials of a head.  The three tiers of a frame are walked by three instances of one loop
+// groups through LDS and writes one partial (max, sum, 128 values); the last block of a head to finish merges
+// the partials.  The three tiers of a frame are walked by three instances of one loop
 // specialised on the row format.  With grouped-query attention the kQ query heads that share a K/V
 // head are handled by the same block, so every compressed row is still read once.
 
@@ -35,7 +35,6 @@ typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
 typedef _Float16 half2_t __attribute__((ext_vector_type(2)));
 
 constexpr int kComputeUnits = 256;
-constexpr int kResidentBlocks = kComputeUnits * 8;      // compute units x blocks of the main kernel that fit on one
 constexpr int kPartialStride = kAttnPartialStride;   // max, sum, 128 values, padded to whole 128-byte lines
 
 union Row16B {
@@ -59,12 +58,24 @@ __device__ __forceinline__ float row16_sum(float v) {
     return v;
 }
 
-// the lane's piece of the query: 8 values as fp32 and as packed halves, and their sum
+// the lane's piece of the query: 8 values as packed halves, in the pairs (2 i, 2 i + 1) and (i, i + 4) that the codes of a row come in,
+// and their sum
 struct QueryPiece {
-    float f[8];
-    half2_t h2[4];
+    half2_t h2[4], across[4];
     float sum;
 };
+__device__ __forceinline__ QueryPiece query_piece(const Row16B& q) {
+    QueryPiece p;
+    p.sum = 0.0f;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) p.sum += (float)q.h[e];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        p.h2[e] = q.h2[e];
+        p.across[e] = (half2_t){q.h[e], q.h[e + 4]};
+    }
+    return p;
+}
 
 // raw piece of one pool row for one lane (16 / 8 / 4 bytes by tier) plus its group's scale and zero
 template <int kTier>
@@ -84,21 +95,66 @@ struct RawRow<SALI_TIER_INT4> {
     float scale, zero;
 };
 
-// frow = row index in the flat pool array of that tier (pool_row0 of the frame and plane + the row
-// inside the frame's run)
-__device__ __forceinline__ void load_row(const Pools& pools, size_t frow, int l, RawRow<SALI_TIER_FP16>& r) {
-    r.u = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(pools.p16) + (frow * 16 + l));
+// the rows of one tier of one frame and plane; uniform over the block, so that a lane's address is a scalar base and 32 bits
+struct TierRows {
+    const char* codes;
+    const float* scale;
+    const uint16_t* zero;
+};
+template <int kTier>
+__device__ __forceinline__ TierRows tier_rows(const Pools& pools, int base, int count, size_t plane) {
+    const size_t row0 = pool_row0(pools, base, count, plane);
+    if constexpr (kTier == SALI_TIER_FP16) return {reinterpret_cast<const char*>(pools.p16 + row0 * kHeadDim), nullptr, nullptr};
+    else if constexpr (kTier == SALI_TIER_INT8) return {reinterpret_cast<const char*>(pools.c8 + row0 * kHeadDim), pools.s8 + row0 * kGroupsPerRow, nullptr};
+    else return {reinterpret_cast<const char*>(pools.c4 + row0 * (kHeadDim / 2)), pools.s4 + row0 * kGroupsPerRow, pools.z4 + row0 * kGroupsPerRow};
 }
-__device__ __forceinline__ void load_row(const Pools& pools, size_t frow, int l, RawRow<SALI_TIER_INT8>& r) {
-    r.u = __builtin_nontemporal_load(reinterpret_cast<const u32x2*>(pools.c8 + frow * kHeadDim) + l);
-    r.scale = pools.s8[frow * kGroupsPerRow + (l >> 2)];
-}
-__device__ __forceinline__ void load_row(const Pools& pools, size_t frow, int l, RawRow<SALI_TIER_INT4>& r) {
-    r.u = __builtin_nontemporal_load(reinterpret_cast<const uint32_t*>(pools.c4 + frow * (kHeadDim / 2)) + l);
-    r.scale = pools.s4[frow * kGroupsPerRow + (l >> 2)];
-    r.zero = (float)__builtin_bit_cast(_Float16, pools.z4[frow * kGroupsPerRow + (l >> 2)]);
+template <typename V>
+__device__ __forceinline__ const V* at_byte(const void* base, uint32_t offset) {
+    return reinterpret_cast<const V*>(static_cast<const char*>(base) + offset);
 }
 
+// the lane's piece of row j
+__device__ __forceinline__ void load_row(const TierRows& t, uint32_t j, uint32_t l, RawRow<SALI_TIER_FP16>& r) {
+    r.u = __builtin_nontemporal_load(at_byte<u32x4>(t.codes, j * (kHeadDim * 2) + l * 16));
+}
+__device__ __forceinline__ void load_row(const TierRows& t, uint32_t j, uint32_t l, RawRow<SALI_TIER_INT8>& r) {
+    r.u = __builtin_nontemporal_load(at_byte<u32x2>(t.codes, j * kHeadDim + l * 8));
+    r.scale = *at_byte<float>(t.scale, j * (kGroupsPerRow * 4) + (l >> 2) * 4);
+}
+__device__ __forceinline__ void load_row(const TierRows& t, uint32_t j, uint32_t l, RawRow<SALI_TIER_INT4>& r) {
+    r.u = __builtin_nontemporal_load(at_byte<uint32_t>(t.codes, j * (kHeadDim / 2) + l * 4));
+    r.scale = *at_byte<float>(t.scale, j * (kGroupsPerRow * 4) + (l >> 2) * 4);
+    r.zero = (float)__builtin_bit_cast(_Float16, *at_byte<uint16_t>(t.zero, j * (kGroupsPerRow * 2) + (l >> 2) * 2));
+}
+
+// The lane's raw values of a row as pairs of halves.  Codes become halves through their place in the mantissa of 1024 (then 1024, and the
+// 128 of a signed byte, are taken off: exact), two at a time.
+__device__ __forceinline__ half2_t half_pair(uint32_t bits, float bias) {
+    const half2_t b = {(_Float16)bias, (_Float16)bias};
+    return __builtin_bit_cast(half2_t, bits) - b;
+}
+// INT4 codes are taken around their middle (K^ = (code - 8) * scale + (zero + 8 * scale), V^ alike): the two parts of a sum then do not
+// cancel as those of positive codes and the smallest value of the group do
+constexpr float kMidCode4 = 8.0f;
+struct HalfPairs {
+    half2_t v[4];
+};
+__device__ __forceinline__ HalfPairs row_pairs(const RawRow<SALI_TIER_FP16>& r) {
+    Row16B v;
+    v.u = r.u;
+    return {{v.h2[0], v.h2[1], v.h2[2], v.h2[3]}};
+}
+__device__ __forceinline__ HalfPairs row_pairs(const RawRow<SALI_TIER_INT8>& r) {
+    const uint32_t x = r.u.x ^ 0x80808080u, y = r.u.y ^ 0x80808080u, exponent = 0x64646464u;
+    return {{half_pair(__builtin_amdgcn_perm(exponent, x, 0x04010400u), 1152.0f), half_pair(__builtin_amdgcn_perm(exponent, x, 0x04030402u), 1152.0f),
+             half_pair(__builtin_amdgcn_perm(exponent, y, 0x04010400u), 1152.0f), half_pair(__builtin_amdgcn_perm(exponent, y, 0x04030402u), 1152.0f)}};
+}
+__device__ __forceinline__ HalfPairs row_pairs(const RawRow<SALI_TIER_INT4>& r) {
+    HalfPairs p;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) p.v[i] = half_pair((r.u >> (4 * i) & 0x000F000Fu) | 0x64006400u, 1024.0f + kMidCode4);
+    return p;
+}
 // The lane's 8 stored values of a row as fp32: the halves of an FP16 row, the raw codes of an
 // INT8 / INT4 row (scale and zero-point are applied once per row, see finish_dot / weight_of).
 __device__ __forceinline__ void row_values(const RawRow<SALI_TIER_FP16>& r, float x[8]) {
@@ -115,15 +171,21 @@ __device__ __forceinline__ void row_values(const RawRow<SALI_TIER_INT8>& r, floa
     }
 }
 __device__ __forceinline__ void row_values(const RawRow<SALI_TIER_INT4>& r, float x[8]) {
-    // nibbles to bytes first (even elements in one word, odd ones in the other): a byte converts to fp32
-    // in one instruction; the empty asm keeps the compiler from folding the bytes back into nibbles
-    uint32_t ev = r.u & 0x0F0F0F0Fu, od = (r.u >> 4) & 0x0F0F0F0Fu;
-    asm volatile("" : "+v"(ev), "+v"(od));
+    const HalfPairs p = row_pairs(r);
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-        x[2 * i] = (float)((ev >> (8 * i)) & 0xFFu);
-        x[2 * i + 1] = (float)((od >> (8 * i)) & 0xFFu);
+        x[i] = (float)p.v[i][0];
+        x[i + 4] = (float)p.v[i][1];
     }
+}
+
+// <q, raw values of the row> of the lane: products of halves, which are exact, summed in fp32; half the operations of one value at a time
+template <int kTier>
+__device__ __forceinline__ float raw_dot(const HalfPairs& x, const QueryPiece& q) {
+    const half2_t (&w)[4] = kTier == SALI_TIER_INT4 ? q.across : q.h2;
+    // two short sums rather than one long one
+    return __builtin_amdgcn_fdot2(w[1], x.v[1], __builtin_amdgcn_fdot2(w[0], x.v[0], 0.0f, false), false) +
+           __builtin_amdgcn_fdot2(w[3], x.v[3], __builtin_amdgcn_fdot2(w[2], x.v[2], 0.0f, false), false);
 }
 
 // <q, K^_row> of the lane from the sum over its raw values: K^ = code * scale (+ zero)
@@ -132,7 +194,7 @@ __device__ __forceinline__ float finish_dot(const RawRow<SALI_TIER_INT8>& r, flo
     return d * r.scale;
 }
 __device__ __forceinline__ float finish_dot(const RawRow<SALI_TIER_INT4>& r, float d, const QueryPiece& q) {
-    return d * r.scale + q.sum * r.zero;
+    return __builtin_fmaf(d, r.scale, q.sum * __builtin_fmaf(kMidCode4, r.scale, r.zero));
 }
 
 // p * V^_row = (p * scale) * code + p * zero: weight on the raw values, and the constant part
@@ -141,7 +203,7 @@ __device__ __forceinline__ float weight_of(const RawRow<SALI_TIER_INT8>& r, floa
 __device__ __forceinline__ float weight_of(const RawRow<SALI_TIER_INT4>& r, float p) { return p * r.scale; }
 __device__ __forceinline__ float offset_of(const RawRow<SALI_TIER_FP16>&, float) { return 0.0f; }
 __device__ __forceinline__ float offset_of(const RawRow<SALI_TIER_INT8>&, float) { return 0.0f; }
-__device__ __forceinline__ float offset_of(const RawRow<SALI_TIER_INT4>& r, float p) { return p * r.zero; }
+__device__ __forceinline__ float offset_of(const RawRow<SALI_TIER_INT4>& r, float p) { return p * __builtin_fmaf(kMidCode4, r.scale, r.zero); }
 
 // online-softmax state of a lane group for one query (max and sum are equal in its 16 lanes); the
 // INT4 zero-points are summed apart (zacc, the same for the lane's 8 values) and folded in at the end
@@ -150,54 +212,52 @@ struct SoftmaxState {
     float acc[8];
 };
 
-// The rows of one tier of one stored frame that fall to this block: groups of 16 * kRowsPerStep rows split,
-// split + n_splits, ...; lane group g takes rows jb + g, jb + 16 + g, ... (kRowsPerStep of them in flight, K
-// and V each).  `base` = first pool row of the frame in this tier, `count` = its rows.  kQ queries share
-// every row that is read.  Returns the split that the next tier's first group falls to, so that the groups
-// of a frame's tiers go round all splits.
+// Rows j0 .. j1 - 1 of one tier of one stored frame: lane group g takes rows j0 + g, j0 + 16 + g, ... (kRowsPerStep of them in
+// flight, K and V each).  `base` = first pool row of the frame in this tier, `count` = its rows.  kQ queries share
+// every row that is read.
 template <int kTier, int kQ, int kRowsPerStep>
-__device__ __forceinline__ int attend_tier(const Pools& pools, size_t plane_k, size_t plane_v, int base, int count,
-                                           int split, int n_splits, int g, int l, const QueryPiece (&q)[kQ],
-                                           float softmax_scale, float mult, SoftmaxState (&st)[kQ]) {
-    constexpr int kGroupRows = 16 * kRowsPerStep;
-    if (count == 0) return split;
-    const size_t row0_k = pool_row0(pools, base, count, plane_k), row0_v = pool_row0(pools, base, count, plane_v);
-    for (int jb = split * kGroupRows; jb < count; jb += n_splits * kGroupRows) {
-        RawRow<kTier> rk[kRowsPerStep], rv[kRowsPerStep];
+__device__ __forceinline__ void attend_rows(const Pools& pools, size_t plane_k, size_t plane_v, int base, int count, int j0, int j1,
+                                            int g, int l, const Row16B (&raw_q)[kQ], float softmax_scale, float mult,
+                                            SoftmaxState (&st)[kQ]) {
+    if (j0 >= j1) return;
+    const TierRows k = tier_rows<kTier>(pools, base, count, plane_k), v = tier_rows<kTier>(pools, base, count, plane_v);
+    // rows past the end repeat the last one and count for nothing (their weight is exp(-inf))
+    struct Step {
+        RawRow<kTier> k[kRowsPerStep], v[kRowsPerStep];
+    };
+    auto request = [&](int jb, Step& step) {
+#pragma unroll
+        for (int r = 0; r < kRowsPerStep; ++r) load_row(k, (uint32_t)min(jb + r * 16 + g, j1 - 1), (uint32_t)l, step.k[r]);
+#pragma unroll
+        for (int r = 0; r < kRowsPerStep; ++r) load_row(v, (uint32_t)min(jb + r * 16 + g, j1 - 1), (uint32_t)l, step.v[r]);
+    };
+    Step next;
+    request(j0, next);
+    // only now: made ahead of the frame table's read, the pieces had that and the first rows wait for the query's trip, behind
+    // the rows of blocks that were quicker
+    QueryPiece q[kQ];
+#pragma unroll
+    for (int iq = 0; iq < kQ; ++iq) q[iq] = query_piece(raw_q[iq]);
+    for (int jb = j0; jb < j1; jb += 16 * kRowsPerStep) {
+        const Step now = next;
+        const RawRow<kTier> (&rk)[kRowsPerStep] = now.k;
+        const RawRow<kTier> (&rv)[kRowsPerStep] = now.v;
+        if (jb + 16 * kRowsPerStep < j1) request(jb + 16 * kRowsPerStep, next);      // under way while this step is worked on
         bool valid[kRowsPerStep];
 #pragma unroll
-        for (int r = 0; r < kRowsPerStep; ++r) {
-            const int j = jb + r * 16 + g;
-            valid[r] = j < count;
-            rk[r] = {};
-            rv[r] = {};
-            if (valid[r]) {
-                load_row(pools, row0_k + (size_t)j, l, rk[r]);
-                load_row(pools, row0_v + (size_t)j, l, rv[r]);
-            }
-        }
+        for (int r = 0; r < kRowsPerStep; ++r) valid[r] = jb + r * 16 + g < j1;
         float s[kQ][kRowsPerStep];
 #pragma unroll
         for (int r = 0; r < kRowsPerStep; ++r) {
-            float x[8];
-            row_values(rk[r], x);
+            const HalfPairs x = row_pairs(rk[r]);
 #pragma unroll
             for (int iq = 0; iq < kQ; ++iq) {
-                float d = 0.0f;
-                if constexpr (kTier == SALI_TIER_FP16) {
-                    Row16B v;
-                    v.u = rk[r].u;
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) d = __builtin_amdgcn_fdot2(q[iq].h2[e], v.h2[e], d, false);
-                } else {
-#pragma unroll
-                    for (int e = 0; e < 8; ++e) d += q[iq].f[e] * x[e];
-                }
+                float d = raw_dot<kTier>(x, q[iq]);
                 d = row16_sum(finish_dot(rk[r], d, q[iq]));
                 s[iq][r] = valid[r] ? softmax_scale * d : -INFINITY;
             }
         }
-        float p[kQ][kRowsPerStep];
+        float p[kQ][kRowsPerStep], corr[kQ];
 #pragma unroll
         for (int iq = 0; iq < kQ; ++iq) {
             float bm = -INFINITY;
@@ -207,18 +267,18 @@ __device__ __forceinline__ int attend_tier(const Pools& pools, size_t plane_k, s
             // nothing seen yet for this lane group: keep the state (every weight below is exp(-inf) = 0,
             // and the reference maximum must stay finite for that)
             const float ref = new_mx == -INFINITY ? 0.0f : new_mx;
-            const float corr = __expf(st[iq].mx - ref);     // first rows: exp(-inf) = 0
-            st[iq].lsum *= corr;
-            st[iq].zacc *= corr;
-#pragma unroll
-            for (int e = 0; e < 8; ++e) st[iq].acc[e] *= corr;
+            corr[iq] = __expf(st[iq].mx - ref);             // first rows: exp(-inf) = 0
+            float sum = 0.0f;
 #pragma unroll
             for (int r = 0; r < kRowsPerStep; ++r) {
                 p[iq][r] = mult * __expf(s[iq][r] - ref);   // absent row: exp(-inf) = 0
-                st[iq].lsum += p[iq][r];
+                sum += p[iq][r];
             }
+            st[iq].lsum = __builtin_fmaf(st[iq].lsum, corr[iq], sum);
             st[iq].mx = new_mx;
         }
+        // the step's rows are added up first, so that the long sums are rounded once a step
+        float sums[kQ][8], zeros[kQ];
 #pragma unroll
         for (int r = 0; r < kRowsPerStep; ++r) {
             float x[8];
@@ -226,50 +286,166 @@ __device__ __forceinline__ int attend_tier(const Pools& pools, size_t plane_k, s
 #pragma unroll
             for (int iq = 0; iq < kQ; ++iq) {
                 const float wgt = weight_of(rv[r], p[iq][r]);
-                st[iq].zacc += offset_of(rv[r], p[iq][r]);
+                zeros[iq] = (r == 0 ? 0.0f : zeros[iq]) + offset_of(rv[r], p[iq][r]);
 #pragma unroll
-                for (int e = 0; e < 8; ++e) st[iq].acc[e] += wgt * x[e];
+                for (int e = 0; e < 8; ++e) sums[iq][e] = r == 0 ? wgt * x[e] : __builtin_fmaf(wgt, x[e], sums[iq][e]);
             }
         }
+#pragma unroll
+        for (int iq = 0; iq < kQ; ++iq) {
+            st[iq].zacc = __builtin_fmaf(st[iq].zacc, corr[iq], zeros[iq]);
+#pragma unroll
+            for (int e = 0; e < 8; ++e) st[iq].acc[e] = __builtin_fmaf(st[iq].acc[e], corr[iq], sums[iq][e]);
+        }
     }
-    const int next = split - (count + kGroupRows - 1) / kGroupRows % n_splits;
-    return next < 0 ? next + n_splits : next;
+}
+
+// Hand-over of partials inside a launch: the block of a head that is the last to arrive merges them, nobody waits.  The partials
+// are written and read past the caches that the compute dies do not share (relaxed agent-scope accesses, each coherent
+// by itself) and a block counts itself in only when its own have arrived, so no fence is needed: an agent-scope fence writes back and
+// invalidates the L2 of the issuing die under the stream that the other blocks are reading (with one in each of
+// 2000 blocks this hand-over measured 4.5 times the time of a merge kernel).  The counter is zero again when the launch ends.
+__device__ __forceinline__ void put(float* p, float v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+__device__ __forceinline__ float2 get_pair(const float* p) {
+    return __builtin_bit_cast(float2, __hip_atomic_load(reinterpret_cast<const unsigned long long*>(p), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+}
+__device__ __forceinline__ bool last_to_arrive(uint32_t* arrived, int blocks, int* s_last) {
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");        // every wave: its stores have arrived
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        const bool last = __hip_atomic_fetch_add(arrived, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == (uint32_t)blocks - 1u;
+        if (last) __hip_atomic_store(arrived, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        *s_last = last ? 1 : 0;
+    }
+    __syncthreads();
+    return *s_last != 0;
+}
+
+// over the 64 lanes, the result in every lane: inside the rows of 16, then row by row through scalar registers
+__device__ __forceinline__ float lane_value(float v, int lane) {
+    return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), lane));
+}
+__device__ __forceinline__ float wave_sum(float v) {
+    v = row16_sum(v);
+    return (lane_value(v, 0) + lane_value(v, 16)) + (lane_value(v, 32) + lane_value(v, 48));
+}
+__device__ __forceinline__ float wave_max(float v) {
+    v = fmaxf(v, dpp_move<0xB1>(v));
+    v = fmaxf(v, dpp_move<0x4E>(v));
+    v = fmaxf(v, dpp_move<0x141>(v));
+    v = fmaxf(v, dpp_move<0x140>(v));
+    return fmaxf(fmaxf(lane_value(v, 0), lane_value(v, 16)), fmaxf(lane_value(v, 32), lane_value(v, 48)));
+}
+
+// A wave's share of merging the partials of NQ queries at once: partials `first`, first + kStep, ... of n (at most kAttnPartials),
+// whose values it adds up weighted (lane i: values 2 i, 2 i + 1); all of it in as few trips as there are: every wave reads all
+// maxima itself (a lane each) while its first kFlight partials are already under way.  lt = the sum of weights.
+template <int NQ, int kStep, int kFlight>
+__device__ __forceinline__ void merge_partials(const float* const (&p)[NQ], int n, int first, float (&big)[NQ], float (&lt)[NQ], float2 (&at)[NQ]) {
+    constexpr int kPerLane = kAttnPartials / 64;
+    const int lane = threadIdx.x & 63;
+    float m[NQ][kPerLane], l[NQ][kPerLane];
+    float2 v[NQ][kFlight];
+    auto request = [&](int k) {
+#pragma unroll
+        for (int q = 0; q < NQ; ++q)
+#pragma unroll
+            for (int u = 0; u < kFlight; ++u)
+                v[q][u] = get_pair(p[q] + (size_t)min(k + u * kStep, n - 1) * kPartialStride + 2 + 2 * lane);
+    };
+#pragma unroll
+    for (int q = 0; q < NQ; ++q)
+#pragma unroll
+        for (int j = 0; j < kPerLane; ++j) {
+            m[q][j] = -INFINITY;
+            l[q][j] = 0.0f;
+            if (64 * j < n && 64 * j + lane < n) {
+                const float2 ml = get_pair(p[q] + (size_t)(64 * j + lane) * kPartialStride);
+                m[q][j] = ml.x;
+                l[q][j] = ml.y;
+            }
+        }
+    request(first);
+#pragma unroll
+    for (int q = 0; q < NQ; ++q) {
+        big[q] = wave_max(fmaxf(fmaxf(m[q][0], m[q][1]), fmaxf(m[q][2], m[q][3])));
+        lt[q] = 0.0f;
+#pragma unroll
+        for (int j = 0; j < kPerLane; ++j) {
+            if (64 * j >= n) break;
+            m[q][j] = big[q] != -INFINITY ? expf(m[q][j] - big[q]) : 0.0f;      // the partial's weight
+            lt[q] += m[q][j] * l[q][j];
+        }
+    }
+    // four sums side by side, added up last: shorter chains, and less rounding
+    float2 sum[NQ][4] = {};
+    for (int k = first; k < n; k += kFlight * kStep) {
+#pragma unroll
+        for (int q = 0; q < NQ; ++q)
+#pragma unroll
+            for (int u = 0; u < kFlight; ++u) {
+                const int ku = k + u * kStep;
+                if (ku < n) {
+                    const float mine = ku < 64 ? m[q][0] : (ku < 128 ? m[q][1] : (ku < 192 ? m[q][2] : m[q][3]));
+                    const float w = lane_value(mine, ku & 63);
+                    sum[q][u & 3].x += w * v[q][u].x;
+                    sum[q][u & 3].y += w * v[q][u].y;
+                }
+            }
+        if (k + kFlight * kStep < n) request(k + kFlight * kStep);
+    }
+#pragma unroll
+    for (int q = 0; q < NQ; ++q) {
+        lt[q] = wave_sum(lt[q]);
+        at[q] = make_float2((sum[q][0].x + sum[q][1].x) + (sum[q][2].x + sum[q][3].x), (sum[q][0].y + sum[q][1].y) + (sum[q][2].y + sum[q][3].y));
+    }
+}
+static_assert(kAttnPartials == 256, "four partials a lane");
+
+// the merged result of query head h: lane i has values 2 i, 2 i + 1 (the caller's arrays are aligned for float only)
+__device__ __forceinline__ void store_result(const AttnOut& o, int h, float big, float lt, float2 at) {
+    const int lane = threadIdx.x & 63;
+    float* dst = o.out + (size_t)h * kHeadDim + 2 * lane;
+    dst[0] = lt > 0.0f ? at.x / lt : 0.0f;
+    dst[1] = lt > 0.0f ? at.y / lt : 0.0f;
+    if (o.lse != nullptr && lane == 0) o.lse[h] = lt > 0.0f ? big + logf(lt) : -INFINITY;
 }
 
 }  // namespace
 
-// grid (n_chunks * n_splits, n_heads).  Block (c, s) of K/V head h takes the frames
-// [frame_lo + c * frames_per_chunk, ...) and of each source frame every n_splits-th group of rows, for kQ of the query heads that share the K/V head (gridDim.z such sets:
-// q_per_kv = kQ * gridDim.z), and writes one partial per query head.
-template <int kQ, int kRowsPerStep>
-__global__ __launch_bounds__(256) void k_attn_partial(const sali_frame_row* __restrict__ rows, Pools pools, int layer,
-                                                      int n_heads, const _Float16* __restrict__ q, int frame_lo,
-                                                      int frame_hi, int tiles, int frames_per_chunk, int n_splits,
-                                                      float softmax_scale, float* __restrict__ partial) {
-    __shared__ float s_m[16], s_l[16];
-    __shared__ float s_acc[16][kHeadDim];
+// blocks of the streaming kernel that fit a compute unit, by the registers that kQ queries take
+constexpr int blocks_per_unit(int kq) { return kq == 4 ? 2 : 4; }
 
-    const int h = blockIdx.y;
-    const int q_first = (h * (int)gridDim.z + (int)blockIdx.z) * kQ;      // first query head of this block
-    const int chunk = blockIdx.x / n_splits, split = blockIdx.x % n_splits;
+// Blocks: parts of the frame range x n_heads x sets, dealt so that a compute die works on one stretch of the range for all heads
+// (xcd_block_id with the part as the slowest index): a frame's rows of a layer are contiguous over the heads, and each die then
+// touches an eighth of the pages.  32 heads, 20 frames: 29.5 us with twelve or twenty parts in launch order, 24.8 with sixteen, which fall that
+// way by themselves.  Block `part` takes the stretch [part * n, (part + 1) * n) of the range's n frames in
+// units of 1 / parts frame, a frame's part of it the same fraction of its groups of 16 rows, for kQ of the query heads that share the K/V
+// head (`sets` such sets: q_per_kv = kQ * sets), and writes one partial per query head; the head's last block merges them.
+template <int kQ, int kRowsPerStep>
+__global__ __launch_bounds__(256, blocks_per_unit(kQ)) void k_attn_partial(
+    const sali_frame_row* __restrict__ rows, const _Float16* __restrict__ q, float* __restrict__ partial, int layer, int n_heads, int sets,
+    int frame_lo, int frame_hi, int tiles, int parts, float softmax_scale, Pools pools, AttnOut result) {
+    __shared__ float s_m[kQ][16], s_l[kQ][16];
+    __shared__ __align__(16) float s_acc[kQ][16][kHeadDim];
+    __shared__ int s_last;
+
+    const BlockId blk = xcd_block_id((int)blockIdx.x, n_heads * sets, 1, parts);
+    const int group = blk.x, part = blk.z;
+    const int h = sets == 1 ? group : group / sets;
+    const int q_first = group * kQ;                             // first query head of this block
+    const long long n = frame_hi - frame_lo;
+    const int f0 = frame_lo + (int)((uint32_t)part * (uint32_t)n / (uint32_t)parts);        // below 2^32: part < 256, n <= 2^24
+    together(pools.p16, pools.c8, pools.s8, pools.c4, pools.s4, pools.z4, pools.n_planes, result.out, result.lse, result.arrived);
     const int g = threadIdx.x >> 4, l = threadIdx.x & 15;
     const size_t plane_k = ((size_t)layer * 2 + 0) * n_heads + h;
     const size_t plane_v = ((size_t)layer * 2 + 1) * n_heads + h;
 
-    QueryPiece qp[kQ];
+    Row16B raw_q[kQ];
     SoftmaxState st[kQ];
 #pragma unroll
     for (int iq = 0; iq < kQ; ++iq) {
-        Row16B qv;
-        qv.u = reinterpret_cast<const u32x4*>(q)[(q_first + iq) * 16 + l];
-        qp[iq].sum = 0.0f;
-#pragma unroll
-        for (int e = 0; e < 8; ++e) {
-            qp[iq].f[e] = (float)qv.h[e];
-            qp[iq].sum += qp[iq].f[e];
-        }
-#pragma unroll
-        for (int e = 0; e < 4; ++e) qp[iq].h2[e] = qv.h2[e];
+        raw_q[iq].u = reinterpret_cast<const u32x4*>(q)[(q_first + iq) * 16 + l];
         st[iq].mx = -INFINITY;
         st[iq].lsum = 0.0f;
         st[iq].zacc = 0.0f;
@@ -277,150 +453,127 @@ __global__ __launch_bounds__(256) void k_attn_partial(const sali_frame_row* __re
         for (int e = 0; e < 8; ++e) st[iq].acc[e] = 0.0f;
     }
 
-    const int f0 = frame_lo + chunk * frames_per_chunk;
-    const int f1 = min(frame_hi, f0 + frames_per_chunk);
-    for (int f = f0; f < f1; ++f) {
+    for (int f = f0; f < frame_hi; ++f) {
+        // the block's part of the frame, in units of 1 / parts
+        const long long at = (long long)(f - frame_lo) * parts, from = part * n - at, to = from + n;
+        if (to <= 0) break;
+        const int lo = from > 0 ? (int)(from < parts ? from : parts) : 0, hi = to < parts ? (int)to : parts;
+        if (lo >= hi) continue;
         // Which stored frame does frame f bring in, and how many times?  A stored frame counts for
         // itself and for the redundant frames behind it (up to the next stored frame or the end of
         // the range); redundant frames at the head of the range, whose source lies before it, are
         // counted at the first of them.  With `tiles` entries per video frame all of this goes by the entries
         // of the same tile, which lie `tiles` apart.  Every thread takes the same decision from the same
-        // (uniform) table reads.
-        const sali_frame_row r = rows[f];
-        bool leader = r.stored != 0;
-        if (!leader && r.src >= 0 && r.src < frame_lo) {
-            leader = true;
-            for (int t = f - tiles; leader && t >= frame_lo; t -= tiles)
-                leader = rows[t].src != r.src;                     // an earlier frame of the run counts them
+        // (uniform) table reads; the two that nearly always decide it are asked for together.
+        sali_frame_row row = rows[f];
+        const bool followed = f + tiles < frame_hi;
+        const int next_stored = rows[followed ? f + tiles : f].stored;
+        together(row.stored, row.src, row.base16, row.n16, next_stored);
+        bool leader = row.stored != 0;
+        const int src = row.src;
+        if (!leader) {
+            if (src >= 0 && src < frame_lo) {
+                leader = true;
+                for (int t = f - tiles; leader && t >= frame_lo; t -= tiles)
+                    leader = rows[t].src != src;                   // an earlier frame of the run counts them
+            }
+            if (!leader) continue;
+            row = rows[src];
         }
-        if (!leader) continue;
-        const int src = r.src;
         int n_uses = 1;
-        for (int t = f + tiles; t < frame_hi && rows[t].stored == 0; t += tiles)
-            if (rows[t].src == src) ++n_uses;
+        if (followed && next_stored == 0)
+            for (int t = f + tiles; t < frame_hi && rows[t].stored == 0; t += tiles)
+                if (rows[t].src == src) ++n_uses;
         const float mult = (float)n_uses;
-        const sali_frame_row row = rows[src];
-        int at = split;
-        at = attend_tier<SALI_TIER_FP16, kQ, kRowsPerStep>(pools, plane_k, plane_v, row.base16, row.n16, at, n_splits, g, l, qp,
-                                                           softmax_scale, mult, st);
-        at = attend_tier<SALI_TIER_INT8, kQ, kRowsPerStep>(pools, plane_k, plane_v, row.base8, row.n8, at, n_splits, g, l, qp,
-                                                           softmax_scale, mult, st);
-        attend_tier<SALI_TIER_INT4, kQ, kRowsPerStep>(pools, plane_k, plane_v, row.base4, row.n4, at, n_splits, g, l, qp,
-                                                      softmax_scale, mult, st);
+        // groups of 16 rows, tier after tier; the block's are u0 .. u1 - 1
+        const int t16 = (row.n16 + 15) / 16, t8 = (row.n8 + 15) / 16, t4 = (row.n4 + 15) / 16, all = t16 + t8 + t4;
+        const int u0 = (int)((uint32_t)(all * lo) / (uint32_t)parts), u1 = (int)((uint32_t)(all * hi) / (uint32_t)parts);
+        auto rows_of = [&](int before, int groups, int count, int& j0, int& j1) {
+            j0 = 16 * max(u0 - before, 0);
+            j1 = min(16 * min(u1 - before, groups), count);
+        };
+        int j0, j1;
+        rows_of(0, t16, row.n16, j0, j1);
+        attend_rows<SALI_TIER_FP16, kQ, kRowsPerStep>(pools, plane_k, plane_v, row.base16, row.n16, j0, j1, g, l, raw_q, softmax_scale, mult, st);
+        rows_of(t16, t8, row.n8, j0, j1);
+        attend_rows<SALI_TIER_INT8, kQ, kRowsPerStep>(pools, plane_k, plane_v, row.base8, row.n8, j0, j1, g, l, raw_q, softmax_scale, mult, st);
+        rows_of(t16 + t8, t4, row.n4, j0, j1);
+        attend_rows<SALI_TIER_INT4, kQ, kRowsPerStep>(pools, plane_k, plane_v, row.base4, row.n4, j0, j1, g, l, raw_q, softmax_scale, mult, st);
     }
 
-    // merge the 16 lane groups, one query head after the other
+    // merge the 16 lane groups, all query heads together
 #pragma unroll
     for (int iq = 0; iq < kQ; ++iq) {
-        if (iq > 0) __syncthreads();
         if (l == 0) {
-            s_m[g] = st[iq].mx;
-            s_l[g] = st[iq].lsum;
+            s_m[iq][g] = st[iq].mx;
+            s_l[iq][g] = st[iq].lsum;
         }
 #pragma unroll
-        for (int e = 0; e < 8; ++e) s_acc[g][8 * l + e] = st[iq].acc[e] + st[iq].zacc;
-        __syncthreads();
-        float* mine = partial + ((size_t)(q_first + iq) * kAttnPartials + blockIdx.x) * kPartialStride;
-        if (threadIdx.x < kHeadDim) {
-            float big = -INFINITY;
-#pragma unroll
-            for (int k = 0; k < 16; ++k) big = fmaxf(big, s_m[k]);
-            float lt = 0.0f, at = 0.0f;
-            if (big != -INFINITY) {
-#pragma unroll
-                for (int k = 0; k < 16; ++k) {
-                    const float w = __expf(s_m[k] - big);
-                    lt += w * s_l[k];
-                    at += w * s_acc[k][threadIdx.x];
-                }
-            }
-            if (threadIdx.x == 0) {
-                mine[0] = big;
-                mine[1] = lt;
-            }
-            mine[2 + threadIdx.x] = at;
-        }
+        for (int e = 0; e < 8; e += 4)
+            *reinterpret_cast<float4*>(&s_acc[iq][g][8 * l + e]) =
+                make_float4(st[iq].acc[e] + st[iq].zacc, st[iq].acc[e + 1] + st[iq].zacc, st[iq].acc[e + 2] + st[iq].zacc,
+                            st[iq].acc[e + 3] + st[iq].zacc);
     }
-}
-
-// grid (query heads), 64 * kWaves threads: merge of a head's partials (n_partials <= kAttnPartials; 0 for an
-// empty frame range: zeros and -inf).  A kernel of its own: the kernel boundary is the only
-// device-wide ordering this needs, and a device-scope fence in each of the ~2000 blocks of the
-// main kernel (last-block hand-over) measured 4.5x slower, because on this chip such a fence writes
-// back and invalidates the L2 of the issuing XCD under the stream that the other blocks are reading.
-// All it costs is its trips to memory, so it makes one: every wave reads all maxima itself (a lane each)
-// while its partials (number wave, wave + kWaves, ...; lane i holds values 2 i, 2 i + 1) are already under
-// way, and the waves meet once.  Two halves of a 256-thread block that read maxima first and then took
-// alternate partials: 5.2 us for 60 partials x 32 heads, 10.1 for 216 x 4; this: 4.0 and 7.1.
-template <int kWaves>
-__global__ __launch_bounds__(64 * kWaves) void k_attn_merge(const float* __restrict__ partial, int n_partials, int slots,
-                                                            float* __restrict__ out, float* __restrict__ lse) {
-    constexpr int kPerLane = kAttnPartials / 64, kFlight = kWaves == 4 ? 8 : 4;
-    __shared__ float2 s_part[kWaves][64];
-    const int h = blockIdx.x, wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)), lane = threadIdx.x & 63;
-    const float* p = partial + (size_t)h * slots * kPartialStride;      // `slots` partials are reserved per query head
-    float m[kPerLane], l[kPerLane];
-#pragma unroll
-    for (int j = 0; j < kPerLane; ++j) {
-        const int k = 64 * j + lane;
-        float2 ml = make_float2(-INFINITY, 0.0f);
-        if (k < n_partials) ml = *reinterpret_cast<const float2*>(p + (size_t)k * kPartialStride);
-        m[j] = ml.x;
-        l[j] = ml.y;
-    }
-    float2 v[kFlight];
-    auto request = [&](int k) {
-#pragma unroll
-        for (int u = 0; u < kFlight; ++u) {
-            const int ku = k + u * kWaves;
-            if (ku < n_partials) v[u] = *reinterpret_cast<const float2*>(p + (size_t)ku * kPartialStride + 2 + 2 * lane);
-        }
-    };
-    if (wave < n_partials) request(wave);
-    float big = fmaxf(fmaxf(m[0], m[1]), fmaxf(m[2], m[3]));
-    for (int off = 32; off > 0; off >>= 1) big = fmaxf(big, __shfl_xor(big, off));
-    float lt = 0.0f;
-#pragma unroll
-    for (int j = 0; j < kPerLane; ++j) {
-        m[j] = big != -INFINITY ? expf(m[j] - big) : 0.0f;      // the partial's weight
-        lt += m[j] * l[j];
-    }
-    float2 at = make_float2(0.0f, 0.0f);
-    for (int k = wave; k < n_partials; k += kFlight * kWaves) {
-#pragma unroll
-        for (int u = 0; u < kFlight; ++u) {
-            const int ku = k + u * kWaves;
-            if (ku < n_partials) {
-                const float mine = ku < 64 ? m[0] : (ku < 128 ? m[1] : (ku < 192 ? m[2] : m[3]));
-                const float w = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, mine), ku & 63));
-                at.x += w * v[u].x;
-                at.y += w * v[u].y;
-            }
-        }
-        if (k + kFlight * kWaves < n_partials) request(k + kFlight * kWaves);
-    }
-    s_part[wave][lane] = at;
     __syncthreads();
-    if (wave != 0) return;
-    for (int off = 32; off > 0; off >>= 1) lt += __shfl_xor(lt, off);
 #pragma unroll
-    for (int k = 1; k < kWaves; ++k) {
-        at.x += s_part[k][lane].x;
-        at.y += s_part[k][lane].y;
+    for (int i = 0; i < (kQ * kHeadDim + 255) / 256; ++i) {
+        const int idx = (int)threadIdx.x + 256 * i, iq = idx / kHeadDim, d = idx % kHeadDim, head = q_first + iq;
+        if (iq >= kQ) break;                // one query: half of the block
+        float big = -INFINITY;
+#pragma unroll
+        for (int k = 0; k < 16; ++k) big = fmaxf(big, s_m[iq][k]);
+        float lts[4] = {}, ats[4] = {};
+        if (big != -INFINITY) {
+#pragma unroll
+            for (int k = 0; k < 16; ++k) {
+                const float w = __expf(s_m[iq][k] - big);
+                lts[k & 3] += w * s_l[iq][k];
+                ats[k & 3] += w * s_acc[iq][k][d];
+            }
+        }
+        const float lt = (lts[0] + lts[1]) + (lts[2] + lts[3]), at = (ats[0] + ats[1]) + (ats[2] + ats[3]);
+        if (parts > 1) {
+            float* mine = partial + ((size_t)head * kAttnPartials + part) * kPartialStride;
+            if (d == 0) {
+                put(mine, big);
+                put(mine + 1, lt);
+            }
+            put(mine + 2 + d, at);
+        } else {
+            result.out[(size_t)head * kHeadDim + d] = lt > 0.0f ? at / lt : 0.0f;
+            if (result.lse != nullptr && d == 0) result.lse[head] = lt > 0.0f ? big + logf(lt) : -INFINITY;
+        }
     }
-    float* dst = out + (size_t)h * kHeadDim + 2 * lane;       // the caller's: aligned for float only
-    dst[0] = lt > 0.0f ? at.x / lt : 0.0f;
-    dst[1] = lt > 0.0f ? at.y / lt : 0.0f;
-    if (lse != nullptr && lane == 0) lse[h] = lt > 0.0f ? big + logf(lt) : -INFINITY;
+    if (parts == 1 || !last_to_arrive(result.arrived + (size_t)group * kArrivedStride, parts, &s_last)) return;
+
+    // four waves: all of them on the one query, two on each of two, one on each of four
+    constexpr int kWaves = 4 / kQ;
+    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)), iq = wave / kWaves, sub = wave % kWaves;
+    const float* const p[1] = {partial + (size_t)(q_first + iq) * kAttnPartials * kPartialStride};
+    float big[1], lt[1];
+    float2 at[1];
+    merge_partials<1, kWaves, kQ == 4 ? 32 : 16>(p, parts, min(sub, parts - 1), big, lt, at);
+    if constexpr (kWaves > 1) {
+        // (with fewer partials than waves the last one is taken more than once: once too often)
+        float2* s_part = reinterpret_cast<float2*>(&s_acc[0][0][0]);
+        s_part[threadIdx.x] = sub < parts ? at[0] : make_float2(0.0f, 0.0f);
+        __syncthreads();
+        if (sub != 0) return;
+#pragma unroll
+        for (int k = 1; k < kWaves; ++k) {
+            const float2 other = s_part[threadIdx.x + 64 * k];
+            at[0].x += other.x;
+            at[0].y += other.y;
+        }
+    }
+    store_result(result, q_first + iq, big[0], lt[0], at[0]);
 }
 
-// four waves where that is at most eight partials a wave, all under way at once; else sixteen
-static void launch_merge(const float* d_partial, int n_partials, int slots, int n_q_heads, float* d_out, float* d_lse_or_null,
-                         hipStream_t s) {
-    if (n_partials > 32)
-        hipLaunchKernelGGL(k_attn_merge<16>, dim3(n_q_heads), dim3(1024), 0, s, d_partial, n_partials, slots, d_out, d_lse_or_null);
-    else
-        hipLaunchKernelGGL(k_attn_merge<4>, dim3(n_q_heads), dim3(256), 0, s, d_partial, n_partials, slots, d_out, d_lse_or_null);
+// an empty range: zeros and -inf
+__global__ __launch_bounds__(256) void k_attn_empty(AttnOut result, int n_q_heads) {
+    const int i = blockIdx.x * 256 + threadIdx.x;
+    if (i < n_q_heads * kHeadDim) result.out[i] = 0.0f;
+    if (result.lse != nullptr && i < n_q_heads) result.lse[i] = -INFINITY;
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -444,7 +597,7 @@ static void launch_merge(const float* d_partial, int n_partials, int slots, int 
 // the matrix cores take fp16 operands; the softmax weights are rounded to fp16 for the second product
 // as well.  Both stay inside the tolerance of the floating-point results (largest error printed by
 // the tests).  Accumulation, softmax state and partials are fp32; partials have the layout of the
-// single-query kernel and are merged by the same k_attn_merge.
+// single-query kernel and are merged the same way, by the last block of 32 queries to finish.
 //
 // What bounds it: the trip to memory of a tile (waves wait for 47 % of their time), then the vector
 // instructions of a tile (610, conversions and softmax).  Hence: a tile's K^ and V^ rows are asked for a
@@ -610,18 +763,18 @@ __device__ __forceinline__ half4_t pf_read_transposed(const _Float16* p) {
 // A stored frame counts for itself and for the redundant frames behind it (up to the next stored frame or
 // the end of the range); redundant frames at the head of the range, whose source lies before it, are
 // counted at the first of them.  With `tiles` entries per video frame: the entries of the same tile, `tiles` apart.
-__device__ __forceinline__ int pf_list_frames(const sali_frame_row* __restrict__ rows, int frame_lo, int frame_hi, int tiles, int g0,
-                                              int f_end, int part, int parts, int lane, int* s_src, PfFrame* list,
+__device__ __forceinline__ int pf_list_frames(const sali_frame_row* __restrict__ rows, int frame_lo, int frame_hi, int tiles, int g0, int f_end, int part, int parts, int lane, int* s_src, PfFrame* list,
                                               int* n_tiles) {
-    const int f = g0 + lane, g_end = min(f_end, g0 + kPfGroup);
+    // entries past the share's are looked at too: which of them is stored next says how often the last ones count
+    const int f = g0 + lane, g_end = min(f_end, g0 + kPfGroup), seen = min(frame_hi, g0 + kPfGroup);
     const bool valid = f < g_end;
     sali_frame_row row = {};
     row.src = -1;
-    if (valid) row = rows[f];
-    const bool stored = valid && row.stored != 0;
+    if (f < seen) row = rows[f];
     s_src[lane] = row.src;
     pf_lds_order();
-    const unsigned long long stored_mask = __ballot(stored);
+    const unsigned long long stored_mask = __ballot(f < seen && row.stored != 0);
+    const bool stored = valid && row.stored != 0;
     bool leader = stored;
     const int src = row.src;
     if (valid && !stored && src >= 0 && src < frame_lo) {
@@ -637,7 +790,7 @@ __device__ __forceinline__ int pf_list_frames(const sali_frame_row* __restrict__
             for (int b = 0; b < 64; b += tiles) same |= 1ull << b;
             behind &= same;
         }
-        const int run_end = behind != 0ull ? f + tiles + __builtin_ctzll(behind) : g_end;
+        const int run_end = behind != 0ull ? f + tiles + __builtin_ctzll(behind) : seen;
         int t = f + tiles;
         for (; t < run_end; t += tiles)
             if (s_src[t - g0] == src) ++n_uses;
@@ -651,9 +804,9 @@ __device__ __forceinline__ int pf_list_frames(const sali_frame_row* __restrict__
         const long long n = frame_hi - frame_lo, at = (long long)(f - frame_lo) * parts;
         const long long lo = max(0ll, part * n - at), hi = min((long long)parts, (part + 1) * n - at);
         const int t = pf_tiles(row.n16) + pf_tiles(row.n8) + pf_tiles(row.n4);
-        if (hi > lo) {
-            i0 = (int)(t * lo / parts);
-            cnt = (int)(t * hi / parts) - i0;
+        if (hi > lo) {                                      // both in 0 .. parts
+            i0 = (int)((uint32_t)(t * (int)lo) / (uint32_t)parts);
+            cnt = (int)((uint32_t)(t * (int)hi) / (uint32_t)parts) - i0;
         }
     }
     int incl = cnt;
@@ -682,12 +835,12 @@ __device__ __forceinline__ int pf_list_frames(const sali_frame_row* __restrict__
 
 }  // namespace
 
-// grid (parts of the frame range, n_heads, ceil(q_per_kv / 32)), 512 threads.  kLongRange: a stored frame of the
+// parts of the frame range x n_heads x ceil(q_per_kv / 32) blocks of 512 threads.  kLongRange: a stored frame of the
 // range may count more than 2^15 times, which takes more than 2^15 frames
 template <bool kLongRange>
 __global__ __launch_bounds__(64 * kPfWaves) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_attn_prefill(
-    const sali_frame_row* __restrict__ rows, Pools pools, int layer, int n_heads, const _Float16* __restrict__ q,
-    int q_per_kv, int frame_lo, int frame_hi, int tiles, float softmax_scale, float* __restrict__ partial) {
+    const sali_frame_row* __restrict__ rows, const _Float16* __restrict__ q, float* __restrict__ partial, int layer, int n_heads, int sets,
+    int q_per_kv, int frame_lo, int frame_hi, int tiles, int parts, float softmax_scale, Pools pools, AttnOut result) {
     __shared__ __align__(16) _Float16 s_tiles[kPfWaves][kPfTileHalves];     // a K^ and a V^ tile per wave; the results at the end
     __shared__ PfFrame s_list[kPfGroup];
     __shared__ int s_src[kPfGroup];
@@ -695,12 +848,30 @@ __global__ __launch_bounds__(64 * kPfWaves) __attribute__((amdgpu_waves_per_eu(2
     __shared__ float s_m[kPfWaves][32], s_l[kPfWaves][32];
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)), lane = threadIdx.x & 63;
     const int m = lane & 31, hh = lane >> 5;
-    const int h = blockIdx.y, part = blockIdx.x, parts = gridDim.x;
-    const int qi = (int)blockIdx.z * 32 + m;                 // this lane's query among the q_per_kv of the K/V head
+    const BlockId blk = xcd_block_id((int)blockIdx.x, n_heads * sets, 1, parts);        // as in k_attn_partial
+    const int group = blk.x, part = blk.z;
+    const int h = sets == 1 ? group : group / sets, set = group - h * sets;
+    together(pools.p16, pools.c8, pools.s8, pools.c4, pools.s4, pools.z4, pools.n_planes, result.out, result.lse, result.arrived);
+    const int qi = set * 32 + m;                 // this lane's query among the q_per_kv of the K/V head
     const size_t plane_k = ((size_t)layer * 2 + 0) * n_heads + h;
     const size_t plane_v = ((size_t)layer * 2 + 1) * n_heads + h;
     _Float16* s_k = s_tiles[wave];
     _Float16* s_v = s_k + kPfRows * kPfKStride;
+
+    // the stretch's frames, the last one rounded up; products below 2^32 (part < 256, at most 2^24 frames)
+    const uint32_t n_range = (uint32_t)(frame_hi - frame_lo);
+    const int f_begin = frame_lo + (int)((uint32_t)part * n_range / (uint32_t)parts);
+    const int f_end = frame_lo + (int)(((uint32_t)(part + 1) * n_range - 1u) / (uint32_t)parts) + 1;
+    auto list_frames = [&](int g0) {
+        if (wave != 0) return;
+        int n_tiles;
+        const int len = pf_list_frames(rows, frame_lo, frame_hi, tiles, g0, f_end, part, parts, lane, s_src, s_list, &n_tiles);
+        if (lane == 0) {
+            s_n[0] = len;
+            s_n[1] = n_tiles;
+        }
+    };
+    list_frames(f_begin);       // ahead of the queries: it is what every wave waits for
 
     // the queries stay in registers, as the B operand wants them (zeros past q_per_kv)
     half8_t qb[8];
@@ -719,18 +890,10 @@ __global__ __launch_bounds__(64 * kPfWaves) __attribute__((amdgpu_waves_per_eu(2
 #pragma unroll
         for (int r = 0; r < 16; ++r) acc[dt][r] = 0.0f;
 
-    const long long n_range = frame_hi - frame_lo;
-    const int f_begin = frame_lo + (int)(part * n_range / parts);
-    const int f_end = frame_lo + (int)(((part + 1) * n_range + parts - 1) / parts);
     for (int g0 = f_begin; g0 < f_end; g0 += kPfGroup) {
-        if (g0 != f_begin) __syncthreads();                 // every wave is through with the list
-        if (wave == 0) {
-            int n_tiles;
-            const int len = pf_list_frames(rows, frame_lo, frame_hi, tiles, g0, f_end, part, parts, lane, s_src, s_list, &n_tiles);
-            if (lane == 0) {
-                s_n[0] = len;
-                s_n[1] = n_tiles;
-            }
+        if (g0 != f_begin) {
+            __syncthreads();                                // every wave is through with the list
+            list_frames(g0);
         }
         __syncthreads();
         const int len = __builtin_amdgcn_readfirstlane(s_n[0]), n_tiles = __builtin_amdgcn_readfirstlane(s_n[1]);
@@ -858,97 +1021,120 @@ __global__ __launch_bounds__(64 * kPfWaves) __attribute__((amdgpu_waves_per_eu(2
 #pragma unroll
         for (int r = 0; r < 16; ++r) mine[(32 * dt + 8 * (r / 4) + 4 * hh + (r % 4)) * kPfOutStride + m] = acc[dt][r] * fac;
     __syncthreads();
-    for (int idx = threadIdx.x; idx < 32 * kHeadDim; idx += 64 * kPfWaves) {
-        const int mm = idx / kHeadDim, d = idx % kHeadDim;
-        const int qq = (int)blockIdx.z * 32 + mm;
-        if (qq >= q_per_kv) continue;
-        float sum = 0.0f;
+    const int queries = min(q_per_kv - set * 32, 32);
+    const int q_first = h * q_per_kv + set * 32;
+    float* first_partial = partial + ((size_t)q_first * parts + part) * kPartialStride;      // `parts` per query
+    if (wave == 0 && hh == 0 && m < queries) {
+        float lt = 0.0f;
+        if (big != -INFINITY)
 #pragma unroll
-        for (int w = 0; w < kPfWaves; ++w) sum += reinterpret_cast<const float*>(s_tiles[w])[d * kPfOutStride + mm];
-        float* dst = partial + (((size_t)h * q_per_kv + qq) * parts + part) * kPartialStride;
-        dst[2 + d] = sum;
-        if (d == 0) {
-            float top = -INFINITY, lt = 0.0f;
-            for (int w = 0; w < kPfWaves; ++w) top = fmaxf(top, s_m[w][mm]);
-            if (top != -INFINITY)
-                for (int w = 0; w < kPfWaves; ++w) lt += s_l[w][mm] * __builtin_amdgcn_exp2f(s_m[w][mm] - top);
-            dst[0] = top * 0.69314718055994530942f;
-            dst[1] = lt;
+            for (int w = 0; w < kPfWaves; ++w) lt += s_l[w][m] * __builtin_amdgcn_exp2f(s_m[w][m] - big);
+        const float natural = big * 0.69314718055994530942f;
+        if (parts > 1) {
+            put(first_partial + (size_t)m * parts * kPartialStride, natural);
+            put(first_partial + (size_t)m * parts * kPartialStride + 1, lt);
+        } else {
+            s_l[0][m] = lt;
+            if (result.lse != nullptr) result.lse[q_first + m] = lt > 0.0f ? natural + logf(lt) : -INFINITY;
         }
     }
+    if (parts == 1) __syncthreads();
+    constexpr int kOuts = 32 * kHeadDim / (64 * kPfWaves);
+    float sum[kOuts];
+#pragma unroll
+    for (int i = 0; i < kOuts; ++i) {
+        const int idx = (int)threadIdx.x + i * 64 * kPfWaves, mm = idx / kHeadDim, d = idx % kHeadDim;
+        sum[i] = 0.0f;
+#pragma unroll
+        for (int w = 0; w < kPfWaves; ++w) sum[i] += reinterpret_cast<const float*>(s_tiles[w])[d * kPfOutStride + mm];
+    }
+#pragma unroll
+    for (int i = 0; i < kOuts; ++i) {
+        const int idx = (int)threadIdx.x + i * 64 * kPfWaves, mm = idx / kHeadDim, d = idx % kHeadDim;
+        if (mm >= queries) continue;
+        if (parts > 1) {
+            put(first_partial + (size_t)mm * parts * kPartialStride + 2 + d, sum[i]);
+        } else {
+            const float lt = s_l[0][mm];
+            result.out[(size_t)(q_first + mm) * kHeadDim + d] = lt > 0.0f ? sum[i] / lt : 0.0f;
+        }
+    }
+    if (parts == 1 || !last_to_arrive(result.arrived + (size_t)group * kArrivedStride, parts, &s_n[0])) return;
+    constexpr int kMine = 32 / kPfWaves;                    // queries of a wave, all at once
+    if (wave * kMine >= queries) return;
+    const float* p[kMine];
+#pragma unroll
+    for (int i = 0; i < kMine; ++i) p[i] = partial + (size_t)(q_first + min(wave * kMine + i, queries - 1)) * parts * kPartialStride;
+    float top[kMine], lt[kMine];
+    float2 at[kMine];
+    merge_partials<kMine, 1, 8>(p, parts, 0, top, lt, at);
+#pragma unroll
+    for (int i = 0; i < kMine; ++i)
+        if (wave * kMine + i < queries) store_result(result, q_first + wave * kMine + i, top[i], lt[i], at[i]);
 }
 
-hipError_t launch_attend(const sali_frame_row* d_rows, Pools pools, int layer, int n_heads, int q_per_kv,
+hipError_t launch_attend(const sali_frame_row* d_rows, const Pools& pools, int layer, int n_heads, int q_per_kv,
                          const void* d_q, int frame_lo, int frame_hi, int tiles, RowsPerFrame kept, float softmax_scale, float* d_partial,
-                         float* d_out, float* d_lse_or_null, hipEvent_t ev_start, hipEvent_t ev_stop, hipStream_t s) {
+                         AttnOut result, hipEvent_t ev_start, hipEvent_t ev_stop, hipStream_t s) {
     const int n_range = frame_hi - frame_lo;
-    int n_partials = 0;
-    if (n_range > 0 && q_per_kv > kAttnMaxQPerKv) {
+    const _Float16* q = reinterpret_cast<const _Float16*>(d_q);
+    if (n_range <= 0) {
+        const int n_q_heads = n_heads * q_per_kv;
+        hipLaunchKernelGGL(k_attn_empty, dim3((n_q_heads * kHeadDim + 255) / 256), dim3(256), 0, s, result, n_q_heads);
+        return hipGetLastError();
+    }
+    if (ev_start != nullptr && hipEventRecord(ev_start, s) != hipSuccess) return hipErrorUnknown;
+    if (q_per_kv > kAttnMaxQPerKv) {
         // matrix-core path: one block of eight waves per compute unit, as many parts of the range as that
         // gives a K/V head, but no more than leave every wave a tile (a frame has up to kTokens / kPfRows + 3),
         // and no more partials than the scratch holds (kAttnSlotsPerHead per K/V head, shared out over its queries).
         // Where one part each would leave a third of the compute units or more idle, three parts each: two rounds
         // of a third of the work.  160 heads x 9 queries x 20 frames 168 -> 133 us a call, 129 heads 167 -> 125
         // (independent blocks of four waves: 141 and 162)
-        const int pairs = n_heads * ((q_per_kv + 31) / 32);
+        const int sets = (q_per_kv + 31) / 32, pairs = n_heads * sets;
         int parts = kComputeUnits / pairs;
         if (parts == 1 && 3 * pairs <= 2 * kComputeUnits) parts = 3;
         const long long fill = ((long long)n_range * (kTokens / kPfRows + 3) + kPfWaves - 1) / kPfWaves;
         if (parts > fill) parts = (int)fill;
         if (parts > kAttnSlotsPerHead / q_per_kv) parts = kAttnSlotsPerHead / q_per_kv;
         if (parts > kAttnPartials) parts = kAttnPartials;
-        n_partials = parts < 1 ? 1 : parts;
-        if (ev_start != nullptr && hipEventRecord(ev_start, s) != hipSuccess) return hipErrorUnknown;
-        const dim3 grid(n_partials, n_heads, (q_per_kv + 31) / 32);
+        if (parts < 1) parts = 1;
+        const dim3 grid(parts * n_heads * sets);
         // the general variant costs 0.7 % (32 heads x 32 queries x 20 frames 143.8 -> 144.8 us for four layers)
         if (n_range > 32768)
-            hipLaunchKernelGGL(k_attn_prefill<true>, grid, dim3(64 * kPfWaves), 0, s, d_rows, pools, layer, n_heads,
-                               reinterpret_cast<const _Float16*>(d_q), q_per_kv, frame_lo, frame_hi, tiles, softmax_scale, d_partial);
+            hipLaunchKernelGGL(k_attn_prefill<true>, grid, dim3(64 * kPfWaves), 0, s, d_rows, q, d_partial, layer, n_heads, sets, q_per_kv,
+                               frame_lo, frame_hi, tiles, parts, softmax_scale, pools, result);
         else
-            hipLaunchKernelGGL(k_attn_prefill<false>, grid, dim3(64 * kPfWaves), 0, s, d_rows, pools, layer, n_heads,
-                               reinterpret_cast<const _Float16*>(d_q), q_per_kv, frame_lo, frame_hi, tiles, softmax_scale, d_partial);
-        if (ev_stop != nullptr && hipEventRecord(ev_stop, s) != hipSuccess) return hipErrorUnknown;
-        const hipError_t e = hipGetLastError();
-        if (e != hipSuccess) return e;
-        launch_merge(d_partial, n_partials, n_partials, n_heads * q_per_kv, d_out, d_lse_or_null, s);
-        return hipGetLastError();
-    }
-    if (n_range > 0) {
+            hipLaunchKernelGGL(k_attn_prefill<false>, grid, dim3(64 * kPfWaves), 0, s, d_rows, q, d_partial, layer, n_heads, sets, q_per_kv,
+                               frame_lo, frame_hi, tiles, parts, softmax_scale, pools, result);
+    } else {
         // eight queries per K/V head run as two sets of four (two blocks read the same rows, the second
         // mostly from cache): a block with eight query states needs 256 registers per lane and was slower
         const int kq = q_per_kv == 8 ? 4 : q_per_kv, sets = q_per_kv / kq;
-        // One resident round of blocks: at 8 blocks of 256 threads per compute unit the chip holds
-        // kResidentBlocks; more blocks than that leave a second, nearly empty round at the end of a
-        // bandwidth-bound kernel.  Blocks of a head: whole frames per block for long ranges, row
-        // groups of a frame split over blocks for short ones (up to 9 groups of 64 rows per tier).
-        int per_head = kResidentBlocks / n_heads;
-        per_head = per_head < 1 ? 1 : (per_head > kAttnPartials ? kAttnPartials : per_head);
-        const int fpc = (n_range + per_head - 1) / per_head;
-        const int n_chunks = (n_range + fpc - 1) / fpc;
-        // Small ranges: with groups of 64 rows fewer than two blocks per compute unit would have any (at most
-        // rows / 64 + 3 groups a frame), and each would be a chain of three tiers' loads and four rows'
-        // arithmetic per lane group.  Groups of 16 rows then, one row per lane group, over up to twice the splits:
-        // 4 queries x 8 heads, 2 frames of 124 / 28 / 84 rows 11.3 -> 6.2 us, 1 query 6.3 -> 4.3.  No more splits
-        // than a frame has groups: with eighteen for frames of 64 rows, fourteen of them empty, 40 heads x 8
-        // queries x 2 frames took 17.6 us (groups of 64 rows: 12.4), and 8.0 with four.  Not fewer than four, for
-        // frames stored under an earlier tier rule that kept more.
-        const bool small = (long long)n_range * ((kept.n16 + kept.n8 + kept.n4) / 64 + 1) * n_heads * sets < 2 * kComputeUnits;
+        // Whole rounds of one block per compute unit, as nearly as the parts allow (a unit with one block more than the others is
+        // where the launch ends: 20 frames x 32 heads 25.6 us with 16 parts, 28.9 with 20, 26.5 with 24): two from sixteen
+        // heads x sets on; one below, where more parts cost more at the merge than they bring (8 heads x 4 queries x 20 frames 19.6 us
+        // with 32 parts, 21.2 with 64); all that fit where parts are few and the remainder is large.  A block takes two groups of 16
+        // rows or more, four rows of a lane group in flight; where there are no more groups than one round has blocks it takes one,
+        // a row per lane group.
+        const int pairs = n_heads * sets;
         const int groups = (kept.n16 + 15) / 16 + (kept.n8 + 15) / 16 + (kept.n4 + 15) / 16;
-        const int most = small ? (groups < 4 ? 4 : (groups < 18 ? groups : 18)) : 9;
-        int n_splits = per_head / n_chunks;
-        n_splits = n_splits < 1 ? 1 : (n_splits > most ? most : n_splits);
-        n_partials = n_chunks * n_splits;
-        if (ev_start != nullptr && hipEventRecord(ev_start, s) != hipSuccess) return hipErrorUnknown;
-        const dim3 grid(n_partials, n_heads, sets);
-        const _Float16* q = reinterpret_cast<const _Float16*>(d_q);
-#define SALI_ATTN_LAUNCH(KQ)                                                                                              \
-    do {                                                                                                                  \
-        if (small)                                                                                                        \
-            hipLaunchKernelGGL((k_attn_partial<KQ, 1>), grid, dim3(256), 0, s, d_rows, pools, layer, n_heads, q, frame_lo, \
-                               frame_hi, tiles, fpc, n_splits, softmax_scale, d_partial);                                        \
-        else                                                                                                              \
-            hipLaunchKernelGGL((k_attn_partial<KQ, 4>), grid, dim3(256), 0, s, d_rows, pools, layer, n_heads, q, frame_lo, \
-                               frame_hi, tiles, fpc, n_splits, softmax_scale, d_partial);                                        \
+        const long long work = (long long)n_range * (groups < 4 ? 4 : groups);      // not fewer than four: frames stored under an earlier rule
+        const bool single = work * pairs <= kComputeUnits;
+        long long parts = kComputeUnits * (pairs > 128 ? blocks_per_unit(kq) : (pairs >= 16 ? 2 : 1)) / pairs;
+        if (single) parts = work;
+        else if (parts > (work + 1) / 2) parts = (work + 1) / 2;
+        if (parts > kAttnPartials) parts = kAttnPartials;
+        if (parts < 1) parts = 1;
+        const dim3 grid((int)parts * n_heads * sets);
+#define SALI_ATTN_LAUNCH(KQ)                                                                                                       \
+    do {                                                                                                                           \
+        if (single)                                                                                                                \
+            hipLaunchKernelGGL((k_attn_partial<KQ, 1>), grid, dim3(256), 0, s, d_rows, q, d_partial, layer, n_heads, sets, frame_lo, \
+                               frame_hi, tiles, (int)parts, softmax_scale, pools, result);                                         \
+        else                                                                                                                       \
+            hipLaunchKernelGGL((k_attn_partial<KQ, 4>), grid, dim3(256), 0, s, d_rows, q, d_partial, layer, n_heads, sets, frame_lo, \
+                               frame_hi, tiles, (int)parts, softmax_scale, pools, result);                                         \
     } while (0)
         switch (kq) {
             case 1: SALI_ATTN_LAUNCH(1); break;
@@ -957,11 +1143,8 @@ hipError_t launch_attend(const sali_frame_row* d_rows, Pools pools, int layer, i
             default: return hipErrorInvalidValue;
         }
 #undef SALI_ATTN_LAUNCH
-        if (ev_stop != nullptr && hipEventRecord(ev_stop, s) != hipSuccess) return hipErrorUnknown;
-        const hipError_t e = hipGetLastError();
-        if (e != hipSuccess) return e;
     }
-    launch_merge(d_partial, n_partials, kAttnPartials, n_heads * q_per_kv, d_out, d_lse_or_null, s);
+    if (ev_stop != nullptr && hipEventRecord(ev_stop, s) != hipSuccess) return hipErrorUnknown;
     return hipGetLastError();
 }
 

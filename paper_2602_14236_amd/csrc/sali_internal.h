@@ -21,6 +21,7 @@ constexpr int kMaxIters = 8;
 constexpr int kAttnPartials = 256;          // partial softmax states per head in the attention kernel
 constexpr int kAttnMaxQPerKv = 8;           // query heads that may share one K/V head
 constexpr int kAttnSlotsPerHead = 4096;     // partial-result slots of the scratch per K/V head (shared out over its queries)
+constexpr int kAttnSets = 2;                // at most so many blocks share a K/V head's rows with different queries
 constexpr int kAttnPartialStride = 160;     // floats per partial: max, sum, 128 values; 640 B = five whole 128-byte lines
 constexpr int kMaxBatch = SALI_MAX_BATCH;   // frames analysed by one set of launches (blockIdx.z / .y)
 constexpr int kMaxTiles = 8;                // images per video frame (a frame's tiles are analysed in one batch)
@@ -324,15 +325,24 @@ hipError_t launch_unpack(const sali_frame_row* d_rows, int first_frame_id, const
 struct RowsPerFrame {
     int n16, n8, n4;
 };
+// results of an attention call, and the arrival counters of its blocks (kAttnSets per K/V head, kArrivedStride words apart, zero
+// between calls).  A counter to a memory line: additions to one line are made one after the other wherever they come from, and with the
+// counters of 32 heads side by side 2000 arrivals took 20 us.
+constexpr int kArrivedStride = 64;
+struct AttnOut {
+    float* out;
+    float* lse;                 // may be NULL
+    uint32_t* arrived;
+};
 // attn_kernels.hip: single-query attention of one layer over frames [frame_lo, frame_hi) for
 // n_heads * q_per_kv queries (q_per_kv in {1, 2, 4, 8}: streaming kernel; 9 .. 64: matrix-core kernel); d_partial holds
 // n_heads * kAttnSlotsPerHead * kAttnPartialStride floats; tiles = cache entries per video frame (an entry's pointer
 // entries lie that far apart); kept = how many rows a stored frame is
 // expected to keep (it shapes the launch, any frame is read whole); the events (may be NULL) bracket
 // the main kernel
-hipError_t launch_attend(const sali_frame_row* d_rows, Pools pools, int layer, int n_heads, int q_per_kv,
+hipError_t launch_attend(const sali_frame_row* d_rows, const Pools& pools, int layer, int n_heads, int q_per_kv,
                          const void* d_q, int frame_lo, int frame_hi, int tiles, RowsPerFrame kept, float softmax_scale, float* d_partial,
-                         float* d_out, float* d_lse_or_null, hipEvent_t ev_start, hipEvent_t ev_stop, hipStream_t s);
+                         AttnOut result, hipEvent_t ev_start, hipEvent_t ev_stop, hipStream_t s);
 
 // saliency_kernels.hip
 // n = frames in the batch (1..kMaxBatch).  launch_gray: RGB -> gray only.  launch_prep: the edge / colour

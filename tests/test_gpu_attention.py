@@ -427,3 +427,47 @@ def test_few_queries_rows_other_than_the_tier_rule_in_force_says(q_per_kv):
         assert err <= 1e-5
         assert np.all(np.abs(lse.cpu().numpy() - exp_lse) <= 1e-5 * (1 + np.abs(exp_lse)))
     ctx.close()
+
+
+@pytest.mark.parametrize("heads", [1, 15, 16, 51, 128, 129, 257, 600, 1100])
+def test_parts_and_their_hand_over_by_number_of_heads(heads):
+    """The number of heads decides how many parts the range is cut into, down to one part that nobody has to merge, and how the
+    blocks are dealt; the last block of a head to finish merges its parts.  Calls with different numbers of queries follow each
+    other on one context, so each finds the arrival counters as the ones before left them: every repetition gives the same
+    bits.  Rows of the FP16 tier only: float64 attention over the stored values; fp32 sums of 200 terms (1e-5 relative) and, from nine
+    queries on, softmax weights rounded to fp16 (2^-11, 2^-25 absolute below the normal numbers)."""
+    from paper_2602_14236_amd import binding
+    frames, k16 = 4, 50
+    p = params(96, 96, tier_mode=1, k_fp16=k16, k_int8=0, k_int4=0, n_layers=1, n_heads=heads, cap_fp16=k16 * frames, cap_int8=1,
+               cap_int4=1, max_frames=frames)
+    ctx = binding.SaliContext(lib_config(p))
+    g = torch.Generator(device="cuda").manual_seed(heads)
+    dense = []
+    for t in range(frames):
+        kv = torch.randn((1, 2, heads, 576, 128), generator=g, device="cuda").to(torch.float16)
+        scores = torch.rand(576, generator=g, device="cuda")
+        ctx.kv_compress(kv, scores, t)
+        dense.append(kv[0][:, :, torch.topk(scores, k16).indices].float())
+    k, v = (torch.cat([d[i] for d in dense], dim=1).double() for i in (0, 1))
+    first = {}
+    for rep in range(3):
+        for n in (1, 8, 33, 2, 9, 4):
+            q = torch.randn((heads * n, 128), generator=torch.Generator(device="cuda").manual_seed(n), device="cuda").to(torch.float16)
+            out, lse = torch.full((heads * n, 128), 7.0, device="cuda"), torch.full((heads * n,), 7.0, device="cuda")
+            ctx.attend_decode_gqa(0, q, n, 0, frames, 128.0 ** -0.5, out, lse)
+            if rep > 0:
+                assert torch.equal(out, first[n][0]) and torch.equal(lse, first[n][1]), f"{n} queries, repetition {rep}"
+                continue
+            first[n] = (out, lse)
+            s = torch.bmm(q.double().view(heads, n, 128), k.transpose(1, 2).contiguous()) * 128.0 ** -0.5
+            pr = torch.softmax(s, dim=-1)
+            exp, size = torch.bmm(pr, v).reshape(-1, 128), torch.bmm(pr, v.abs()).reshape(-1, 128)
+            bound = 1e-5 * size
+            if n > 8:
+                bound = (2.0 ** -11 + 1e-5) * size + 2.0 ** -24 * (pr.amax(-1, keepdim=True) * v.abs().sum(1, keepdim=True)).reshape(-1, 128)
+            err = (out.double() - exp).abs()
+            print(f"{heads} heads, {n} queries: largest error / bound {(err / bound).max():.3f}", flush=True)
+            assert bool((err <= bound).all())
+            assert bool(((lse.double() - torch.logsumexp(s, dim=-1).reshape(-1)).abs() <= 1e-5 * (1 + lse.double().abs())).all())
+    assert ctx.get_status() == 0
+    ctx.close()
