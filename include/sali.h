@@ -320,7 +320,8 @@ int sali_step_batch(sali_ctx* ctx, const uint8_t* const* d_rgb_frames, const voi
  *   d_out      device, fp32 [n_heads][128]; zeros where the range holds no token
  *   d_lse_or_null  device, fp32 [n_heads]; -inf where the range holds no token
  * Asynchronous on `stream`, which must be ordered after the stores of the frames read.  Uses one
- * partial-result area of the context: calls on one context must not overlap each other.
+ * partial-result area of the context and counters of the blocks that have finished: calls on one context must not overlap
+ * each other (if they do, their results and those of later calls are undefined until sali_reset).
  * SALI_ERR_SHAPE if layer or the frame range is out of range (frame_lo == frame_hi is allowed). */
 int sali_attend_decode(sali_ctx* ctx, int32_t layer, const void* d_q_fp16, int32_t frame_lo, int32_t frame_hi,
                        float softmax_scale, float* d_out, float* d_lse_or_null, void* stream);

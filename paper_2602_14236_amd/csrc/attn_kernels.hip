@@ -11,9 +11,12 @@
 //
 // One query per head makes Q K^T and P V matrix-vector products: 2 flops per byte read, so the
 // kernel is bound by HBM and written as a stream, not for MFMA; the arithmetic is arranged so that
-// the vector ALU stays below the memory time (about 5 operations per INT8 element pair instead of
-// 12 when every value is first rounded to fp16: the group scale is applied once per row to the dot
-// product and to the softmax weight, the INT4 zero-point through sum(q) and a separate accumulator).
+// the vector ALU stays below the memory time (the group scale is applied once per row to the dot
+// product and to the softmax weight, the INT4 zero-point through sum(q) and a separate accumulator; dot products
+// take codes as pairs of halves).  A layer of 32 heads over 20 frames (131 MB): 25.5 us, a frame more 0.97 (6.8 TB/s), what does not
+// depend on the size 6.  With the merge in a kernel of its own, 60 parts a head that did not all fit the chip at once (73 registers:
+// six blocks per compute unit, not eight), launch order and one code at a time: 28.4, 9 of it fixed; 8 heads x 8 queries 41.5 -> 28.5, 4 heads
+// over 12 frames 17.3 -> 9.3, one frame 12.9 -> 6.9 (kernel to kernel).
 // The compressed rows are read once, in pool order (attention does not care about token order),
 // with the lane mapping of the pack / unpack kernels: a row is handled by 16 adjacent lanes holding
 // 8 consecutive head-dim values each, a 32-value quantisation group is one lane quad, the dot
@@ -233,8 +236,7 @@ __device__ __forceinline__ void attend_rows(const Pools& pools, size_t plane_k, 
     };
     Step next;
     request(j0, next);
-    // only now: made ahead of the frame table's read, the pieces had that and the first rows wait for the query's trip, behind
-    // the rows of blocks that were quicker
+    // only now, so that the first rows need not wait for the query's trip
     QueryPiece q[kQ];
 #pragma unroll
     for (int iq = 0; iq < kQ; ++iq) q[iq] = query_piece(raw_q[iq]);
@@ -603,8 +605,8 @@ __global__ __launch_bounds__(256) void k_attn_empty(AttnOut result, int n_q_head
 // instructions of a tile (610, conversions and softmax).  Hence: a tile's K^ and V^ rows are asked for a
 // whole tile ahead, across tiers and frames; the launch is one block of eight waves per compute unit, forced
 // to one by its LDS, so that all start at once; and a block writes one partial instead of one per wave.
-// 32 heads x 32 queries over 20 frames (173 / 200 / 203 rows, 118 MB): 34.5 us + 4.6 us of merge.  The same
-// tiles as 512 independent blocks of four waves that should just have fitted twice per compute unit, a
+// 32 heads x 32 queries over 20 frames (173 / 200 / 203 rows, 118 MB): 34.6 us a call, of which tiles stream for 19 at 6.1 TB/s; 36.1 with
+// the merge in a kernel of its own and 64-bit divisions in the list of frames (34.5 + 4.6 by the kernels).  The same tiles as 512 independent blocks of four waves that should just have fitted twice per compute unit, a
 // tier's loads one tile ahead and a partial per wave, took 69.6 us + 8.0 us of merge: such blocks do not
 // pack perfectly, the last of them ran alone in a second round (mean wave lifetime 26 us).
 typedef _Float16 half4_t __attribute__((ext_vector_type(4)));
