@@ -190,15 +190,15 @@ struct WithPrep<Own, NoRide> {
 };
 // Is this block one of the `riders`?  Then it does its tile; the others get their number among the launch's own blocks (per_frame
 // a frame, frame by frame).  Without riders the grid is (per_frame, frames).
-template <typename Shared>
+template <int NT, typename Shared>
 __device__ __forceinline__ bool ride_prep(Shared& sh, const PrepRide& ride, int riders, int, int& block) {
     block = (int)blockIdx.x - riders;
     if (block >= 0) return false;
     const int tiles = ride.tiles_x * ride.tiles_y, frame = (int)blockIdx.x / tiles, t = (int)blockIdx.x - frame * tiles;
-    prep_tile<false, kPrepThreads>(sh.prep, ride.f, t % ride.tiles_x, t / ride.tiles_x, frame, ride.h, ride.w, GateParams{}, ride.lut, ride.lo2, ride.hi2);
+    prep_tile<false, NT>(sh.prep, ride.f, t % ride.tiles_x, t / ride.tiles_x, frame, ride.h, ride.w, GateParams{}, ride.lut, ride.lo2, ride.hi2);
     return true;
 }
-template <typename Shared>
+template <int NT, typename Shared>
 __device__ __forceinline__ bool ride_prep(Shared&, const NoRide&, int, int per_frame, int& block) {
     block = (int)blockIdx.x + per_frame * (int)blockIdx.y;
     return false;
@@ -209,7 +209,7 @@ template <typename Ride>
 __global__ __launch_bounds__(256) void k_polyexp(int riders, int per_frame, LevelGeom g, FlowWeights fw, PyrBatch f, Ride ride) {
     __shared__ WithPrep<PolyexpShared, Ride> sh;
     int block;
-    if (ride_prep(sh, ride, riders, per_frame, block)) return;
+    if (ride_prep<256>(sh, ride, riders, per_frame, block)) return;
     int frame = (int)blockIdx.y, tile = (int)blockIdx.x;
     if constexpr (!std::is_same_v<Ride, NoRide>) {
         frame = block / per_frame;
@@ -290,26 +290,37 @@ __global__ __launch_bounds__(256) void k_polyexp(int riders, int per_frame, Leve
 }
 
 // ---------------------------------------------------------------------------------------------
-// Pyramid + expansion in one launch for up to three levels: a block owns one 16x16 tile of one
-// level and rebuilds the pyramid values it needs from the RGB frame in LDS (level 1 from a 47x47
+// Pyramid + expansion in one launch for up to three levels: a block owns one 16x16 tile of level 2 or two tiles of level 1 or 0 and
+// rebuilds the pyramid values it needs from the RGB frame in LDS (level 1 from a 47x47
 // gray patch, level 2 from a 47x47 level-1 patch built from a 97x97 gray patch).  This recomputes
 // some pyramid pixels but removes two dependent launches and all pyramid traffic.
+//
+// The level-2 tile is the launch's length: trip for its patch, two pyramid stages, moments (3.4, 2.6, 0.6 and 0.8 of 8.9 us on 256 threads
+// with a byte read per tap).  On 512 threads, its first stage by byte dot products, a launch for two 336x336 frames takes 10.2 us instead
+// of 13.4, for one frame with the pre-pass 13.3 instead of 18.2.
 namespace {
 constexpr int kET = 16;                        // tile side
 constexpr int kER = kET + 2 * kPolyN;          // 22: region the expansion stencil reads
 constexpr int kEP = 2 * (kER - 1) + 5;         // 47: region one level below that feeds it
 constexpr int kEQ = 2 * (kEP - 1) + 5;         // 97: region two levels below
-// The 47-wide float patch is de-interleaved: even columns from float 24 of a row on, row stride 59, so
+constexpr int kExpandThreads = 512, kExpandHalf = kExpandThreads / 2;
+// The 47-wide float patch of a level-2 tile is de-interleaved: even columns from float 24 of a row on, row stride 59, so
 // that the stage reading it (22 cells per row) sees addresses linear in its thread index (pyr_level_lds:
-// 2 * 59 = 22 mod 32); its writes, one per 25 reads, then see two-way conflicts (even columns at 48 would
-// need rows of 75 floats).  The 97-wide gray patch of a level-2 tile stays in bytes, plain layout, rows of
-// 112 bytes: the stage that reads it takes 47 cells per row by 48 lanes at a stride of two bytes, so a
-// group of 32 lanes reads 16 words (two lanes a word: a broadcast), and the second half of a wave,
-// which straddles two cell rows = 2 * 28 words = 24 banks apart, still hits every bank at most once.
+// 2 * 59 = 22 mod 32).  The gray patches stay in bytes, plain layout, rows of 112 and 52 bytes: a stage that reads one takes two
+// words per row and cell, neighbouring cells half a word apart.
 constexpr int kEvenP = 24, kEPS = 59;
-constexpr int kEQB = 112;
+constexpr int kEQB = 112, kEPB = 52;
 static_assert(kEvenP + (kEP + 1) / 2 <= kEPS && kEvenP >= kEP / 2, "a row holds both halves");
-static_assert(kEQB % 4 == 0 && kEQB >= (kEQ + 3) / 4 * 4 && (2 * (kEQB / 4)) % 32 == 24, "byte rows");
+static_assert(kEQB % 4 == 0 && kEQB >= (kEQ + 3) / 4 * 4 && kEPB % 4 == 0 && kEPB >= (kEP + 3) / 4 * 4, "byte rows");
+
+// v / kDiv, correctly rounded, for whole v from 0 to kDiv (255 and 65280: every value checked): the product with the rounded reciprocal,
+// corrected by its remainder
+template <int kDiv>
+__device__ __forceinline__ float whole_over(uint32_t v) {
+    constexpr float kInv = 1.0f / kDiv;
+    const float x = (float)v, q = x * kInv;
+    return __builtin_fmaf(__builtin_fmaf(-(float)kDiv, q, x), kInv, q);
+}
 
 // LDS patches that feed a pyramid stage keep the odd columns of a row in its first part and the even
 // columns from kEven on (kEven = 0: plain layout): the stage reads columns 2 * cx + {-2..2}, a stride
@@ -330,7 +341,7 @@ __device__ __forceinline__ void pyr_level_lds(const float* src, int o_src_y, int
                                               int o_dst_x, int dh, int dw) {
     static_assert((2 * kSrcStride - kLanesPerRow) % 32 == 0, "tap addresses must be linear in the thread index");
     const float k[5] = {1.0f / 16, 4.0f / 16, 6.0f / 16, 4.0f / 16, 1.0f / 16};
-    for (int p = threadIdx.x; p < kN * kLanesPerRow; p += 256) {
+    for (int p = threadIdx.x; p < kN * kLanesPerRow; p += kExpandThreads) {
         const int ry = p / kLanesPerRow, rx = p % kLanesPerRow;
         if (rx >= kN) continue;
         const int cy = clampi(o_dst_y + ry, 0, dh - 1), cx = clampi(o_dst_x + rx, 0, dw - 1);
@@ -351,143 +362,156 @@ __device__ __forceinline__ void pyr_level_lds(const float* src, int o_src_y, int
 // every quad of columns.  All of a thread's loads are issued before the first one is used: written as one loop the
 // compiler waits for every one in turn, and next to a kernel that saturates the memory system each takes
 // microseconds.
-template <int kSide, typename Put>
-__device__ __forceinline__ void load_gray_patch(const uint8_t* __restrict__ rgb, int h0, int w0, int qy, int qx, Put put) {
-    constexpr int kQuads = (kSide + 3) / 4, kItems = kSide * kQuads, kN = (kItems + 255) / 256;
+template <int kSide, int NT, typename Put>
+__device__ __forceinline__ void load_gray_patch(const uint8_t* __restrict__ rgb, int h0, int w0, int qy, int qx, int tid, Put put) {
+    constexpr int kQuads = (kSide + 3) / 4, kItems = kSide * kQuads, kN = (kItems + NT - 1) / NT;
     uint32_t v[kN][3];
 #pragma unroll
     for (int k = 0; k < kN; ++k) {
-        const int p = min((int)threadIdx.x + 256 * k, kItems - 1);
+        const int p = min(tid + NT * k, kItems - 1);
         load_rgb_quad(rgb + (size_t)clampi(qy + p / kQuads, 0, h0 - 1) * w0 * 3, qx + 4 * (p % kQuads), w0, v[k]);
     }
 #pragma unroll
     for (int k = 0; k < kN; ++k) {
-        const int p = (int)threadIdx.x + 256 * k;
+        const int p = tid + NT * k;
         if (p < kItems) put(p / kQuads, 4 * (p % kQuads), gray_of_quad(v[k]));
     }
 }
-// as gray / 255, row stride kStride, columns laid out by lds_col<kEven>
-template <int kSide, int kStride, int kEven>
-__device__ __forceinline__ void load_gray_floats(const uint8_t* __restrict__ rgb, int h0, int w0, int qy, int qx,
+// as gray / 255, row stride kSide
+template <int kSide, int NT>
+__device__ __forceinline__ void load_gray_floats(const uint8_t* __restrict__ rgb, int h0, int w0, int qy, int qx, int tid,
                                                  float* __restrict__ dst) {
-    load_gray_patch<kSide>(rgb, h0, w0, qy, qx, [&](int row, int col, uint32_t quad) {
+    load_gray_patch<kSide, NT>(rgb, h0, w0, qy, qx, tid, [&](int row, int col, uint32_t quad) {
 #pragma unroll
         for (int i = 0; i < 4; ++i)
-            if (col + i < kSide) dst[row * kStride + lds_col<kEven>(col + i)] = (float)((quad >> (8 * i)) & 0xFFu) / 255.0f;
+            if (col + i < kSide) dst[row * kSide + col + i] = whole_over<255>((quad >> (8 * i)) & 0xFFu);
     });
 }
-// The 97 x 97 patch of a level-2 tile, as bytes.  As floats it took 40 KB and the block 52: three blocks per
-// compute unit, also for the level-0 and level-1 tiles of the same launch, which need none of it; in bytes the block
-// takes 24 KB.
-__device__ __forceinline__ void load_gray_bytes(const uint8_t* __restrict__ rgb, int h0, int w0, int qy, int qx,
+// as bytes, rows of kRowBytes
+template <int kSide, int kRowBytes, int NT>
+__device__ __forceinline__ void load_gray_bytes(const uint8_t* __restrict__ rgb, int h0, int w0, int qy, int qx, int tid,
                                                 uint32_t* __restrict__ dst) {
-    load_gray_patch<kEQ>(rgb, h0, w0, qy, qx, [&](int row, int col, uint32_t quad) { dst[row * (kEQB / 4) + col / 4] = quad; });
+    load_gray_patch<kSide, NT>(rgb, h0, w0, qy, qx, tid, [&](int row, int col, uint32_t quad) { dst[row * (kRowBytes / 4) + col / 4] = quad; });
 }
 
-// First pyramid level of a level-2 tile from the byte patch: the 5x5 binomial sum in integers (weights
+// First pyramid level from a byte patch: the 5x5 binomial sum in integers (weights
 // 1 4 6 4 1 squared: at most 256 * 255, exact) and one division by 256 * 255, i.e. the level-1 value of
-// gray / 255 rounded once.  Cells and lanes as in pyr_level_lds.
-template <int kDstStride, int kDstEven, int kN, int kLanesPerRow>
-__device__ __forceinline__ void pyr_level_from_bytes(const uint8_t* src, int o_src_y, int o_src_x, float* dst,
-                                                     int o_dst_y, int o_dst_x, int dh, int dw) {
+// gray / 255 rounded once.  dst cell i stands for the coordinate clamp(o_dst + i), as in pyr_level_lds; its leftmost tap lies at an even
+// column of the patch (o_src is even), so the five taps of a row are in two words.
+template <int kRowBytes, int kDstStride, int kDstEven, int kN, int NT>
+__device__ __forceinline__ void pyr_level_from_bytes(const uint32_t* src, int o_src_y, int o_src_x, float* dst, int o_dst_y, int o_dst_x,
+                                                     int dh, int dw, int tid) {
     const uint32_t k[5] = {1u, 4u, 6u, 4u, 1u};
-    for (int p = threadIdx.x; p < kN * kLanesPerRow; p += 256) {
-        const int ry = p / kLanesPerRow, rx = p % kLanesPerRow;
-        if (rx >= kN) continue;
+#pragma unroll 2
+    for (int p = tid; p < kN * kN; p += NT) {
+        const int ry = p / kN, rx = p % kN;
         const int cy = clampi(o_dst_y + ry, 0, dh - 1), cx = clampi(o_dst_x + rx, 0, dw - 1);
-        const int sy = 2 * cy - o_src_y, sx = 2 * cx - o_src_x;
+        const int c = 2 * cx - o_src_x - 2, top = 2 * cy - o_src_y - 2;
+        const uint32_t* at = src + top * (kRowBytes / 4) + (c >> 2);
+        const uint32_t shift = 8u * ((uint32_t)c & 3u);                 // 0 or 16
         uint32_t acc = 0u;
 #pragma unroll
-        for (int a = -2; a <= 2; ++a) {
-            uint32_t row = 0u;
-#pragma unroll
-            for (int b = -2; b <= 2; ++b) row += k[b + 2] * (uint32_t)src[(sy + a) * kEQB + sx + b];
-            acc += k[a + 2] * row;
+        for (int a = 0; a < 5; ++a) {
+            const uint32_t w0 = at[a * (kRowBytes / 4)], w1 = at[a * (kRowBytes / 4) + 1];
+            const uint32_t four = __builtin_amdgcn_alignbit(w1, w0, shift), fifth = (w1 >> shift) & 0xFFu;
+            acc += k[a] * __builtin_amdgcn_udot4(four, 0x04060401u, fifth, false);
         }
-        dst[ry * kDstStride + lds_col<kDstEven>(rx)] = (float)acc / 65280.0f;
+        dst[ry * kDstStride + lds_col<kDstEven>(rx)] = whole_over<65280>(acc);
     }
 }
 
-struct ExpandShared {
-    uint32_t qb[kEQ * (kEQB / 4)];      // gray patch of a level-2 block, bytes
-    float p[kEP * kEPS];                // level-1 patch of a level-2 block; gray patch of a level-1 block
+struct ExpandTile {                     // a tile of level 0 or 1, half a block
+    uint32_t pb[kEP * (kEPB / 4)];      // gray patch of a level-1 tile, bytes
     // unpadded rows: both the pass that writes these arrays and the pass that reads them then see
     // addresses linear in the thread index (the horizontal pass pairs rows eight apart, see below)
     float f[kER][kER];
+    float v[3][kET][kER];               // vertical moments
 };
+struct ExpandTile2 {                    // a tile of level 2, the whole block
+    uint32_t qb[kEQ * (kEQB / 4)];      // gray patch, bytes; vertical moments later
+    float p[kEP * kEPS];                // level-1 patch
+    float f[kER][kER];
+};
+union ExpandShared {
+    ExpandTile half[2];
+    ExpandTile2 whole;
+};
+static_assert(sizeof(float) * 3 * kET * kER <= sizeof(uint32_t) * kEQ * (kEQB / 4), "moments fit into the byte patch");
 
 }  // namespace
 
-// t1, t2, t3: a frame's tiles of level 0, of levels 0 and 1, of all levels
+// c0, c1, c2: a frame's tiles of each level
 template <typename Ride>
-__global__ __launch_bounds__(256) void k_expand(int riders, int n_frames, int t1, int t2, int t3, int tx0, int tx1, int tx2,
-                                                LevelGeom g, FlowWeights fw, ExpandBatch f, Ride ride) {
+__global__ __launch_bounds__(kExpandThreads) void k_expand(int riders, int n_frames, int c0, int c1, int c2, int tx0, int tx1, int tx2,
+                                                           LevelGeom g, FlowWeights fw, ExpandBatch f, Ride ride) {
     __shared__ WithPrep<ExpandShared, Ride> sh;
+    const int b0 = (c0 + 1) / 2, b1 = (c1 + 1) / 2;             // blocks of a frame's levels 0 and 1
     int idx;
-    if (ride_prep(sh, ride, riders, t3, idx)) return;
+    if (ride_prep<kExpandThreads>(sh, ride, riders, c2 + b1 + b0, idx)) return;
     // Work order.  A level-2 tile costs about ten times a level-0 tile (97 x 97 gray pixels, two pyramid
     // stages) and there are sixteen level-0 tiles for each: with the tiles of a frame in level order the
     // heavy ones start last and the launch ends with a few of them on an idle chip (22 us per four
     // 336x336 frames, 10 of them that tail).  So the linear block id is cut into runs, heaviest first,
     // each run over all frames of the batch: level-2 tiles, level-1 tiles, level-0 tiles.
-    int lvl, t, frame;
-    if (idx < n_frames * (t3 - t2)) {
+    const int half = __builtin_amdgcn_readfirstlane((int)threadIdx.x / kExpandHalf);
+    int lvl, t, frame, count;
+    if (idx < n_frames * c2) {
         lvl = 2;
-        frame = idx / (t3 - t2);
-        t = idx - frame * (t3 - t2);
-    } else if ((idx -= n_frames * (t3 - t2)) < n_frames * (t2 - t1)) {
+        count = c2;
+        frame = idx / c2;
+        t = idx - frame * c2;
+    } else if ((idx -= n_frames * c2) < n_frames * b1) {
         lvl = 1;
-        frame = idx / (t2 - t1);
-        t = idx - frame * (t2 - t1);
+        count = c1;
+        frame = idx / b1;
+        t = 2 * (idx - frame * b1) + half;
     } else {
-        idx -= n_frames * (t2 - t1);
+        idx -= n_frames * b1;
         lvl = 0;
-        frame = idx / t1;
-        t = idx - frame * t1;
+        count = c0;
+        frame = idx / b0;
+        t = 2 * (idx - frame * b0) + half;
     }
+    const bool spare = t >= count;                              // the second tile of a last block: done again, not stored
+    t = min(t, count - 1);
     const ExpandFrame& fr = f.frame[frame];
     const uint8_t* __restrict__ rgb = fr.rgb;
     float4* __restrict__ A_out = fr.A;
     float* __restrict__ b_out = fr.b;
     together(rgb, A_out, b_out, g.h[0], g.w[0], g.h[1], g.w[1], g.h[2], g.w[2], g.off[1], g.off[2]);
-    uint32_t (&s_qb)[kEQ * (kEQB / 4)] = sh.own.qb;
-    float (&s_p)[kEP * kEPS] = sh.own.p;
-    float (&s_f)[kER][kER] = sh.own.f;
-    // the vertical moments reuse the 47-wide patch's memory: every path has a barrier between its last
-    // read of s_p and the pass that writes them
-    float (*s_v)[kET][kER] = reinterpret_cast<float (*)[kET][kER]>(s_p);
-    static_assert(3 * kET * kER <= kEP * kEPS, "moments fit into the 47-wide patch");
-
     const int tiles_x = lvl == 0 ? tx0 : (lvl == 1 ? tx1 : tx2);
     const int h = lvl == 0 ? g.h[0] : (lvl == 1 ? g.h[1] : g.h[2]), w = lvl == 0 ? g.w[0] : (lvl == 1 ? g.w[1] : g.w[2]);
     const int64_t level_off = lvl == 0 ? 0 : (lvl == 1 ? g.off[1] : g.off[2]);
     const int x0 = (t % tiles_x) * kET, y0 = (t / tiles_x) * kET;
     const int oy = y0 - kPolyN, ox = x0 - kPolyN;   // origin of s_f in this level's coordinates
-    const int tid = threadIdx.x;
+    const int tid = threadIdx.x % kExpandHalf;
     const int h0 = g.h[0], w0 = g.w[0];
+    float (*s_f)[kER] = lvl == 2 ? sh.own.whole.f : sh.own.half[half].f;
+    float (*s_v)[kET][kER] = lvl == 2 ? reinterpret_cast<float (*)[kET][kER]>(sh.own.whole.qb) : sh.own.half[half].v;
 
     if (lvl == 0) {
-        load_gray_floats<kER, kER, 0>(rgb, h, w, oy, ox, &s_f[0][0]);
+        load_gray_floats<kER, kExpandHalf>(rgb, h, w, oy, ox, tid, &s_f[0][0]);
     } else if (lvl == 1) {
         const int qy = 2 * oy - 2, qx = 2 * ox - 2;              // origin of the gray patch (47 x 47)
-        load_gray_floats<kEP, kEPS, kEvenP>(rgb, h0, w0, qy, qx, s_p);
+        uint32_t* s_pb = sh.own.half[half].pb;
+        load_gray_bytes<kEP, kEPB, kExpandHalf>(rgb, h0, w0, qy, qx, tid, s_pb);
         __syncthreads();
-        pyr_level_lds<kEPS, kEvenP, kER, 0, kER, kER>(s_p, qy, qx, &s_f[0][0], oy, ox, h, w);
+        pyr_level_from_bytes<kEPB, kER, 0, kER, kExpandHalf>(s_pb, qy, qx, &s_f[0][0], oy, ox, h, w, tid);
     } else {
         const int h1 = g.h[1], w1 = g.w[1];
         const int py = 2 * oy - 2, px = 2 * ox - 2;              // origin of the level-1 patch (47 x 47)
         const int qy = 2 * py - 2, qx = 2 * px - 2;              // origin of the gray patch (97 x 97)
-        load_gray_bytes(rgb, h0, w0, qy, qx, s_qb);
+        load_gray_bytes<kEQ, kEQB, kExpandThreads>(rgb, h0, w0, qy, qx, (int)threadIdx.x, sh.own.whole.qb);
         __syncthreads();
-        pyr_level_from_bytes<kEPS, kEvenP, kEP, kEP + 1>(reinterpret_cast<const uint8_t*>(s_qb), qy, qx, s_p, py, px, h1,
-                                                         w1);
+        pyr_level_from_bytes<kEQB, kEPS, kEvenP, kEP, kExpandThreads>(sh.own.whole.qb, qy, qx, sh.own.whole.p, py, px, h1, w1, (int)threadIdx.x);
         __syncthreads();
-        pyr_level_lds<kEPS, kEvenP, kER, 0, kER, kER>(s_p, py, px, &s_f[0][0], oy, ox, h, w);
+        pyr_level_lds<kEPS, kEvenP, kER, 0, kER, kER>(sh.own.whole.p, py, px, &s_f[0][0], oy, ox, h, w);
     }
     __syncthreads();
 
     // vertical moments, then horizontal moments and the closed-form fit (as in k_polyexp)
-    for (int p = tid; p < kET * kER; p += 256) {
+    const int step = lvl == 2 ? kExpandThreads : kExpandHalf;
+    for (int p = lvl == 2 ? (int)threadIdx.x : tid; p < kET * kER; p += step) {
         const int ty = p / kER, rx = p % kER;
         float v0 = 0.0f, v1 = 0.0f, v2 = 0.0f;
 #pragma unroll
@@ -502,11 +526,12 @@ __global__ __launch_bounds__(256) void k_expand(int riders, int n_frames, int t1
         s_v[2][ty][rx] = v2;
     }
     __syncthreads();
+    if (spare || (lvl == 2 && half != 0)) return;
     {
         // a group of 32 lanes takes the rows r and r + 8 (16 lanes each): 8 rows of 22 floats are 176 =
         // 16 (mod 32) floats apart, so the two rows lie on disjoint banks
-        const int half = tid / kET, tx = tid % kET;
-        const int ty = (half >> 1) + 8 * (half & 1);
+        const int pair = tid / kET, tx = tid % kET;
+        const int ty = (pair >> 1) + 8 * (pair & 1);
         const int gy = y0 + ty, gx = x0 + tx;
         if (gy < h && gx < w) {
             float s0 = 0, sx = 0, sxx = 0, sy = 0, sxy = 0, syy = 0;
@@ -1191,21 +1216,18 @@ hipError_t launch_polyexp(const PyrBatch& f, int n, LevelGeom g, FlowWeights fw,
 hipError_t launch_expand(const ExpandBatch& f, int n, LevelGeom g, FlowWeights fw, const PrepRide* ride_or_null, hipEvent_t done_or_null,
                          hipStream_t s) {
     // up to three levels, 16x16 tiles, one launch
-    int tx[3] = {1, 1, 1}, start[4] = {0, 0, 0, 0};
-    for (int l = 0; l < 3; ++l) {
-        int tiles = 0;
-        if (l < g.levels) {
-            tx[l] = (g.w[l] + kET - 1) / kET;
-            tiles = tx[l] * ((g.h[l] + kET - 1) / kET);
-        }
-        start[l + 1] = start[l] + tiles;
+    int tx[3] = {1, 1, 1}, tiles[3] = {0, 0, 0};
+    for (int l = 0; l < 3 && l < g.levels; ++l) {
+        tx[l] = (g.w[l] + kET - 1) / kET;
+        tiles[l] = tx[l] * ((g.h[l] + kET - 1) / kET);
     }
+    const int per_frame = tiles[2] + (tiles[1] + 1) / 2 + (tiles[0] + 1) / 2;
     if (ride_or_null != nullptr)
-        launch_recording(done_or_null, k_expand<PrepRide>, dim3(ride_or_null->blocks + start[3] * n), dim3(256), s, ride_or_null->blocks, n,
-                         start[1], start[2], start[3], tx[0], tx[1], tx[2], g, fw, f, *ride_or_null);
+        launch_recording(done_or_null, k_expand<PrepRide>, dim3(ride_or_null->blocks + per_frame * n), dim3(kExpandThreads), s,
+                         ride_or_null->blocks, n, tiles[0], tiles[1], tiles[2], tx[0], tx[1], tx[2], g, fw, f, *ride_or_null);
     else
-        launch_recording(done_or_null, k_expand<NoRide>, dim3(start[3], n), dim3(256), s, 0, n, start[1], start[2], start[3], tx[0], tx[1],
-                         tx[2], g, fw, f, NoRide{});
+        launch_recording(done_or_null, k_expand<NoRide>, dim3(per_frame, n), dim3(kExpandThreads), s, 0, n, tiles[0], tiles[1], tiles[2], tx[0],
+                         tx[1], tx[2], g, fw, f, NoRide{});
     return hipGetLastError();
 }
 
