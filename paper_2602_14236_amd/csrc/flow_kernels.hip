@@ -559,25 +559,35 @@ __global__ __launch_bounds__(kExpandThreads) void k_expand(int riders, int n_fra
 // ---------------------------------------------------------------------------------------------
 namespace {
 
-// 2 * the coarser flow at (y / 2, x / 2), bilinear, coordinates clamped to it.  The weights are 1 and 0 or both a half, and past the
-// last row or column (an odd pixel of an even size) both samples are the last one.
-__device__ __forceinline__ float2 transfer_at(const float2* __restrict__ coarse, int gy, int gx, int ch, int cw) {
-    const int y0 = gy >> 1, x0 = gx >> 1, y1 = min(y0 + (gy & 1), ch - 1), x1 = min(x0 + (gx & 1), cw - 1);
-    const uint32_t r0 = pix(y0, cw, 0), r1 = pix(y1, cw, 0);
-    const float2 a = ld_at(coarse, r0 + (uint32_t)x0), b = ld_at(coarse, r0 + (uint32_t)x1);
-    const float2 c = ld_at(coarse, r1 + (uint32_t)x0), d = ld_at(coarse, r1 + (uint32_t)x1);
+// Prior displacement of a pixel in the first update of a level that is not the coarsest: 2 * the coarser flow at (y / 2, x / 2), bilinear,
+// coordinates clamped to it.  The weights are 1 and 0 or both a half, and past the last row or column (an odd pixel of an even size)
+// both samples are the last one.
+struct CoarseCell {
+    float2 a, b, c, d;
+};
+__device__ __forceinline__ float2 transfer_of(const CoarseCell& v) {
     // each pair's mean is exact but for one rounding of the sum, as is 2 * the mean of the two
-    const float tx = 0.5f * (a.x + b.x), ty = 0.5f * (a.y + b.y), bx = 0.5f * (c.x + d.x), by = 0.5f * (c.y + d.y);
+    const float tx = 0.5f * (v.a.x + v.b.x), ty = 0.5f * (v.a.y + v.b.y), bx = 0.5f * (v.c.x + v.d.x), by = 0.5f * (v.c.y + v.d.y);
     return make_float2(tx + bx, ty + by);
 }
 
-// prior displacement of a pixel: 0 (coarsest level), 2 * bilinear(coarser flow; y/2, x/2) for
-// the first update of a finer level, or the previous update's result
-__device__ __forceinline__ float2 prior_at(const float2* __restrict__ d_in, int mode, int gy, int gx, int w, int ch,
-                                           int cw) {
-    if (mode == 0) return make_float2(0.0f, 0.0f);
-    if (mode == 1) return transfer_at(d_in, gy, gx, ch, cw);
-    return ld_at(d_in, pix(gy, w, gx));
+// The coarser flow under a region of a finer level that starts at (ry, rx) (odd) and is 2 (CX - 1) x 2 (CY - 1) pixels large, in LDS.  A cell of
+// it serves up to sixteen of the loads that priors took one by one (four a pixel), which were half as much
+// work for the load path as the samples: first updates of 3 x 1920x1080 128 -> 107 us, one 35 -> 31, 15 x 640x360 57 -> 49.
+template <int CX, int CY>
+struct CoarsePatch {
+    float2 v[CX * CY];
+};
+template <int NT, int CX, int CY>
+__device__ __forceinline__ void load_coarse(CoarsePatch<CX, CY>& patch, const float2* __restrict__ coarse, int ry, int rx, int ch, int cw) {
+    for (int p = threadIdx.x; p < CX * CY; p += NT)
+        patch.v[p] = ld_at(coarse, pix(clampi((ry >> 1) + p / CX, 0, ch - 1), cw, clampi((rx >> 1) + p % CX, 0, cw - 1)));
+}
+template <int CX, int CY>
+__device__ __forceinline__ float2 transfer_from(const CoarsePatch<CX, CY>& patch, int ry, int rx, int y, int x, int ch, int cw) {
+    const int r0 = ((y >> 1) - (ry >> 1)) * CX, r1 = (min((y >> 1) + (y & 1), ch - 1) - (ry >> 1)) * CX;
+    const int c0 = (x >> 1) - (rx >> 1), c1 = min((x >> 1) + (x & 1), cw - 1) - (rx >> 1);
+    return transfer_of({patch.v[r0 + c0], patch.v[r0 + c1], patch.v[r1 + c0], patch.v[r1 + c1]});
 }
 
 // size of a level and the coordinates of its last row and column, in scalar registers
@@ -736,9 +746,14 @@ __global__ __launch_bounds__(kSmallThreads) void k_flow_small(int tiles_x, int t
     static_assert((8 * R) % 32 == 16, "rows eight apart sit 16 banks apart");
     __shared__ float s_in[5][R][R];
     __shared__ float2 s_dp[T][T];            // prior of the tile's own pixels, for the solve
+    __shared__ CoarsePatch<R / 2 + 1, R / 2 + 1> s_coarse;
 
     const int tid = threadIdx.x;
     const int x0 = blk.x * T, y0 = blk.y * T;
+    if (prior_mode == 1) {
+        load_coarse<NT>(s_coarse, fr.d_in, y0 - kWinR, x0 - kWinR, ch, cw);
+        __syncthreads();
+    }
 
     // per-cell A^T A and A^T db at the clamped coordinate of the cell
 #pragma unroll 2
@@ -746,7 +761,8 @@ __global__ __launch_bounds__(kSmallThreads) void k_flow_small(int tiles_x, int t
         const int ry = p / R, rx = p % R;
         const int gy = clampi(y0 - kWinR + ry, 0, h - 1), gx = clampi(x0 - kWinR + rx, 0, w - 1);
         const OldCell old = old_cell(fr.A1, fr.b1, pix(gy, w, gx));
-        const float2 dp = prior_at(fr.d_in, prior_mode, gy, gx, w, ch, cw);
+        const float2 dp = prior_mode == 0 ? make_float2(0.0f, 0.0f)
+                          : prior_mode == 1 ? transfer_from(s_coarse, y0 - kWinR, x0 - kWinR, gy, gx, ch, cw) : ld_at(fr.d_in, pix(gy, w, gx));
         if (ry >= kWinR && ry < kWinR + T && rx >= kWinR && rx < kWinR + T) s_dp[ry - kWinR][rx - kWinR] = dp;
         float t[5];
         flow_terms(old, fr.A2, fr.b2, extent, gy, gx, dp, t);
@@ -824,7 +840,7 @@ __global__ __launch_bounds__(kSmallThreads) void k_flow_small(int tiles_x, int t
 // ---------------------------------------------------------------------------------------------
 // One update of a large level: tiles 32 wide on 512 threads, the window passes on the matrix cores.
 //
-// Three 1920x1080 frames: 73 us an update, one: 28, fifteen 640x360: 45.  With the windows on the vector ALU (110
+// Three 1920x1080 frames: 84 to 90 us an update, one: 28, fifteen 640x360: 44.  With the windows on the vector ALU (110
 // multiply-adds and as many LDS reads a pixel and 1.6 rows of halo, 32x16 tiles, per-cell index arithmetic, divisions)
 // 518 vector instructions a pixel kept the ALU 91 % busy: 102, 37 and 59 us.  Now it is 45 % busy (260 instructions)
 // and the trips of the warped samples bound the kernel: 12 000 of a block's 21 000 cycles.  Everything that costs a block
@@ -835,9 +851,8 @@ __global__ __launch_bounds__(kSmallThreads) void k_flow_small(int tiles_x, int t
 // (v_mfma_f32_16x16x4f32, the row pass's result the column pass's operand) took 100: 28 and 32 terms for eleven.
 constexpr int kTileX = 32, kTileThreads = 512;
 //
-// kFirst: the first update of a level (prior_mode 0 or 1).  The others know that a prior is one load, and ask for those of
-// all the thread's cells before the first sample; a first update takes 81, 31 and 51 us.  The samples of the coarser flow that
-// a first update needs leave no registers for that.
+// kFirst: the first update of a level (prior_mode 0 or 1), whose priors come from the coarser level's flow, staged in LDS: 107, 31 and 49 us.  The
+// others know that a prior is one load.  Both have the priors of all the thread's cells before the first sample.
 template <int TY, bool kFirst>
 __global__ __launch_bounds__(kTileThreads, 8) void k_flow_tile(int tiles_x, int tiles_y, int n, int h, int w, int ch, int cw, int first_mode,
                                                                FlowWeights fw, FlowBatch f) {
@@ -850,11 +865,31 @@ __global__ __launch_bounds__(kTileThreads, 8) void k_flow_tile(int tiles_x, int 
     float2* __restrict__ d_out = fr.d_out;
     constexpr int TX = kTileX, NT = kTileThreads, RX = TX + 2 * kWinR, RY = TY + 2 * kWinR;
     constexpr int P = (RX + 3) / 4 * 4;              // row stride: the row pass reads sixteen bytes at a time
+    // With the coarser flow a block takes 40 900 bytes: still four per compute unit.
+    constexpr int CX = RX / 2 + 1, CY = RY / 2 + 1;
+    static_assert(kWinR % 2 == 1 && TX % 2 == 0 && TY % 2 == 0, "the region starts at an odd and ends at an even coordinate");
     __shared__ __align__(16) float s_in[5][RY * P];
+    __shared__ typename std::conditional<kFirst, CoarsePatch<CX, CY>, NoRide>::type s_coarse;
     __shared__ float s_w[kFirTable];
     const int tid = threadIdx.x, wave0 = tid & ~63;
     const int x0 = blk.x * TX, y0 = blk.y * TY;
     fir_table(s_w, fw);
+    if constexpr (kFirst) {
+        if (prior_mode == 1) {
+            load_coarse<NT>(s_coarse, d_in, y0 - kWinR, x0 - kWinR, ch, cw);
+            __syncthreads();
+        }
+    }
+    // priors of N pixels of a column, rows row_of(0 .. N - 1), all asked for before the first is used
+    auto priors = [&](int px, auto row_of, auto& prior) {
+        constexpr int N = sizeof(prior) / sizeof(float2);
+#pragma unroll
+        for (int k = 0; k < N; ++k) {
+            if constexpr (!kFirst) prior[k] = ld_at(d_in, pix(row_of(k), w, px));
+            else if (prior_mode == 0) prior[k] = make_float2(0.0f, 0.0f);
+            else prior[k] = transfer_from(s_coarse, y0 - kWinR, x0 - kWinR, row_of(k), px, ch, cw);
+        }
+    };
     {
         // per-cell terms at the clamped coordinate of the cell: a thread stays in its column (of 504 threads, twelve
         // rows at a time), so that only the row's coordinate changes
@@ -863,18 +898,13 @@ __global__ __launch_bounds__(kTileThreads, 8) void k_flow_tile(int tiles_x, int 
         const int gx = clampi(x0 - kWinR + rx, 0, w - 1);
         if (r0 < kRows) {
             float2 prior[kSteps];
-            if constexpr (!kFirst) {
-#pragma unroll
-                for (int k = 0; k < kSteps; ++k)
-                    prior[k] = prior_at(d_in, 2, clampi(y0 - kWinR + min(r0 + k * kRows, RY - 1), 0, h - 1), gx, w, 0, 0);
-            }
+            priors(gx, [&](int k) { return clampi(y0 - kWinR + min(r0 + k * kRows, RY - 1), 0, h - 1); }, prior);
 #pragma unroll
             for (int k = 0; k < kSteps; ++k) {
                 const int ry = r0 + k * kRows;
                 if (k == kSteps - 1 && ry >= RY) continue;
                 const int gy = clampi(y0 - kWinR + ry, 0, h - 1);
                 __builtin_amdgcn_sched_barrier(0);      // cell by cell: two interleaved need more registers than there are
-                if constexpr (kFirst) prior[k] = prior_at(d_in, prior_mode, gy, gx, w, ch, cw);
                 float t[5];
                 flow_terms(old_cell(fr.A1, fr.b1, pix(gy, w, gx)), fr.A2, fr.b2, extent, gy, gx, prior[k], t);
 #pragma unroll
@@ -891,8 +921,7 @@ __global__ __launch_bounds__(kTileThreads, 8) void k_flow_tile(int tiles_x, int 
     const int gx = x0 + tx;
     float2 dp[kFirOut];
     if (wave0 < kSolve) {
-#pragma unroll
-        for (int i = 0; i < kFirOut; ++i) dp[i] = prior_at(d_in, prior_mode, min(y0 + ty + i, h - 1), min(gx, w - 1), w, ch, cw);
+        priors(min(gx, w - 1), [&](int i) { return min(y0 + ty + i, h - 1); }, dp);
     }
     {
         // Row pass, in place: the sums stay in registers until all of the block's taps are read.  A second array
@@ -933,7 +962,8 @@ __global__ __launch_bounds__(kTileThreads, 8) void k_flow_tile(int tiles_x, int 
 // That is several times the work per pixel of a launch per update, and it pays where a level is so
 // small that its blocks, one per compute unit, leave the chip idle and an update is a chain of
 // launch, trips to memory and window passes: 84x84 18.1 -> 11.5 us for three updates (tile 16x8), 168x168
-// 18.0 -> 12.4, two frames of it 18.1 -> 14.9 (16x16), 336x336 19.2 -> 17.5 (32x16).  With more than one
+// 18.0 -> 12.4, two frames of it 18.1 -> 14.9 (16x16), 336x336 19.2 -> 17.5 (32x16); now 10.2, 11.2
+// and 17.2 (arguments in one trip, coarser flow in LDS, row passes on the matrix cores).  With more than one
 // block per compute unit it loses (168x168 x 4: 21.5 against 27).  All of that on an idle chip, one launch after
 // the other; next to kernels that fill the wave slots a block of 1024 threads waits longer for room than the three
 // launches take.  The results are the same bits (tests/test_gpu_step.py: calls of one to sixteen frames, whose levels take other
@@ -950,6 +980,7 @@ struct FusedTile {
     alignas(16) float in[kFloats];
     float2 p[SY * SX];          // priors of the first update, then of the third
     float2 q[PY * PX];          // priors of the second update
+    CoarsePatch<SX / 2 + 1, SY / 2 + 1> coarse;
     float w[kFirTable];
 };
 
@@ -968,6 +999,13 @@ __device__ __forceinline__ void fused_update(FusedTile<TX, TY>& sh, float2* prio
     constexpr int P = (RX + 3) / 4 * 4;             // row stride: the row pass reads sixteen bytes at a time
     const int tid = threadIdx.x, wave0 = tid & ~63;
     const int ox = x0 - 5 * (kLeft + 1), oy = y0 - 5 * (kLeft + 1), h = extent.h, w = extent.w;
+    if constexpr (I == 0) {
+        static_assert(5 * kFusedUpdates % 2 == 1 && TX % 2 == 0 && TY % 2 == 0, "the region starts at an odd and ends at an even coordinate");
+        if (prior_mode == 1) {
+            load_coarse<NT>(sh.coarse, f.d_in, oy, ox, ch, cw);
+            __syncthreads();
+        }
+    }
     {
         // a thread stays in its column, kRows rows at a time, and asks for all that does not depend on the prior first, then
         // for the priors of all its cells
@@ -980,14 +1018,14 @@ __device__ __forceinline__ void fused_update(FusedTile<TX, TY>& sh, float2* prio
 #pragma unroll
             for (int k = 0; k < kSteps; ++k)
                 old[k] = old_cell(f.A1, f.b1, pix(clampi(oy + min(r0 + k * kRows, RY - 1), 0, h - 1), w, gx));
-            auto priors = [&](auto of) {
+            auto row = [&](int k) { return clampi(oy + min(r0 + k * kRows, RY - 1), 0, h - 1); };
 #pragma unroll
-                for (int k = 0; k < kSteps; ++k) dp[k] = of(clampi(oy + min(r0 + k * kRows, RY - 1), 0, h - 1));
-            };
-            if constexpr (I > 0) priors([&](int gy) { return prior[(gy - oy) * RX + (gx - ox)]; });   // in the region: the tile meets the image
-            else if (prior_mode == 0) priors([](int) { return make_float2(0.0f, 0.0f); });
-            else if (prior_mode == 1) priors([&](int gy) { return transfer_at(f.d_in, gy, gx, ch, cw); });
-            else priors([&](int gy) { return ld_at(f.d_in, pix(gy, w, gx)); });
+            for (int k = 0; k < kSteps; ++k) {
+                if constexpr (I > 0) dp[k] = prior[(row(k) - oy) * RX + (gx - ox)];     // in the region: the tile meets the image
+                else if (prior_mode == 0) dp[k] = make_float2(0.0f, 0.0f);
+                else if (prior_mode == 1) dp[k] = transfer_from(sh.coarse, oy, ox, row(k), gx, ch, cw);
+                else dp[k] = ld_at(f.d_in, pix(row(k), w, gx));
+            }
 #pragma unroll
             for (int k = 0; k < kSteps; ++k) {
                 const int ry = r0 + k * kRows;
