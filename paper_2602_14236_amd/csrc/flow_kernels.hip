@@ -33,7 +33,8 @@ namespace sali {
 namespace {
 
 constexpr int kT = 32;                       // tile side of the expansion kernel
-constexpr int kPR = kT + 2 * kPolyN;         // 38
+constexpr int kPR = kT + 2 * kPolyN;             // 38
+constexpr int kPW = 40;                      // row of the region in whole quads: columns x0 - 4 .. x0 + 35
 
 // Element i of an array whose base is uniform over the wave: base + 32-bit byte offset (an image level
 // has fewer than 2^28 pixels, so i * 16 fits), which the hardware adds itself; with 64-bit indices a
@@ -44,6 +45,15 @@ __device__ __forceinline__ V ld_at(const V* __restrict__ base, uint32_t i) {
 }
 __device__ __forceinline__ uint32_t pix(int y, int w, int x) {          // y * w + x, both factors below 2^24
     return __umul24((uint32_t)y, (uint32_t)w) + (uint32_t)x;
+}
+
+// v / kDiv, correctly rounded, for whole v from 0 to kDiv (255 and 65280: every value checked): the product with the rounded reciprocal,
+// corrected by its remainder
+template <int kDiv>
+__device__ __forceinline__ float whole_over(uint32_t v) {
+    constexpr float kInv = 1.0f / kDiv;
+    const float x = (float)v, q = x * kInv;
+    return __builtin_fmaf(__builtin_fmaf(-(float)kDiv, q, x), kInv, q);
 }
 
 }  // namespace
@@ -170,12 +180,35 @@ __global__ __launch_bounds__(256) void k_pyr_pair(int tiles_x, int tiles_y, int 
 // equations decouple:  b = (sx, sy) / m2,  A_xx = (sxx - m2 s0) / (m4 - m2^2),  A_yy likewise,
 // A_xy = sxy / (2 m2^2), where s* are the weighted correlations of f with 1, x, y, x^2, y^2, xy.
 //
+// Bound by the vector ALU, then by its writes (20 bytes a pixel): two 1920x1080 frames of five levels 26.5 us, 4.1 TB/s.  Cell by cell, with
+// clamped coordinates, byte loads, a division each and 28 instructions a moment (values under the symmetric weights are now summed and subtracted
+// in pairs first): 31.6.
+//
 // The launch that completes the expansions may carry the saliency pre-pass of its frames (Ride = PrepRide): blocks
 // 0 .. ride.blocks - 1, so that these, the longest, start first.  Neither needs anything of the other.
 namespace {
 struct PolyexpShared {
-    float f[kPR][kPR], v[3][kT][kPR];
+    __attribute__((aligned(16))) float f[kPR][kPW], v[3][kT][kPW];
 };
+// the moments of seven values under the symmetric weights, from their sums and differences in pairs
+struct PolyTaps {
+    float g[4], kg[4], kkg[4];      // g_k, k g_k, k^2 g_k
+};
+__device__ __forceinline__ PolyTaps poly_taps(const FlowWeights& fw) {
+    PolyTaps t;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        t.g[k] = fw.poly_g[kPolyN + k];
+        t.kg[k] = t.g[k] * (float)k;
+        t.kkg[k] = t.g[k] * (float)(k * k);
+    }
+    return t;
+}
+__device__ __forceinline__ float moment0(const PolyTaps& t, float f0, const float (&sum)[3]) {
+    return t.g[0] * f0 + t.g[1] * sum[0] + t.g[2] * sum[1] + t.g[3] * sum[2];
+}
+__device__ __forceinline__ float moment1(const PolyTaps& t, const float (&diff)[3]) { return t.kg[1] * diff[0] + t.kg[2] * diff[1] + t.kg[3] * diff[2]; }
+__device__ __forceinline__ float moment2(const PolyTaps& t, const float (&sum)[3]) { return t.kkg[1] * sum[0] + t.kkg[2] * sum[1] + t.kkg[3] * sum[2]; }
 // LDS of a block that is either kind
 template <typename Own, typename Ride>
 struct WithPrep {
@@ -221,66 +254,109 @@ __global__ __launch_bounds__(256) void k_polyexp(int riders, int per_frame, Leve
     float4* __restrict__ A_out = fr.A;
     float* __restrict__ b_out = fr.b;
     together(y8, pyr, A_out, b_out);
-    // unpadded rows: the passes that write and read these arrays column-wise address them linearly
-    // in the thread index (with a pad of one float, a group of 32 lanes that straddles two rows has
-    // two lanes on one bank: 23 % of the kernel's LDS cycles were bank conflicts)
-    float (&s_f)[kPR][kPR] = sh.own.f;
-    float (&s_v)[3][kT][kPR] = sh.own.v;
+    float (&s_f)[kPR][kPW] = sh.own.f;
+    float (&s_v)[3][kT][kPW] = sh.own.v;
 
     int lvl = 0;
-    while (lvl + 1 < g.levels && tile >= g.tile_start[lvl + 1]) ++lvl;
+#pragma unroll
+    for (int l = 1; l < kMaxLevels; ++l) lvl += l < g.levels && tile >= g.tile_start[l] ? 1 : 0;
     const int h = g.h[lvl], w = g.w[lvl];
-    together(h, w, g.tile_start[lvl], g.tiles_x[lvl], g.off[lvl]);
-    const int t = tile - g.tile_start[lvl];
-    const int x0 = (t % g.tiles_x[lvl]) * kT, y0 = (t / g.tiles_x[lvl]) * kT;
-    const float* src = pyr + g.off[lvl];
+    const int first = g.tile_start[lvl], tiles_x = g.tiles_x[lvl];
+    const int64_t level_off = g.off[lvl];
+    together(h, w, first, tiles_x, level_off);
+    const int t = tile - first;
+    const int x0 = (t % tiles_x) * kT, y0 = (t / tiles_x) * kT;
+    const float* src = pyr + level_off;
     const int tid = threadIdx.x;
 
-    for (int p = tid; p < kPR * kPR; p += 256) {
-        const int ry = p / kPR, rx = p % kPR;
-        const int gy = clampi(y0 - kPolyN + ry, 0, h - 1), gx = clampi(x0 - kPolyN + rx, 0, w - 1);
-        const size_t gi = (size_t)gy * w + gx;
-        s_f[ry][rx] = (lvl == 0) ? (float)y8[gi] / 255.0f : src[gi];
+    // The region, a quad of columns at a time: 38 rows of ten.  Out-of-image cells hold the value at the clamped coordinate, which is exactly
+    // what a replicate-border stencil centred on an in-image pixel reads.
+    constexpr int kQuads = kPW / 4, kItems = kPR * kQuads, kN = (kItems + 255) / 256;
+    auto region = [&](auto quad_at) {
+#pragma unroll
+        for (int k = 0; k < kN; ++k) {
+            const int p = min(tid + 256 * k, kItems - 1);               // the last ones are made again, the same
+            const int gy = clampi(y0 - kPolyN + p / kQuads, 0, h - 1), x = x0 - 4 + 4 * (p % kQuads);
+            *reinterpret_cast<float4*>(&s_f[p / kQuads][4 * (p % kQuads)]) = quad_at((size_t)gy * w, x);
+        }
+    };
+    if (lvl == 0) {
+        region([&](size_t row, int x) {
+            uint32_t q;
+            if (x >= 0 && x + 3 < w) {
+                __builtin_memcpy(&q, y8 + row + x, 4);
+            } else {
+                q = 0u;
+#pragma unroll
+                for (int i = 0; i < 4; ++i) q |= (uint32_t)y8[row + clampi(x + i, 0, w - 1)] << (8 * i);
+            }
+            return make_float4(whole_over<255>(q & 0xFFu), whole_over<255>((q >> 8) & 0xFFu), whole_over<255>((q >> 16) & 0xFFu), whole_over<255>(q >> 24));
+        });
+    } else {
+        region([&](size_t row, int x) {
+            float4 q;
+            if (x >= 0 && x + 3 < w) {
+                __builtin_memcpy(&q, src + row + x, 16);
+            } else {
+                q = make_float4(src[row + clampi(x, 0, w - 1)], src[row + clampi(x + 1, 0, w - 1)], src[row + clampi(x + 2, 0, w - 1)],
+                                src[row + clampi(x + 3, 0, w - 1)]);
+            }
+            return q;
+        });
     }
     __syncthreads();
 
-    // Out-of-image cells of the region hold the value at the clamped coordinate, which is exactly
-    // what a replicate-border stencil centred on an in-image pixel reads.  Vertical moments:
-    for (int p = tid; p < kT * kPR; p += 256) {
-        const int ty = p / kPR, rx = p % kPR;
-        float v0 = 0.0f, v1 = 0.0f, v2 = 0.0f;
+    // vertical moments: a quad of columns, two rows
+    const PolyTaps taps = poly_taps(fw);
+    for (int p = tid; p < (kT / 2) * kQuads; p += 256) {
+        const int ty = 2 * (p / kQuads), c = 4 * (p % kQuads);
+        float f[8][4];
 #pragma unroll
-        for (int k = -kPolyN; k <= kPolyN; ++k) {
-            const float f = s_f[ty + kPolyN + k][rx] * fw.poly_g[k + kPolyN];
-            v0 += f;
-            v1 += f * (float)k;
-            v2 += f * (float)(k * k);
+        for (int k = 0; k < 8; ++k) *reinterpret_cast<float4*>(f[k]) = *reinterpret_cast<const float4*>(&s_f[ty + k][c]);
+#pragma unroll
+        for (int r = 0; r < 2; ++r) {
+            float m[3][4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                float sum[3], diff[3];
+#pragma unroll
+                for (int k = 0; k < 3; ++k) {
+                    sum[k] = f[r + 4 + k][i] + f[r + 2 - k][i];
+                    diff[k] = f[r + 4 + k][i] - f[r + 2 - k][i];
+                }
+                m[0][i] = moment0(taps, f[r + 3][i], sum);
+                m[1][i] = moment1(taps, diff);
+                m[2][i] = moment2(taps, sum);
+            }
+#pragma unroll
+            for (int j = 0; j < 3; ++j) *reinterpret_cast<float4*>(&s_v[j][ty + r][c]) = make_float4(m[j][0], m[j][1], m[j][2], m[j][3]);
         }
-        s_v[0][ty][rx] = v0;
-        s_v[1][ty][rx] = v1;
-        s_v[2][ty][rx] = v2;
     }
     __syncthreads();
 
-    for (int p = tid; p < kT * kT; p += 256) {
-        const int ty = p / kT, tx = p % kT;
-        const int gy = y0 + ty, gx = x0 + tx;
-        if (gy >= h || gx >= w) continue;
-        float s0 = 0, sx = 0, sxx = 0, sy = 0, sxy = 0, syy = 0;
+    // horizontal moments and the fit: a thread's four pixels lie in a column, eight rows apart
+    const int tx = tid % kT, gx = x0 + tx;
+    if (gx >= w) return;
 #pragma unroll
-        for (int k = -kPolyN; k <= kPolyN; ++k) {
-            const float gk = fw.poly_g[k + kPolyN];
-            const float a0 = s_v[0][ty][tx + kPolyN + k] * gk;
-            const float a1 = s_v[1][ty][tx + kPolyN + k] * gk;
-            const float a2 = s_v[2][ty][tx + kPolyN + k] * gk;
-            s0 += a0;
-            sx += a0 * (float)k;
-            sxx += a0 * (float)(k * k);
-            sy += a1;
-            sxy += a1 * (float)k;
-            syy += a2;
-        }
-        const size_t gi = g.off[lvl] + (size_t)gy * w + gx;
+    for (int r = 0; r < kT / 8; ++r) {
+        const int ty = tid / kT + 8 * r, gy = y0 + ty;
+        if (gy >= h) break;
+        float v[3][7];
+#pragma unroll
+        for (int j = 0; j < 3; ++j)
+#pragma unroll
+            for (int k = 0; k < 7; ++k) v[j][k] = s_v[j][ty][tx + 1 + k];
+        float sum[3][3], diff[3][3];
+#pragma unroll
+        for (int j = 0; j < 3; ++j)
+#pragma unroll
+            for (int k = 0; k < 3; ++k) {
+                sum[j][k] = v[j][4 + k] + v[j][2 - k];
+                diff[j][k] = v[j][4 + k] - v[j][2 - k];
+            }
+        const float s0 = moment0(taps, v[0][3], sum[0]), sx = moment1(taps, diff[0]), sxx = moment2(taps, sum[0]);
+        const float sy = moment0(taps, v[1][3], sum[1]), sxy = moment1(taps, diff[1]), syy = moment0(taps, v[2][3], sum[2]);
+        const size_t gi = level_off + (size_t)gy * w + gx;
         const float axx = (sxx - fw.m2 * s0) * fw.inv_den;
         const float ayy = (syy - fw.m2 * s0) * fw.inv_den;
         const float axy = sxy * fw.inv_2m2sq;
@@ -312,15 +388,6 @@ constexpr int kEvenP = 24, kEPS = 59;
 constexpr int kEQB = 112, kEPB = 52;
 static_assert(kEvenP + (kEP + 1) / 2 <= kEPS && kEvenP >= kEP / 2, "a row holds both halves");
 static_assert(kEQB % 4 == 0 && kEQB >= (kEQ + 3) / 4 * 4 && kEPB % 4 == 0 && kEPB >= (kEP + 3) / 4 * 4, "byte rows");
-
-// v / kDiv, correctly rounded, for whole v from 0 to kDiv (255 and 65280: every value checked): the product with the rounded reciprocal,
-// corrected by its remainder
-template <int kDiv>
-__device__ __forceinline__ float whole_over(uint32_t v) {
-    constexpr float kInv = 1.0f / kDiv;
-    const float x = (float)v, q = x * kInv;
-    return __builtin_fmaf(__builtin_fmaf(-(float)kDiv, q, x), kInv, q);
-}
 
 // LDS patches that feed a pyramid stage keep the odd columns of a row in its first part and the even
 // columns from kEven on (kEven = 0: plain layout): the stage reads columns 2 * cx + {-2..2}, a stride
