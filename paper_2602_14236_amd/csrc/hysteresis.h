@@ -17,18 +17,6 @@ __device__ __forceinline__ uint32_t uf_load(const uint32_t* parent, uint32_t idx
     return __hip_atomic_load(parent + idx, __ATOMIC_RELAXED, kScope);
 }
 
-// Is the component of a weak pixel (its key) without a strong pixel?  For kernels that run after all links
-// are final: ordinary cached loads.  A strong key on the way decides; the root need not be reached.
-__device__ __forceinline__ bool uf_stays_weak(const uint32_t* __restrict__ parent, uint32_t key) {
-    uint32_t k = key;
-    while (k & kWeakBit) {
-        const uint32_t p = parent[k & ~kWeakBit];
-        if (p == k) return true;
-        k = p;
-    }
-    return false;
-}
-
 // Joins the components of two pixels as far as the classes need it: "has a strong pixel" must reach the weak
 // components; two that are strong already are not joined, and a walk ends at the first strong key, whose
 // component's root is strong (keys decrease along links and strong keys are the smaller ones).  Both walks
@@ -67,7 +55,9 @@ __device__ __forceinline__ void uf_spread_strong(uint32_t* parent, uint32_t ka, 
 __host__ __device__ inline int border_rows(int h, int w) { return ((h - 1) / kTile) * w; }
 __host__ __device__ inline int border_items(int h, int w) { return border_rows(h, w) + ((w - 1) / kTile) * h; }
 
-__device__ __forceinline__ void union_border(const uint8_t* __restrict__ cls, uint32_t* parent, int h, int w, int item) {
+// (`there`: the item exists; stop(), uniform: asked once the classes are under way, true leaves everything as it is)
+template <typename Stop>
+__device__ __forceinline__ void union_border(const uint8_t* __restrict__ cls, uint32_t* parent, int h, int w, int item, bool there, Stop stop) {
     const int n_rows = border_rows(h, w);
     const bool row = item < n_rows;
     const int i = row ? item : item - n_rows, len = row ? w : h;
@@ -82,7 +72,7 @@ __device__ __forceinline__ void union_border(const uint8_t* __restrict__ cls, ui
         c[0][j] = in ? cls[gi + (j - 1) * along] : 0;
         c[1][j] = in ? cls[gi + across + (j - 1) * along] : 0;
     }
-    if (c[0][1] == 0) return;
+    if (stop() || !there || c[0][1] == 0) return;
     const uint32_t me = (uint32_t)gi | (c[0][1] == 1 ? kWeakBit : 0u);
     // Straight across, unless the pair before makes that contact: it lies in the same two tiles, whose pixels
     // are joined in LDS (so not for the first pair of a tile: round a corner of four tiles each contact

@@ -273,6 +273,13 @@ __device__ __forceinline__ void together(const T& first, const Rest&... rest) {
 #endif
 
 #ifdef __HIPCC__
+// Element i of an array whose base is uniform over the wave: base + 32-bit byte offset (an image level
+// has fewer than 2^28 pixels, so i * 16 fits), which the hardware adds itself; with 64-bit indices a
+// quarter of the gather's vector instructions were address arithmetic.
+template <typename V>
+__device__ __forceinline__ V ld_at(const V* __restrict__ base, uint32_t i) {
+    return *reinterpret_cast<const V*>(reinterpret_cast<const char*>(base) + i * (uint32_t)sizeof(V));
+}
 __device__ __forceinline__ int clampi(int v, int lo, int hi) { return v < lo ? lo : (v > hi ? hi : v); }
 
 // Y8 of one pixel, and of four pixels in three words (bytes RGBR GBRG BRGB)

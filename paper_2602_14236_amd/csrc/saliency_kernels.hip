@@ -70,19 +70,19 @@ __global__ __launch_bounds__(NT) void k_prep(const uint32_t* __restrict__ lut_wo
 
 // hysteresis, cross-tile part; blockIdx.y = frame of the batch.  A thread per border pixel: with a thread per
 // image pixel, nearly all of them idle, and walks to the root also between strong components sixteen 640x360
-// frames took 44 us in the pipeline, one frame alone 16.8; now 23.5 and 9.6 (chains of trips past the L2).
+// frames took 44 us in the pipeline, one frame alone 16.8; then 23.5 and 10.4 (chains of trips past the L2), and 9.2 alone since the
+// frame's skip flag is asked for with an item's first loads instead of ahead of them.
 // kGated: the pre-pass ran ahead of the flow and could not ask the reuse rule; it is evaluated here, from the motions.
 template <bool kGated>
 __global__ __launch_bounds__(256) void k_union(int h, int w, int n_items, GateParams gp, PrepBatch f) {
     if constexpr (kGated) {
         __shared__ int s_cnt[4];
         if (frame_redundant<256>(f.frame, (int)blockIdx.y, gp, s_cnt)) return;
-    } else {
-        const PrepFrame& frame = f.frame[blockIdx.y];
-        together(frame.skip, frame.cls, frame.parent);
-        if (*frame.skip != 0u) return;              // redundant frame, says the pre-pass
     }
-    union_item(f, (int)blockIdx.y, h, w, (int)(blockIdx.x * 256 + threadIdx.x), n_items);
+    const PrepFrame& frame = f.frame[blockIdx.y];
+    together(frame.skip, frame.cls, frame.parent);
+    union_item(frame, h, w, (int)(blockIdx.x * 256 + threadIdx.x), n_items,
+               [&] { return !kGated && *frame.skip != 0u; });       // redundant frame, says the pre-pass
 }
 
 // Gate (Eq. 6), tier assignment and compaction indices of frame `b` of a launch of `n_frames`, by
@@ -211,6 +211,8 @@ __device__ __forceinline__ void pool_tail(TierShared& sh, int* s_cnt, const Pool
 // such a fence writes back and invalidates the issuing XCD's L2: with 144 blocks per frame it made the
 // K/V kernels running next to it 7 % slower (5 400 -> 5 700 frames/s without), and at 1920x1080 (576
 // blocks per frame) it cost the pooling kernel itself 110 us per four-frame launch against 33 us of work.
+// Bound by trips to memory, then (large frames) by the adds on each patch's many pixels: see PatchPixels and patch_sum.  Sixteen 640x360
+// frames 27.8 -> 15.2 us in the pipeline, motions of four 1920x1080 frames 12.8 -> 11.9.
 // kGated: as in k_union.
 template <int kWaves, bool kMotion, bool kGated>
 __global__ __launch_bounds__(kTierThreads) void k_pool(uint8_t* __restrict__ salmap, int h, int w, GateParams gp, PoolBatch f) {
@@ -223,23 +225,22 @@ __global__ __launch_bounds__(kTierThreads) void k_pool(uint8_t* __restrict__ sal
     constexpr int kStride = 64 * kWaves;
     if constexpr (!kMotion) {
         __shared__ uint32_t s_pq[kTierThreads / 64];
+        const PoolFrame& frame = f.frame[b];
         if constexpr (kGated) {
             __shared__ int s_cnt[kTierThreads / 64];
             if (frame_redundant<kTierThreads>(f.frame, b, gp, s_cnt)) return;
-        } else {
-            const PoolFrame& frame = f.frame[b];
-            together(frame.skip, frame.cls, frame.parent, frame.var, frame.msum, frame.scores);
-            if (*frame.skip != 0u) return;                  // redundant frame, says the pre-pass
         }
+        auto stop = [&] { return !kGated && *frame.skip != 0u; };       // redundant frame, says the pre-pass
         if constexpr (kWaves == 1) {
-            score_by_wave(f, b, token, h, w, salmap);
+            score_by_wave(frame, token, h, w, salmap, stop);
         } else {
             const PatchBox box = patch_box(token, h, w);
-            uint32_t q = patch_sum<kStride>(f, b, box, p_first, h, w, salmap);
+            uint32_t q = patch_sum<kStride>(frame, box, p_first, h, w, salmap, stop);
+            if (q == kNoSum) return;
             for (int off = 32; off > 0; off >>= 1) q += __shfl_down(q, off);
             if (lane == 0) s_pq[wave] = q;
             __syncthreads();
-            if (threadIdx.x == 0) store_score(f, b, token, s_pq[0] + s_pq[1] + s_pq[2] + s_pq[3], box.area);
+            if (threadIdx.x == 0) store_score(frame, token, s_pq[0] + s_pq[1] + s_pq[2] + s_pq[3], box.area);
         }
     } else {
         __shared__ float s_pm[kTierThreads / 64];
@@ -252,15 +253,13 @@ __global__ __launch_bounds__(kTierThreads) void k_pool(uint8_t* __restrict__ sal
             return;
         }
         const PatchBox box = patch_box(token, h, w);
+        const PatchPixels pixel(box, w);
         float mag = 0.0f;
         constexpr int kUnroll = 4;                          // four pixels per pass, their loads issued together
         for (int p0 = p_first; p0 < box.area; p0 += kStride * kUnroll) {
             float2 d[kUnroll];
 #pragma unroll
-            for (int u = 0; u < kUnroll; ++u) {
-                const int pp = p0 + u * kStride < box.area ? p0 + u * kStride : 0;
-                d[u] = flow[(size_t)(box.ya + pp / box.pw) * w + (box.xa + pp % box.pw)];
-            }
+            for (int u = 0; u < kUnroll; ++u) d[u] = ld_at(flow, pixel(min(p0 + u * kStride, box.area - 1)));
 #pragma unroll
             for (int u = 0; u < kUnroll; ++u)
                 if (p0 + u * kStride < box.area) mag += d[u].x * d[u].x + d[u].y * d[u].y;
