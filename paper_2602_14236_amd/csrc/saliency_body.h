@@ -56,8 +56,9 @@ __device__ __forceinline__ bool frame_redundant(const Frame* frames, int b, cons
 // A block per 32x32 tile: 256 threads in the chained step, so that blocks find room on compute units that a bandwidth
 // kernel of another stream keeps busy; 512 or 1024 in the stand-alone call and where it rides on blocks of that size.
 //
-// Four 1920x1080 frames: 107 us, one 640x360 frame: 16 (11 on 1024 threads); bound by the trips of a block's stages (image and tables
-// from memory, then LDS; 20 waves per compute unit), the vector ALU 61 % busy.  Taken tap by tap, byte
+// Four 1920x1080 frames: 97 us (103 before the last instructions were taken out), sixteen 640x360 frames 37 (40.6), one 10.3 on 1024
+// threads; bound by the vector ALU (76 % of the cycles of a busy compute unit, 288 instructions a pixel; the LDS 37 %), then by the trips of
+// a block's stages (image and tables from memory, then LDS; seven blocks per compute unit).  Taken tap by tap, byte
 // by byte, with clamped coordinates, the stencils were 612 instructions per pixel instead of 305, the ALU
 // 90 % busy, and the kernel took 150 and 24 us.  So each
 // stage takes strips of four pixels as words: byte dot products along rows, packed 16-bit arithmetic down
@@ -86,22 +87,25 @@ struct PrepShared {
             uint2 s[3][kRegB][kTile / 4];
         } var;
     };
-    // gray image and its row sums; from the hysteresis on the tile's union-find links (key = local index | weak bit)
+    // gray image and its row sums, then the blurred image in place of the gray one; from the hysteresis on the tile's union-find
+    // links (key = local index | weak bit)
     union {
         struct {
-            uint32_t y[kReg][kQuadsY];
+            union {
+                uint32_t y[kReg][kQuadsY];
+                uint32_t b[kRegB][kStripsB];
+                uint8_t b8[kRegB][kRegB];
+            };
             uint2 h[kReg][kStripsB];
         } gray;
         uint32_t lbl[kTile * kTile];
     };
-    // blurred image
+    // LAB values; once their row sums are taken the gradients, (gx, gy) as 16-bit halves
     union {
-        uint32_t b[kRegB][kStripsB];
-        uint8_t b8[kRegB][kRegB];
+        __attribute__((aligned(16))) uint8_t lab[3][kRegB][kRegB];
+        __attribute__((aligned(16))) uint32_t grad[kRegM][kGradW];
     };
-    __attribute__((aligned(16))) uint32_t grad[kRegM][kGradW];      // (gx, gy) as 16-bit halves
-    __attribute__((aligned(16))) uint8_t lab[3][kRegB][kRegB];
-    unsigned long long sum[kPrepMaxThreads / 64];
+    uint32_t sum[kPrepMaxThreads / 32];
     int gate[kPrepMaxThreads / 64];
     uint32_t row[kTile];        // a tile row's edge candidates, a bit each
     uint32_t n_contacts;
@@ -111,6 +115,9 @@ struct PrepShared {
 __device__ __forceinline__ short2_t byte_pair(uint32_t lo, uint32_t hi, int i) {
     const uint32_t sel = 0x0c000c00u | (uint32_t)i | ((uint32_t)(i + 1) << 16);
     return __builtin_bit_cast(short2_t, __builtin_amdgcn_perm(hi, lo, sel));
+}
+__device__ __forceinline__ uint32_t dot2(uint32_t a, uint32_t b, uint32_t c) {
+    return __builtin_amdgcn_udot2(__builtin_bit_cast(ushort2_t, a), __builtin_bit_cast(ushort2_t, b), c, false);
 }
 __device__ __forceinline__ int grad_m2(uint32_t g) {
     const short2_t v = __builtin_bit_cast(short2_t, g);
@@ -148,7 +155,7 @@ __device__ __forceinline__ void prep_tile(PrepShared& sh, const PrepBatch& f, in
     for (int k = 0; k < kPrepQuads; ++k) {
         const int p = min(tid + k * NT, kReg * kQuadsY - 1);
         const int x = x0 - kHalo + 4 * (p % kQuadsY);
-        load_rgb_quad(rgb + (size_t)clampi(y0 - kHalo + p / kQuadsY, 0, h - 1) * w * 3, x, w, crgb[k]);
+        load_rgb_quad(rgb + __umul24((uint32_t)clampi(y0 - kHalo + p / kQuadsY, 0, h - 1), 3u * (uint32_t)w), x, w, crgb[k]);
     }
     u32x4 lut[kLutQuads];
 #pragma unroll
@@ -185,18 +192,30 @@ __device__ __forceinline__ void prep_tile(PrepShared& sh, const PrepBatch& f, in
             const int p = tid + k * NT;
             const int ry = p / kQuadsY - 2, quad = p % kQuadsY;          // row of the region, cells 4 quad - 2 ..
             if (ry < 0 || ry >= kRegB) continue;
-            uint32_t lab[3] = {0u, 0u, 0u};                              // four pixels, a byte each
+            // four pixels: L a byte each; a and b in 16.16, the whole part a half each, clamped and packed by pairs
+            uint32_t lab[3] = {0u, 0u, 0u};
+            int ab[2][4];
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
                 auto byte = [&](int j) { return (crgb[k][j >> 2] >> (8 * (j & 3))) & 0xFFu; };
-                const int lr = s_lin[byte(3 * i)], lg = s_lin[byte(3 * i + 1)], lb = s_lin[byte(3 * i + 2)];
-                const int tx = (1777 * lr + 1541 * lg + 778 * lb + 2048) >> 12;
-                const int ty = (871 * lr + 2929 * lg + 296 * lb + 2048) >> 12;
-                const int tz = (73 * lr + 448 * lg + 3575 * lb + 2048) >> 12;
+                const uint32_t rg = (uint32_t)s_lin[byte(3 * i)] | ((uint32_t)s_lin[byte(3 * i + 1)] << 16), lb = s_lin[byte(3 * i + 2)];
+                auto row = [&](uint32_t of_r, uint32_t of_g, uint32_t of_b) {
+                    return dot2(rg, of_r | (of_g << 16), __umul24(lb, of_b) + 2048u) >> 12;
+                };
+                const uint32_t tx = row(1777u, 1541u, 778u), ty = row(871u, 2929u, 296u), tz = row(73u, 448u, 3575u);
                 const int fx = s_fl[tx], fy = s_fl[ty], fz = s_fl[tz];
                 lab[0] |= (uint32_t)s_l8[ty] << (8 * i);
-                lab[1] |= (uint32_t)clampi((500 * (fx - fy) + 4194304 + 16384) >> 15, 0, 255) << (8 * i);
-                lab[2] |= (uint32_t)clampi((200 * (fy - fz) + 4194304 + 16384) >> 15, 0, 255) << (8 * i);
+                ab[0][i] = __mul24(1000, fx - fy) + 2 * (4194304 + 16384);
+                ab[1][i] = __mul24(400, fy - fz) + 2 * (4194304 + 16384);
+            }
+#pragma unroll
+            for (int c = 0; c < 2; ++c) {
+                const short2_t none = {0, 0}, all = {255, 255};
+                auto whole = [&](int i) {
+                    const short2_t v = __builtin_bit_cast(short2_t, __builtin_amdgcn_perm((uint32_t)ab[c][i + 1], (uint32_t)ab[c][i], 0x07060302u));
+                    return __builtin_bit_cast(uint32_t, __builtin_elementwise_min(__builtin_elementwise_max(v, none), all));
+                };
+                lab[1 + c] = __builtin_amdgcn_perm(whole(2), whole(0), 0x06040200u);
             }
 #pragma unroll
             for (int c = 0; c < 3; ++c) {
@@ -232,7 +251,7 @@ __device__ __forceinline__ void prep_tile(PrepShared& sh, const PrepBatch& f, in
             return __builtin_bit_cast(uint32_t, (ushort2_t)(sum >> eight));
         };
         const uint32_t lo = column(r[0].x, r[1].x, r[2].x, r[3].x, r[4].x), hi = column(r[0].y, r[1].y, r[2].y, r[3].y, r[4].y);
-        sh.b[ry][sx] = __builtin_amdgcn_perm(hi, lo, 0x06040200u);
+        sh.gray.b[ry][sx] = __builtin_amdgcn_perm(hi, lo, 0x06040200u);
     }
     // stage 4a: colour variance, 25 * sum v^2 - (sum v)^2 over 5x5 per channel: sums over the five cells of a row
     // (the tables are done with: their memory holds these)
@@ -261,7 +280,7 @@ __device__ __forceinline__ void prep_tile(PrepShared& sh, const PrepBatch& f, in
         for (int p = tid; p < kRegB * kRegB; p += NT) {
             const int ry = p / kRegB, rx = p % kRegB;
             const int cy = clampi(y0 - 2 + ry, 0, h - 1) - (y0 - 2), cx = clampi(x0 - 2 + rx, 0, w - 1) - (x0 - 2);
-            if (cy != ry || cx != rx) sh.b8[ry][rx] = sh.b8[cy][cx];
+            if (cy != ry || cx != rx) sh.gray.b8[ry][rx] = sh.gray.b8[cy][cx];
         }
         __syncthreads();
     }
@@ -274,7 +293,7 @@ __device__ __forceinline__ void prep_tile(PrepShared& sh, const PrepBatch& f, in
         short2_t d[3][2], sm[3][2];
 #pragma unroll
         for (int a = 0; a < 3; ++a) {
-            const uint32_t w0 = sh.b[ry + a][sx], w1 = sx + 1 < kStripsB ? sh.b[ry + a][sx + 1] : 0u;
+            const uint32_t w0 = sh.gray.b[ry + a][sx], w1 = sx + 1 < kStripsB ? sh.gray.b[ry + a][sx + 1] : 0u;
             const short2_t two = {2, 2};
             const short2_t p01 = byte_pair(w0, w1, 0), p12 = byte_pair(w0, w1, 1), p23 = byte_pair(w0, w1, 2),
                            p34 = byte_pair(w0, w1, 3), p45 = byte_pair(w0, w1, 4);
@@ -302,7 +321,7 @@ __device__ __forceinline__ void prep_tile(PrepShared& sh, const PrepBatch& f, in
         *reinterpret_cast<uint4*>(&sh.grad[ry][4 * sx]) = make_uint4(g[0], g[1], g[2], g[3]);
     }
     // stage 4b: the variance of four pixels from five rows of sums
-    unsigned long long local_sum = 0ull;
+    uint32_t local_sum = 0u;                                            // 30 431 700 a pixel at most: half a wave's stay below 2^32
     if (tid < kTile * kTile / 4) {
         const int vy = tid >> 3, sx = tid & 7;
         const int gy = y0 + vy, gx0 = x0 + 4 * sx;
@@ -334,10 +353,10 @@ __device__ __forceinline__ void prep_tile(PrepShared& sh, const PrepBatch& f, in
             v[i] = t;
         }
         if (gy < h) {
-            uint32_t* dst = var_out + (size_t)gy * w + gx0;
+            uint32_t* dst = var_out + (__umul24((uint32_t)gy, (uint32_t)w) + (uint32_t)gx0);
             if (gx0 + 3 < w && (w & 3) == 0) {
                 *reinterpret_cast<uint4*>(dst) = make_uint4(v[0], v[1], v[2], v[3]);
-                local_sum += (unsigned long long)v[0] + v[1] + v[2] + v[3];
+                local_sum += v[0] + v[1] + v[2] + v[3];
             } else {
 #pragma unroll
                 for (int i = 0; i < 4; ++i)
@@ -348,13 +367,13 @@ __device__ __forceinline__ void prep_tile(PrepShared& sh, const PrepBatch& f, in
             }
         }
     }
-    for (int off = 32; off > 0; off >>= 1) local_sum += __shfl_down(local_sum, off);
-    if ((tid & 63) == 0) sh.sum[tid >> 6] = local_sum;
+    for (int off = 16; off > 0; off >>= 1) local_sum += __shfl_down(local_sum, off);
+    if ((tid & 31) == 0) sh.sum[tid >> 5] = local_sum;
     __syncthreads();
     // block sum of V -> one atomic
     if (tid == 0) {
         unsigned long long t = 0ull;
-        for (int k = 0; k < NT / 64; ++k) t += sh.sum[k];
+        for (int k = 0; k < NT / 32; ++k) t += sh.sum[k];
         atomicAdd(msum_acc, t);
     }
 
@@ -362,6 +381,7 @@ __device__ __forceinline__ void prep_tile(PrepShared& sh, const PrepBatch& f, in
     // p = tid + NT q sits in tile row p / 32, so a wave always holds two complete tile rows.
     const int tx = tid % kTile;
     const int gx = x0 + tx;
+    const uint32_t pixel0 = __umul24((uint32_t)(y0 + tid / kTile), (uint32_t)w) + (uint32_t)gx;      // its first pixel, in the image
     int cls[kPrepPx];
 #pragma unroll
     for (int q = 0; q < kPrepPx; ++q) {
@@ -370,19 +390,19 @@ __device__ __forceinline__ void prep_tile(PrepShared& sh, const PrepBatch& f, in
         cls[q] = 0;
         if (gy < h && gx < w) {
             const uint32_t* at = &sh.grad[ty + 1][tx + 1];
-            const short2_t v = __builtin_bit_cast(short2_t, *at);
-            const int sgx = v.x, sgy = v.y;
-            const int xx = __mul24(sgx, sgx), yy = __mul24(sgy, sgy), m2 = xx + yy;
-            const int ax = abs(sgx), ay = abs(sgy);
-            const int s2 = __mul24(ax + ay, ax + ay);
+            const uint32_t g = *at;
+            const short2_t v = __builtin_bit_cast(short2_t, g);
+            const int sgx = v.x, sgy = v.y, m2 = grad_m2(g);
+            // the sector: (|gx| + |gy|)^2 against 2 gx^2 and 2 gy^2, both sides less |g|^2
+            const int cross = 2 * __mul24(sgx, sgy), diff = m2 - 2 * __mul24(sgy, sgy), size = max(cross, -cross);
             int step;                         // first-listed neighbour; the second is its mirror
-            if (s2 < 2 * xx) step = -1;
-            else if (s2 < 2 * yy) step = -kGradW;
-            else if (__mul24(sgx, sgy) > 0) step = -kGradW - 1;
+            if (size < diff) step = -1;
+            else if (size < -diff) step = -kGradW;
+            else if (cross > 0) step = -kGradW - 1;
             else step = -kGradW + 1;
             const int n1 = grad_m2(at[step]), n2 = grad_m2(at[-step]);
             if (m2 > n1 && m2 >= n2) cls[q] = m2 >= hi2 ? 2 : (m2 >= lo2 ? 1 : 0);
-            cls_out[(size_t)gy * w + gx] = (uint8_t)cls[q];
+            cls_out[pixel0 + (uint32_t)(q * (NT / kTile)) * (uint32_t)w] = (uint8_t)cls[q];
         }
     }
 
@@ -403,16 +423,14 @@ __device__ __forceinline__ void prep_tile(PrepShared& sh, const PrepBatch& f, in
         head_key[q] = (uint32_t)p | (cls[q] == 1 ? kWeakBit : 0u);
         left_is_cand[q] = false;
         if (cls[q] != 0) {
-            const uint32_t zeros = ~row_c;
-            const uint32_t below = zeros & ((1u << tx) - 1u);
-            const uint32_t above = (tx == 31) ? 0u : (zeros & ~((2u << tx) - 1u));
-            const int start = below == 0u ? 0 : 32 - __builtin_clz(below);
-            const int end = above == 0u ? 31 : __builtin_ctz(above) - 1;
-            const uint32_t run = (end == 31 ? 0xFFFFFFFFu : ((2u << end) - 1u)) & ~((1u << start) - 1u);
-            const uint32_t strong_in_run = row_s & run;
-            head_key[q] = strong_in_run != 0u ? (uint32_t)(ty * kTile + __builtin_ctz(strong_in_run))
-                                              : ((uint32_t)(ty * kTile + start) | kWeakBit);
-            left_is_cand[q] = tx > 0 && ((row_c >> (tx - 1)) & 1u) != 0u;
+            // candidates from this pixel to the left and to the right, itself among them; then the run's first strong pixel
+            const uint32_t gaps_left = ~(row_c << (31 - tx)), gaps_right = ~(row_c >> tx);
+            const int left = gaps_left == 0u ? 32 : __builtin_clz(gaps_left), right = gaps_right == 0u ? 32 : __builtin_ctz(gaps_right);
+            const int start = tx + 1 - left;
+            const uint32_t strong = row_s >> start;
+            const int first = strong == 0u ? 32 : __builtin_ctz(strong);
+            head_key[q] = (uint32_t)(ty * kTile + start) + (first < left + right - 1 ? (uint32_t)first : kWeakBit);
+            left_is_cand[q] = left > 1;
         }
         s_lbl[p] = head_key[q];
         if (tx == 0) sh.row[ty] = row_c;
@@ -454,7 +472,7 @@ __device__ __forceinline__ void prep_tile(PrepShared& sh, const PrepBatch& f, in
 #pragma unroll
             for (int side = 0; side < 2; ++side) {
                 if (want[q][side]) {
-                    const uint32_t at = first + (uint32_t)__popcll(m[q][side] & ~(~0ull << (tid & 63)));
+                    const uint32_t at = __builtin_amdgcn_mbcnt_hi((uint32_t)(m[q][side] >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m[q][side], first));
                     auto pack = [](uint32_t key) { return (key & 0x3FFu) | (key >> 21 & 0x400u); };
                     sh.contact[at] = pack(head_key[q]) | (pack(other[q][side]) << 16);
                 }
@@ -495,8 +513,8 @@ __device__ __forceinline__ void prep_tile(PrepShared& sh, const PrepBatch& f, in
         const int ty = (tid + q * NT) / kTile;
         if (y0 + ty >= h || gx >= w) continue;
         const uint32_t rl = root[q] & ~kWeakBit;
-        const size_t rg = (size_t)(y0 + (int)(rl / kTile)) * w + (x0 + (int)(rl % kTile));
-        parent_out[(size_t)(y0 + ty) * w + gx] = (uint32_t)rg | (root[q] & kWeakBit);
+        const uint32_t rg = __umul24((uint32_t)y0 + rl / kTile, (uint32_t)w) + (uint32_t)x0 + rl % kTile;
+        parent_out[pixel0 + (uint32_t)(q * (NT / kTile)) * (uint32_t)w] = rg | (root[q] & kWeakBit);
     }
 }
 
