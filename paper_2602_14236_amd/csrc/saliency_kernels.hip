@@ -90,22 +90,34 @@ __global__ __launch_bounds__(256) void k_union(int h, int w, int n_items, GatePa
 // n_static = #{dP_i < tau_t}, R = n_static / 576, redundant iff R > theta_R; a frame without
 // predecessor (no flow) is never redundant.  The last such block of the launch (arrival counter,
 // nobody waits) writes the frame-table rows and advances the pool cursors in video order.
+// Bound by the trips of a single chain: arguments, scores and motions, ranking, hand-over, rows.  The hand-over records are written and
+// read past the caches that the compute dies do not share and a block counts itself in when its own has arrived, so it needs no
+// device-scope fence (two of them, an L2 written back and one given up).
 __device__ __forceinline__ void pool_tail(TierShared& sh, int* s_cnt, const PoolBatch& f, int b, int n_frames,
                                           float tau_t, float theta_r, const TierLaunch& tl, uint32_t* batch_done) {
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
     // gate: n_static = #{dP_i < tau_t}, R = n_static / 576, redundant iff R > theta_R; a frame
     // without predecessor (no flow) is never redundant
-    const bool have_flow = f.frame[b].flow != nullptr;
+    const PoolFrame& frame = f.frame[b];
+    const float* const scores_of = frame.scores;
+    const float* const dp = frame.dp;
+    const bool have_flow = frame.flow != nullptr;
+    together(scores_of, dp, frame.flow, frame.gate, frame.tcounts);
     // the scores are asked for now, with the patch motions: one memory round trip instead of two on the
     // critical path of the batch (a redundant frame does not use them)
-    const TierScores scores = tier_load_scores(f.frame[b].scores);
+    const TierScores scores = tier_load_scores(scores_of);
+    CursorRegs cr = {};                 // of the block that turns out to be the last: nobody else moves them
+    if (threadIdx.x == 0) cr = cursor_load(tl.cur);
     // a tiled frame's patches are those of all its tiles (entries b0 .. b0 + tiles - 1 of the launch): the
     // block of every tile counts them all and so reaches the frame's one decision on its own
     const int tiles = tl.tiles;
-    const int b0 = b - b % tiles;
     int n = 0;
-    if (have_flow)
+    if (have_flow && tiles == 1) {
+        n = count_static<kTierThreads>(dp, tau_t);
+    } else if (have_flow) {
+        const int b0 = b - b % tiles;
         for (int j = 0; j < tiles; ++j) n += count_static<kTierThreads>(f.frame[b0 + j].dp, tau_t);
+    }
     for (int off = 32; off > 0; off >>= 1) n += __shfl_down(n, off);
     if (lane == 0) s_cnt[wave] = n;
     __syncthreads();
@@ -124,8 +136,8 @@ __device__ __forceinline__ void pool_tail(TierShared& sh, int* s_cnt, const Pool
         gt.r_frame = have_flow ? r : 0.0f;
         gt.redundant = redundant ? 1 : 0;
         gt.reserved = 0;
-        *f.frame[b].gate = gt;
-        int32_t* out = reinterpret_cast<int32_t*>(f.frame[b].tcounts);
+        *frame.gate = gt;
+        int32_t* out = reinterpret_cast<int32_t*>(frame.tcounts);
         __hip_atomic_store(out + 0, tc.state, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 #pragma unroll
         for (int t = 0; t < 4; ++t)
@@ -133,11 +145,11 @@ __device__ __forceinline__ void pool_tail(TierShared& sh, int* s_cnt, const Pool
 #pragma unroll
         for (int j = 0; j < 3; ++j)
             __hip_atomic_store(out + 5 + j, tc.q[j], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        __threadfence();                // counts, tiers, slots and order lists before the arrival
-        const bool last = atomicAdd(batch_done, 1u) == (uint32_t)n_frames - 1u;
-        if (last) {
-            __threadfence();
-            *batch_done = 0u;
+        bool last = n_frames == 1;
+        if (!last) {
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");        // the record has arrived
+            last = __hip_atomic_fetch_add(batch_done, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == (uint32_t)n_frames - 1u;
+            if (last) __hip_atomic_store(batch_done, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         }
         s_cnt[0] = last ? 1 : 0;
     }
@@ -149,7 +161,9 @@ __device__ __forceinline__ void pool_tail(TierShared& sh, int* s_cnt, const Pool
         // code than this one wave should have to fetch
         TierCounts* all = reinterpret_cast<TierCounts*>(&sh);
         static_assert(sizeof(TierCounts) * kMaxBatch <= sizeof(TierShared), "records fit the ranking's memory");
-        if ((int)threadIdx.x < n_frames) {
+        if (n_frames == 1) {
+            if (threadIdx.x == 0) all[0] = tc;
+        } else if ((int)threadIdx.x < n_frames) {
             const int32_t* in = reinterpret_cast<const int32_t*>(f.frame[threadIdx.x].tcounts);
             TierCounts rec = {};
             rec.state = __hip_atomic_load(in + 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -157,8 +171,6 @@ __device__ __forceinline__ void pool_tail(TierShared& sh, int* s_cnt, const Pool
             for (int t = 0; t < 4; ++t) rec.cnt[t] = __hip_atomic_load(in + 1 + t, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             all[threadIdx.x] = rec;
         }
-        CursorRegs cr = {};
-        if (threadIdx.x == 0) cr = cursor_load(tl.cur);
         __syncthreads();
         if (threadIdx.x != 0) return;
 #pragma unroll 1
@@ -171,8 +183,6 @@ __device__ __forceinline__ void pool_tail(TierShared& sh, int* s_cnt, const Pool
     // Adaptive thresholds: the ranking above gave each frame's quantiles; its tiers depend on the
     // thresholds the frame before it left, so this block assigns them frame by frame (576 compares and
     // the compaction indices per frame, the whole block) and thread 0 commits and moves the thresholds.
-    CursorRegs cr = {};
-    if (threadIdx.x == 0) cr = cursor_load(tl.cur);
     if (threadIdx.x < 3) sh.tau[threadIdx.x] = tl.cur->adapt_tau[threadIdx.x];
     __syncthreads();
     for (int i = 0; i < n_frames; ++i) {
@@ -275,11 +285,17 @@ __global__ __launch_bounds__(kTierThreads) void k_pool(uint8_t* __restrict__ sal
     }
 }
 
-// the tail as a launch of its own: one block per frame
+// the tail as a launch of its own: one block per frame.  A kernel per tier mode and with or without a budget: a few blocks run this code
+// once, after kernels that left nothing of it in the instruction caches.  Of one kernel for all (scratch for the budget's call, scalar
+// registers spilled) with fences at the hand-over one frame by thresholds took 4.1 us and takes 2.8; by counts four took 14.5 and take 13.2,
+// sixteen 19.0 and 16.2.
+template <int kMode, bool kBudget>
 __global__ __launch_bounds__(kTierThreads) void k_pool_tail(uint32_t* batch_done, float tau_t, float theta_r, TierLaunch tl,
                                                             PoolBatch f) {
     __shared__ TierShared sh;
     __shared__ int s_cnt[kTierThreads / 64];
+    tl.tp.mode = kMode;
+    if constexpr (!kBudget) tl.budget = 0;
     pool_tail(sh, s_cnt, f, (int)blockIdx.x, (int)gridDim.x, tau_t, theta_r, tl, batch_done);
 }
 
@@ -339,7 +355,11 @@ hipError_t launch_scores(const PoolBatch& f, int n, int h, int w, uint8_t* d_sal
 
 hipError_t launch_tail(const PoolBatch& f, int n, const TierLaunch& tier, GateParams gp, uint32_t* d_done_counter,
                        hipEvent_t done_or_null, hipStream_t s) {
-    launch_recording(done_or_null, k_pool_tail, dim3(n), dim3(kTierThreads), s, d_done_counter, gp.tau_t, gp.theta_r, tier, f);
+    const bool budget = tier.budget > 0;
+    auto* const kernel = tier.tp.mode == 0 ? (budget ? k_pool_tail<0, true> : k_pool_tail<0, false>)
+                         : tier.tp.mode == 1 ? (budget ? k_pool_tail<1, true> : k_pool_tail<1, false>)
+                                             : (budget ? k_pool_tail<2, true> : k_pool_tail<2, false>);
+    launch_recording(done_or_null, kernel, dim3(n), dim3(kTierThreads), s, d_done_counter, gp.tau_t, gp.theta_r, tier, f);
     return hipGetLastError();
 }
 

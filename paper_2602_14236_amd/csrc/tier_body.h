@@ -28,7 +28,7 @@ struct TierCounts {
 
 struct TierShared {
     uint32_t key[kTokens];          // order-preserving integer image of the scores
-    int group_cnt[kTierGroups][4];
+    __attribute__((aligned(16))) int group_cnt[kTierGroups][4];
     unsigned long long taken[3][kTierGroups];       // top-k counts: tokens of rank below each cutoff, a bit each
     int nan_flag;
     int q[3];                       // adaptive thresholds: quantiles found by the ranking
@@ -121,35 +121,32 @@ __device__ __forceinline__ TierCounts tier_finish(TierShared& sh, const int* tie
         }
     }
     __syncthreads();
-    int cnt[4] = {0, 0, 0, 0};
-    int before[kTierSlots];
+    // sums over the groups, two tiers a word (576 at most): in all, and of the groups before those of the thread's tokens (uniform
+    // over a wave); tier by tier with a compare for each they were three times the instructions
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    uint2 cnt = make_uint2(0u, 0u), before[kTierSlots] = {};
 #pragma unroll
-    for (int k = 0; k < kTierSlots; ++k) before[k] = 0;
     for (int g = 0; g < kTierGroups; ++g) {
-#pragma unroll
-        for (int t = 0; t < 4; ++t) {
-            const int c = sh.group_cnt[g][t];
-            cnt[t] += c;
-#pragma unroll
-            for (int k = 0; k < kTierSlots; ++k) {
-                const int i = tid + k * kTierThreads;
-                if (g < (i >> 6) && t == tier[k]) before[k] += c;
-            }
-        }
+        constexpr int kWaves = kTierThreads / 64;
+        if (wave == g % kWaves) before[g / kWaves] = cnt;
+        const uint4 c = *reinterpret_cast<const uint4*>(sh.group_cnt[g]);
+        cnt.x += c.x | (c.y << 16);
+        cnt.y += c.z | (c.w << 16);
     }
-
+    const int n[4] = {(int)(cnt.x & 0xFFFFu), (int)(cnt.x >> 16), (int)(cnt.y & 0xFFFFu), (int)(cnt.y >> 16)};
 #pragma unroll
     for (int k = 0; k < kTierSlots; ++k) {
         const int i = tid + k * kTierThreads;
         if (i >= kTokens) continue;
-        const int slot = before[k] + in_group[k];
+        const uint32_t two = tier[k] > 1 ? before[k].y : before[k].x;
+        const int slot = (int)((tier[k] & 1) ? two >> 16 : two & 0xFFFFu) + in_group[k];
         tier_out[i] = (uint8_t)tier[k];
         slot_out[i] = (uint16_t)slot;
-        const int tier_base = (tier[k] > 0 ? cnt[0] : 0) + (tier[k] > 1 ? cnt[1] : 0) + (tier[k] > 2 ? cnt[2] : 0);
+        const int tier_base = (tier[k] > 0 ? n[0] : 0) + (tier[k] > 1 ? n[1] : 0) + (tier[k] > 2 ? n[2] : 0);
         order_out[tier_base + slot] = (uint16_t)i;
     }
 #pragma unroll
-    for (int t = 0; t < 4; ++t) res.cnt[t] = cnt[t];
+    for (int t = 0; t < 4; ++t) res.cnt[t] = n[t];
     return res;
 }
 
