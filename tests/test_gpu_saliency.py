@@ -131,3 +131,15 @@ def test_block_sizes_of_the_pre_pass(h, w):
     img[:, : w // 2] = (128 + 60 * np.sin(xx / 3.3) * np.sin(yy / 4.7) + rng.normal(0, 3, (h, w)))[:, : w // 2, None]
     _check(ctx, np.clip(img, 0, 255).astype(np.uint8), 8, 120)
     ctx.close()
+
+
+@pytest.mark.parametrize("h,w", [(384, 768), (384, 769), (360, 24), (768, 768), (792, 768)])
+def test_patches_of_whole_and_broken_passes(h, w):
+    """Scores of patches whose pixels fill a wave's pass of 512 exactly (16 x 32), run over it by a few (16 x 33), are one pixel wide,
+    fill two passes (the last size with a wave per patch) and have a block each; weak noise, so that links are walked in every pass."""
+    from paper_2602_14236_amd import binding
+    ctx = binding.SaliContext(lib_config(params(h, w, flow_levels=1, canny_lo=8, canny_hi=600)))
+    rng = np.random.default_rng(h * 7 + w)
+    print("passes", h, w, flush=True)
+    _check(ctx, rng.integers(0, 256, (h, w, 3)).astype(np.uint8), 8, 600)
+    ctx.close()
