@@ -224,7 +224,8 @@ __device__ __forceinline__ void attend_rows(const Pools& pools, size_t plane_k, 
                                             SoftmaxState (&st)[kQ]) {
     if (j0 >= j1) return;
     const TierRows k = tier_rows<kTier>(pools, base, count, plane_k), v = tier_rows<kTier>(pools, base, count, plane_v);
-    // rows past the end repeat the last one and count for nothing (their weight is exp(-inf))
+    // rows past the end repeat the last one; they count for nothing: their scores are -inf, and their values are taken out, since a weight
+    // of zero does not take out an infinity
     struct Step {
         RawRow<kTier> k[kRowsPerStep], v[kRowsPerStep];
     };
@@ -241,9 +242,9 @@ __device__ __forceinline__ void attend_rows(const Pools& pools, size_t plane_k, 
 #pragma unroll
     for (int iq = 0; iq < kQ; ++iq) q[iq] = query_piece(raw_q[iq]);
     for (int jb = j0; jb < j1; jb += 16 * kRowsPerStep) {
-        const Step now = next;
+        Step now = next;
         const RawRow<kTier> (&rk)[kRowsPerStep] = now.k;
-        const RawRow<kTier> (&rv)[kRowsPerStep] = now.v;
+        RawRow<kTier> (&rv)[kRowsPerStep] = now.v;
         if (jb + 16 * kRowsPerStep < j1) request(jb + 16 * kRowsPerStep, next);      // under way while this step is worked on
         bool valid[kRowsPerStep];
 #pragma unroll
@@ -279,6 +280,10 @@ __device__ __forceinline__ void attend_rows(const Pools& pools, size_t plane_k, 
             st[iq].lsum = __builtin_fmaf(st[iq].lsum, corr[iq], sum);
             st[iq].mx = new_mx;
         }
+        if (jb + 16 * kRowsPerStep > j1)                    // the last step
+#pragma unroll
+            for (int r = 0; r < kRowsPerStep; ++r)
+                if (!valid[r]) rv[r] = {};
         // the step's rows are added up first, so that the long sums are rounded once a step
         float sums[kQ][8], zeros[kQ];
 #pragma unroll

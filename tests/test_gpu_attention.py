@@ -471,3 +471,34 @@ def test_parts_and_their_hand_over_by_number_of_heads(heads):
             assert bool(((lse.double() - torch.logsumexp(s, dim=-1).reshape(-1)).abs() <= 1e-5 * (1 + lse.double().abs())).all())
     assert ctx.get_status() == 0
     ctx.close()
+
+
+@pytest.mark.parametrize("heads,q_per_kv", [(1, 1), (32, 1), (2, 2), (32, 4), (3, 8)])
+@pytest.mark.parametrize("rows", [1, 15, 17, 64, 70, 130])
+def test_infinite_values_stay_in_their_column(heads, q_per_kv, rows):
+    """FP16 rows are used as stored, so an infinity among the values makes that column of the result infinite and no other.  It sits in
+    the last row of the frame's run: lane groups without a row of their own ask for that one again and must not add it."""
+    from paper_2602_14236_amd import binding
+    p = params(96, 96, tier_mode=1, k_fp16=rows, k_int8=0, k_int4=0, n_layers=1, n_heads=heads, cap_fp16=2 * rows, cap_int8=1, cap_int4=1,
+               max_frames=2)
+    ctx = binding.SaliContext(lib_config(p))
+    g = torch.Generator(device="cuda").manual_seed(rows)
+    scores = torch.linspace(1.0, 0.0, 576, device="cuda")              # the first tokens are kept, in order
+    kept = []
+    for t in range(2):
+        kv = torch.randn((1, 2, heads, 576, 128), generator=g, device="cuda").to(torch.float16)
+        kv[0, 1, :, rows - 1, 5 + t] = float("inf") if t == 0 else float("-inf")
+        ctx.kv_compress(kv, scores, t)
+        kept.append(kv[0, :, :, :rows].double())
+    k, v = (torch.cat([d[i] for d in kept], dim=1) for i in (0, 1))
+    n = q_per_kv
+    q = torch.randn((heads * n, 128), generator=g, device="cuda").to(torch.float16)
+    out, lse = torch.empty((heads * n, 128), device="cuda"), torch.empty(heads * n, device="cuda")
+    ctx.attend_decode_gqa(0, q, n, 0, 2, 128.0 ** -0.5, out, lse)
+    pr = torch.softmax(torch.bmm(q.double().view(heads, n, 128), k.transpose(1, 2).contiguous()) * 128.0 ** -0.5, dim=-1)
+    assert bool((out[:, 5] == float("inf")).all()) and bool((out[:, 6] == float("-inf")).all())
+    rest = [d for d in range(128) if d not in (5, 6)]
+    v = v[:, :, rest].contiguous()
+    err = (out[:, rest].double() - torch.bmm(pr, v).reshape(heads * n, -1)).abs()
+    assert bool((err <= 1e-5 * torch.bmm(pr, v.abs()).reshape(heads * n, -1)).all())
+    ctx.close()
