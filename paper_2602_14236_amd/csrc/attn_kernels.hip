@@ -23,9 +23,11 @@
 // product is reduced over the 16 lanes with four DPP moves.  Every lane group keeps an
 // online-softmax state (running max, sum and 8 output values per lane); a block merges its 16 lane
 // groups through LDS and writes one partial (max, sum, 128 values); the last block of a head to finish merges
-// the partials.  The three tiers of a frame are walked by three instances of one loop
+// the partials, or a launch of its own where they are many (in_launch_parts).  The three tiers of a frame are walked by three instances of one loop
 // specialised on the row format.  With grouped-query attention the kQ query heads that share a K/V
 // head are handled by the same block, so every compressed row is still read once.
+
+#include <type_traits>
 
 #include "sali_internal.h"
 
@@ -224,8 +226,8 @@ __device__ __forceinline__ void attend_rows(const Pools& pools, size_t plane_k, 
                                             SoftmaxState (&st)[kQ]) {
     if (j0 >= j1) return;
     const TierRows k = tier_rows<kTier>(pools, base, count, plane_k), v = tier_rows<kTier>(pools, base, count, plane_v);
-    // rows past the end repeat the last one; they count for nothing: their scores are -inf, and their values are taken out, since a weight
-    // of zero does not take out an infinity
+    // Rows past the end repeat the last one; they count for nothing: their scores are -inf, and FP16 values are taken out, since a weight of zero
+    // does not take out an infinity (quantised ones are finite, or unspecified)
     struct Step {
         RawRow<kTier> k[kRowsPerStep], v[kRowsPerStep];
     };
@@ -280,10 +282,11 @@ __device__ __forceinline__ void attend_rows(const Pools& pools, size_t plane_k, 
             st[iq].lsum = __builtin_fmaf(st[iq].lsum, corr[iq], sum);
             st[iq].mx = new_mx;
         }
-        if (jb + 16 * kRowsPerStep > j1)                    // the last step
+        if constexpr (kTier == SALI_TIER_FP16)
+            if (jb + 16 * kRowsPerStep > j1)                // the last step
 #pragma unroll
-            for (int r = 0; r < kRowsPerStep; ++r)
-                if (!valid[r]) rv[r] = {};
+                for (int r = 0; r < kRowsPerStep; ++r)
+                    if (!valid[r]) rv[r] = {};
         // the step's rows are added up first, so that the long sums are rounded once a step
         float sums[kQ][8], zeros[kQ];
 #pragma unroll
@@ -344,78 +347,70 @@ __device__ __forceinline__ float wave_max(float v) {
     return fmaxf(fmaxf(lane_value(v, 0), lane_value(v, 16)), fmaxf(lane_value(v, 32), lane_value(v, 48)));
 }
 
-// A wave's share of merging the partials of NQ queries at once: partials `first`, first + kStep, ... of n (at most kAttnPartials),
+// A wave's share of merging the partials of a query: partials `first`, first + kStep, ... of n (at most kAttnPartials),
 // whose values it adds up weighted (lane i: values 2 i, 2 i + 1); all of it in as few trips as there are: every wave reads all
-// maxima itself (a lane each) while its first kFlight partials are already under way.  lt = the sum of weights.
-template <int NQ, int kStep, int kFlight>
-__device__ __forceinline__ void merge_partials(const float* const (&p)[NQ], int n, int first, float (&big)[NQ], float (&lt)[NQ], float2 (&at)[NQ]) {
+// maxima itself (a lane each) while its first kFlight partials are already under way.
+struct Merged {
+    float big, lt;              // largest score, sum of weights
+    float2 at;
+};
+template <int kStep, int kFlight>
+__device__ __forceinline__ Merged merge_partials(const float* p, int n, int first) {
     constexpr int kPerLane = kAttnPartials / 64;
     const int lane = threadIdx.x & 63;
-    float m[NQ][kPerLane], l[NQ][kPerLane];
-    float2 v[NQ][kFlight];
+    float2 ml[kPerLane], v[kFlight];
     auto request = [&](int k) {
 #pragma unroll
-        for (int q = 0; q < NQ; ++q)
-#pragma unroll
-            for (int u = 0; u < kFlight; ++u)
-                v[q][u] = get_pair(p[q] + (size_t)min(k + u * kStep, n - 1) * kPartialStride + 2 + 2 * lane);
+        for (int u = 0; u < kFlight; ++u) v[u] = get_pair(p + (size_t)min(k + u * kStep, n - 1) * kPartialStride + 2 + 2 * lane);
     };
 #pragma unroll
-    for (int q = 0; q < NQ; ++q)
-#pragma unroll
-        for (int j = 0; j < kPerLane; ++j) {
-            m[q][j] = -INFINITY;
-            l[q][j] = 0.0f;
-            if (64 * j < n && 64 * j + lane < n) {
-                const float2 ml = get_pair(p[q] + (size_t)(64 * j + lane) * kPartialStride);
-                m[q][j] = ml.x;
-                l[q][j] = ml.y;
-            }
-        }
+    for (int j = 0; j < kPerLane; ++j) {
+        ml[j] = make_float2(-INFINITY, 0.0f);
+        if (64 * j < n) ml[j] = get_pair(p + (size_t)min(64 * j + lane, n - 1) * kPartialStride);
+    }
     request(first);
+    Merged r = {-INFINITY, 0.0f, {}};
+    float m[kPerLane];
 #pragma unroll
-    for (int q = 0; q < NQ; ++q) {
-        big[q] = wave_max(fmaxf(fmaxf(m[q][0], m[q][1]), fmaxf(m[q][2], m[q][3])));
-        lt[q] = 0.0f;
+    for (int j = 0; j < kPerLane; ++j) {
+        m[j] = 64 * j + lane < n ? ml[j].x : -INFINITY;
+        r.big = fmaxf(r.big, m[j]);
+    }
+    r.big = wave_max(r.big);
 #pragma unroll
-        for (int j = 0; j < kPerLane; ++j) {
-            if (64 * j >= n) break;
-            m[q][j] = big[q] != -INFINITY ? expf(m[q][j] - big[q]) : 0.0f;      // the partial's weight
-            lt[q] += m[q][j] * l[q][j];
-        }
+    for (int j = 0; j < kPerLane; ++j) {
+        if (64 * j >= n) break;
+        m[j] = r.big != -INFINITY ? expf(m[j] - r.big) : 0.0f;      // the partial's weight
+        r.lt += 64 * j + lane < n ? m[j] * ml[j].y : 0.0f;
     }
     // four sums side by side, added up last: shorter chains, and less rounding
-    float2 sum[NQ][4] = {};
+    float2 sum[4] = {};
     for (int k = first; k < n; k += kFlight * kStep) {
 #pragma unroll
-        for (int q = 0; q < NQ; ++q)
-#pragma unroll
-            for (int u = 0; u < kFlight; ++u) {
-                const int ku = k + u * kStep;
-                if (ku < n) {
-                    const float mine = ku < 64 ? m[q][0] : (ku < 128 ? m[q][1] : (ku < 192 ? m[q][2] : m[q][3]));
-                    const float w = lane_value(mine, ku & 63);
-                    sum[q][u & 3].x += w * v[q][u].x;
-                    sum[q][u & 3].y += w * v[q][u].y;
-                }
+        for (int u = 0; u < kFlight; ++u) {
+            const int ku = k + u * kStep;
+            if (ku < n) {
+                const float mine = ku < 64 ? m[0] : (ku < 128 ? m[1] : (ku < 192 ? m[2] : m[3]));
+                const float w = lane_value(mine, ku & 63);
+                sum[u & 3].x += w * v[u].x;
+                sum[u & 3].y += w * v[u].y;
             }
+        }
         if (k + kFlight * kStep < n) request(k + kFlight * kStep);
     }
-#pragma unroll
-    for (int q = 0; q < NQ; ++q) {
-        lt[q] = wave_sum(lt[q]);
-        at[q] = make_float2((sum[q][0].x + sum[q][1].x) + (sum[q][2].x + sum[q][3].x), (sum[q][0].y + sum[q][1].y) + (sum[q][2].y + sum[q][3].y));
-    }
+    r.lt = wave_sum(r.lt);
+    r.at = make_float2((sum[0].x + sum[1].x) + (sum[2].x + sum[3].x), (sum[0].y + sum[1].y) + (sum[2].y + sum[3].y));
+    return r;
 }
 static_assert(kAttnPartials == 256, "four partials a lane");
 
 // the merged result of query head h: lane i has values 2 i, 2 i + 1 (the caller's arrays are aligned for float only)
-__device__ __forceinline__ void store_result(const AttnOut& o, int h, float big, float lt, float2 at) {
+__device__ __forceinline__ void store_result(const AttnOut& o, int h, const Merged& r) {
     const int lane = threadIdx.x & 63;
     float* dst = o.out + (size_t)h * kHeadDim + 2 * lane;
-    dst[0] = lt > 0.0f ? at.x / lt : 0.0f;
-    dst[1] = lt > 0.0f ? at.y / lt : 0.0f;
-    if (o.lse != nullptr && lane == 0) o.lse[h] = lt > 0.0f ? big + logf(lt) : -INFINITY;
+    dst[0] = r.lt > 0.0f ? r.at.x / r.lt : 0.0f;
+    dst[1] = r.lt > 0.0f ? r.at.y / r.lt : 0.0f;
+    if (o.lse != nullptr && lane == 0) o.lse[h] = r.lt > 0.0f ? r.big + logf(r.lt) : -INFINITY;
 }
 
 }  // namespace
@@ -428,8 +423,8 @@ constexpr int blocks_per_unit(int kq) { return kq == 4 ? 2 : 4; }
 // touches an eighth of the pages.  32 heads, 20 frames: 29.5 us with twelve or twenty parts in launch order, 24.8 with sixteen, which fall that
 // way by themselves.  Block `part` takes the stretch [part * n, (part + 1) * n) of the range's n frames in
 // units of 1 / parts frame, a frame's part of it the same fraction of its groups of 16 rows, for kQ of the query heads that share the K/V
-// head (`sets` such sets: q_per_kv = kQ * sets), and writes one partial per query head; the head's last block merges them.
-template <int kQ, int kRowsPerStep>
+// head (`sets` such sets: q_per_kv = kQ * sets), and writes one partial per query head; kInLaunch: the head's last block merges them.
+template <int kQ, int kRowsPerStep, bool kInLaunch>
 __global__ __launch_bounds__(256, blocks_per_unit(kQ)) void k_attn_partial(
     const sali_frame_row* __restrict__ rows, const _Float16* __restrict__ q, float* __restrict__ partial, int layer, int n_heads, int sets,
     int frame_lo, int frame_hi, int tiles, int parts, float softmax_scale, Pools pools, AttnOut result) {
@@ -551,29 +546,52 @@ __global__ __launch_bounds__(256, blocks_per_unit(kQ)) void k_attn_partial(
             if (result.lse != nullptr && d == 0) result.lse[head] = lt > 0.0f ? big + logf(lt) : -INFINITY;
         }
     }
-    if (parts == 1 || !last_to_arrive(result.arrived + (size_t)group * kArrivedStride, parts, &s_last)) return;
+    if constexpr (kInLaunch) {
+        if (parts == 1 || !last_to_arrive(result.arrived + (size_t)group * kArrivedStride, parts, &s_last)) return;
+        // four waves: all of them on the one query, two on each of two, one on each of four
+        constexpr int kWaves = 4 / kQ;
+        const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)), iq = wave / kWaves, sub = wave % kWaves;
+        Merged r = merge_partials<kWaves, kQ == 4 ? 32 : 16>(partial + (size_t)(q_first + iq) * kAttnPartials * kPartialStride, parts,
+                                                             min(sub, parts - 1));
+        if constexpr (kWaves > 1) {
+            // (with fewer partials than waves the last one is taken more than once: once too often)
+            float2* s_part = reinterpret_cast<float2*>(&s_acc[0][0][0]);
+            s_part[threadIdx.x] = sub < parts ? r.at : make_float2(0.0f, 0.0f);
+            __syncthreads();
+            if (sub != 0) return;
+#pragma unroll
+            for (int k = 1; k < kWaves; ++k) {
+                const float2 other = s_part[threadIdx.x + 64 * k];
+                r.at.x += other.x;
+                r.at.y += other.y;
+            }
+        }
+        store_result(result, q_first + iq, r);
+    }
+}
 
-    // four waves: all of them on the one query, two on each of two, one on each of four
-    constexpr int kWaves = 4 / kQ;
-    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)), iq = wave / kWaves, sub = wave % kWaves;
-    const float* const p[1] = {partial + (size_t)(q_first + iq) * kAttnPartials * kPartialStride};
-    float big[1], lt[1];
-    float2 at[1];
-    merge_partials<1, kWaves, kQ == 4 ? 32 : 16>(p, parts, min(sub, parts - 1), big, lt, at);
+// The merge as a launch of its own: `parts` partials of `slots` reserved for each of n_q queries, kWaves waves a query.  All of a
+// query's partials are under way at once: up to 8 with one wave, 32 with four, 128 with sixteen.
+template <int kWaves>
+__global__ __launch_bounds__(kWaves < 4 ? 256 : 64 * kWaves) void k_attn_merge(const float* __restrict__ partial, int parts, int slots, int n_q,
+                                                                             AttnOut result) {
+    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)), lane = threadIdx.x & 63, sub = wave % kWaves;
+    const int h = kWaves < 4 ? (int)blockIdx.x * 4 + wave : (int)blockIdx.x;
+    if (h >= n_q) return;
+    Merged r = merge_partials<kWaves, 8>(partial + (size_t)h * slots * kPartialStride, parts, min(sub, parts - 1));
     if constexpr (kWaves > 1) {
-        // (with fewer partials than waves the last one is taken more than once: once too often)
-        float2* s_part = reinterpret_cast<float2*>(&s_acc[0][0][0]);
-        s_part[threadIdx.x] = sub < parts ? at[0] : make_float2(0.0f, 0.0f);
+        __shared__ float2 s_part[kWaves][64];
+        s_part[sub][lane] = r.at;
         __syncthreads();
         if (sub != 0) return;
 #pragma unroll
         for (int k = 1; k < kWaves; ++k) {
-            const float2 other = s_part[threadIdx.x + 64 * k];
-            at[0].x += other.x;
-            at[0].y += other.y;
+            if (k >= parts) break;              // with fewer partials than waves the last one is taken more than once
+            r.at.x += s_part[k][lane].x;
+            r.at.y += s_part[k][lane].y;
         }
     }
-    store_result(result, q_first + iq, big[0], lt[0], at[0]);
+    store_result(result, h, r);
 }
 
 // an empty range: zeros and -inf
@@ -604,14 +622,14 @@ __global__ __launch_bounds__(256) void k_attn_empty(AttnOut result, int n_q_head
 // the matrix cores take fp16 operands; the softmax weights are rounded to fp16 for the second product
 // as well.  Both stay inside the tolerance of the floating-point results (largest error printed by
 // the tests).  Accumulation, softmax state and partials are fp32; partials have the layout of the
-// single-query kernel and are merged the same way, by the last block of 32 queries to finish.
+// single-query kernel; a launch of its own merges them.
 //
 // What bounds it: the trip to memory of a tile (waves wait for 47 % of their time), then the vector
 // instructions of a tile (610, conversions and softmax).  Hence: a tile's K^ and V^ rows are asked for a
 // whole tile ahead, across tiers and frames; the launch is one block of eight waves per compute unit, forced
 // to one by its LDS, so that all start at once; and a block writes one partial instead of one per wave.
-// 32 heads x 32 queries over 20 frames (173 / 200 / 203 rows, 118 MB): 34.6 us a call, of which tiles stream for 19 at 6.1 TB/s; 36.1 with
-// the merge in a kernel of its own and 64-bit divisions in the list of frames (34.5 + 4.6 by the kernels).  The same tiles as 512 independent blocks of four waves that should just have fitted twice per compute unit, a
+// 32 heads x 32 queries over 20 frames (173 / 200 / 203 rows, 118 MB): 32.2 us a call, of which tiles stream for 19 at 6.1 TB/s; 34.6 with
+// the merge in the launch (in_launch_parts), 36.1 with 64-bit divisions in the list of frames.  The same tiles as 512 independent blocks of four waves that should just have fitted twice per compute unit, a
 // tier's loads one tile ahead and a partial per wave, took 69.6 us + 8.0 us of merge: such blocks do not
 // pack perfectly, the last of them ran alone in a second round (mean wave lifetime 26 us).
 typedef _Float16 half4_t __attribute__((ext_vector_type(4)));
@@ -858,7 +876,7 @@ __global__ __launch_bounds__(64 * kPfWaves) __attribute__((amdgpu_waves_per_eu(2
     const BlockId blk = xcd_block_id((int)blockIdx.x, n_heads * sets, 1, parts);        // as in k_attn_partial
     const int group = blk.x, part = blk.z;
     const int h = sets == 1 ? group : group / sets, set = group - h * sets;
-    together(pools.p16, pools.c8, pools.s8, pools.c4, pools.s4, pools.z4, pools.n_planes, result.out, result.lse, result.arrived);
+    together(pools.p16, pools.c8, pools.s8, pools.c4, pools.s4, pools.z4, pools.n_planes, result.out, result.lse);
     const int qi = set * 32 + m;                 // this lane's query among the q_per_kv of the K/V head
     const size_t plane_k = ((size_t)layer * 2 + 0) * n_heads + h;
     const size_t plane_v = ((size_t)layer * 2 + 1) * n_heads + h;
@@ -1038,8 +1056,8 @@ __global__ __launch_bounds__(64 * kPfWaves) __attribute__((amdgpu_waves_per_eu(2
             for (int w = 0; w < kPfWaves; ++w) lt += s_l[w][m] * __builtin_amdgcn_exp2f(s_m[w][m] - big);
         const float natural = big * 0.69314718055994530942f;
         if (parts > 1) {
-            put(first_partial + (size_t)m * parts * kPartialStride, natural);
-            put(first_partial + (size_t)m * parts * kPartialStride + 1, lt);
+            first_partial[(size_t)m * parts * kPartialStride] = natural;
+            first_partial[(size_t)m * parts * kPartialStride + 1] = lt;
         } else {
             s_l[0][m] = lt;
             if (result.lse != nullptr) result.lse[q_first + m] = lt > 0.0f ? natural + logf(lt) : -INFINITY;
@@ -1060,24 +1078,43 @@ __global__ __launch_bounds__(64 * kPfWaves) __attribute__((amdgpu_waves_per_eu(2
         const int idx = (int)threadIdx.x + i * 64 * kPfWaves, mm = idx / kHeadDim, d = idx % kHeadDim;
         if (mm >= queries) continue;
         if (parts > 1) {
-            put(first_partial + (size_t)mm * parts * kPartialStride + 2 + d, sum[i]);
+            first_partial[(size_t)mm * parts * kPartialStride + 2 + d] = sum[i];
         } else {
             const float lt = s_l[0][mm];
             result.out[(size_t)(q_first + mm) * kHeadDim + d] = lt > 0.0f ? sum[i] / lt : 0.0f;
         }
     }
-    if (parts == 1 || !last_to_arrive(result.arrived + (size_t)group * kArrivedStride, parts, &s_n[0])) return;
-    constexpr int kMine = 32 / kPfWaves;                    // queries of a wave, all at once
-    if (wave * kMine >= queries) return;
-    const float* p[kMine];
-#pragma unroll
-    for (int i = 0; i < kMine; ++i) p[i] = partial + (size_t)(q_first + min(wave * kMine + i, queries - 1)) * parts * kPartialStride;
-    float top[kMine], lt[kMine];
-    float2 at[kMine];
-    merge_partials<kMine, 1, 8>(p, parts, 0, top, lt, at);
-#pragma unroll
-    for (int i = 0; i < kMine; ++i)
-        if (wave * kMine + i < queries) store_result(result, q_first + wave * kMine + i, top[i], lt[i], at[i]);
+}
+
+// Does the last block of a head merge its parts, or a launch of its own?  In the launch one block reads them all: that saves a launch, on the GPU
+// (one query a head: 4 to 16 parts 5.4 against 6.6 us a call, 128 parts 8.7 against 9.0) and on the host (32 calls of 4 queries a head and 32 parts
+// 273 against 307 us, the host's time, though 9.3 against 8.4 us each on the GPU), until its compute unit is what the call waits for (two
+// queries: 32 parts 7.1 either way, 74 parts 8.6 against 7.8, 256 parts 17.2 against 13.3; four: 37 parts 9.5 against 8.1, 64 parts 11.8 against
+// 9.8).  32 queries behind the matrix cores gain nothing from eight parts on (32 heads x 24 frames 40.6 against 39.8) and lose by the number of
+// parts: 11 parts 15.4 against 10.7, 63 parts 29.8 against 12.4.
+constexpr int in_launch_parts(int kq, bool one_group) { return kq == 1 ? kAttnPartials : (kq == 2 ? 64 : (one_group ? 32 : 1)); }
+
+// Parts where there are more heads x sets than half of the compute units: equal loads for the units, at least nearly two blocks each; a block more
+// costs little.  320 sets of 4 queries x 8 frames 205.9 us with one part (a unit in four has two blocks), 132.4 with four; 160 heads x 8 frames
+// 48.1 with six, 45.6 with three; 200 sets 108.9 with two, 89.1 with five.
+static int balanced_parts(int pairs, int kq) {
+    int best = 1;
+    double least = INFINITY;
+    for (int p = 1; p <= 8; ++p) {
+        const double blocks = (double)p * pairs / kComputeUnits;
+        const double cost = ceil(blocks) / blocks + (kq == 4 ? 0.03 : 0.06) * blocks;
+        if (blocks >= 1.8 && cost < least) {
+            least = cost;
+            best = p;
+        }
+    }
+    return best;
+}
+
+static void launch_merge(const float* d_partial, int parts, int slots, int n_q, const AttnOut& result, hipStream_t s) {
+    if (parts <= 8) hipLaunchKernelGGL(k_attn_merge<1>, dim3((n_q + 3) / 4), dim3(256), 0, s, d_partial, parts, slots, n_q, result);
+    else if (parts <= 32) hipLaunchKernelGGL(k_attn_merge<4>, dim3(n_q), dim3(256), 0, s, d_partial, parts, slots, n_q, result);
+    else hipLaunchKernelGGL(k_attn_merge<16>, dim3(n_q), dim3(1024), 0, s, d_partial, parts, slots, n_q, result);
 }
 
 hipError_t launch_attend(const sali_frame_row* d_rows, const Pools& pools, int layer, int n_heads, int q_per_kv,
@@ -1091,6 +1128,8 @@ hipError_t launch_attend(const sali_frame_row* d_rows, const Pools& pools, int l
         return hipGetLastError();
     }
     if (ev_start != nullptr && hipEventRecord(ev_start, s) != hipSuccess) return hipErrorUnknown;
+    int parts, slots;               // partials per query, made and reserved
+    bool merged;                    // the launch leaves results
     if (q_per_kv > kAttnMaxQPerKv) {
         // matrix-core path: one block of eight waves per compute unit, as many parts of the range as that
         // gives a K/V head, but no more than leave every wave a tile (a frame has up to kTokens / kPfRows + 3),
@@ -1099,13 +1138,15 @@ hipError_t launch_attend(const sali_frame_row* d_rows, const Pools& pools, int l
         // of a third of the work.  160 heads x 9 queries x 20 frames 168 -> 133 us a call, 129 heads 167 -> 125
         // (independent blocks of four waves: 141 and 162)
         const int sets = (q_per_kv + 31) / 32, pairs = n_heads * sets;
-        int parts = kComputeUnits / pairs;
+        parts = kComputeUnits / pairs;
         if (parts == 1 && 3 * pairs <= 2 * kComputeUnits) parts = 3;
         const long long fill = ((long long)n_range * (kTokens / kPfRows + 3) + kPfWaves - 1) / kPfWaves;
         if (parts > fill) parts = (int)fill;
         if (parts > kAttnSlotsPerHead / q_per_kv) parts = kAttnSlotsPerHead / q_per_kv;
         if (parts > kAttnPartials) parts = kAttnPartials;
         if (parts < 1) parts = 1;
+        slots = parts;
+        merged = parts == 1;
         const dim3 grid(parts * n_heads * sets);
         // the general variant costs 0.7 % (32 heads x 32 queries x 20 frames 143.8 -> 144.8 us for four layers)
         if (n_range > 32768)
@@ -1121,37 +1162,42 @@ hipError_t launch_attend(const sali_frame_row* d_rows, const Pools& pools, int l
         // Whole rounds of one block per compute unit, as nearly as the parts allow (a unit with one block more than the others is
         // where the launch ends: 20 frames x 32 heads 25.6 us with 16 parts, 28.9 with 20, 26.5 with 24): two from sixteen
         // heads x sets on; one below, where more parts cost more at the merge than they bring (8 heads x 4 queries x 20 frames 19.6 us
-        // with 32 parts, 21.2 with 64); all that fit where parts are few and the remainder is large.  A block takes two groups of 16
-        // rows or more, four rows of a lane group in flight; where there are no more groups than one round has blocks it takes one,
-        // a row per lane group.
+        // with 32 parts, 21.2 with 64); no more than 128 for one head (24 frames 9.6 us, 11.8 with 256).  Shares of a block: two groups of 16 rows
+        // or more; one where 64 blocks have them all (one flight of the merge: a head x 56 groups x 4 queries 8.1 us, with two a block 8.8, but
+        // 148 groups 10.0 and 9.4); eight or more where heads x sets fill half the chip alone (160 heads x 14 groups 8.1 us with
+        // one part, 11.2 with six).  Shares of up to two groups are taken a row per lane group at a time, others four: 4 heads x 74 groups x 4 queries
+        // 9.0 and 10.9 us.
         const int pairs = n_heads * sets;
         const int groups = (kept.n16 + 15) / 16 + (kept.n8 + 15) / 16 + (kept.n4 + 15) / 16;
         const long long work = (long long)n_range * (groups < 4 ? 4 : groups);      // not fewer than four: frames stored under an earlier rule
-        const bool single = work * pairs <= kComputeUnits;
-        long long parts = kComputeUnits * (pairs > 128 ? blocks_per_unit(kq) : (pairs >= 16 ? 2 : 1)) / pairs;
-        if (single) parts = work;
-        else if (parts > (work + 1) / 2) parts = (work + 1) / 2;
-        if (parts > kAttnPartials) parts = kAttnPartials;
+        const bool one_group = work <= 64 && work * pairs <= kComputeUnits;
+        const long long most = one_group ? work : (pairs > 128 ? work / 8 : (work + 1) / 2);
+        parts = pairs > 128 ? balanced_parts(pairs, kq) : kComputeUnits * (pairs >= 16 ? 2 : 1) / pairs;
+        if (parts > 128) parts = 128;
+        if (parts > most) parts = (int)most;
         if (parts < 1) parts = 1;
-        const dim3 grid((int)parts * n_heads * sets);
-#define SALI_ATTN_LAUNCH(KQ)                                                                                                       \
-    do {                                                                                                                           \
-        if (single)                                                                                                                \
-            hipLaunchKernelGGL((k_attn_partial<KQ, 1>), grid, dim3(256), 0, s, d_rows, q, d_partial, layer, n_heads, sets, frame_lo, \
-                               frame_hi, tiles, (int)parts, softmax_scale, pools, result);                                         \
-        else                                                                                                                       \
-            hipLaunchKernelGGL((k_attn_partial<KQ, 4>), grid, dim3(256), 0, s, d_rows, q, d_partial, layer, n_heads, sets, frame_lo, \
-                               frame_hi, tiles, (int)parts, softmax_scale, pools, result);                                         \
-    } while (0)
+        const bool one_row = work <= 2 * parts;
+        slots = kAttnPartials;
+        merged = parts <= in_launch_parts(kq, one_group);
+        const dim3 grid(parts * n_heads * sets);
+        auto go = [&](auto queries) {
+            constexpr int kQ = decltype(queries)::value;
+            auto* const kernel = one_row ? (merged ? k_attn_partial<kQ, 1, true> : k_attn_partial<kQ, 1, false>)
+                                         : (merged ? k_attn_partial<kQ, 4, true> : k_attn_partial<kQ, 4, false>);
+            hipLaunchKernelGGL(kernel, grid, dim3(256), 0, s, d_rows, q, d_partial, layer, n_heads, sets, frame_lo, frame_hi, tiles, parts,
+                               softmax_scale, pools, result);
+        };
         switch (kq) {
-            case 1: SALI_ATTN_LAUNCH(1); break;
-            case 2: SALI_ATTN_LAUNCH(2); break;
-            case 4: SALI_ATTN_LAUNCH(4); break;
+            case 1: go(std::integral_constant<int, 1>{}); break;
+            case 2: go(std::integral_constant<int, 2>{}); break;
+            case 4: go(std::integral_constant<int, 4>{}); break;
             default: return hipErrorInvalidValue;
         }
-#undef SALI_ATTN_LAUNCH
     }
     if (ev_stop != nullptr && hipEventRecord(ev_stop, s) != hipSuccess) return hipErrorUnknown;
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess || merged) return e;
+    launch_merge(d_partial, parts, slots, n_heads * q_per_kv, result, s);
     return hipGetLastError();
 }
 

@@ -15,7 +15,7 @@ from oracle.attention import attend_decode
 from oracle.cache import SaliCacheOracle
 from paper_2602_14236_amd import synth
 
-from _util import fp16_operand_bounds as _fp16_operand_bounds, lib_config, oracle_config, params, workload_params
+from _util import fp16_operand_bounds as _fp16_operand_bounds, lib_config, oracle_config, params, pool_arrays, workload_params
 
 pytestmark = pytest.mark.gpu
 
@@ -469,6 +469,48 @@ def test_parts_and_their_hand_over_by_number_of_heads(heads):
             print(f"{heads} heads, {n} queries: largest error / bound {(err / bound).max():.3f}", flush=True)
             assert bool((err <= bound).all())
             assert bool(((lse.double() - torch.logsumexp(s, dim=-1).reshape(-1)).abs() <= 1e-5 * (1 + lse.double().abs())).all())
+    assert ctx.get_status() == 0
+    ctx.close()
+
+
+@pytest.mark.parametrize("heads,frames,counts,tiles", [
+    (1, 2, (20, 20, 24), 1), (1, 10, (20, 20, 24), 1), (1, 11, (20, 20, 24), 1),        # 12 parts, 60 of a group each, 33 of two
+    (1, 24, (20, 20, 24), 1), (1, 60, (20, 20, 24), 1),                                 # 72 parts, 128 parts
+    (2, 24, (1, 40, 17), 2), (5, 30, (33, 0, 50), 3), (8, 30, (100, 90, 77), 1), (40, 4, (33, 50, 17), 1), (70, 3, (17, 100, 30), 1),
+])
+def test_parts_that_cut_tiers_pointer_frames_and_tiles(heads, frames, counts, tiles):
+    """Parts of the range begin and end inside tiers and frames, at pointer entries and among the tiles of a frame; their number, and with
+    it who merges them (a block of the launch, or a launch with one, four or sixteen waves a query), goes from a few to 128.  Reference:
+    float64 attention over the stored codes.  Up to eight queries fp32 sums, 1e-5 of the largest output; above, the bounds of fp16 operands."""
+    from types import SimpleNamespace
+    from paper_2602_14236_amd import binding
+    k16, k8, k4 = counts
+    p = params(96, 96, tier_mode=1, k_fp16=k16, k_int8=k8, k_int4=k4, n_layers=1, n_heads=heads, cap_fp16=k16 * frames + 1,
+               cap_int8=k8 * frames + 1, cap_int4=k4 * frames + 1, max_frames=frames, tiles_per_frame=tiles)
+    ctx = binding.SaliContext(lib_config(p))
+    g = torch.Generator(device="cuda").manual_seed(heads + frames)
+    rgb = torch.randint(0, 256, (96, 96, 3), generator=g, device="cuda", dtype=torch.uint8)
+    for t in range(0, frames, tiles):
+        ctx.set_gate_thresholds(*((1e9, 0.0) if (t // tiles) % 5 in (2, 4) else (1.0, 2.0)))       # redundant, or not
+        kv = [torch.randn((1, 2, heads, 576, 128), generator=g, device="cuda").to(torch.float16) for _ in range(tiles)]
+        ctx.step_batch([rgb] * tiles, kv, t)
+    table = ctx.read_frame_table(0, frames)
+    assert [r.stored for r in table] == [0 if (t // tiles) % 5 in (2, 4) else 1 for t in range(frames)]
+    pools = pool_arrays(ctx)
+    cache = SimpleNamespace(rows=dict(enumerate(table)), cfg=SimpleNamespace(n_heads=heads, head_dim=128), pool16=pools["fp16"],
+                            codes8=pools["codes8"], scale8=pools["scale8"], codes4=pools["codes4"], scale4=pools["scale4"], zero4=pools["zero4"])
+    sm = 128.0 ** -0.5
+    for n in (1, 2, 4, 8, 9, 33):
+        q = _q(n, heads * n)
+        out, lse = torch.empty((heads * n, 128), device="cuda"), torch.empty(heads * n, device="cuda")
+        for lo, hi in ((0, frames), (min(2 * tiles, frames - tiles), frames)):
+            ctx.attend_decode_gqa(0, q, n, lo, hi, sm, out, lse)
+            exp, exp_lse = attend_decode(cache, 0, q.cpu().numpy(), lo, hi, sm, q_per_kv=n)
+            err, lse_err = np.abs(out.cpu().numpy() - exp), np.abs(lse.cpu().numpy() - exp_lse)
+            bound, lse_bound = (1e-5 * np.abs(exp).max(), 1e-5 * (1 + np.abs(exp_lse))) if n <= 8 else \
+                _fp16_operand_bounds(cache, q.cpu().numpy(), lo, hi, sm, n)
+            print(f"{heads} heads, {n} queries, frames [{lo}, {hi}): largest error / bound {(err / bound).max():.3f}", flush=True)
+            assert np.all(err <= bound) and np.all(lse_err <= lse_bound)
     assert ctx.get_status() == 0
     ctx.close()
 
