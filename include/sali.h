@@ -321,7 +321,7 @@ int sali_step_batch(sali_ctx* ctx, const uint8_t* const* d_rgb_frames, const voi
  *   d_lse_or_null  device, fp32 [n_heads]; -inf where the range holds no token
  * Asynchronous on `stream`, which must be ordered after the stores of the frames read.  Uses one
  * partial-result area of the context and counters of the blocks that have finished: calls on one context must not overlap
- * each other (if they do, their results and those of later calls are undefined until sali_reset).
+ * each other (if they do, their results are undefined; calls issued when they are done are not affected).
  * SALI_ERR_SHAPE if layer or the frame range is out of range (frame_lo == frame_hi is allowed). */
 int sali_attend_decode(sali_ctx* ctx, int32_t layer, const void* d_q_fp16, int32_t frame_lo, int32_t frame_hi,
                        float softmax_scale, float* d_out, float* d_lse_or_null, void* stream);
@@ -352,8 +352,9 @@ int sali_attend_decode_gqa(sali_ctx* ctx, int32_t layer, const void* d_q_fp16, i
  *   - the array's device address is looked up once per GPU in sali_create; SALI_ERR_STATE if the
  *     current device is not the one the context was created on.
  *   - all calls on one GPU share the array (whatever the context): calls that overlap on one GPU,
- *     on different streams or contexts, race.  Nothing of a previous call's contents is read: every
- *     partial the merge step reads is written by the same call first.
+ *     on different streams or contexts, race.  Nothing of a previous call's contents of it is read: every
+ *     partial that is merged is written by the same call first.  The blocks that have finished are counted
+ *     in memory of the context; counts start at zero in every call, also after calls that overlapped.
  * It does not replace or share state with sali_attend_decode, which may run next to it. */
 #define SALI_STATIC_ATTEND_MAX_HEADS 64
 int sali_attend_decode_static(sali_ctx* ctx, int32_t layer, const void* d_q_fp16, int32_t frame_lo, int32_t frame_hi,

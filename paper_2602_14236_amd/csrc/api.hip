@@ -190,7 +190,7 @@ ScratchLayout scratch_layout(const sali_config& c, const LevelGeom& g) {
         s.expB[i] = take(px * sizeof(float));
     }
     s.attn_partial = take((size_t)c.n_heads * kAttnSlotsPerHead * kAttnPartialStride * sizeof(float));
-    for (size_t& at : s.attn_arrived) at = take((size_t)c.n_heads * kAttnSets * kArrivedStride * sizeof(uint32_t));
+    for (size_t& at : s.attn_arrived) at = take(arrival_words(c.n_heads) * sizeof(uint32_t));
     s.total = o;
     return s;
 }
@@ -239,10 +239,10 @@ struct LanePtrArray {
 // Block l < kLanes clears lane l's records; all blocks together the frame table and, one thread, the cursors.  One
 // thread that wrote the records of all lanes one after the other took 8 of the 23 us of the smallest compress and
 // read-back.
-__global__ __launch_bounds__(256) void k_reset(Cursors* cur, sali_frame_row* rows, int max_frames, int n_arrived, uint32_t* arrived0,
-                                               uint32_t* arrived1, int tau0, int tau1, int tau2, LanePtrArray lanes) {
+__global__ __launch_bounds__(256) void k_reset(Cursors* cur, sali_frame_row* rows, int max_frames, int n_arrived, uint4* arrived0,
+                                               uint4* arrived1, int tau0, int tau1, int tau2, LanePtrArray lanes) {
     const int i = blockIdx.x * 256 + threadIdx.x;
-    if (i < n_arrived) arrived0[(size_t)i * kArrivedStride] = arrived1[(size_t)i * kArrivedStride] = 0u;
+    if (i < n_arrived) arrived0[i] = arrived1[i] = make_uint4(0u, 0u, 0u, 0u);
     if (i < max_frames) {
         sali_frame_row r = {};
         r.frame_id = -1;
@@ -864,10 +864,10 @@ int sali_reset(sali_ctx* c, void* stream) {
     for (int l = 0; l < kLanes; ++l) lanes.lane[l] = c->lane_ptrs(l);
     // the adaptive thresholds start from the configured ones, on the 2^-16 lattice
     auto lattice = [](float x) { return (int)floorf(fminf(fmaxf(x, 0.0f), 1.0f) * 65536.0f); };
-    const int n_arrived = c->cfg.n_heads * kAttnSets, items = n_arrived > c->cfg.max_frames ? n_arrived : c->cfg.max_frames;
+    const int n_arrived = (int)(arrival_words(c->cfg.n_heads) / 4), items = n_arrived > c->cfg.max_frames ? n_arrived : c->cfg.max_frames;
     const int blocks = (items + 255) / 256;
     hipLaunchKernelGGL(k_reset, dim3(blocks > kLanes ? blocks : kLanes), dim3(256), 0, s, c->cursors(), c->rows(), c->cfg.max_frames, n_arrived,
-                       c->sc<uint32_t>(c->sl.attn_arrived[0]), c->sc<uint32_t>(c->sl.attn_arrived[1]), lattice(c->cfg.tau_high),
+                       c->sc<uint4>(c->sl.attn_arrived[0]), c->sc<uint4>(c->sl.attn_arrived[1]), lattice(c->cfg.tau_high),
                        lattice(c->cfg.tau_med), lattice(c->cfg.tau_low), lanes);
     SALI_TRY(hipGetLastError());
     c->n_analysed = 0;
@@ -1016,8 +1016,7 @@ int sali_attend_decode_static(sali_ctx* c, int32_t layer, const void* d_q_fp16, 
     SALI_TRY(hipGetDevice(&dev));
     if (dev != c->device || c->static_scratch == nullptr) return SALI_ERR_STATE;
     // every partial that is merged is written by the same call (one per block, empty blocks included), so nothing of the
-    // previous call's contents has to be cleared; the blocks are counted in the context's own memory, so that calls of other
-    // contexts, which may not overlap with this one, leave no wrong count behind if they do
+    // previous call's contents has to be cleared; the blocks are counted in the context's own memory
     const hipError_t e = launch_attend(c->rows(), c->pools, layer, c->cfg.n_heads, 1, d_q_fp16, frame_lo, frame_hi,
                                        tiles_of(c->cfg), kept_per_frame(c->cfg), softmax_scale, c->static_scratch,
                                        AttnOut{d_out, d_lse_or_null, c->sc<uint32_t>(c->sl.attn_arrived[1])}, nullptr, nullptr,

@@ -314,19 +314,16 @@ __device__ __forceinline__ void attend_rows(const Pools& pools, size_t plane_k, 
 // are written and read past the caches that the compute dies do not share (relaxed agent-scope accesses, each coherent
 // by itself) and a block counts itself in only when its own have arrived, so no fence is needed: an agent-scope fence writes back and
 // invalidates the L2 of the issuing die under the stream that the other blocks are reading (with one in each of
-// 2000 blocks this hand-over measured 4.5 times the time of a merge kernel).  The counter is zero again when the launch ends.
+// 2000 blocks this hand-over measured 4.5 times the time of a merge kernel).
 __device__ __forceinline__ void put(float* p, float v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
 __device__ __forceinline__ float2 get_pair(const float* p) {
     return __builtin_bit_cast(float2, __hip_atomic_load(reinterpret_cast<const unsigned long long*>(p), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
 }
-__device__ __forceinline__ bool last_to_arrive(uint32_t* arrived, int blocks, int* s_last) {
+__device__ __forceinline__ bool last_to_arrive(uint32_t* arrived, int head_set, int parts, int* s_last) {
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");        // every wave: its stores have arrived
     __syncthreads();
-    if (threadIdx.x == 0) {
-        const bool last = __hip_atomic_fetch_add(arrived, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == (uint32_t)blocks - 1u;
-        if (last) __hip_atomic_store(arrived, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        *s_last = last ? 1 : 0;
-    }
+    if (threadIdx.x == 0)
+        *s_last = last_arrival(atomicInc(arrived + arrival_counter(head_set, parts), (uint32_t)parts - 1u), parts) ? 1 : 0;       // relaxed, agent scope
     __syncthreads();
     return *s_last != 0;
 }
@@ -547,7 +544,7 @@ __global__ __launch_bounds__(256, blocks_per_unit(kQ)) void k_attn_partial(
         }
     }
     if constexpr (kInLaunch) {
-        if (parts == 1 || !last_to_arrive(result.arrived + (size_t)group * kArrivedStride, parts, &s_last)) return;
+        if (parts == 1 || !last_to_arrive(result.arrived, group, parts, &s_last)) return;
         // four waves: all of them on the one query, two on each of two, one on each of four
         constexpr int kWaves = 4 / kQ;
         const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)), iq = wave / kWaves, sub = wave % kWaves;

@@ -7,6 +7,7 @@
 #include <stddef.h>
 #include <stdint.h>
 
+#include "arith.h"
 #include "sali.h"
 
 namespace sali {
@@ -18,7 +19,6 @@ constexpr int kGroup = 32;                  // quantisation group along head_dim
 constexpr int kGroupsPerRow = kHeadDim / kGroup;
 constexpr int kMaxLevels = 6;
 constexpr int kMaxIters = 8;
-constexpr int kAttnPartials = 256;          // partial softmax states per head in the attention kernel
 constexpr int kAttnMaxQPerKv = 8;           // query heads that may share one K/V head
 constexpr int kAttnSlotsPerHead = 4096;     // partial-result slots of the scratch per K/V head (shared out over its queries)
 constexpr int kAttnSets = 2;                // at most so many blocks share a K/V head's rows with different queries
@@ -332,10 +332,8 @@ hipError_t launch_unpack(const sali_frame_row* d_rows, int first_frame_id, const
 struct RowsPerFrame {
     int n16, n8, n4;
 };
-// results of an attention call, and the arrival counters of its blocks (kAttnSets per K/V head, kArrivedStride words apart, zero
-// between calls).  A counter to a memory line: additions to one line are made one after the other wherever they come from, and with the
-// counters of 32 heads side by side 2000 arrivals took 20 us.
-constexpr int kArrivedStride = 64;
+// results of an attention call, and the arrival counters of its blocks (arrival_counter of kAttnSets per K/V head; zero between calls)
+inline size_t arrival_words(int n_heads) { return (size_t)n_heads * kAttnSets * kAttnPartials; }
 struct AttnOut {
     float* out;
     float* lse;                 // may be NULL

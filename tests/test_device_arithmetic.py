@@ -1,0 +1,50 @@
+"""Arithmetic that the kernels share with the host (csrc/arith.h), on the CPU: a program with the header's own code, built with the host compiler."""
+import os
+import subprocess
+
+import pytest
+
+CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2602_14236_amd", "csrc")
+
+
+def _run(tmp_path, body):
+    src, exe = tmp_path / "check.cpp", tmp_path / "check"
+    src.write_text('#include <cstdio>\n#include <cstdlib>\n#include <vector>\n#include "arith.h"\nusing namespace sali;\n' + body)
+    subprocess.run(["g++", "-std=c++17", "-O2", "-ffp-contract=off", "-Wall", "-Werror", "-I", CSRC, str(src), "-o", str(exe)], check=True)
+    done = subprocess.run([str(exe)], capture_output=True, text=True, timeout=100)
+    assert done.returncode == 0, done.stdout
+
+
+@pytest.mark.parametrize("seed", range(4))
+def test_arrivals_of_overlapping_calls_leave_no_count_behind(tmp_path, seed):
+    """Calls with any numbers of heads and parts whose blocks arrive in any order, mixed with those of other calls: when all have
+    arrived every counter is at zero, and a call by itself has one last block a head, the one that arrives last."""
+    _run(tmp_path, """
+int main() {
+    srand(%d);
+    std::vector<uint32_t> counters(64 * kAttnPartials);
+    auto arrive = [&](int head, int parts) {
+        uint32_t& c = counters[arrival_counter(head, parts)];
+        const uint32_t before = c;
+        c = before >= (uint32_t)parts - 1u ? 0u : before + 1u;         // what atomicInc(&c, parts - 1) does
+        return last_arrival(before, parts);
+    };
+    struct Block { int head, parts; };
+    for (int round = 0; round < 400; ++round) {
+        std::vector<Block> blocks;
+        for (int calls = rand() %% 4 + 2; calls > 0; --calls) {
+            const int heads = rand() %% 64 + 1, parts = rand() %% 3 ? rand() %% 20 + 2 : rand() %% 255 + 2;
+            for (int b = 0; b < heads * parts; ++b) blocks.push_back({b %% heads, parts});
+        }
+        for (size_t i = blocks.size(); i > 1; --i) std::swap(blocks[i - 1], blocks[rand() %% i]);
+        for (const Block& b : blocks) arrive(b.head, b.parts);
+        for (uint32_t c : counters)
+            if (c != 0) { printf("round %%d: a counter is left at %%u\\n", round, c); return 1; }
+        const int parts = rand() %% 256 + 1;
+        for (int head = 0; head < 64; ++head)
+            for (int k = 0; k < parts; ++k)
+                if (arrive(head, parts) != (k == parts - 1)) { printf("round %%d: block %%d of %%d\\n", round, k, parts); return 1; }
+    }
+    return 0;
+}
+""" % seed)
