@@ -1087,9 +1087,9 @@ __global__ __launch_bounds__(64 * kPfWaves) __attribute__((amdgpu_waves_per_eu(2
 // (one query a head: 4 to 16 parts 5.4 against 6.6 us a call, 128 parts 8.7 against 9.0) and on the host (32 calls of 4 queries a head and 32 parts
 // 273 against 307 us, the host's time, though 9.3 against 8.4 us each on the GPU), until its compute unit is what the call waits for (two
 // queries: 32 parts 7.1 either way, 74 parts 8.6 against 7.8, 256 parts 17.2 against 13.3; four: 37 parts 9.5 against 8.1, 64 parts 11.8 against
-// 9.8).  32 queries behind the matrix cores gain nothing from eight parts on (32 heads x 24 frames 40.6 against 39.8) and lose by the number of
+// 9.8, so only in the short calls where the host's time counts, those that take a row at a time).  32 queries behind the matrix cores gain nothing from eight parts on (32 heads x 24 frames 40.6 against 39.8) and lose by the number of
 // parts: 11 parts 15.4 against 10.7, 63 parts 29.8 against 12.4.
-constexpr int in_launch_parts(int kq, bool one_group) { return kq == 1 ? kAttnPartials : (kq == 2 ? 64 : (one_group ? 32 : 1)); }
+constexpr int in_launch_parts(int kq, bool one_row) { return kq == 1 ? kAttnPartials : (kq == 2 ? 64 : (one_row ? 32 : 1)); }
 
 // Parts where there are more heads x sets than half of the compute units: equal loads for the units, at least nearly two blocks each; a block more
 // costs little.  320 sets of 4 queries x 8 frames 205.9 us with one part (a unit in four has two blocks), 132.4 with four; 160 heads x 8 frames
@@ -1167,15 +1167,14 @@ hipError_t launch_attend(const sali_frame_row* d_rows, const Pools& pools, int l
         const int pairs = n_heads * sets;
         const int groups = (kept.n16 + 15) / 16 + (kept.n8 + 15) / 16 + (kept.n4 + 15) / 16;
         const long long work = (long long)n_range * (groups < 4 ? 4 : groups);      // not fewer than four: frames stored under an earlier rule
-        const bool one_group = work <= 64 && work * pairs <= kComputeUnits;
-        const long long most = one_group ? work : (pairs > 128 ? work / 8 : (work + 1) / 2);
+        const long long most = work <= 64 && work * pairs <= kComputeUnits ? work : (pairs > 128 ? work / 8 : (work + 1) / 2);
         parts = pairs > 128 ? balanced_parts(pairs, kq) : kComputeUnits * (pairs >= 16 ? 2 : 1) / pairs;
         if (parts > 128) parts = 128;
         if (parts > most) parts = (int)most;
         if (parts < 1) parts = 1;
         const bool one_row = work <= 2 * parts;
         slots = kAttnPartials;
-        merged = parts <= in_launch_parts(kq, one_group);
+        merged = parts <= in_launch_parts(kq, one_row);
         const dim3 grid(parts * n_heads * sets);
         auto go = [&](auto queries) {
             constexpr int kQ = decltype(queries)::value;
