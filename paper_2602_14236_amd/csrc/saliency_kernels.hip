@@ -137,16 +137,16 @@ __device__ __forceinline__ void pool_tail(TierShared& sh, int* s_cnt, const Pool
         gt.redundant = redundant ? 1 : 0;
         gt.reserved = 0;
         *frame.gate = gt;
-        int32_t* out = reinterpret_cast<int32_t*>(frame.tcounts);
-        __hip_atomic_store(out + 0, tc.state, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-#pragma unroll
-        for (int t = 0; t < 4; ++t)
-            __hip_atomic_store(out + 1 + t, tc.cnt[t], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-#pragma unroll
-        for (int j = 0; j < 3; ++j)
-            __hip_atomic_store(out + 5 + j, tc.q[j], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        bool last = n_frames == 1;
+        bool last = n_frames == 1;              // hands nothing over
         if (!last) {
+            int32_t* out = reinterpret_cast<int32_t*>(frame.tcounts);
+            __hip_atomic_store(out + 0, tc.state, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+#pragma unroll
+            for (int t = 0; t < 4; ++t)
+                __hip_atomic_store(out + 1 + t, tc.cnt[t], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+#pragma unroll
+            for (int j = 0; j < 3; ++j)
+                __hip_atomic_store(out + 5 + j, tc.q[j], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             asm volatile("s_waitcnt vmcnt(0)" ::: "memory");        // the record has arrived
             last = __hip_atomic_fetch_add(batch_done, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == (uint32_t)n_frames - 1u;
             if (last) __hip_atomic_store(batch_done, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -186,13 +186,19 @@ __device__ __forceinline__ void pool_tail(TierShared& sh, int* s_cnt, const Pool
     if (threadIdx.x < 3) sh.tau[threadIdx.x] = tl.cur->adapt_tau[threadIdx.x];
     __syncthreads();
     for (int i = 0; i < n_frames; ++i) {
-        // the frame's hand-over record, the same words for every thread
-        const int32_t* in = reinterpret_cast<const int32_t*>(f.frame[i].tcounts);
+        // the frame's hand-over record, the same words for every thread; a frame by itself is the block's own
         TierCounts tci = {};
-        tci.state = __hip_atomic_load(in + 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         int q[3];
+        if (n_frames == 1) {
+            tci.state = tc.state;
 #pragma unroll
-        for (int j = 0; j < 3; ++j) q[j] = __hip_atomic_load(in + 5 + j, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            for (int j = 0; j < 3; ++j) q[j] = tc.q[j];
+        } else {
+            const int32_t* in = reinterpret_cast<const int32_t*>(f.frame[i].tcounts);
+            tci.state = __hip_atomic_load(in + 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+#pragma unroll
+            for (int j = 0; j < 3; ++j) q[j] = __hip_atomic_load(in + 5 + j, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
         const bool ranked = tci.state == 3;
         if (ranked)
             tci = tier_assign_adaptive(sh, tier_load_scores(f.frame[i].scores), tl.tier + (size_t)i * kTokens,
