@@ -22,4 +22,23 @@ constexpr int kAttnPartials = 256;          // partial softmax states per head i
 SALI_BOTH size_t arrival_counter(int head_set, int parts) { return (size_t)head_set * kAttnPartials + (size_t)(parts - 1); }
 SALI_BOTH bool last_arrival(uint32_t before, int parts) { return before >= (uint32_t)parts - 1u; }
 
+// v / kDiv, correctly rounded, for whole v from 0 to kDiv (255 and 65280: every value checked): the product with the rounded reciprocal,
+// corrected by its remainder
+template <int kDiv>
+SALI_BOTH float whole_over(uint32_t v) {
+    constexpr float kInv = 1.0f / kDiv;
+    const float x = (float)v, q = x * kInv;
+    return __builtin_fmaf(__builtin_fmaf(-(float)kDiv, q, x), kInv, q);
+}
+
+// Row of a patch's pixel by a product: exact for numbers below 2^16 and rows of 2 to 2^16 pixels
+// (larger patches divide: from 6000 pixels a side on)
+struct PatchRow {
+    uint32_t width, inverse;
+    bool small;
+    SALI_BOTH PatchRow(uint32_t pixels_a_row, uint32_t area)
+        : width(pixels_a_row), inverse(0xFFFFFFFFu / pixels_a_row + 1u), small(area <= 65536u && pixels_a_row > 1u) {}
+    SALI_BOTH uint32_t operator()(uint32_t pixel) const { return small ? (uint32_t)((uint64_t)pixel * inverse >> 32) : pixel / width; }
+};
+
 }  // namespace sali

@@ -40,15 +40,6 @@ __device__ __forceinline__ uint32_t pix(int y, int w, int x) {          // y * w
     return __umul24((uint32_t)y, (uint32_t)w) + (uint32_t)x;
 }
 
-// v / kDiv, correctly rounded, for whole v from 0 to kDiv (255 and 65280: every value checked): the product with the rounded reciprocal,
-// corrected by its remainder
-template <int kDiv>
-__device__ __forceinline__ float whole_over(uint32_t v) {
-    constexpr float kInv = 1.0f / kDiv;
-    const float x = (float)v, q = x * kInv;
-    return __builtin_fmaf(__builtin_fmaf(-(float)kDiv, q, x), kInv, q);
-}
-
 }  // namespace
 
 // ---------------------------------------------------------------------------------------------

@@ -534,17 +534,15 @@ __device__ __forceinline__ PatchBox patch_box(int token, int h, int w) {
     const int xa = (pc * w) / kGrid, xb = ((pc + 1) * w) / kGrid;
     return {ya, xa, xb - xa, (xb - xa) * (yb - ya)};
 }
-// Pixel number of a patch -> its place in the image.  The row by a product: exact for numbers below 2^16 and rows of 2 to 2^16 pixels
-// (larger patches divide: from 6000 pixels a side on)
+// Pixel number of a patch -> its place in the image
 struct PatchPixels {
-    uint32_t first, pw, inverse, w;
-    bool small;
+    uint32_t first, w;
+    PatchRow row_of;
     __device__ __forceinline__ PatchPixels(const PatchBox& box, int width)
-        : first((uint32_t)box.ya * (uint32_t)width + (uint32_t)box.xa), pw((uint32_t)box.pw), inverse(0xFFFFFFFFu / (uint32_t)box.pw + 1u),
-          w((uint32_t)width), small(box.area <= 65536 && box.pw > 1) {}
+        : first((uint32_t)box.ya * (uint32_t)width + (uint32_t)box.xa), w((uint32_t)width), row_of((uint32_t)box.pw, (uint32_t)box.area) {}
     __device__ __forceinline__ uint32_t operator()(int pixel) const {
-        const uint32_t p = (uint32_t)pixel, row = small ? __umulhi(p, inverse) : p / pw;
-        return first + row * w + (p - row * pw);
+        const uint32_t p = (uint32_t)pixel, row = row_of(p);
+        return first + row * w + (p - row * row_of.width);
     }
 };
 // The pixels of a pass are asked for together, and the walks of weak ones move in step: a walk's step is a trip to memory, and one

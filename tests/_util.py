@@ -1,4 +1,7 @@
 """Shared helpers of the GPU parity tests: one parameter dict -> library config and oracle config."""
+import os
+import subprocess
+
 import numpy as np
 
 from oracle.cache import OracleConfig
@@ -145,3 +148,13 @@ def fp16_operand_bounds(orc, q, lo, hi, sm, q_per_kv):
         bound[j] = 2.0 * u * (2.0 + 2.0 * s_abs.max()) * (p @ np.abs(v[h])) + 1e-6
         lse_bound[j] = 2.0 * u * (1.0 + s_abs.max()) + 1e-6
     return bound, lse_bound
+
+
+def run_host_program(tmp_path, body):
+    """Builds a C++ program around csrc/arith.h, the arithmetic that the kernels share with the host, with the host compiler and runs it."""
+    csrc = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2602_14236_amd", "csrc")
+    src, exe = tmp_path / "check.cpp", tmp_path / "check"
+    src.write_text('#include <cstdio>\n#include <cstdlib>\n#include <vector>\n#include "arith.h"\nusing namespace sali;\n' + body)
+    subprocess.run(["g++", "-std=c++17", "-O2", "-ffp-contract=off", "-Wall", "-Werror", "-I", csrc, str(src), "-o", str(exe)], check=True)
+    done = subprocess.run([str(exe)], capture_output=True, text=True, timeout=100)
+    assert done.returncode == 0, done.stdout

@@ -1,25 +1,14 @@
 """Arithmetic that the kernels share with the host (csrc/arith.h), on the CPU: a program with the header's own code, built with the host compiler."""
-import os
-import subprocess
-
 import pytest
 
-CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2602_14236_amd", "csrc")
-
-
-def _run(tmp_path, body):
-    src, exe = tmp_path / "check.cpp", tmp_path / "check"
-    src.write_text('#include <cstdio>\n#include <cstdlib>\n#include <vector>\n#include "arith.h"\nusing namespace sali;\n' + body)
-    subprocess.run(["g++", "-std=c++17", "-O2", "-ffp-contract=off", "-Wall", "-Werror", "-I", CSRC, str(src), "-o", str(exe)], check=True)
-    done = subprocess.run([str(exe)], capture_output=True, text=True, timeout=100)
-    assert done.returncode == 0, done.stdout
+from _util import run_host_program
 
 
 @pytest.mark.parametrize("seed", range(4))
 def test_arrivals_of_overlapping_calls_leave_no_count_behind(tmp_path, seed):
     """Calls with any numbers of heads and parts whose blocks arrive in any order, mixed with those of other calls: when all have
     arrived every counter is at zero, and a call by itself has one last block a head, the one that arrives last."""
-    _run(tmp_path, """
+    run_host_program(tmp_path, """
 int main() {
     srand(%d);
     std::vector<uint32_t> counters(64 * kAttnPartials);
@@ -48,3 +37,17 @@ int main() {
     return 0;
 }
 """ % seed)
+
+
+def test_whole_numbers_over_255_and_65280_are_rounded_as_a_division(tmp_path):
+    run_host_program(tmp_path, """
+template <int kDiv>
+int check() {
+    for (uint32_t v = 0; v <= (uint32_t)kDiv; ++v) {
+        const volatile float n = (float)v, d = (float)kDiv;
+        if (whole_over<kDiv>(v) != n / d) { printf("%u / %d\\n", v, kDiv); return 1; }
+    }
+    return 0;
+}
+int main() { return check<255>() | check<65280>(); }
+""")
