@@ -792,7 +792,7 @@ __global__ __launch_bounds__(kSmallThreads) void k_flow_small(int tiles_x, int t
     constexpr int T = kSmallTile, NT = kSmallThreads, R = T + 2 * kWinR;       // 26: tile and halo
     // A group of 32 lanes of a window pass reads two rows (16 lanes each), which must lie 16 banks apart.  The two
     // rows of a group are eight apart (window_item) and the rows are unpadded: 8 * 26 = 16 mod 32; the pass that
-    // writes the terms then sees addresses linear in the thread index, and a block takes 16 KB, so that eight
+    // writes the terms then sees addresses linear in the thread index, and a block takes 17 136 bytes, so that eight
     // blocks fill every wave slot of a compute unit.
     static_assert((8 * R) % 32 == 16, "rows eight apart sit 16 banks apart");
     __shared__ float s_in[5][R][R];
@@ -1400,12 +1400,13 @@ hipError_t launch_flow_updates(const FlowBatch& level0, int n, int64_t level_off
     hipLaunchKernelGGL(KERNEL, dim3((w + TX - 1) / TX, (h + TY - 1) / TY, n), dim3(NT), 0, s, (w + TX - 1) / TX, (h + TY - 1) / TY, \
                        frames_sharing_runs((w + TX - 1) / TX, (h + TY - 1) / TY, n), h, w, ch, cw, prior_mode, fw, f)
     // The shape whose rounds of blocks cost least.  A round is a block per compute unit; launches of 1, 2, 3 .. rounds
-    // measured over thirty levels (84x84 to 1920x1080, one to fifteen frames, an idle chip, in us, the first update of a
-    // level and the others averaged) lie on a line each:
-    //   32x32 tiles   7.7  10.6  14.2 .. 29 (eight)        least work per pixel: 1.7 cells
-    //   32x16 tiles   6.5   8.4  10.1  11.9                2.1 cells
-    //   16x16 tiles   5.8   6.8   7.9   9.0  10.2          2.6 cells, the shortest block
-    // e.g. 640x360 7.8 / 8.5 / 9.1, two frames of 480x270 10.2 / 8.6 / 9.2, 168x168 x 8 frames 9.7 / 9.6 / 8.8.
+    // measured over thirteen frame sizes and their halves (42x42 to 1920x1080, one to fifteen frames, an idle chip, in us) lie on a line each, the
+    // first update of a level and the others:
+    //   32x32 tiles   8.5  11.7  14.6  17.9 .. 30 (eight)    6.7  10.1  12.3  15.9 .. 27        least work per pixel: 1.7 cells
+    //   32x16 tiles   7.0   9.6  11.6  13.5                  5.9   7.8   9.6  11.4              2.1 cells
+    //   16x16 tiles   6.6   7.3   8.3  10.2  12.1            5.5   6.3   7.5   8.8   9.6        2.6 cells, the shortest block
+    // The costs below are lines through both (as they were before the coarser flow was staged in LDS).  Of 288 launches they choose a shape that is
+    // more than 3 % slower than the best for 24, at most 22 % (first update of 84x84 x 15 frames 9.9 us, in 16x16 tiles 8.1).
     auto rounds = [&](int tx, int ty) { return (tiles_of(tx, ty, n, h, w) + kComputeUnits - 1) / kComputeUnits; };
     const long long cost32 = 93 + 60 * rounds(kTileX, 32), cost16 = 95 + 36 * rounds(kTileX, 16),
                     cost_small = 94 + 22 * rounds(kSmallTile, kSmallTile);             // twentieths of a us

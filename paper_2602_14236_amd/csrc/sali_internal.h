@@ -234,9 +234,10 @@ struct FlowWeights {
 // neighbouring tiles land on different XCDs and every L2 ends up holding every frame.  This maps
 // the hardware id to a logical (x, y, z) such that each XCD works through one contiguous run of the
 // (z, y, x) order: tiles that share halos share an L2, and an L2 holds an eighth of the data.  Large frames are cut into eight
-// runs each instead (gz = 0) and so go one after the other, which leaves the expansion that two flows share in the last-level
-// cache: flow updates of three 1920x1080 frames 1 % faster, 15 x 320x180 4 % slower (more tiles have neighbours elsewhere), 15 x
-// 640x360 (240 tiles) the same.
+// runs each instead (gz = 0) and so go one after the other.  More tiles then have neighbours elsewhere and the halos are fetched again (a flow
+// update of three 1920x1080 frames by itself reads 359 MB, not 330, of three 960x540 92, not 82), but the expansion that two flows share is still
+// in the last-level cache, and that counts for more: the analysis of four 1920x1080 frames 790 -> 773 us, of eight 960x540 421 -> 416, of four
+// 883x1327 with two levels 416 -> 401.  Smaller frames: 15 x 320x180 4 % slower, 15 x 640x360 (240 tiles) the same.
 // The grid comes as arguments: the leading ones are in registers when a block starts, the launch's own record is not.
 struct BlockId {
     int x, y, z;
